@@ -55,21 +55,7 @@ def genomes_for(codes):
     return out
 
 
-def table_arrays(k, W):
-    """Table arrays one insert or lookup touches: 1 (key and mask in one
-    word), 2 (key word + mask byte), or the key words of a wide key (top
-    word, low word, middle words) plus a mask byte unless the mask fits in
-    the top word."""
-    if k <= 27:
-        return 1
-    if W == 1:
-        return 2
-    himask = 2 * k <= 64 * (W - 1) + 54
-    return (2 if W == 2 else 3) + (0 if himask else 1)
-
-
-def slot_bytes(k, W):
-    return 8 * W + (0 if k <= 27 or (W >= 2 and 2 * k <= 64 * (W - 1) + 54) else 1)
+SLOT_BYTES = 8  # an exact-table slot is one 64-bit word whatever k
 
 
 def algorithmic_bytes(c, bases, k, W, h, blocked, filter_bytes, table_bytes, nonzero_granules):
@@ -86,8 +72,7 @@ def algorithmic_bytes(c, bases, k, W, h, blocked, filter_bytes, table_bytes, non
                  the first clear one, (1 - r^h) / (1 - r) words on average
                  for a filter whose fraction r of bits is set (the fill
                  ratio of the Theoretical Analysis); record and
-                 decision: the table arrays of one slot per candidate --
-                 charged only for a structure larger than the 256 MB
+                 decision: one slot word per candidate -- charged only for a structure larger than the 256 MB
                  last-level cache (a smaller one is probed on chip).
     c: positions, edge_positions, candidates, junctions, edges, bloom_popcount."""
     pos, epos, cand = c["positions"], c["edge_positions"], c["candidates"]
@@ -95,7 +80,6 @@ def algorithmic_bytes(c, bases, k, W, h, blocked, filter_bytes, table_bytes, non
     genome = bases / 4
     f_hbm = filter_bytes > MALL_BYTES
     t_hbm = table_bytes > MALL_BYTES
-    arrays = table_arrays(k, W)
     fill_probes = epos * (1 if blocked else h)
     if blocked:
         query_probes = pos
@@ -105,12 +89,11 @@ def algorithmic_bytes(c, bases, k, W, h, blocked, filter_bytes, table_bytes, non
     out = {
         "fill": genome + (GRANULE * (fill_probes + nonzero_granules) if f_hbm else 0),
         "query": genome + pos / 8 + (GRANULE * query_probes if f_hbm and query_probes else 0),
-        "record": genome + pos / 8 + (GRANULE * arrays * cand if t_hbm else 0),
-        "decide": genome + 2 * pos / 8 + (GRANULE * arrays * cand if t_hbm else 0),
+        "record": genome + pos / 8 + (GRANULE * cand if t_hbm else 0),
+        "decide": genome + 2 * pos / 8 + (GRANULE * cand if t_hbm else 0),
         "compact": pos / 8 + genome + nj * (8 + 8 * W + 1) + ne * 24,
     }
-    probes = {"fill": fill_probes, "query": query_probes, "record": arrays * cand,
-              "decide": arrays * cand}
+    probes = {"fill": fill_probes, "query": query_probes, "record": cand, "decide": cand}
     return out, probes, {"filter_in_hbm": f_hbm, "table_in_hbm": t_hbm}
 
 
@@ -308,7 +291,7 @@ def primate_leg(args, stream, genomes, bases, flags, steps, warmup, d_in=None, o
     nz = nonzero_granules_dev(out["bloom"], b // 32)
     c = counts_of(st)
     alg, probes, where = algorithmic_bytes(c, bases, k, W, h, blocked, b // 8,
-                                           c["table_capacity"] * slot_bytes(k, W), nz)
+                                           c["table_capacity"] * SLOT_BYTES, nz)
     rec = {"value": bases / 1e9 / (ms * 1e-3), "ms_per_step": ms, "steps": steps,
            "config": plan.config, "kernel_ms": km,
            "pass12_ms": sum(km[n] for n in ("fill", "query", "record", "decide")),
@@ -464,7 +447,7 @@ def bacterial_leg(args, stream):
         c = counts_of(st)
         nz = nonzero_granules_dev(plan.device_outputs()["bloom"], b // 32)
         alg, probes, where = algorithmic_bytes(c, bases, k, W, h, bool(flags), b // 8,
-                                               c["table_capacity"] * slot_bytes(k, W), nz)
+                                               c["table_capacity"] * SLOT_BYTES, nz)
         rec = {"value": bases / 1e9 / (ms * 1e-3), "ms_per_step": ms, "kernel_ms": km,
                "tuned": tuned, "counts": c, "residency": where, "method_probes": probes,
                "roofline": roofline(alg, km, "bacterial_%s" % name)}

@@ -39,7 +39,6 @@ constexpr uint32_t FILL_CHUNK = 8;                 // deduplicating fill: tiles 
 constexpr uint32_t RECORD_RUN = 8;                 // record in runs: tiles per visit
 constexpr uint32_t FILL_DD = 4096;                 // deduplicating fill: LDS table entries
 constexpr uint64_t EMPTY_KEY = ~0ull;
-constexpr uint64_t PENDING_BIT = 1ull << 63;       // two-word keys: high word claimed
 constexpr uint32_t MAX_PROBE = 1u << 12;           // exact-table probe bound (then regrow)
 constexpr uint64_t TABLE_ALIGN = 64;               // set tables start and end on 512-byte key rows
 constexpr uint64_t TABLE_TAIL = MAX_PROBE;         // spare slots past a set's capacity (never probed)
@@ -163,30 +162,21 @@ struct BloomArgs {
     uint32_t blocked;          // blocked layout: 64-bit blocks keyed by the middle (k-1)-mer
 };
 
-// Exact-table layouts:
-//   packed (k <= 27): one 64-bit word per slot, key << 8 | in/out mask
-//   split  (k <= 31): key words + 8-bit masks packed 4 per 32-bit word
-//   wide   (k <= 63): low and high key words + masks
-//   wide4  (k <= 127): low, middle (2 per slot) and top key words + masks
-// Pointers are the pools' bases; a tile's set shifts them by table_off.
+// Exact-table slot words, one 64-bit word per slot:
+//   packed     (k <= 27): key << 8 | in/out mask
+//   reference  (k >= 28): hash tag | position << 8 | in/out mask, the position
+//              (global base index) being where the sequence reads the key
+// keys is the pools' base; a tile's set shifts it by table_off.
 struct TableArgs {
-    unsigned long long *keys;     // slot words (packed) / key or low key words
-    unsigned long long *keys_hi;  // top key words (two and four words), else null
-    unsigned long long *keys_mid; // four-word keys: words 1 and 2, two per slot, else null
-    uint32_t *masks;              // split and wide layouts (not himask)
+    unsigned long long *keys;     // slot words
     uint64_t lomask;              // (1 << cap_e) - 1 (a set's; filled per tile)
     uint32_t cap_m, cap_e;        // a set's capacity: cap_m << cap_e home slots
     uint32_t packed;
-    uint32_t himask;              // wide keys: the mask in bits HIMASK_SHIFT.. of keys_hi
+    uint32_t ref_shift;           // reference words: the tag starts at this bit
     uint32_t pow2;                // table mode: every set's capacity is 2^cap_e (cap_m = 1)
     uint32_t pad;
 };
 constexpr uint32_t PACKED_MAX_K = 27;  // 2k + 8 <= 62 bits
-// Wide keys whose top word has at most HIMASK_SHIFT key bits keep their edge
-// mask in that word, above the key bits (the pending bit stays bit 63).
-constexpr uint32_t HIMASK_SHIFT = 54;
-constexpr uint64_t HIKEY_BITS = (1ull << HIMASK_SHIFT) - 1;
-
 struct OutArgs {
     uint64_t *pos;             // genome coordinate per junction
     uint64_t *vertex;          // W words per junction
@@ -255,7 +245,7 @@ hipError_t launch_census(int W, const SeqArgs &a, unsigned long long *counters, 
 hipError_t launch_popcount(const uint32_t *pool, uint64_t n_words, const uint64_t *bloom_starts,
                            uint32_t n_sets, SetCounters *set_cnt, hipStream_t s);
 // a3: exact in/out edge masks of every candidate k-mer.
-hipError_t launch_table_clear(int W, const TableArgs &pool, uint64_t slots, hipStream_t s);
+hipError_t launch_table_clear(const TableArgs &pool, uint64_t slots, hipStream_t s);
 hipError_t launch_record(int W, const SeqArgs &a, const uint64_t *c1, const TableArgs &pool,
                          Counters *cnt, uint32_t grid, hipStream_t s);
 

@@ -12,13 +12,14 @@
 // Algorithm 1 counts.  This stores one entry per distinct candidate k-mer
 // instead of up to 8 per junction (Theoretical Analysis section).
 //
-//   k_record   loop 1: insert-or-find the normalised k-mer (atomicCAS on the
-//              key word), then atomicOr its edge bits (load first, skip when
-//              already set).  Two-word keys (k >= 32) claim the high word
-//              with a pending bit, publish the low word, then release.
+//   k_record   loop 1: insert-or-find the normalised k-mer (one atomicCAS on
+//              its slot word), then atomicOr its edge bits (skipped when the
+//              word read already has them).
 //   k_decide   loop 2: a candidate stays a junction when its k-mer is a
 //              sentinel or has more than one in- or out-edge; one wave
 //              ballot per 64 positions writes the J bitmap.
+#include <type_traits>
+
 #include "device.hpp"
 
 namespace tp {
@@ -37,26 +38,21 @@ __device__ __forceinline__ void stage_tile2(const SeqArgs &a, uint64_t tile, uin
                                                    (BLOCK - TILE / 64)];
 }
 
-__global__ void k_table_clear(unsigned long long *keys, unsigned long long *keys_hi,
-                              uint32_t *masks, uint64_t cap) {
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < cap;
-         i += (uint64_t)gridDim.x * blockDim.x) {
-        keys[i] = EMPTY_KEY;
-        if (keys_hi)
-            keys_hi[i] = EMPTY_KEY;
-        if (masks && (i & 3) == 0)
-            masks[i >> 2] = 0;
-    }
+__global__ void k_table_clear(ulonglong2 *keys, uint64_t pairs) {
+    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < pairs;
+         i += (uint64_t)gridDim.x * blockDim.x)
+        keys[i] = make_ulonglong2(EMPTY_KEY, EMPTY_KEY);
 }
 
-hipError_t launch_table_clear(int W, const TableArgs &pool, uint64_t slots, hipStream_t s) {
+// slots: even (capacities and spare tails are multiples of 64 slots).
+hipError_t launch_table_clear(const TableArgs &pool, uint64_t slots, hipStream_t s) {
     if (slots == 0)
         return hipSuccess;
-    uint64_t g = (slots + BLOCK - 1) / BLOCK;
+    uint64_t g = (slots / 2 + BLOCK - 1) / BLOCK;
     if (g > 16384)
         g = 16384;
-    hipLaunchKernelGGL(k_table_clear, dim3((uint32_t)g), dim3(BLOCK), 0, s, pool.keys,
-                       W >= 2 ? pool.keys_hi : nullptr, pool.packed ? nullptr : pool.masks, slots);
+    hipLaunchKernelGGL(k_table_clear, dim3((uint32_t)g), dim3(BLOCK), 0, s,
+                       (ulonglong2 *)pool.keys, slots / 2);
     return hipGetLastError();
 }
 
@@ -66,42 +62,15 @@ __device__ __forceinline__ TableArgs table_of(const SeqArgs &a, const TableArgs 
     const SetDesc &d = a.sets[set];
     TableArgs t = pool;
     t.keys = pool.keys + d.table_off;
-    if (pool.keys_hi)
-        t.keys_hi = pool.keys_hi + d.table_off;
-    if (pool.keys_mid)
-        t.keys_mid = pool.keys_mid + 2 * d.table_off;
-    if (pool.masks)
-        t.masks = pool.masks + d.table_off / 4;
     t.cap_m = d.table_m;
     t.cap_e = d.table_e;
     t.lomask = (1ull << d.table_e) - 1;
     return t;
 }
 
-__device__ __forceinline__ unsigned long long ld(unsigned long long *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ uint32_t ld_mask(const uint32_t *masks, uint64_t s) {
-    return __hip_atomic_load(&masks[s >> 2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// OR edge bits m into slot s's mask byte, given an earlier reading mw of its
-// word.  Mask bits are only ever set, so a stale reading costs at most an
-// atomic that was not needed; it never skips one that was.
-__device__ __forceinline__ void or_mask(uint32_t *masks, uint64_t s, uint32_t m, uint32_t mw) {
-    const uint32_t mm = m << (8 * (uint32_t)(s & 3));
-    if ((mw & mm) != mm)
-        __hip_atomic_fetch_or(&masks[s >> 2], mm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ int mask_byte(uint32_t mw, uint64_t s) {
-    return (int)((mw >> (8 * (uint32_t)(s & 3))) & 0xFFu);
-}
-
-// A lookup starts at the key's home slot (first_slot) with that slot's word
-// (first_word) and continues from there (*_from) to the next slots.  Two
-// table modes, fixed per run (the kernels are instantiated for each):
+// A lookup starts at the key's home slot (home_slot of its hash) and goes on
+// to the slots after it, a pair of slots at a time.  Two table modes, fixed
+// per run (the kernels are instantiated for each):
 //   P2    capacity 2^e: the home slot is the low e hash bits and probes wrap
 //         at the capacity (a mask on the path from key to address);
 //   any   capacity m << e (m < 2^32): m blocks of 2^e slots.  The home
@@ -113,18 +82,17 @@ __device__ __forceinline__ int mask_byte(uint32_t mw, uint64_t s) {
 // Home slots are even, so a lookup can read the pair of slots it starts in
 // with one 16-byte load (capacities and set regions are multiples of 64
 // slots, so pairs never straddle them).
-template <bool P2, class T>
-__device__ __forceinline__ uint64_t first_slot(const TableArgs &t, T key) {
-    const uint64_t h = slot_hash(key);
+template <bool P2>
+__device__ __forceinline__ uint64_t home_slot(const TableArgs &t, uint64_t h) {
     if (P2)
         return h & t.lomask & ~1ull;
     const uint64_t top = __umulhi((uint32_t)(h >> 32), t.cap_m);
     return ((top << t.cap_e) | (h & t.lomask)) & ~1ull;
 }
 
-template <bool P2>
-__device__ __forceinline__ uint64_t next_slot(const TableArgs &t, uint64_t s) {
-    return P2 ? (s + 1) & t.lomask : (s & ~t.lomask) | ((s + 1) & t.lomask);
+template <bool P2, class T>
+__device__ __forceinline__ uint64_t first_slot(const TableArgs &t, T key) {
+    return home_slot<P2>(t, slot_hash(key));
 }
 
 // The next pair of slots after the pair starting at s (s even).
@@ -143,14 +111,50 @@ __device__ __forceinline__ u64x2 load_pair(const TableArgs &t, uint64_t s) {
     return *(const u64x2 *)(t.keys + s);
 }
 
-// Insert-or-find of a one-word key by slot pairs, starting with the pair pr
-// of slots s, s + 1 (s even): claim an empty slot by atomicCAS (packed slots
-// take the key and its edge bits at once), or OR the edge bits into the
-// key's slot.  1 when this call claimed a new slot, 0 when the key was
-// present, -1 on overflow.
+// Slot words.  Packed (k <= 27): key << 8 | edge bits.  Reference (k >= 28):
+// the key does not fit beside its edge bits, so the word holds instead where
+// the sequence reads it, tag | p << 8 | edge bits, p the global base index of
+// the occurrence that claimed the slot and tag the bits above it (ref_tag).
+// A word whose tag matches is compared with the packed sequence at p, so a
+// lookup is as exact as one that stores the key.  One 64-bit word per slot
+// whatever k: a claim is one compare-and-swap, where storing the key took an
+// atomic per key word and one to publish it (and those atomics, at the
+// device's ~27 G/s, were the whole record), and the table is cleared, probed
+// and cached at a half to a quarter of the bytes.  62 x 5 Mbp, b = 2^30: 73M
+// keys at k = 63, record 16.3 -> 6.0 ms and decision 6.6 -> 3.9; 135M keys at
+// k = 100, 27.3 -> 8.5 and 10.6 -> 6.2.  The compare reads two to
+// five words of the sequence, mostly lines that neighbouring positions read
+// too (consecutive k-mers were claimed by consecutive positions).
+
+// The tag: hash bits above the position and the edge bits.  Any-size tables
+// take the block from the high hash word, so there the low word's top bits
+// come first (they are free of the home slot's).
 template <bool P2>
-__device__ __forceinline__ int insert_pair(const TableArgs &t, uint64_t key, uint32_t m,
-                                           uint64_t s, u64x2 pr, uint32_t &probes) {
+__device__ __forceinline__ uint64_t ref_tag(const TableArgs &t, uint64_t h) {
+    const uint64_t x = P2 ? h : (h << 32 | h >> 32);
+    return x >> t.ref_shift << t.ref_shift;
+}
+
+// Whether the sequence reads the k-mer st, on either strand, at the position
+// that slot word names: x ^ ones is the value of the reverse complement of
+// the window x, and it is st.rc when x is st as read, st.fwd when x is its
+// reverse complement.
+template <class T>
+__device__ __forceinline__ bool ref_is(const SeqArgs &a, const TableArgs &t,
+                                       unsigned long long word, const Strands<T> &st) {
+    const uint64_t p = (word & ((1ull << t.ref_shift) - 1)) >> 8;
+    const T z = KT<T>::window(a.seq + (p >> 5), (uint32_t)(p & 31), a.k) ^ KT<T>::ones(2 * a.k);
+    return z == st.rc || (!a.single && z == st.fwd);
+}
+
+// Insert-or-find by slot pairs, starting with the pair pr of slots s, s + 1
+// (s even): claim an empty slot for own (the key's slot word with the edge
+// bits m) by atomicCAS, or OR the edge bits into the key's slot.  same(w):
+// whether the slot word w is the key's.  1 when this call claimed a new slot,
+// 0 when the key was present, -1 on overflow.
+template <bool P2, class Same>
+__device__ __forceinline__ int insert_pair(const TableArgs &t, unsigned long long own, uint32_t m,
+                                           uint64_t s, u64x2 pr, Same &&same, uint32_t &probes) {
     for (uint32_t i = 0; i < MAX_PROBE / 2; ++i) {
         if (i)
             pr = load_pair(t, s);
@@ -159,32 +163,16 @@ __device__ __forceinline__ int insert_pair(const TableArgs &t, uint64_t key, uin
         for (uint32_t half = 0; half < 2; ++half) {
             const uint64_t slot = s + half;
             unsigned long long cur = half ? pr.y : pr.x;
-            if (t.packed) {
-                if (cur == EMPTY_KEY) {
-                    cur = atomicCAS(&t.keys[slot], EMPTY_KEY, (unsigned long long)((key << 8) | m));
-                    if (cur == EMPTY_KEY)
-                        return 1;
-                }
-                if ((cur >> 8) == key) {
-                    if ((cur & m) != m)
-                        __hip_atomic_fetch_or(&t.keys[slot], (unsigned long long)m,
-                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    return 0;
-                }
-            } else {
-                const uint32_t mw = ld_mask(t.masks, slot);
-                int claimed = 0;
-                if (cur == EMPTY_KEY) {
-                    cur = atomicCAS(&t.keys[slot], EMPTY_KEY, (unsigned long long)key);
-                    if (cur == EMPTY_KEY) {
-                        cur = key;
-                        claimed = 1;
-                    }
-                }
-                if (cur == key) {
-                    or_mask(t.masks, slot, m, mw);
-                    return claimed;
-                }
+            if (cur == EMPTY_KEY) {
+                cur = atomicCAS(&t.keys[slot], EMPTY_KEY, own);
+                if (cur == EMPTY_KEY)
+                    return 1;
+            }
+            if (same(cur)) {
+                if ((cur & m) != m)
+                    __hip_atomic_fetch_or(&t.keys[slot], (unsigned long long)m, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT);
+                return 0;
             }
         }
         s = next_pair<P2>(t, s);
@@ -192,253 +180,26 @@ __device__ __forceinline__ int insert_pair(const TableArgs &t, uint64_t key, uin
     return -1;
 }
 
-// Record reads slots other waves are writing (device-coherent loads); the
-// decision reads a finished table (plain, cacheable loads).
-__device__ __forceinline__ unsigned long long first_word(const TableArgs &t, uint64_t s, bool wide) {
-    return wide ? ld(&t.keys_hi[s]) : ld(&t.keys[s]);
-}
-
-__device__ __forceinline__ unsigned long long first_word_ro(const TableArgs &t, uint64_t s,
-                                                            bool wide) {
-    return wide ? t.keys_hi[s] : t.keys[s];
-}
-
-// Insert-or-find of a one-word key, then OR of its edge bits, starting at
-// slot s whose word is cur.  Packed slots hold key << 8 | mask (the key field
-// of an empty slot, all ones, never equals a key of 2k <= 54 bits); split
-// slots hold the key with the mask in a separate byte.  Returns 1 when this
-// call claimed a new slot, 0 when the key was present, -1 on overflow.
-template <bool P2>
-__device__ __forceinline__ int insert_from(const TableArgs &t, uint64_t key, uint32_t m,
-                                           uint64_t s, unsigned long long cur,
-                                           uint32_t &probes) {
-    for (uint32_t i = 0; i < MAX_PROBE; ++i) {
-        ++probes;
+// Edge bits of the key's slot (same(w) as above), or -1 when absent; pr
+// holds the words of slots s and s + 1 (s even).
+template <bool P2, class Same>
+__device__ __forceinline__ int find_pair(const TableArgs &t, uint64_t s, u64x2 pr, Same &&same,
+                                         uint32_t &probes) {
+    for (uint32_t i = 0; i < MAX_PROBE / 2; ++i) {
         if (i)
-            cur = ld(&t.keys[s]);
-        const uint32_t mw = t.packed ? 0u : ld_mask(t.masks, s);  // issued with the key word
-        if (t.packed) {
-            if (cur == EMPTY_KEY) {
-                cur = atomicCAS(&t.keys[s], EMPTY_KEY, (unsigned long long)((key << 8) | m));
-                if (cur == EMPTY_KEY)
-                    return 1;
-            }
-            if ((cur >> 8) == key) {
-                if ((cur & m) != m)
-                    __hip_atomic_fetch_or(&t.keys[s], (unsigned long long)m, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
-                return 0;
-            }
-        } else {
-            int claimed = 0;
-            if (cur == EMPTY_KEY) {
-                cur = atomicCAS(&t.keys[s], EMPTY_KEY, (unsigned long long)key);
-                if (cur == EMPTY_KEY) {
-                    cur = key;
-                    claimed = 1;
-                }
-            }
-            if (cur == key) {
-                or_mask(t.masks, s, m, mw);
-                return claimed;
-            }
+            pr = load_pair(t, s);
+        ++probes;
+#pragma unroll
+        for (uint32_t half = 0; half < 2; ++half) {
+            const unsigned long long w = half ? pr.y : pr.x;
+            if (w == EMPTY_KEY)
+                return -1;
+            if (same(w))
+                return (int)(w & 0xFFu);
         }
-        s = next_slot<P2>(t, s);
+        s = next_pair<P2>(t, s);
     }
     return -1;
-}
-
-// Two-word keys: the high word (< 2^62 for k <= 63) is claimed with
-// PENDING_BIT set, the low word written, then the high word published without
-// the bit.  A finder that sees its high word pending reads the same slot
-// again on the next trip.  The loop leaves only by a wave-wide vote, so no
-// lane's claim-and-publish sits on a divergent exit path (which the
-// structurised control flow would run after the loop, behind its own
-// waiters): a claimer publishes in the same trip in which it claims.  The
-// trip bound turns any unexpected livelock into an overflow report.
-//
-// Ordering without acquire/release: on a part whose dies have separate L2s,
-// agent-scope acquire and release each cost a whole-L2 invalidate or
-// write-back.  Every access here is instead a relaxed device-coherent atomic,
-// performed at the coherence point.  The claimer writes the low word with an
-// exchange and waits for its result before it issues the publishing
-// exchange, so the low word is in place before any lane can see the high
-// word published; a finder reads the low word only after its load of the
-// published high word has returned.
-// Multi-word keys: the top word lives in keys_hi, the others in keys (word
-// 0) and keys_mid (words 1 and 2 of four-word keys).
-__device__ __forceinline__ uint64_t top_word(u128 k) { return (uint64_t)(k >> 64); }
-__device__ __forceinline__ uint64_t top_word(const u256 &k) { return k.w3; }
-
-__device__ __forceinline__ unsigned long long xchg(unsigned long long *p, uint64_t v) {
-    return __hip_atomic_exchange(p, (unsigned long long)v, __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Write the lower words of key into slot s; the result depends on every
-// exchange's returned value (so using it waits for all of them).
-__device__ __forceinline__ unsigned long long put_low(const TableArgs &t, uint64_t s, u128 k) {
-    return xchg(&t.keys[s], (uint64_t)k);
-}
-__device__ __forceinline__ unsigned long long put_low(const TableArgs &t, uint64_t s,
-                                                      const u256 &k) {
-    const unsigned long long a = xchg(&t.keys[s], k.w0);
-    const unsigned long long b = xchg(&t.keys_mid[2 * s], k.w1);
-    const unsigned long long c = xchg(&t.keys_mid[2 * s + 1], k.w2);
-    return a ^ b ^ c;
-}
-
-// Lower words of slot s equal those of key: device-coherent loads (record)
-// or plain loads of a finished table (decision), all issued before any
-// comparison so they are in flight together.
-__device__ __forceinline__ bool low_equal(const TableArgs &t, uint64_t s, u128 k) {
-    return ld(&t.keys[s]) == (uint64_t)k;
-}
-__device__ __forceinline__ bool low_equal(const TableArgs &t, uint64_t s, const u256 &k) {
-    const unsigned long long a = ld(&t.keys[s]), b = ld(&t.keys_mid[2 * s]),
-                             c = ld(&t.keys_mid[2 * s + 1]);
-    return ((a ^ k.w0) | (b ^ k.w1) | (c ^ k.w2)) == 0;
-}
-__device__ __forceinline__ bool low_equal_ro(const TableArgs &t, uint64_t s, u128 k) {
-    return t.keys[s] == (uint64_t)k;
-}
-__device__ __forceinline__ bool low_equal_ro(const TableArgs &t, uint64_t s, const u256 &k) {
-    const uint64_t a = t.keys[s], b = t.keys_mid[2 * s], c = t.keys_mid[2 * s + 1];
-    return ((a ^ k.w0) | (b ^ k.w1) | (c ^ k.w2)) == 0;
-}
-
-template <bool P2, class T>
-__device__ __forceinline__ int insert_wide(const TableArgs &t, const T &key, uint32_t m,
-                                           uint64_t s, unsigned long long cur, uint32_t &visits) {
-    const unsigned long long khi = top_word(key);
-    int result = 2;  // 2 = in progress, 1 = claimed, 0 = found, -1 = overflow
-    uint32_t probes = 0;
-    bool reload = false;
-    for (uint32_t trip = 0; trip < 4 * MAX_PROBE; ++trip) {
-        if (!__any(result == 2))
-            break;
-        if (result != 2)
-            continue;
-        ++visits;
-        if (reload)
-            cur = ld(&t.keys_hi[s]);
-        reload = true;
-        const uint32_t mw = t.himask ? 0u : ld_mask(t.masks, s);  // issued with the top word
-        bool claimed = false;
-        if (cur == EMPTY_KEY) {
-            const unsigned long long prev = atomicCAS(&t.keys_hi[s], EMPTY_KEY, khi | PENDING_BIT);
-            if (prev == EMPTY_KEY)
-                claimed = true;
-            else
-                cur = prev;
-        }
-        bool advance = false;
-        if (claimed) {
-            const unsigned long long was = put_low(t, s, key);
-            // use the exchanges' results, so they have completed before the publish
-            __asm__ volatile("" : : "v"(was));
-            if (t.himask) {
-                (void)xchg(&t.keys_hi[s], khi | (unsigned long long)m << HIMASK_SHIFT);
-            } else {
-                (void)xchg(&t.keys_hi[s], khi);
-                or_mask(t.masks, s, m, mw);
-            }
-            result = 1;
-        } else if ((cur & (t.himask ? HIKEY_BITS : ~PENDING_BIT)) == khi) {
-            // pending: the lower words are not published yet, look again next trip
-            if (!(cur & PENDING_BIT)) {
-                if (low_equal(t, s, key)) {
-                    if (t.himask) {
-                        const unsigned long long mm = (unsigned long long)m << HIMASK_SHIFT;
-                        if ((cur & mm) != mm)
-                            __hip_atomic_fetch_or(&t.keys_hi[s], mm, __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_AGENT);
-                    } else {
-                        or_mask(t.masks, s, m, mw);
-                    }
-                    result = 0;
-                } else {
-                    advance = true;
-                }
-            }
-        } else {
-            advance = true;
-        }
-        if (advance) {
-            if (++probes >= MAX_PROBE)
-                result = -1;
-            else
-                s = next_slot<P2>(t, s);
-        }
-    }
-    return result == 2 ? -1 : result;
-}
-
-template <bool P2>
-__device__ __forceinline__ int insert_from(const TableArgs &t, u128 key, uint32_t m, uint64_t s,
-                                           unsigned long long cur, uint32_t &visits) {
-    return insert_wide<P2>(t, key, m, s, cur, visits);
-}
-template <bool P2>
-__device__ __forceinline__ int insert_from(const TableArgs &t, const u256 &key, uint32_t m,
-                                           uint64_t s, unsigned long long cur,
-                                           uint32_t &visits) {
-    return insert_wide<P2>(t, key, m, s, cur, visits);
-}
-
-// Edge bits of the slot holding key, starting at slot s with word cur, or -1
-// when absent.
-template <bool P2>
-__device__ __forceinline__ int find_from(const TableArgs &t, uint64_t key, uint64_t s,
-                                         unsigned long long cur, uint32_t &probes) {
-    for (uint32_t i = 0; i < MAX_PROBE; ++i) {
-        ++probes;
-        if (i)
-            cur = t.keys[s];
-        if (t.packed) {
-            if ((cur >> 8) == key)
-                return (int)(cur & 0xFFu);
-        } else {
-            if (cur == key)
-                return mask_byte(t.masks[s >> 2], s);
-        }
-        if (cur == EMPTY_KEY)
-            return -1;
-        s = next_slot<P2>(t, s);
-    }
-    return -1;
-}
-
-template <bool P2, class T>
-__device__ __forceinline__ int find_wide(const TableArgs &t, const T &key, uint64_t s,
-                                         unsigned long long cur, uint32_t &probes) {
-    const unsigned long long khi = top_word(key);
-    for (uint32_t i = 0; i < MAX_PROBE; ++i) {
-        ++probes;
-        if (i)
-            cur = t.keys_hi[s];
-        if (t.himask) {
-            if (cur != EMPTY_KEY && (cur & HIKEY_BITS) == khi && low_equal_ro(t, s, key))
-                return (int)((cur >> HIMASK_SHIFT) & 0xFFu);
-        } else if (cur == khi && low_equal_ro(t, s, key)) {
-            return mask_byte(t.masks[s >> 2], s);
-        }
-        if (cur == EMPTY_KEY)
-            return -1;
-        s = next_slot<P2>(t, s);
-    }
-    return -1;
-}
-
-template <bool P2>
-__device__ __forceinline__ int find_from(const TableArgs &t, u128 key, uint64_t s,
-                                         unsigned long long cur, uint32_t &probes) {
-    return find_wide<P2>(t, key, s, cur, probes);
-}
-template <bool P2>
-__device__ __forceinline__ int find_from(const TableArgs &t, const u256 &key, uint64_t s,
-                                         unsigned long long cur, uint32_t &probes) {
-    return find_wide<P2>(t, key, s, cur, probes);
 }
 
 // Whether a set's table overflowed in this attempt (thread 0 only): the
@@ -457,6 +218,21 @@ __device__ __forceinline__ uint32_t overflow_seen(const SeqArgs &a, uint32_t set
     return flag;
 }
 
+// Host-side dispatch on the k-mer width, the table mode and the slot words:
+// f(value of the k-mer type, power-of-two table, reference words); packed
+// words are one-word k-mers'.
+template <class F> hipError_t by_table(int W, const TableArgs &t, F &&f) {
+    return by_width(W, [&](auto tag) {
+        if constexpr (KT<decltype(tag)>::W == 1) {
+            if (t.packed)
+                return t.pow2 ? f(tag, std::true_type{}, std::false_type{})
+                              : f(tag, std::false_type{}, std::false_type{});
+        }
+        return t.pow2 ? f(tag, std::true_type{}, std::true_type{})
+                      : f(tag, std::false_type{}, std::true_type{});
+    });
+}
+
 // ------------------------------------------------------------- record (a3)
 
 // The normalised k-mer of position p (at offset r of the staged words w) in
@@ -465,8 +241,9 @@ __device__ __forceinline__ uint32_t overflow_seen(const SeqArgs &a, uint32_t set
 // k-mer is normalised (both orientations for a palindrome).
 template <class T>
 __device__ __forceinline__ T record_key(const uint64_t *w, uint32_t r, uint32_t k, uint64_t p,
-                                        uint64_t gs, uint64_t ge, bool single, uint32_t &m) {
-    const Strands<T> st = strands(KT<T>::window(w, r, k), k);
+                                        uint64_t gs, uint64_t ge, bool single, uint32_t &m,
+                                        Strands<T> &st) {
+    st = strands(KT<T>::window(w, r, k), k);
     const bool has_pred = p > gs, has_succ = p + k < ge;
     const uint32_t pa = has_pred ? base_at(w, r - 1) : 0;
     const uint32_t sb = has_succ ? base_at(w, r + k) : 0;
@@ -491,7 +268,7 @@ __device__ __forceinline__ T record_key(const uint64_t *w, uint32_t r, uint32_t 
     return canon;
 }
 
-template <class T, bool P2>
+template <class T, bool P2, bool REF>
 __global__ __launch_bounds__(BLOCK) void k_record(SeqArgs a, const uint64_t *c1, TableArgs pool,
                                                   Counters *cnt) {
     __shared__ uint64_t w[STAGE_WORDS];
@@ -502,7 +279,6 @@ __global__ __launch_bounds__(BLOCK) void k_record(SeqArgs a, const uint64_t *c1,
     SetSum keys = setsum_begin();
     const uint32_t k = a.k;
     const bool single = a.single != 0;
-    const bool wide = KT<T>::W >= 2;
     const uint32_t lane = threadIdx.x & 63;
     if (threadIdx.x == 0)
         block_probes = 0;
@@ -547,13 +323,23 @@ __global__ __launch_bounds__(BLOCK) void k_record(SeqArgs a, const uint64_t *c1,
                 ge = a.strings[si].gend;
             }
             uint32_t m;
-            const T canon = record_key<T>(w, (uint32_t)(p - t0) + 32, k, p, gs, ge, single, m);
-            const uint64_t slot = first_slot<P2>(t, canon);
+            Strands<T> st;
+            const T canon = record_key<T>(w, (uint32_t)(p - t0) + 32, k, p, gs, ge, single, m, st);
+            const uint64_t hash = slot_hash(canon);
+            const uint64_t slot = home_slot<P2>(t, hash);
+            const u64x2 pr = load_pair(t, slot);
             int rc;
-            if constexpr (KT<T>::W == 1)
-                rc = insert_pair<P2>(t, (uint64_t)canon, m, slot, load_pair(t, slot), my_probes);
-            else
-                rc = insert_from<P2>(t, canon, m, slot, first_word(t, slot, wide), my_probes);
+            if constexpr (REF) {
+                const unsigned long long own = ref_tag<P2>(t, hash) | p << 8 | m;
+                rc = insert_pair<P2>(t, own, m, slot, pr, [&](unsigned long long x) {
+                    return (x ^ own) >> t.ref_shift == 0 && ref_is(a, t, x, st);
+                }, my_probes);
+            } else {
+                const uint64_t key = (uint64_t)canon;
+                rc = insert_pair<P2>(t, key << 8 | m, m, slot, pr, [&](unsigned long long x) {
+                    return x >> 8 == key;
+                }, my_probes);
+            }
             if (rc > 0)
                 ++keys.v;
             else if (rc < 0)
@@ -574,13 +360,9 @@ hipError_t launch_record(int W, const SeqArgs &a, const uint64_t *c1, const Tabl
                          Counters *cnt, uint32_t grid, hipStream_t s) {
     if (a.n_tiles == 0)
         return hipSuccess;
-    return by_width(W, [&](auto tag) {
-        using T = decltype(tag);
-        if (pool.pow2)
-            hipLaunchKernelGGL((k_record<T, true>), dim3(grid), dim3(BLOCK), 0, s, a, c1, pool, cnt);
-        else
-            hipLaunchKernelGGL((k_record<T, false>), dim3(grid), dim3(BLOCK), 0, s, a, c1, pool,
-                               cnt);
+    return by_table(W, pool, [&](auto tag, auto p2, auto ref) {
+        hipLaunchKernelGGL((k_record<decltype(tag), decltype(p2)::value, decltype(ref)::value>),
+                           dim3(grid), dim3(BLOCK), 0, s, a, c1, pool, cnt);
         return hipGetLastError();
     });
 }
@@ -665,8 +447,9 @@ __global__ __launch_bounds__(BLOCK) void k_rbin_count(SeqArgs a, const uint64_t 
                 ge = a.strings[si].gend;
             }
             uint32_t m;
+            Strands<uint64_t> st;
             const uint64_t key =
-                record_key<uint64_t>(w, (uint32_t)(p - t0) + 32, k, p, gs, ge, single, m);
+                record_key<uint64_t>(w, (uint32_t)(p - t0) + 32, k, p, gs, ge, single, m, st);
             const uint64_t item = key << 8 | m;
             const uint64_t r = rbin_block<P2>(t, item);
             if (r >= rb.r_lo && r < rb.r_hi) {
@@ -965,41 +748,10 @@ hipError_t launch_record_binned(const SeqArgs &a, const uint64_t *c1, const Tabl
 
 // ------------------------------------------------------------- decide (a4)
 
-// Lookups a decision thread keeps in flight at once: two one-word keys (a
-// pair of slots each), one wide key (whose compare needs its lower words
-// after the top word).
-template <class T> struct DecideGroup {
-    static constexpr uint32_t N = KT<T>::W == 1 ? 2 : 1;
-};
+// Lookups a decision thread keeps in flight at once (a pair of slots each).
+constexpr uint32_t DECIDE_GROUP = 2;
 
-// One-word lookup by slot pairs: pr holds the words of slots s and s + 1 (s
-// even); the next pair is loaded with one 16-byte read when the key lies
-// further on.  Edge bits of the key's slot, or -1 when absent.
-template <bool P2>
-__device__ __forceinline__ int find_pair(const TableArgs &t, uint64_t key, uint64_t s, u64x2 pr,
-                                         uint32_t &probes) {
-    for (uint32_t i = 0; i < MAX_PROBE / 2; ++i) {
-        if (i)
-            pr = load_pair(t, s);
-        ++probes;
-#pragma unroll
-        for (uint32_t half = 0; half < 2; ++half) {
-            const unsigned long long w = half ? pr.y : pr.x;
-            if (t.packed) {
-                if ((w >> 8) == key)
-                    return (int)(w & 0xFFu);
-            } else if (w == key) {
-                return mask_byte(t.masks[(s + half) >> 2], s + half);
-            }
-            if (w == EMPTY_KEY)
-                return -1;
-        }
-        s = next_pair<P2>(t, s);
-    }
-    return -1;
-}
-
-template <class T, bool P2>
+template <class T, bool P2, bool REF>
 __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const uint64_t *c1,
                                                   TableArgs pool, uint64_t *jbits,
                                                   bool accumulate, Counters *cnt) {
@@ -1012,7 +764,6 @@ __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const 
     SetSum junc = setsum_begin();
     const uint32_t k = a.k;
     const bool single = a.single != 0;
-    const bool wide = KT<T>::W >= 2;
     const T *sent = (const T *)sa.table;
     const uint32_t lane = threadIdx.x & 63;
     for (uint32_t i = threadIdx.x; i < (1u << sa.pf_log2) / 32; i += BLOCK)
@@ -1050,11 +801,12 @@ __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const 
         // word (and, on a sentinel-prefilter hit, the sentinel-table word) is
         // loaded at once, so that many random reads are in flight per lane
         // before any is needed; then each lookup is resolved.
-        for (uint32_t g0 = 0; g0 < TILE / BLOCK; g0 += DecideGroup<T>::N) {
-            constexpr uint32_t G = DecideGroup<T>::N;
-            constexpr bool ONE = KT<T>::W == 1;
-            T canon[G];
+        // (The k-mer itself is read again from LDS where a lookup needs it, so
+        // that a group of wide k-mers fits the registers.)
+        for (uint32_t g0 = 0; g0 < TILE / BLOCK; g0 += DECIDE_GROUP) {
+            constexpr uint32_t G = DECIDE_GROUP;
             uint64_t slot[G];
+            unsigned long long id[G];  // packed: the key; reference: its tag
             u64x2 cur[G];
             uint32_t ss[G];
             T sx[G];
@@ -1062,44 +814,49 @@ __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const 
 #pragma unroll
             for (uint32_t j = 0; j < G; ++j) {
                 const uint32_t q = (g0 + j) * BLOCK + threadIdx.x;  // position in the tile
-                canon[j] = 0;
                 slot[j] = 0;
+                id[j] = 0;
                 ss[j] = 0;
                 if ((cw[q >> 6] >> lane) & 1ull) {
-                    canon[j] = norm(strands(KT<T>::window(w, q + 32, k), k), single);
+                    const T canon = norm(strands(KT<T>::window(w, q + 32, k), k), single);
                     look |= 1u << j;
-                    slot[j] = first_slot<P2>(t, canon[j]);
-                    if (slog2 && prefilter_hit(canon[j], pf, sa.pf_log2)) {
+                    const uint64_t hash = slot_hash(canon);
+                    slot[j] = home_slot<P2>(t, hash);
+                    id[j] = REF ? ref_tag<P2>(t, hash) : (uint64_t)canon;
+                    if (slog2 && prefilter_hit(canon, pf, sa.pf_log2)) {
                         maybe_sent |= 1u << j;
-                        ss[j] = sent_home(canon[j], slog2);
+                        ss[j] = sent_home(canon, slog2);
                     }
                 }
             }
 #pragma unroll
             for (uint32_t j = 0; j < G; ++j) {
                 cur[j].x = cur[j].y = 0;
-                if ((look >> j) & 1u) {
-                    if (ONE)
-                        cur[j] = load_pair(t, slot[j]);
-                    else
-                        cur[j].x = first_word_ro(t, slot[j], wide);
-                }
+                if ((look >> j) & 1u)
+                    cur[j] = load_pair(t, slot[j]);
                 sx[j] = ((maybe_sent >> j) & 1u) ? stab[ss[j]] : T(0);
             }
 #pragma unroll
             for (uint32_t j = 0; j < G; ++j) {
                 if (!((look >> j) & 1u))
                     continue;
-                if (((maybe_sent >> j) & 1u) &&
-                    sent_probe_from(stab, slog2, canon[j], ss[j], sx[j])) {
-                    junction |= 1u << j;  // a sentinel k-mer
-                    continue;
+                const uint32_t q = (g0 + j) * BLOCK + threadIdx.x;
+                if ((maybe_sent >> j) & 1u) {
+                    const T canon = norm(strands(KT<T>::window(w, q + 32, k), k), single);
+                    if (sent_probe_from(stab, slog2, canon, ss[j], sx[j])) {
+                        junction |= 1u << j;  // a sentinel k-mer
+                        continue;
+                    }
                 }
-                int m;
-                if constexpr (ONE)
-                    m = find_pair<P2>(t, (uint64_t)canon[j], slot[j], cur[j], my_probes);
-                else
-                    m = find_from<P2>(t, canon[j], slot[j], cur[j].x, my_probes);
+                const int m = find_pair<P2>(t, slot[j], cur[j], [&](unsigned long long x) {
+                    if (!REF)
+                        return x >> 8 == id[j];
+                    if ((x ^ id[j]) >> t.ref_shift != 0)
+                        return false;
+                    // this position's own word, or one that reads the same k-mer
+                    return (x & ((1ull << t.ref_shift) - 1)) >> 8 == t0 + q ||
+                           ref_is(a, t, x, strands(KT<T>::window(w, q + 32, k), k));
+                }, my_probes);
                 if (m < 0)
                     ++my_missing;
                 else if (__popc((uint32_t)m & 15u) > 1 || __popc((uint32_t)m >> 4) > 1)
@@ -1126,22 +883,28 @@ __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const 
         atomicAdd(&cnt->table_probes, block_probes);
 }
 
-// Resident workgroups per CU of both table modes' instantiations (the fewer).
+// Resident workgroups per CU (the fewest over the kernel's table modes and
+// slot words).
 hipError_t pass2_occupancy(KernelId which, int W, int *blocks) {
-    return by_width(W, [&](auto tag) {
-        using T = decltype(tag);
-        const void *fn[2] = {
-            which == K_RECORD ? (const void *)k_record<T, true> : (const void *)k_decide<T, true>,
-            which == K_RECORD ? (const void *)k_record<T, false> : (const void *)k_decide<T, false>};
-        int n[2] = {0, 0};
-        for (int i = 0; i < 2; ++i) {
-            const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n[i], fn[i], BLOCK, 0);
-            if (e != hipSuccess)
-                return e;
-        }
-        *blocks = std::min(n[0], n[1]);
-        return hipSuccess;
-    });
+    *blocks = 1 << 30;
+    for (uint32_t v = 0; v < 4; ++v) {
+        TableArgs t{};
+        t.pow2 = v & 1;
+        t.packed = v >> 1;
+        const hipError_t e = by_table(W, t, [&](auto tag, auto p2, auto ref) {
+            using T = decltype(tag);
+            constexpr bool P2 = decltype(p2)::value, REF = decltype(ref)::value;
+            int n = 0;
+            const void *fn = which == K_RECORD ? (const void *)k_record<T, P2, REF>
+                                               : (const void *)k_decide<T, P2, REF>;
+            const hipError_t x = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, BLOCK, 0);
+            *blocks = std::min(*blocks, n);
+            return x;
+        });
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_decide(int W, const SeqArgs &a, const SentArgs &sa, const uint64_t *c1,
@@ -1149,14 +912,9 @@ hipError_t launch_decide(int W, const SeqArgs &a, const SentArgs &sa, const uint
                          uint32_t grid, hipStream_t s) {
     if (a.n_tiles == 0)
         return hipSuccess;
-    return by_width(W, [&](auto tag) {
-        using T = decltype(tag);
-        if (pool.pow2)
-            hipLaunchKernelGGL((k_decide<T, true>), dim3(grid), dim3(BLOCK), 0, s, a, sa, c1, pool,
-                               jbits, accumulate, cnt);
-        else
-            hipLaunchKernelGGL((k_decide<T, false>), dim3(grid), dim3(BLOCK), 0, s, a, sa, c1,
-                               pool, jbits, accumulate, cnt);
+    return by_table(W, pool, [&](auto tag, auto p2, auto ref) {
+        hipLaunchKernelGGL((k_decide<decltype(tag), decltype(p2)::value, decltype(ref)::value>),
+                           dim3(grid), dim3(BLOCK), 0, s, a, sa, c1, pool, jbits, accumulate, cnt);
         return hipGetLastError();
     });
 }

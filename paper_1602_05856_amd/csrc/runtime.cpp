@@ -658,22 +658,34 @@ static std::vector<SetDesc> set_descs(const tp_plan *p) {
 
 bool tp::table_packed(const tp_plan *p) { return p->k <= PACKED_MAX_K; }
 
-bool tp::table_himask(const tp_plan *p) {
-    return p->W >= 2 && 2 * p->k <= 64 * (uint32_t)(p->W - 1) + HIMASK_SHIFT;
+// Reference slot words: the positions take the fewest bits that leave their
+// field never all ones (so no word equals an empty slot), the tag the rest.
+uint32_t tp::table_ref_shift(const tp_plan *p) {
+    uint32_t bits = 1;
+    while (p->total > (1ull << bits) - 1)
+        ++bits;
+    return bits + 8;
+}
+
+// Bytes that tp_config.table_budget counts per slot: the key's words and an
+// edge-mask byte, or the mask inside the top word where it fits.  (A slot
+// takes 8 bytes whatever k; the budget's unit stays, since the rounds it
+// leads to decide a run's first-pass candidates.)
+static uint64_t budget_slot_bytes(const tp_plan *p) {
+    const bool in_word = table_packed(p) || (p->W >= 2 && 2 * p->k <= 64u * (p->W - 1) + 54);
+    return 8ull * p->W + (in_word ? 0 : 1);
 }
 
 std::vector<uint64_t> tp::table_caps(const tp_plan *p, const std::vector<double> &keys,
                                      bool *pow2) {
     const size_t nsets = keys.size();
     const double load = p->cfg.table_load;
-    const uint64_t slot_bytes =
-        8ull * p->W + (table_packed(p) || table_himask(p) ? 0 : 1);
     std::vector<uint64_t> exact(nsets), caps(nsets);
     uint64_t waste = 0;
     for (size_t i = 0; i < nsets; ++i) {
         const double want = std::min(std::ceil(std::max(keys[i], 1.0) / load), (double)MAX_TABLE);
         exact[i] = std::max((uint64_t)want, MIN_TABLE);
-        waste += (pow2_ceil(exact[i]) - exact[i]) * slot_bytes;
+        waste += (pow2_ceil(exact[i]) - exact[i]) * 8;
     }
     *pow2 = p->cfg.table_shape == 1 || (p->cfg.table_shape == 0 && waste <= POW2_WASTE_BYTES);
     for (size_t i = 0; i < nsets; ++i) {
@@ -1190,8 +1202,6 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
         if (a.sketch)
             est = hll_estimate(hll.data());
         const bool packed = table_packed(p);
-        // wide keys with room in the top word carry their mask there
-        const bool himask = table_himask(p);
         {
             // keys <= candidate positions; one set: the sketch's estimate
             // (+15% for its error) when smaller.  A table that overflows is
@@ -1210,10 +1220,9 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             // each round's table (about 1/rounds of this one) fits
             const uint64_t budget = p->cfg.table_budget;
             if (split && rounds == 1 && budget) {
-                const uint64_t slot_bytes = 8ull * W + (packed || himask ? 0 : 1);
                 uint64_t bytes = 0;
                 for (uint32_t i = 0; i < nsets; ++i)
-                    bytes += (caps[i] + TABLE_TAIL) * slot_bytes;
+                    bytes += (caps[i] + TABLE_TAIL) * budget_slot_bytes(p);
                 if (bytes > budget) {
                     const double want = std::ceil(1.15 * (double)bytes / (double)budget);
                     *split = (uint32_t)std::min<double>(MAX_ROUNDS, std::max(2.0, want));
@@ -1238,30 +1247,27 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             }
             TableArgs t;
             t.packed = packed ? 1u : 0u;
-            t.himask = himask ? 1u : 0u;
+            t.ref_shift = table_ref_shift(p);
             // the last run's outputs are dead from here on: spare them if the
             // table does not fit beside them
             const std::initializer_list<DevBuf *> outputs = {&p->d_pos, &p->d_vertex, &p->d_strand,
                                                              &p->d_edges, &p->d_rbin};
             {
                 const int rcr = reserve(p, {{&p->d_keys, slots * 8},
-                                            {&p->d_masks, !packed && !himask ? slots : 0},
-                                            {&p->d_keys_hi, W >= 2 ? slots * 8 : 0},
-                                            {&p->d_keys_mid, W == 4 ? slots * 16 : 0}});
+                                            {&p->d_seq, packed ? 0 : p->input_bytes}});
                 if (rcr)
                     return rcr;
             }
             HIPCHK(ensure_spare(p->d_keys, slots * 8, outputs));
-            if (!packed && !himask)
-                HIPCHK(ensure_spare(p->d_masks, slots, outputs));
-            if (W >= 2)
-                HIPCHK(ensure_spare(p->d_keys_hi, slots * 8, outputs));
-            if (W == 4)
-                HIPCHK(ensure_spare(p->d_keys_mid, slots * 16, outputs));
+            if (!packed && round == 0 && round_attempts == 1) {
+                // the table names positions of this run's input, which the
+                // caller may change or free afterwards: a copy of it beside
+                // the table keeps tp_debug_table's keys readable
+                HIPCHK(ensure_spare(p->d_seq, p->input_bytes, outputs));
+                HIPCHK(hipMemcpyAsync(p->d_seq.p, d_input, p->input_bytes,
+                                      hipMemcpyDeviceToDevice, s));
+            }
             t.keys = p->d_keys.as<unsigned long long>();
-            t.keys_hi = W >= 2 ? p->d_keys_hi.as<unsigned long long>() : nullptr;
-            t.keys_mid = W == 4 ? p->d_keys_mid.as<unsigned long long>() : nullptr;
-            t.masks = packed || himask ? nullptr : p->d_masks.as<uint32_t>();
             t.cap_m = t.cap_e = 0;  // per set, from its descriptor
             t.lomask = 0;
             t.pow2 = p->table_pow2 ? 1u : 0u;
@@ -1292,9 +1298,9 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
                 if (rbin) {
                     TableArgs tail = t;
                     tail.keys = t.keys + p->sets[0].table_cap;
-                    HIPCHK(launch_table_clear(W, tail, TABLE_TAIL, q));
+                    HIPCHK(launch_table_clear(tail, TABLE_TAIL, q));
                 } else {
-                    HIPCHK(launch_table_clear(W, t, slots, q));
+                    HIPCHK(launch_table_clear(t, slots, q));
                 }
                 if (qbase)  // the record's and the decision's tile queues
                     HIPCHK(launch_zero(qbase + 2 * NXCD, 2 * NXCD * sizeof(unsigned int), q));
@@ -1398,8 +1404,7 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
     const uint64_t nblocks = (p->bitmap_words + SCAN_WORDS - 1) / SCAN_WORDS;
     // the exact tables are dead from here on: spare them if the outputs do
     // not fit beside them (the next run allocates them again)
-    const std::initializer_list<DevBuf *> tables = {&p->d_keys, &p->d_keys_hi, &p->d_keys_mid,
-                                                    &p->d_masks};
+    const std::initializer_list<DevBuf *> tables = {&p->d_keys};
     // the binned record's own scratch goes first when the outputs must grow
     if (p->d_rbin.p && (p->d_pos.cap < nj * 8 || p->d_vertex.cap < nj * 8 * W ||
                         p->d_strand.cap < nj || p->d_edges.cap < ne * sizeof(tp_edge)))
@@ -1714,54 +1719,54 @@ extern "C" int tp_debug_table(const tp_plan *p, uint32_t set, uint64_t *keys, ui
                                "table was released to fit the outputs)");
     const uint64_t off = p->last_off[set], slots = p->last_cap[set] + TABLE_TAIL;
     const int W = p->W;
-    const bool packed = table_packed(p), himask = table_himask(p);
-    std::vector<uint64_t> lo(slots), hi, mid;
-    std::vector<uint8_t> mk;
+    const bool packed = table_packed(p);
+    const uint32_t ref_shift = table_ref_shift(p);
+    std::vector<uint64_t> word(slots), seq;
     HIPCHK(hipDeviceSynchronize());
-    HIPCHK(hipMemcpy(lo.data(), p->d_keys.as<uint64_t>() + off, slots * 8, hipMemcpyDeviceToHost));
-    if (W >= 2) {
-        hi.resize(slots);
-        HIPCHK(hipMemcpy(hi.data(), p->d_keys_hi.as<uint64_t>() + off, slots * 8,
-                         hipMemcpyDeviceToHost));
-    }
-    if (W == 4) {
-        mid.resize(2 * slots);
-        HIPCHK(hipMemcpy(mid.data(), p->d_keys_mid.as<uint64_t>() + 2 * off, slots * 16,
-                         hipMemcpyDeviceToHost));
-    }
-    if (!packed && !himask) {
-        mk.resize(slots);
-        HIPCHK(hipMemcpy(mk.data(), p->d_masks.as<uint8_t>() + off, slots, hipMemcpyDeviceToHost));
-    }
-    // occupied slots: the key word (one word) or the top word (wide) is not empty
+    HIPCHK(hipMemcpy(word.data(), p->d_keys.as<uint64_t>() + off, slots * 8,
+                     hipMemcpyDeviceToHost));
     uint64_t n = 0;
     for (uint64_t i = 0; i < slots; ++i)
-        n += (W == 1 ? lo[i] : hi[i]) != EMPTY_KEY;
+        n += word[i] != EMPTY_KEY;
     *n_out = n;
     if (n > cap)
         return fail(TP_EINVAL, "cap is smaller than the number of table entries");
     if (n && (!keys || !masks))
         return fail(TP_EINVAL, "keys or masks is NULL");
+    if (!packed && n) {
+        seq.resize(p->input_bytes / 8);
+        HIPCHK(hipMemcpy(seq.data(), p->d_seq.p, seq.size() * 8, hipMemcpyDeviceToHost));
+    }
+    // the normalised k-mer at global base index pos, low word first
+    auto kmer_at = [&](uint64_t pos, uint64_t *kw) {
+        uint64_t f[4] = {0, 0, 0, 0}, r[4] = {0, 0, 0, 0};
+        auto put = [](uint64_t *v, uint32_t digit, uint64_t base) {  // base * 4^digit
+            v[digit / 32] |= base << (2 * (digit % 32));
+        };
+        for (uint32_t t = 0; t < p->k; ++t) {
+            const uint64_t c = (seq[(pos + t) / 32] >> (2 * ((pos + t) % 32))) & 3;
+            put(f, p->k - 1 - t, c);
+            put(r, t, 3 - c);
+        }
+        bool rc = false;
+        if (!(p->flags & TP_FLAG_SINGLE_STRAND))
+            for (int i = 3; i >= 0; --i)
+                if (f[i] != r[i]) {
+                    rc = r[i] < f[i];
+                    break;
+                }
+        for (int i = 0; i < W; ++i)
+            kw[i] = rc ? r[i] : f[i];
+    };
     uint64_t e = 0;
     for (uint64_t i = 0; i < slots; ++i) {
-        const uint64_t top = W == 1 ? lo[i] : hi[i];
-        if (top == EMPTY_KEY)
+        if (word[i] == EMPTY_KEY)
             continue;
-        uint64_t *kw = keys + e * W;
-        uint8_t m = 0;
-        if (W == 1) {
-            kw[0] = packed ? top >> 8 : top;
-            m = packed ? (uint8_t)(top & 0xFF) : mk[i];
-        } else {
-            kw[0] = lo[i];
-            if (W == 4) {
-                kw[1] = mid[2 * i];
-                kw[2] = mid[2 * i + 1];
-            }
-            kw[W - 1] = himask ? top & HIKEY_BITS : top;
-            m = himask ? (uint8_t)((top >> HIMASK_SHIFT) & 0xFF) : mk[i];
-        }
-        masks[e++] = m;
+        if (packed)
+            keys[e] = word[i] >> 8;
+        else
+            kmer_at((word[i] & ((1ull << ref_shift) - 1)) >> 8, keys + e * W);
+        masks[e++] = (uint8_t)(word[i] & 0xFF);
     }
     return TP_OK;
 }

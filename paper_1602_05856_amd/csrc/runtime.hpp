@@ -147,9 +147,10 @@ void class_partition(const uint64_t *e, uint32_t classes, uint32_t *bound);
 // *pow2 receives the mode.  (tp_run sizes from candidate counts and the
 // sketch, the caller-memory run from a stated bound.)
 std::vector<uint64_t> table_caps(const tp_plan *p, const std::vector<double> &keys, bool *pow2);
-// Table layout flags of a plan: packed one-word slots, mask in the top word.
+// Slot words of a plan's exact tables: packed (else reference words), and the
+// first tag bit of reference words.
 bool table_packed(const tp_plan *p);
-bool table_himask(const tp_plan *p);
+uint32_t table_ref_shift(const tp_plan *p);
 // Set descriptors for given table capacities (offsets laid out in order).
 std::vector<SetDesc> set_descs_for(const tp_plan *p, const std::vector<uint64_t> &caps, bool pow2,
                                    uint64_t *slots);
@@ -186,10 +187,10 @@ struct WsState {
              o_gbase = 0, o_sent_raw = 0, o_sent = 0, o_sent_owner = 0, o_pf = 0, o_bloom = 0,
              o_c1 = 0, o_c1u = 0,
              o_j = 0, o_cnt = 0, o_set_cnt = 0, o_census = 0, o_bounds = 0, o_keys = 0,
-             o_keys_hi = 0, o_keys_mid = 0, o_masks = 0, o_blockcnt = 0, o_blockoff = 0,
+             o_blockcnt = 0, o_blockoff = 0,
              o_queue = 0;
     uint64_t slots = 0, nblocks = 0;
-    bool pow2 = true, packed = false, himask = false;
+    bool pow2 = true;
     std::vector<SetDesc> desc;
     std::vector<uint64_t> bloom_starts;
     uint32_t grid[K_COUNT] = {};
@@ -228,7 +229,7 @@ struct tp_plan {
     bool order_uploaded = false;           // tile_order on the device matches cfg
     tp::DevBuf d_tiles, d_tile_info, d_sets, d_bloom_starts, d_strings, d_gbase;
     tp::DevBuf d_sent_raw, d_sent, d_sent_owner, d_pf, d_bloom, d_c1, d_j, d_cnt, d_set_cnt, d_hll;
-    tp::DevBuf d_keys, d_keys_hi, d_keys_mid, d_masks, d_blockcnt, d_blockoff;
+    tp::DevBuf d_keys, d_seq, d_blockcnt, d_blockoff;  // d_seq: the input a reference table names
     tp::DevBuf d_pos, d_vertex, d_strand, d_edges, d_joff;
     tp::DevBuf d_c1u, d_census;            // rounds: union of candidates, class census
     tp::DevBuf d_bin;                      // binned fill: counts, offsets, region starts
@@ -260,7 +261,7 @@ struct tp_plan {
         for (tp::DevBuf *b : {&d_tiles, &d_tile_info, &d_sets, &d_bloom_starts, &d_strings,
                               &d_gbase, &d_sent_raw, &d_sent, &d_sent_owner, &d_pf, &d_bloom,
                               &d_c1, &d_j,
-                              &d_cnt, &d_set_cnt, &d_hll, &d_keys, &d_keys_hi, &d_keys_mid, &d_masks,
+                              &d_cnt, &d_set_cnt, &d_hll, &d_keys, &d_seq,
                               &d_blockcnt, &d_blockoff, &d_pos, &d_vertex, &d_strand,
                               &d_edges, &d_joff, &d_c1u, &d_census, &d_bin, &d_queue, &d_rbin})
             f(*b);

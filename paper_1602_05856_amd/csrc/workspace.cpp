@@ -56,8 +56,6 @@ extern "C" int tp_plan_workspace_layout(tp_plan *p, double key_fraction, double 
     const uint64_t W = (uint64_t)p->W;
     const bool pass1_only = (p->flags & TP_FLAG_PASS1_ONLY) != 0;
     const uint32_t rounds = p->rounds;
-    w.packed = table_packed(p);
-    w.himask = table_himask(p);
 
     // exact tables for at most key_fraction x positions keys per set
     std::vector<double> keys(nsets);
@@ -99,12 +97,8 @@ extern "C" int tp_plan_workspace_layout(tp_plan *p, double key_fraction, double 
     w.o_set_cnt = c.take(nsets * sizeof(SetCounters));
     w.o_census = rounds > 1 ? c.take((uint64_t)nsets * CLASS_Q * 8) : 0;
     w.o_bounds = rounds > 1 ? c.take((uint64_t)nsets * (rounds + 1) * 4) : 0;
-    if (!pass1_only) {
+    if (!pass1_only)
         w.o_keys = c.take(w.slots * 8);
-        w.o_keys_hi = W >= 2 ? c.take(w.slots * 8) : 0;
-        w.o_keys_mid = W == 4 ? c.take(w.slots * 16) : 0;
-        w.o_masks = (!w.packed && !w.himask) ? c.take(align_up(w.slots, 4)) : 0;
-    }
     w.o_blockcnt = c.take(w.nblocks * 4);
     w.o_blockoff = c.take((w.nblocks + 1) * 8);
     w.o_queue = c.take(4 * NXCD * sizeof(unsigned int));  // tile queues of the tile kernels
@@ -229,13 +223,10 @@ int ws_run(tp_plan *p, const uint8_t *d_input, uint8_t *base, uint8_t *outb, hip
     uint64_t *jbits = (uint64_t *)(base + w.o_j);
 
     TableArgs t{};
-    t.packed = w.packed ? 1u : 0u;
-    t.himask = w.himask ? 1u : 0u;
+    t.packed = table_packed(p) ? 1u : 0u;
+    t.ref_shift = table_ref_shift(p);
     t.pow2 = w.pow2 ? 1u : 0u;
     t.keys = (unsigned long long *)(base + w.o_keys);
-    t.keys_hi = W >= 2 ? (unsigned long long *)(base + w.o_keys_hi) : nullptr;
-    t.keys_mid = W == 4 ? (unsigned long long *)(base + w.o_keys_mid) : nullptr;
-    t.masks = (w.packed || w.himask) ? nullptr : (uint32_t *)(base + w.o_masks);
 
     // tile queues (tp_config.tile_queue): NXCD counters per tile kernel
     unsigned int *qbase = p->cfg.tile_queue ? (unsigned int *)(base + w.o_queue) : nullptr;
@@ -267,7 +258,7 @@ int ws_run(tp_plan *p, const uint8_t *d_input, uint8_t *base, uint8_t *outb, hip
                                nsets, scnt, s));
         if (pass1_only)
             continue;
-        HIPCHK(launch_table_clear(W, t, w.slots, s));
+        HIPCHK(launch_table_clear(t, w.slots, s));
         HIPCHK(launch_record(W, queued(K_RECORD), c1, t, cnt, w.grid[K_RECORD], s));
         HIPCHK(launch_decide(W, queued(K_DECIDE), sa, c1, t, jbits, round > 0, cnt,
                              w.grid[K_DECIDE], s));

@@ -99,16 +99,15 @@ def algorithmic_bytes(c, bases, k, W, h, blocked, filter_bytes, table_bytes, non
 
 def binned_fill_bytes(st, c, bases, filter_bytes, fill_ms):
     """Streaming bytes of the binned fill (one round): the input read once;
-    one 8-byte slot per position staged and read back; every item (one per
-    edge position) written by the bucket scatter, read twice and written by
-    the region split, read by the apply; the filter written by the first
-    chunk and read and written by every later one.  These replace the
-    direct-probe bytes in the fill's roofline entry when the fill ran
-    binned (the model follows the schedule)."""
+    every item (4 bytes, one per edge position) written to its bucket and
+    read back, and, where a filter above 128 MiB has several regions to a
+    bucket, written to its region and read once more; the filter zeroed, then
+    read and written by every chunk.  These replace the direct-probe bytes in
+    the fill's roofline entry when the fill ran binned (the model follows the
+    schedule)."""
     chunks = st["fill_chunks"]
-    items = c["edge_positions"]
-    nbytes = (bases / 4 + 16 * c["positions"] + 8 * items * (1 + 3 + 1) +
-              filter_bytes * (2 * chunks - 1))
+    levels = 1 if filter_bytes <= 128 << 20 else 2
+    nbytes = (bases / 4 + 8 * levels * c["edge_positions"] + filter_bytes * (2 * chunks + 1))
     gbs = nbytes / (fill_ms * 1e-3) / 1e9
     return {"chunks": chunks, "streaming_bytes": nbytes, "achieved_gbs": gbs,
             "frac": gbs / HBM_PEAK_GBS}
@@ -775,10 +774,10 @@ def membench_leg(args):
 
 # ----------------------------------------------------------------- profiles
 
-# kernels inside each timed phase of a run (the binned fill is five launches
-# per chunk)
-PROFILE_KERNELS = (("k_fill", "fill"), ("k_bin_count", "fill"), ("k_bin_scan", "fill"),
-                   ("k_bin_scatter", "fill"), ("k_bin_split", "fill"), ("k_bin_apply", "fill"),
+# kernels inside each timed phase of a run (the binned fill is two or three
+# launches per chunk)
+PROFILE_KERNELS = (("k_fill", "fill"), ("k_bin_items", "fill"), ("k_bin_split", "fill"),
+                   ("k_bin_apply", "fill"),
                    ("k_query", "query"), ("k_popcount", "query"),
                    ("k_record", "record"), ("k_rbin_", "record"),
                    ("k_decide", "decide"), ("k_emit", "compact"),

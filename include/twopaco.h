@@ -304,22 +304,24 @@ typedef struct {
                               workgroup takes this many consecutive tiles
                               (2048 positions each) of its walk per visit,
                               1..64                                          */
-    uint32_t fill_binned;  /* blocked filter, fill: 0 = binned when some
-                              set's filter is at least 1 GiB, else atomic;
-                              1 = atomic (each edge's block loaded, then an
-                              atomicOr for bits still clear, in HBM); 2 =
-                              binned: per chunk of positions, every
-                              edge's filter effect is written as an
-                              8-byte item, the items partitioned by 64 KiB
-                              region of the pool in two streaming passes,
-                              and each region's items ORed into the region
-                              in LDS.  Same filter bits either way.  Binned
-                              needs 16 bytes per chunk position of scratch,
-                              held in the exact table's key buffer (the
-                              table is not live during the fill), and a
-                              pool of at most 32 GiB (else atomic).  Runs
-                              on caller memory (tp_run_ws, tp_run_noalloc)
-                              always fill atomically.                        */
+    uint32_t fill_binned;  /* blocked filter, fill: 0 = binned unless the
+                              filter pool is large for the positions (more
+                              than 24 bytes each and 128 MiB besides), else
+                              atomic; 1 = atomic (each edge's block loaded,
+                              then an atomicOr for bits still clear, in HBM);
+                              2 = binned: per chunk of positions, every
+                              edge's filter effect is written as a 4-byte
+                              item, the items partitioned by region of the
+                              pool (64 or 128 KiB) in one or two streaming
+                              passes, and each region's items ORed into the
+                              region in LDS.  Same filter bits either way.
+                              Binned needs about 4.5 bytes per chunk position
+                              and pass of scratch, held in the exact table's
+                              key buffer (the table is not live during the
+                              fill), and a pool of at most 32 GiB; where the
+                              scratch is not to be had the fill is atomic.
+                              Runs on caller memory (tp_run_ws,
+                              tp_run_noalloc) always fill atomically.        */
     uint32_t bin_chunk_tiles; /* binned fill: tiles (2048 positions each)
                               per chunk, 1..2^20; 0 = 2^20 (2^31
                               positions), or more, up to 2^22, when the

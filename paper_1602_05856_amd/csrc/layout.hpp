@@ -46,20 +46,27 @@ constexpr uint32_t TABLE_BLOCK_LOG2 = 13;          // any-size tables: blocks of
 static_assert(TABLE_TAIL % TABLE_ALIGN == 0, "set regions stay aligned");
 constexpr uint32_t CLASS_Q_LOG2 = 10;              // k-mer class subranges (rounds)
 constexpr uint32_t CLASS_Q = 1u << CLASS_Q_LOG2;
-// Binned fill (blocked filter): the filter pool in regions of BIN_REGION
-// blocks (one workgroup's LDS), BIN_SUB regions to a bucket.
-constexpr uint32_t BIN_REGION_LOG2 = 13;           // 8192 blocks = 64 KiB
-constexpr uint32_t BIN_REGION = 1u << BIN_REGION_LOG2;
-constexpr uint32_t BIN_SUB_LOG2 = 9;
-constexpr uint32_t BIN_SUB = 1u << BIN_SUB_LOG2;
-constexpr uint32_t BIN_MAX_BUCKETS = 1024;         // pools up to 2^32 blocks (32 GiB)
+// Binned fill (blocked filter): the filter pool in regions of up to 2^14
+// blocks (one workgroup's LDS), buckets of one or more regions.
+constexpr uint32_t BIN_REGION_LOG2 = 13;           // 8192 blocks = 64 KiB (2^14 at most)
+constexpr uint32_t BIN_BUCKETS = 1024;
+constexpr uint32_t BIN_MAX_BUCKETS = 2048;         // pools up to 2^32 blocks (32 GiB)
+constexpr uint32_t BIN_LOCAL_LOG2 = 21;            // an item's block bits: buckets of up to 2^21 blocks
+constexpr uint32_t BIN_BLOCK = 1024;               // threads of the binned fill's kernels
+constexpr uint32_t BIN_PER = 16;                   // items per thread per batch
+constexpr uint32_t BIN_BATCH = BIN_BLOCK * BIN_PER;
+constexpr uint32_t BIN_TILES = BIN_BATCH / TILE;   // tiles per batch (of one- and two-word k-mers)
+constexpr uint32_t BIN_CHUNK_TILES_MAX = 1u << 20; // 2^31 positions per chunk (explicit)
+// Binned record: buckets of RBIN_SUB table blocks.
+constexpr uint32_t RBIN_MAX_BUCKETS = 1024;
+constexpr uint32_t RBIN_SUB_LOG2 = 9;
+constexpr uint32_t RBIN_SUB = 1u << RBIN_SUB_LOG2;
 constexpr uint32_t BIN_SPLIT_BLOCK = 1024;         // threads of the bucket split
 constexpr uint32_t BIN_SCAN_BLOCK = 1024;          // threads of the offset scan
-constexpr uint32_t BIN_CHUNK_TILES_MAX = 1u << 20; // 2^31 positions per chunk (explicit)
 constexpr uint32_t BIN_SPLIT_PER = 16;             // bucket split: items per thread per batch
 constexpr uint32_t BIN_SCATTER_PER = 16;           // bucket scatter: items per thread per batch
 constexpr uint32_t BIN_SCATTER_BLOCK = 1024;       // bucket scatter: threads per workgroup
-constexpr uint32_t BIN_APPLY_BLOCK = 1024;         // threads of a region's (a block's) apply
+constexpr uint32_t BIN_APPLY_BLOCK = 1024;         // threads of a block's apply
 constexpr uint32_t BIN_WG_PER_CU = 8;              // count and scatter workgroups per CU
 
 // A string of S: a maximal N-free run of one genome, of length >= k.
@@ -204,28 +211,41 @@ hipError_t launch_sentinels(int W, const SeqArgs &a, void *raw, void *tab, uint3
                             uint64_t tab_slots, uint32_t *prefilter, uint32_t pf_log2,
                             hipStream_t s);
 // a1: insert every normalised (k+1)-mer into its set's Bloom filter.
-// Binned fill of a blocked filter pool (the same bits as launch_fill): per
-// chunk of tiles, every edge's filter effect becomes one 64-bit item
-// (global block << 16 | offset | stride << 6 | pair << 12), the items are
-// staged in position order, partitioned by bucket and then by region in two
-// streaming passes, and one workgroup per region applies its items to the
-// region with LDS atomics and writes it back.  Scratch: items_a and items_b
-// hold one slot per position of a chunk; counts and offsets one entry per
-// (bucket, workgroup), region_off one per region of the last bucket rounded
-// up.
+// Binned fill of a blocked filter pool (the same bits as launch_fill; the
+// pool zeroed beforehand): per chunk of tiles, every edge's filter effect
+// becomes a 4-byte item of its bucket, the items of a bucket of several
+// regions are split by region, and one workgroup per region ORs its items in
+// LDS and writes the region back.
 struct BinArgs {
-    uint64_t *items_a;         // chunk items by bucket
-    uint64_t *items_b;         // chunk items in position order, then by region (4-byte)
-    uint32_t *counts;          // [bucket * grid + workgroup]
-    uint64_t *offsets;         // exclusive scan of counts, n + 1 entries
-    uint64_t *region_off;      // per region: first item in items_b; then the total
-    uint64_t tile_lo, tile_hi; // the chunk's tiles, memory order
-    uint64_t n_blocks;         // 64-bit blocks of the filter pool
-    uint32_t n_buckets;        // ceil(regions / BIN_SUB)
-    uint32_t grid;             // workgroups of the count and scatter kernels
-    uint32_t first;            // first chunk: regions start from zero
-    uint32_t pad;
+    uint32_t *items_a;          // items by bucket
+    uint32_t *items_b;          // items by region (buckets of several regions)
+    unsigned long long *cursor; // per bucket, then (several regions) per region: items claimed
+    const uint64_t *off;        // room: per bucket its first item in items_a, then the end
+    const uint64_t *roff;       // per region its first item in items_b, then the end
+    uint64_t t_lo, t_hi;        // the chunk: a range of the first-pass tile order
+    uint64_t n_blocks;          // 64-bit blocks of the filter pool
+    uint32_t n_buckets, bucket_log2, region_log2, n_regions;
+    uint32_t slices;            // batches a bucket has room for (the split's grid)
+    uint32_t n_cu;
+    SetCounters *popcount;      // last chunk of a one-set pool: its filter popcount, else null
 };
+// Blocks of a bucket and of a region for a pool: one region per bucket where
+// BIN_BUCKETS regions cover the pool (the larger regions only where they make
+// that so: they leave one apply workgroup per CU instead of two), else about
+// 256 buckets of up to 2^21 blocks, split by region afterwards (a batch's
+// longer runs: 654 Mbp over 128 filters of 1.4 GB in all, k_bin_items 4.15 ms
+// against 4.67 with 1024 buckets).  Pools beyond 16 GiB need up to 2048
+// buckets, for an item's block bits.
+inline void bin_shape(uint64_t n_blocks, uint32_t *bucket_log2, uint32_t *region_log2) {
+    const uint64_t last = n_blocks ? n_blocks - 1 : 0;
+    *region_log2 = BIN_REGION_LOG2;
+    if ((last >> BIN_REGION_LOG2) >= BIN_BUCKETS && (last >> (BIN_REGION_LOG2 + 1)) < BIN_BUCKETS)
+        ++*region_log2;
+    *bucket_log2 = *region_log2;
+    if ((last >> *region_log2) >= BIN_BUCKETS)
+        while ((last >> *bucket_log2) >= BIN_BUCKETS / 4 && *bucket_log2 < BIN_LOCAL_LOG2)
+            ++*bucket_log2;
+}
 hipError_t launch_fill_binned(int W, const SeqArgs &a, const BloomArgs &pool, Counters *cnt,
                               BinArgs b, uint32_t tiles_per_chunk, hipStream_t s);
 hipError_t launch_fill(int W, const SeqArgs &a, const BloomArgs &pool, Counters *cnt,
@@ -264,7 +284,7 @@ struct RecBinArgs {
     unsigned long long *ctl;   // [0] staging items claimed, [1] nonzero: scratch too small
     uint64_t cap;              // items each of items_a and items_b hold
     uint64_t r_lo, r_hi;       // the pass's home blocks
-    uint32_t n_buckets;        // ceil((r_hi - r_lo) / BIN_SUB)
+    uint32_t n_buckets;        // ceil((r_hi - r_lo) / RBIN_SUB)
     uint32_t grid;             // workgroups of the count, histogram and scatter kernels
 };
 // table: set 0's table (keys, cap_m, cap_e, lomask, pow2 filled in).

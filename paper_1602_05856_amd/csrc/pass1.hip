@@ -325,275 +325,302 @@ hipError_t launch_fill(int W, const SeqArgs &a, const BloomArgs &pool, Counters 
 //
 // The same filter as k_fill, built without random atomics: a chunk of tiles
 // at a time, every edge's filter effect becomes an item, the items are
-// partitioned by region of the pool in two streaming passes (bucket, then
-// region within the bucket), and each region is applied in LDS.  A filter is
-// the OR of its edges' bits, so the order of application does not matter.
+// partitioned by region of the pool, and each region is applied in LDS.  A
+// filter is the OR of its edges' bits, so the order of application does not
+// matter, and an item that finds no room in its bucket is applied to the pool
+// directly (the pool is zeroed first and a region is read before its items
+// are ORed in).
 //
-//   k_bin_count    per workgroup (a static range of the chunk's tiles): its
-//                  items, staged in position order, and counted per bucket
-//   k_bin_scan     exclusive scan of the counts, bucket-major: each
-//                  (bucket, workgroup) pair gets its own range of items_a
-//   k_bin_scatter  the staged items, each written to its pair's range
-//   k_bin_split    per bucket: its items counted and written by region, as
-//                  4-byte items (the block's low bits and the bits it sets)
-//
-// The scatter and the split sort each batch by destination in LDS first, so
-// that a destination's items of the batch leave as one contiguous run.
+//   k_bin_items    batches of 8 tiles: the items of the batch, sorted by
+//                  bucket in LDS, appended to their buckets
+//   k_bin_split    buckets of several regions: batches of a bucket's items,
+//                  sorted by region in LDS, appended to their regions
 //   k_bin_apply    per region: the region's blocks in LDS, its items ORed in,
 //                  the blocks written back
+//
+// An item is 4 bytes: its block within the bucket (21 bits), and the 11 bits
+// that fix the filter bits it sets -- the pairs' masks are 32 templates (one
+// per odd stride d) rotated by s = a + j*h*d mod 64, so (d, s) stand for the
+// offset, stride and pair.  Room per bucket and region is laid out from the
+// edge count (a hash spreads them evenly), so nothing is counted beforehand:
+// an item is written and read once per level, 8 or 16 bytes an edge in all.
 
-constexpr uint32_t BIN_BUCKET_SHIFT = 16 + BIN_REGION_LOG2 + BIN_SUB_LOG2;
-constexpr uint32_t BIN_REGION_SHIFT = 16 + BIN_REGION_LOG2;
-constexpr uint32_t BIN_PER = TILE / BLOCK;  // positions per thread per tile
-static_assert(BIN_MAX_BUCKETS % BLOCK == 0, "bucket scan: whole counters per thread");
+constexpr uint32_t BIN_EFFECT_BITS = 11;
 
-// The filter effect of edge e: its block in the pool (the set's first block
-// plus its block in the set's filter), and the offset, stride and pair that
-// fix its bits there.
-template <class T>
-__device__ __forceinline__ uint64_t bin_item(const BloomArgs &f, uint64_t block0,
-                                             const Strands<T> &e, uint32_t k, bool single) {
-    const T mid_ones = KT<T>::ones(2 * (k - 1));
-    const uint32_t x = (uint32_t)(e.fwd >> (2 * k)), y = (uint32_t)(e.fwd & 3);
-    const MiddleKey key = middle_key((T)((e.fwd >> 2) & mid_ones), (T)((e.rc >> 2) & mid_ones),
-                                     single, f.mask >> 6);
-    const uint32_t j = pair_index(key.orient, x, y, e.fwd <= e.rc);
-    return (block0 + key.block) << 16 | (uint64_t)(key.a | key.d << 6 | j << 12);
+__device__ __forceinline__ uint32_t bin_effect(const MiddleKey &m, uint32_t j, uint32_t h) {
+    return (m.d >> 1) << 6 | ((m.a + j * h * m.d) & 63u);
 }
 
-// Every item of this workgroup's tiles (a contiguous share of the chunk), a
-// tile at a time: per thread, v[q] is the item of position
-// tile*TILE + q*BLOCK + thread, or BIN_NONE.  The edges are those k_fill
-// inserts: every (k+1)-mer within a string, of the round's class when there
-// are rounds.  tile_done(tile, v) is called by the whole workgroup for
-// every tile of the share.
-template <class T, class F>
-__device__ __forceinline__ void bin_walk(const SeqArgs &a, const BloomArgs &pool,
-                                         const BinArgs &b, uint64_t *w, F &&tile_done) {
-    const uint32_t L = a.k + 1;
-    const bool single = a.single != 0;
-    const uint64_t n = b.tile_hi - b.tile_lo;
-    const uint64_t per = (n + b.grid - 1) / b.grid;
-    const uint64_t t_lo = b.tile_lo + min(n, (uint64_t)blockIdx.x * per);
-    const uint64_t t_hi = b.tile_lo + min(n, (uint64_t)(blockIdx.x + 1) * per);
-    for (uint64_t tile = t_lo; tile < t_hi; ++tile) {
-        const TileInfo ti = a.tiles[tile];
-        const uint32_t lo = ti.str_lo, hi = ti.str_hi;
-        uint64_t v[BIN_PER];
-        if (lo == hi) {
+// Filter bits of template t (one per odd stride, t = bits u*d mod 64, u < h)
+// rotated left by s.
+__device__ __forceinline__ uint64_t rotl64(uint64_t t, uint32_t s) {
+    return t << s | t >> ((64u - s) & 63u);
+}
+
+__device__ __forceinline__ uint64_t stride_template(uint32_t d, uint32_t h) {
+    uint64_t m = 0;
+    for (uint32_t t = 0; t < h; ++t)
+        m |= 1ull << ((t * d) & 63u);
+    return m;
+}
+
+// An item without room: straight into the pool (as insert_blocked does).
+__device__ __forceinline__ uint32_t bin_direct(const BloomArgs &pool, uint64_t block,
+                                               uint32_t item) {
+    unsigned long long *p = (unsigned long long *)pool.words + block;
+    const uint64_t m = rotl64(stride_template((item >> 5 & 62u) | 1u, pool.h), item & 63u);
+    const unsigned long long cur =
+        __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((cur & m) == m)
+        return 0;
+    __hip_atomic_fetch_or(p, (unsigned long long)m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return 1;
+}
+
+// Shared memory of a sort of NT * PER items into at most NB bins.
+template <uint32_t NB, uint32_t NT, uint32_t PER> struct BinSort {
+    uint32_t srt[NT * PER];
+    uint32_t cnt[NB];        // a bin's items of the batch, then its first place in the bin
+    uint32_t start[NB + 1];  // a bin's first item in srt
+    uint32_t wtot[NT / 64], total;
+};
+
+// Append a batch of items, PER per thread, to their bins: at[q] is bin << 14 |
+// rank (the item's number in its bin, from an atomic add on sh.cnt), or ~0 for
+// none.  The items are sorted by bin in LDS and a bin's items written as one
+// run by a group of 2^lpb lanes; bin i has room for off[i+1] - off[i] items
+// from out + off[i], of which cursor[i] are claimed.  direct(bin, item) takes
+// an item without room.  sh.cnt is zero again on return.  Whole workgroup;
+// ends synchronised.
+template <uint32_t NB, uint32_t NT, uint32_t PER, class Direct>
+__device__ __forceinline__ void bin_append(BinSort<NB, NT, PER> &sh, const uint32_t (&item)[PER],
+                                           const uint32_t (&at)[PER], uint32_t nb, uint32_t lpb,
+                                           unsigned long long *cursor, const uint64_t *off,
+                                           uint32_t *out, Direct direct) {
+    constexpr uint32_t E = (NB + NT - 1) / NT;
+    __syncthreads();  // every rank is taken
+    // this thread's bins claim their room; the adds return while the scan runs
+    uint64_t base[E];
 #pragma unroll
-            for (uint32_t q = 0; q < BIN_PER; ++q)
-                v[q] = BIN_NONE;
-            tile_done(tile, v);
-            continue;
+    for (uint32_t e = 0; e < E; ++e) {
+        const uint32_t bin = threadIdx.x * E + e, c = bin < nb ? sh.cnt[bin] : 0;
+        base[e] = c ? atomicAdd(&cursor[bin], (unsigned long long)c) : 0;
+    }
+    lds_scan<NB, NT>(sh.cnt, sh.start, sh.wtot, &sh.total);
+    if (threadIdx.x == 0)
+        sh.start[NB] = sh.total;
+#pragma unroll
+    for (uint32_t e = 0; e < E; ++e)  // (a claim beyond 2^32 - 2^15 has no room anyhow)
+        if (threadIdx.x * E + e < NB)
+            sh.cnt[threadIdx.x * E + e] = (uint32_t)min(base[e], (uint64_t)0xFFFF7FFFu);
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q)
+        if (at[q] != ~0u)
+            sh.srt[sh.start[at[q] >> 14] + (at[q] & 0x3FFFu)] = item[q];
+    __syncthreads();
+    const uint32_t l = threadIdx.x & ((1u << lpb) - 1);
+    for (uint32_t bin = threadIdx.x >> lpb; bin < nb; bin += NT >> lpb) {
+        const uint32_t s0 = sh.start[bin], n = sh.start[bin + 1] - s0, b0 = sh.cnt[bin];
+        const uint64_t o = off[bin];
+        const uint32_t room = (uint32_t)min(off[bin + 1] - o, (uint64_t)0xFFFF7FFFu);
+        for (uint32_t i = l; i < n; i += 1u << lpb) {
+            const uint32_t it = sh.srt[s0 + i];
+            if (b0 + i < room)
+                out[o + b0 + i] = it;
+            else
+                direct(bin, it);
         }
-        const uint64_t t0 = tile * TILE;
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < NB; i += NT)
+        sh.cnt[i] = 0;
+    __syncthreads();
+}
+
+// Lanes that write a bin's run: about as many as a batch has items per bin.
+__device__ __forceinline__ uint32_t bin_lanes(uint32_t nb, uint32_t batch) {
+    uint32_t lpb = 6;
+    while (lpb > 3 && (nb << lpb) > batch)
+        --lpb;
+    return lpb;
+}
+
+// A batch's tile: its range of strings, its set's filter, and its string when
+// it has just one.
+struct BinTile {
+    uint64_t t0, gs, ge;
+    uint64_t mask;       // the set's filter bits - 1
+    uint32_t block0;     // its first block in the pool
+    uint32_t lo, hi, cls_lo, cls_hi;
+};
+
+// The edges are those k_fill inserts: every (k+1)-mer within a string, of the
+// round's class when there are rounds.
+template <class T, uint32_t NB, uint32_t NT, uint32_t PER, bool CLASSES>
+__global__ __launch_bounds__(NT) void k_bin_items(SeqArgs a, BloomArgs pool, BinArgs b,
+                                                         Counters *cnt) {
+    constexpr uint32_t TILES = NT * PER / TILE;
+    __shared__ BinSort<NB, NT, PER> sh;
+    __shared__ uint64_t w[TILES][STAGE_WORDS];
+    __shared__ BinTile tl[TILES];
+    const uint32_t L = a.k + 1, k = a.k;
+    const bool single = a.single != 0;
+    const uint32_t lpb = bin_lanes(b.n_buckets, NT * PER);
+    const uint64_t batches = (b.t_hi - b.t_lo + TILES - 1) / TILES;
+    const T mid_ones = KT<T>::ones(2 * (k - 1));
+    uint32_t atomics = 0;
+    for (uint32_t i = threadIdx.x; i < NB; i += NT)
+        sh.cnt[i] = 0;
+    for (uint64_t batch = blockIdx.x; batch < batches; batch += gridDim.x) {
+        const uint64_t e0 = b.t_lo + batch * TILES;
+        const uint32_t nt = (uint32_t)min((uint64_t)TILES, b.t_hi - e0);
+        if (threadIdx.x < TILES) {
+            BinTile x{};
+            if (threadIdx.x < nt) {
+                const uint64_t tile = a.tile_order[e0 + threadIdx.x];
+                const TileInfo ti = a.tiles[tile];
+                const SetDesc &d = a.sets[ti.set];
+                x.t0 = tile * TILE;
+                x.lo = ti.str_lo;
+                x.hi = ti.str_hi;
+                x.block0 = (uint32_t)(d.bloom_off >> 1);
+                x.mask = d.bloom_mask;
+                x.cls_lo = d.cls_lo;
+                x.cls_hi = d.cls_hi;
+                if (x.lo + 1 == x.hi) {
+                    x.gs = a.strings[x.lo].gstart;
+                    x.ge = a.strings[x.lo].gend;
+                }
+            }
+            tl[threadIdx.x] = x;  // without strings (lo == hi): no edge
+        }
+        for (uint32_t i = threadIdx.x; i < nt * STAGE_WORDS; i += NT) {
+            const uint32_t j = i / STAGE_WORDS, u = i % STAGE_WORDS;
+            const int64_t gw = (int64_t)((uint64_t)a.tile_order[e0 + j] * TILE_WORDS) - 1 + u;
+            w[j][u] = (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull;
+        }
         __syncthreads();
-        stage_tile(a, tile, w);
-        __syncthreads();
-        const TileSet ts = tile_set_of(a, pool, ti.set);
-        const uint64_t block0 = a.sets[ti.set].bloom_off >> 1;
-        uint32_t si = hi;
-        uint64_t gs = 0, ge = 0;
+        uint32_t item[PER], at[PER];
 #pragma unroll
-        for (uint32_t q = 0; q < BIN_PER; ++q) {
-            v[q] = BIN_NONE;
-            const uint64_t p = t0 + q * BLOCK + threadIdx.x;
-            if (p >= ge) {
-                si = find_string(a.strings, lo, hi, p);
-                gs = si != hi ? a.strings[si].gstart : ~0ull;
-                ge = si != hi ? a.strings[si].gend : 0;
+        for (uint32_t q = 0; q < PER; ++q) {
+            item[q] = 0;
+            at[q] = ~0u;
+            const uint32_t j = q * NT / TILE, r = (q * NT & (TILE - 1)) + threadIdx.x;
+            const BinTile &x = tl[j];
+            const uint64_t p = x.t0 + r;
+            uint64_t gs = x.gs, ge = x.ge;
+            if (x.hi - x.lo > 1) {
+                const uint32_t si = find_string(a.strings, x.lo, x.hi, p);
+                gs = si != x.hi ? a.strings[si].gstart : ~0ull;
+                ge = si != x.hi ? a.strings[si].gend : 0;
             }
             if (p < gs || p + L > ge)
                 continue;
-            const uint32_t r = (uint32_t)(p - t0) + 32;
-            const Strands<T> e = strands(KT<T>::window(w, r, L), L);
-            if (a.classes) {
+            const Strands<T> e = strands(KT<T>::window(w[j], r + 32, L), L);
+            if (CLASSES) {
                 T pre, suf;
-                edge_kmers(e, a.k, single, &pre, &suf);
-                if (!in_class(class_subrange(pre), ts.cls_lo, ts.cls_hi) &&
-                    !in_class(class_subrange(suf), ts.cls_lo, ts.cls_hi))
+                edge_kmers(e, k, single, &pre, &suf);
+                if (!in_class(class_subrange(pre), x.cls_lo, x.cls_hi) &&
+                    !in_class(class_subrange(suf), x.cls_lo, x.cls_hi))
                     continue;
             }
-            v[q] = bin_item(ts.f, block0, e, a.k, single);
+            const uint32_t c0 = (uint32_t)(e.fwd >> (2 * k)), c1 = (uint32_t)(e.fwd & 3);
+            const MiddleKey key = middle_key((T)((e.fwd >> 2) & mid_ones),
+                                             (T)((e.rc >> 2) & mid_ones), single, x.mask >> 6);
+            const uint32_t pair = pair_index(key.orient, c0, c1, e.fwd <= e.rc);
+            const uint32_t block = x.block0 + (uint32_t)key.block;
+            item[q] = (block & ((1u << b.bucket_log2) - 1)) << BIN_EFFECT_BITS |
+                      bin_effect(key, pair, pool.h);
+            const uint32_t bucket = block >> b.bucket_log2;
+            at[q] = bucket << 14 | atomicAdd(&sh.cnt[bucket], 1u);
         }
-        tile_done(tile, v);
+        bin_append<NB, NT, PER>(sh, item, at, b.n_buckets, lpb, b.cursor, b.off, b.items_a,
+                            [&](uint32_t bucket, uint32_t it) {
+                                atomics += bin_direct(
+                                    pool, ((uint64_t)bucket << b.bucket_log2) +
+                                              (it >> BIN_EFFECT_BITS), it);
+                            });
     }
+    if (atomics)
+        atomicAdd(&cnt->fill_atomics, (unsigned long long)atomics);
 }
 
-// sorted_write by a field of the item: bin (v >> SHIFT) mod NB.
-template <uint32_t NB, uint32_t NT, uint32_t PER, uint32_t SHIFT>
-__device__ __forceinline__ void sorted_write(const uint64_t (&v)[PER], uint32_t *cnt,
-                                             uint32_t *start, uint32_t *wtot, uint32_t *total,
-                                             uint64_t *srt, uint64_t *cursor, uint64_t *out) {
-    sorted_write_by<NB, NT, PER>(
-        v, [](uint64_t x) { return (uint32_t)(x >> SHIFT) & (NB - 1); }, cnt, start, wtot, total,
-        srt, cursor, out);
-}
-
-// The items of the chunk, one slot per position (BIN_NONE where there is
-// none), written to items_b in position order; per workgroup, its items per
-// bucket.
-template <class T>
-__global__ __launch_bounds__(BLOCK) void k_bin_count(SeqArgs a, BloomArgs pool, BinArgs b) {
-    __shared__ uint64_t w[STAGE_WORDS];
-    __shared__ uint32_t hist[BIN_MAX_BUCKETS];
-    for (uint32_t i = threadIdx.x; i < BIN_MAX_BUCKETS; i += BLOCK)
-        hist[i] = 0;
-    __syncthreads();
-    uint64_t *stage = b.items_b;
-    bin_walk<T>(a, pool, b, w, [&](uint64_t tile, const uint64_t (&v)[BIN_PER]) {
-        uint64_t *dst = stage + (tile - b.tile_lo) * TILE + threadIdx.x;
+// One batch of one bucket's items (blockIdx.y: the bucket, blockIdx.x: the
+// batch) appended to the bucket's regions.
+__global__ __launch_bounds__(BIN_BLOCK) void k_bin_split(BloomArgs pool, BinArgs b,
+                                                         Counters *cnt) {
+    constexpr uint32_t NT = BIN_BLOCK, PER = BIN_PER, NB = 1u << (BIN_LOCAL_LOG2 - BIN_REGION_LOG2);
+    __shared__ BinSort<NB, NT, PER> sh;
+    const uint32_t bucket = blockIdx.y, shift = b.region_log2 + BIN_EFFECT_BITS;
+    const uint32_t sub = 1u << (b.bucket_log2 - b.region_log2), r0 = bucket * sub;
+    const uint64_t o = b.off[bucket];
+    const uint64_t n = min((uint64_t)b.cursor[bucket], b.off[bucket + 1] - o);
+    const uint64_t i0 = (uint64_t)blockIdx.x * BIN_BATCH;
+    if (i0 >= n)
+        return;
+    for (uint32_t i = threadIdx.x; i < NB; i += NT)
+        sh.cnt[i] = 0;
+    uint32_t item[PER], at[PER], atomics = 0;
 #pragma unroll
-        for (uint32_t q = 0; q < BIN_PER; ++q) {
-            dst[q * BLOCK] = v[q];
-            if (v[q] != BIN_NONE)
-                atomicAdd(&hist[v[q] >> BIN_BUCKET_SHIFT], 1u);
-        }
-    });
+    for (uint32_t q = 0; q < PER; ++q) {
+        const uint64_t i = i0 + q * NT + threadIdx.x;
+        item[q] = i < n ? b.items_a[o + i] : 0;
+    }
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < b.n_buckets; i += BLOCK)
-        b.counts[(uint64_t)i * b.grid + blockIdx.x] = hist[i];
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+        const uint32_t reg = item[q] >> shift;
+        at[q] = i0 + q * NT + threadIdx.x < n ? reg << 14 | atomicAdd(&sh.cnt[reg], 1u) : ~0u;
+    }
+    const uint32_t nb = min(sub, b.n_regions - r0);
+    bin_append<NB, NT, PER>(sh, item, at, nb, bin_lanes(nb, NT * PER), b.cursor + b.n_buckets + r0, b.roff + r0,
+                        b.items_b, [&](uint32_t, uint32_t it) {
+                            atomics += bin_direct(pool, ((uint64_t)bucket << b.bucket_log2) +
+                                                            (it >> BIN_EFFECT_BITS), it);
+                        });
+    if (atomics)
+        atomicAdd(&cnt->fill_atomics, (unsigned long long)atomics);
 }
 
-// Each workgroup's staged items (the positions of its share of the chunk,
-// as k_bin_count walked them) written to its (bucket, workgroup) ranges of
-// items_a, a sorted batch of BIN_SCATTER_PER items per thread at a time.
-__global__ __launch_bounds__(BIN_SCATTER_BLOCK) void k_bin_scatter(BinArgs b) {
-    constexpr uint32_t NT = BIN_SCATTER_BLOCK, PER = BIN_SCATTER_PER;
-    __shared__ uint64_t cursor[BIN_MAX_BUCKETS];
-    __shared__ uint32_t cnt[BIN_MAX_BUCKETS];
-    __shared__ uint32_t start[BIN_MAX_BUCKETS];
-    __shared__ uint64_t srt[NT * PER];
-    __shared__ uint32_t wtot[NT / 64];
-    __shared__ uint32_t total;
-    for (uint32_t i = threadIdx.x; i < BIN_MAX_BUCKETS; i += NT) {
-        cursor[i] = i < b.n_buckets ? b.offsets[(uint64_t)i * b.grid + blockIdx.x] : 0;
-        cnt[i] = 0;
-    }
-    __syncthreads();
-    const uint64_t n = b.tile_hi - b.tile_lo;
-    const uint64_t per = (n + b.grid - 1) / b.grid;
-    const uint64_t p_lo = min(n, (uint64_t)blockIdx.x * per) * TILE;
-    const uint64_t p_hi = min(n, (uint64_t)(blockIdx.x + 1) * per) * TILE;
-    const uint64_t *stage = b.items_b;
-    // every thread runs the same number of batches (the workgroup syncs in each)
-    for (uint64_t i0 = p_lo; i0 < p_hi; i0 += PER * NT) {
-        uint64_t v[PER];
-#pragma unroll
-        for (uint32_t q = 0; q < PER; ++q) {
-            const uint64_t j = i0 + (uint64_t)q * NT + threadIdx.x;
-            v[q] = j < p_hi ? stage[j] : BIN_NONE;
-        }
-        sorted_write<BIN_MAX_BUCKETS, NT, PER, BIN_BUCKET_SHIFT>(v, cnt, start, wtot, &total, srt,
-                                                                cursor, b.items_a);
-    }
-}
-
-__global__ __launch_bounds__(BIN_SCAN_BLOCK) void k_bin_scan(const uint32_t *counts, uint64_t n,
-                                                            uint64_t *offsets) {
-    bin_offsets_scan(counts, n, offsets);
-}
-
-// One workgroup per bucket: its items (the ranges of all its pairs, which
-// lie back to back) counted by region, then written region by region into
-// the same range of items_b, a sorted batch at a time; region_off gets each
-// region's first item.
-__global__ __launch_bounds__(BIN_SPLIT_BLOCK) void k_bin_split(BinArgs b) {
-    constexpr uint32_t NT = BIN_SPLIT_BLOCK, PER = BIN_SPLIT_PER;
-    __shared__ uint32_t cnt[BIN_SUB];
-    __shared__ uint32_t start[BIN_SUB];
-    __shared__ uint64_t cursor[BIN_SUB];
-    __shared__ uint64_t srt[NT * PER];
-    __shared__ uint32_t wtot[NT / 64];
-    __shared__ uint32_t total;
-    const uint32_t bk = blockIdx.x;
-    const uint64_t lo = b.offsets[(uint64_t)bk * b.grid];
-    const uint64_t hi = b.offsets[(uint64_t)(bk + 1) * b.grid];
-    for (uint32_t i = threadIdx.x; i < BIN_SUB; i += NT)
-        cnt[i] = 0;
-    __syncthreads();
-    for (uint64_t i = lo + threadIdx.x; i < hi; i += PER * NT) {
-        uint64_t v[PER];
-#pragma unroll
-        for (uint32_t q = 0; q < PER; ++q) {
-            const uint64_t j = i + (uint64_t)q * NT;
-            v[q] = j < hi ? b.items_a[j] : BIN_NONE;
-        }
-#pragma unroll
-        for (uint32_t q = 0; q < PER; ++q)
-            if (v[q] != BIN_NONE)
-                atomicAdd(&cnt[(uint32_t)(v[q] >> BIN_REGION_SHIFT) & (BIN_SUB - 1)], 1u);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t c = lo;
-        for (uint32_t q = 0; q < BIN_SUB; ++q) {
-            cursor[q] = c;
-            b.region_off[(uint64_t)bk * BIN_SUB + q] = c;
-            c += cnt[q];
-            cnt[q] = 0;
-        }
-        if (bk + 1 == b.n_buckets)
-            b.region_off[(uint64_t)b.n_buckets * BIN_SUB] = c;
-    }
-    __syncthreads();
-    // every thread runs the same number of batches (the workgroup syncs in each)
-    for (uint64_t i0 = lo; i0 < hi; i0 += PER * NT) {
-        uint64_t v[PER];
-#pragma unroll
-        for (uint32_t q = 0; q < PER; ++q) {
-            const uint64_t j = i0 + (uint64_t)q * NT + threadIdx.x;
-            v[q] = j < hi ? b.items_a[j] : BIN_NONE;
-        }
-        // out as 4-byte items: the block within its region and the bits it sets
-        sorted_write_by<BIN_SUB, NT, PER>(
-            v, [](uint64_t x) { return (uint32_t)(x >> BIN_REGION_SHIFT) & (BIN_SUB - 1); }, cnt,
-            start, wtot, &total, srt, cursor, (uint32_t *)b.items_b);
-    }
-}
-
-// One workgroup per region: the region's blocks (zero in the first chunk)
-// in LDS, its items ORed in, the blocks written back.  Counts the items that
-// set a bit not yet set.
-__global__ __launch_bounds__(BIN_APPLY_BLOCK) void k_bin_apply(BloomArgs pool, BinArgs b,
-                                                             Counters *cnt) {
-    constexpr uint32_t NT = BIN_APPLY_BLOCK;
-    __shared__ __align__(16) unsigned long long reg[BIN_REGION];
-    __shared__ uint32_t fresh_wg;
-    const uint64_t r = blockIdx.x;
-    const uint64_t blk0 = r << BIN_REGION_LOG2;
-    const uint32_t nb = (uint32_t)min((uint64_t)BIN_REGION, b.n_blocks - blk0);
-    unsigned long long *blocks = (unsigned long long *)pool.words + blk0;
+// One workgroup per region: the region's blocks in LDS, its items ORed in, the
+// blocks written back.  Counts the items that set a bit not yet set and, in
+// the last chunk of a one-set pool, the filter's bits.
+template <uint32_t REGION_LOG2>
+__global__ __launch_bounds__(BIN_BLOCK) void k_bin_apply(BloomArgs pool, BinArgs b, Counters *cnt) {
+    constexpr uint32_t NT = BIN_BLOCK, U = 4;
+    __shared__ __align__(16) unsigned long long reg[1u << REGION_LOG2];
+    __shared__ uint64_t tmpl[32];
+    __shared__ uint32_t fresh_wg, bits_wg;
+    const uint64_t r = blockIdx.x, blk0 = r << REGION_LOG2;
+    const uint32_t nb = (uint32_t)min(1ull << REGION_LOG2, b.n_blocks - blk0);
+    const bool split = b.bucket_log2 != REGION_LOG2;
+    const uint64_t o = split ? b.roff[r] : b.off[r];
+    const uint64_t room = (split ? b.roff[r + 1] : b.off[r + 1]) - o;
+    const uint64_t n = min((uint64_t)b.cursor[split ? b.n_buckets + r : r], room);
+    const uint32_t *items = (split ? b.items_b : b.items_a) + o;
+    if (threadIdx.x < 32)
+        tmpl[threadIdx.x] = stride_template(2 * threadIdx.x + 1, pool.h);
     if (threadIdx.x == 0)
-        fresh_wg = 0;
-    // blocks in pairs (the pool and every region start 16-byte aligned)
-    const uint32_t np = nb / 2;
+        fresh_wg = bits_wg = 0;
+    // blocks in pairs (the pool's size and every region's start are even)
+    ulonglong2 *blocks = (ulonglong2 *)((unsigned long long *)pool.words + blk0);
     ulonglong2 *reg2 = (ulonglong2 *)reg;
-    const ulonglong2 *src2 = (const ulonglong2 *)blocks;
-    for (uint32_t i = threadIdx.x; i < np; i += NT)
-        reg2[i] = b.first ? make_ulonglong2(0, 0) : src2[i];
-    if (threadIdx.x == 0 && (nb & 1))
-        reg[nb - 1] = b.first ? 0ull : blocks[nb - 1];
+    for (uint32_t i = threadIdx.x; i < nb / 2; i += NT)
+        reg2[i] = blocks[i];
     __syncthreads();
-    const uint64_t lo = b.region_off[r], hi = b.region_off[r + 1];
-    const uint32_t *items = (const uint32_t *)b.items_b;  // 4-byte items of the split
-    constexpr uint32_t U = 4;
-    uint32_t fresh = 0;
-    for (uint64_t i = lo + threadIdx.x; i < hi; i += U * NT) {
+    constexpr uint32_t lmask = (1u << REGION_LOG2) - 1;
+    uint32_t fresh = 0, bits = 0;
+    for (uint64_t i = threadIdx.x; i < n; i += U * NT) {
         uint32_t v[U];
 #pragma unroll
-        for (uint32_t q = 0; q < U; ++q) {
-            const uint64_t j = i + (uint64_t)q * NT;
-            v[q] = j < hi ? items[j] : 0u;
-        }
+        for (uint32_t q = 0; q < U; ++q)
+            v[q] = i + (uint64_t)q * NT < n ? items[i + (uint64_t)q * NT] : 0u;
 #pragma unroll
         for (uint32_t q = 0; q < U; ++q) {
-            if (i + (uint64_t)q * NT < hi) {
-                const uint32_t local = (v[q] >> 16) & (BIN_REGION - 1);
-                const unsigned long long m = pair_mask(v[q] & 63, (v[q] >> 6) & 63,
-                                                       (v[q] >> 12) & 15, pool.h);
-                const unsigned long long old = atomicOr(&reg[local], m);
+            if (i + (uint64_t)q * NT < n) {
+                const uint64_t m = rotl64(tmpl[v[q] >> 6 & 31u], v[q] & 63u);
+                const unsigned long long old =
+                    atomicOr(&reg[(v[q] >> BIN_EFFECT_BITS) & lmask], (unsigned long long)m);
                 fresh += (old & m) != m;
             }
         }
@@ -601,35 +628,69 @@ __global__ __launch_bounds__(BIN_APPLY_BLOCK) void k_bin_apply(BloomArgs pool, B
     if (fresh)
         atomicAdd(&fresh_wg, fresh);
     __syncthreads();
-    ulonglong2 *dst2 = (ulonglong2 *)blocks;
-    for (uint32_t i = threadIdx.x; i < np; i += NT)
-        dst2[i] = reg2[i];
-    if (threadIdx.x == 0 && (nb & 1))
-        blocks[nb - 1] = reg[nb - 1];
+    for (uint32_t i = threadIdx.x; i < nb / 2; i += NT) {
+        const ulonglong2 x = reg2[i];
+        blocks[i] = x;
+        bits += (uint32_t)(__popcll(x.x) + __popcll(x.y));
+    }
+    if (b.popcount)
+        atomicAdd(&bits_wg, bits);
+    __syncthreads();
     if (threadIdx.x == 0 && fresh_wg)
         atomicAdd(&cnt->fill_atomics, (unsigned long long)fresh_wg);
+    if (threadIdx.x == 0 && b.popcount && bits_wg)
+        atomicAdd(&b.popcount->bloom_popcount, (unsigned long long)bits_wg);
+}
+
+// Items per thread of k_bin_items: four-word k-mers take half (registers).
+template <class T> struct ItemsPer {
+    static constexpr uint32_t N = KT<T>::W == 4 ? BIN_PER / 2 : BIN_PER;
+};
+
+template <class T, uint32_t NB>
+static void bin_items_t(const SeqArgs &a, const BloomArgs &pool, const BinArgs &b, Counters *cnt,
+                        hipStream_t s) {
+    constexpr uint32_t NT = BIN_BLOCK, PER = ItemsPer<T>::N, TILES = NT * PER / TILE;
+    const uint64_t batches = (b.t_hi - b.t_lo + TILES - 1) / TILES;
+    const uint32_t grid = (uint32_t)min(batches, (uint64_t)b.n_cu);
+    if (a.classes)
+        hipLaunchKernelGGL((k_bin_items<T, NB, NT, PER, true>), dim3(grid), dim3(NT), 0, s, a,
+                           pool, b, cnt);
+    else
+        hipLaunchKernelGGL((k_bin_items<T, NB, NT, PER, false>), dim3(grid), dim3(NT), 0, s, a,
+                           pool, b, cnt);
 }
 
 hipError_t launch_fill_binned(int W, const SeqArgs &a, const BloomArgs &pool, Counters *cnt,
                               BinArgs b, uint32_t tiles_per_chunk, hipStream_t s) {
     if (a.n_tiles == 0)
         return hipSuccess;
-    const uint64_t regions = (b.n_blocks + BIN_REGION - 1) >> BIN_REGION_LOG2;
-    const uint64_t n_counts = (uint64_t)b.n_buckets * b.grid;
+    const bool split = b.bucket_log2 != b.region_log2;
+    const uint64_t n_cursor = b.n_buckets + (split ? b.n_regions : 0u);
+    SetCounters *const popcount = b.popcount;
     return by_width(W, [&](auto tag) {
         using T = decltype(tag);
         for (uint64_t t0 = 0; t0 < a.n_tiles; t0 += tiles_per_chunk) {
-            b.tile_lo = t0;
-            b.tile_hi = min(a.n_tiles, t0 + tiles_per_chunk);
-            b.first = t0 == 0 ? 1u : 0u;
-            hipLaunchKernelGGL(k_bin_count<T>, dim3(b.grid), dim3(BLOCK), 0, s, a, pool, b);
-            hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(BIN_SCAN_BLOCK), 0, s, b.counts, n_counts,
-                               b.offsets);
-            hipLaunchKernelGGL(k_bin_scatter, dim3(b.grid), dim3(BIN_SCATTER_BLOCK), 0, s, b);
-            hipLaunchKernelGGL(k_bin_split, dim3(b.n_buckets), dim3(BIN_SPLIT_BLOCK), 0, s, b);
-            hipLaunchKernelGGL(k_bin_apply, dim3((uint32_t)regions), dim3(BIN_APPLY_BLOCK), 0, s,
-                               pool, b, cnt);
-            const hipError_t e = hipGetLastError();
+            b.t_lo = t0;
+            b.t_hi = min(a.n_tiles, t0 + tiles_per_chunk);
+            b.popcount = b.t_hi == a.n_tiles ? popcount : nullptr;
+            hipError_t e = launch_zero(b.cursor, n_cursor * sizeof(unsigned long long), s);
+            if (e != hipSuccess)
+                return e;
+            if (b.n_buckets <= BIN_BUCKETS)
+                bin_items_t<T, BIN_BUCKETS>(a, pool, b, cnt, s);
+            else
+                bin_items_t<T, BIN_MAX_BUCKETS>(a, pool, b, cnt, s);
+            if (split)
+                hipLaunchKernelGGL(k_bin_split, dim3(b.slices, b.n_buckets), dim3(BIN_BLOCK), 0, s,
+                                   pool, b, cnt);
+            if (b.region_log2 == BIN_REGION_LOG2)
+                hipLaunchKernelGGL(k_bin_apply<BIN_REGION_LOG2>, dim3(b.n_regions),
+                                   dim3(BIN_BLOCK), 0, s, pool, b, cnt);
+            else
+                hipLaunchKernelGGL(k_bin_apply<BIN_REGION_LOG2 + 1>, dim3(b.n_regions),
+                                   dim3(BIN_BLOCK), 0, s, pool, b, cnt);
+            e = hipGetLastError();
             if (e != hipSuccess)
                 return e;
         }

@@ -375,7 +375,7 @@ hipError_t launch_record(int W, const SeqArgs &a, const uint64_t *c1, const Tabl
 // [r_lo, r_hi); every candidate whose home block is among them becomes an
 // item, the slot word it contributes (key << 8 | edge bits, packed slots);
 // the items are partitioned by block in two streaming steps (bucket of
-// BIN_SUB blocks, then block; each batch sorted in LDS so that a
+// RBIN_SUB blocks, then block; each batch sorted in LDS so that a
 // destination's items leave as one run); and each block is built in LDS from
 // empty and written out whole.  Same keys and edge bits as k_record (slots
 // within a block may differ: they follow the order of insertion), no table
@@ -522,8 +522,8 @@ __device__ __forceinline__ void rbin_share(const RecBinArgs &rb, uint64_t *lo, u
 
 template <bool P2>
 __global__ __launch_bounds__(BLOCK) void k_rbin_hist(TableArgs t, RecBinArgs rb) {
-    __shared__ uint32_t hist[BIN_MAX_BUCKETS];
-    for (uint32_t i = threadIdx.x; i < BIN_MAX_BUCKETS; i += BLOCK)
+    __shared__ uint32_t hist[RBIN_MAX_BUCKETS];
+    for (uint32_t i = threadIdx.x; i < RBIN_MAX_BUCKETS; i += BLOCK)
         hist[i] = 0;
     __syncthreads();
     uint64_t lo, hi;
@@ -532,7 +532,7 @@ __global__ __launch_bounds__(BLOCK) void k_rbin_hist(TableArgs t, RecBinArgs rb)
         for (uint64_t i = lo + threadIdx.x; i < hi; i += BLOCK) {
             const uint64_t x = rb.items_b[i];
             if (x != BIN_NONE)
-                atomicAdd(&hist[(uint32_t)((rbin_block<P2>(t, x) - rb.r_lo) >> BIN_SUB_LOG2)], 1u);
+                atomicAdd(&hist[(uint32_t)((rbin_block<P2>(t, x) - rb.r_lo) >> RBIN_SUB_LOG2)], 1u);
         }
     }
     __syncthreads();
@@ -548,13 +548,13 @@ __global__ __launch_bounds__(BIN_SCAN_BLOCK) void k_rbin_scan(const uint32_t *co
 template <bool P2>
 __global__ __launch_bounds__(BIN_SCATTER_BLOCK) void k_rbin_scatter(TableArgs t, RecBinArgs rb) {
     constexpr uint32_t NT = BIN_SCATTER_BLOCK, PER = BIN_SCATTER_PER;
-    __shared__ uint64_t cursor[BIN_MAX_BUCKETS];
-    __shared__ uint32_t cnt[BIN_MAX_BUCKETS];
-    __shared__ uint32_t start[BIN_MAX_BUCKETS];
+    __shared__ uint64_t cursor[RBIN_MAX_BUCKETS];
+    __shared__ uint32_t cnt[RBIN_MAX_BUCKETS];
+    __shared__ uint32_t start[RBIN_MAX_BUCKETS];
     __shared__ uint64_t srt[NT * PER];
     __shared__ uint32_t wtot[NT / 64];
     __shared__ uint32_t total;
-    for (uint32_t i = threadIdx.x; i < BIN_MAX_BUCKETS; i += NT) {
+    for (uint32_t i = threadIdx.x; i < RBIN_MAX_BUCKETS; i += NT) {
         cursor[i] = i < rb.n_buckets ? rb.offsets[(uint64_t)i * rb.grid + blockIdx.x] : 0;
         cnt[i] = 0;
     }
@@ -564,7 +564,7 @@ __global__ __launch_bounds__(BIN_SCATTER_BLOCK) void k_rbin_scatter(TableArgs t,
     uint64_t lo, hi;
     rbin_share(rb, &lo, &hi);
     const auto bucket_of = [&](uint64_t x) {
-        return (uint32_t)((rbin_block<P2>(t, x) - rb.r_lo) >> BIN_SUB_LOG2);
+        return (uint32_t)((rbin_block<P2>(t, x) - rb.r_lo) >> RBIN_SUB_LOG2);
     };
     // every thread runs the same number of batches (the workgroup syncs in each)
     for (uint64_t i0 = lo; i0 < hi; i0 += PER * NT) {
@@ -574,7 +574,7 @@ __global__ __launch_bounds__(BIN_SCATTER_BLOCK) void k_rbin_scatter(TableArgs t,
             const uint64_t j = i0 + (uint64_t)q * NT + threadIdx.x;
             v[q] = j < hi ? rb.items_b[j] : BIN_NONE;
         }
-        sorted_write_by<BIN_MAX_BUCKETS, NT, PER>(v, bucket_of, cnt, start, wtot, &total, srt,
+        sorted_write_by<RBIN_MAX_BUCKETS, NT, PER>(v, bucket_of, cnt, start, wtot, &total, srt,
                                                   cursor, rb.items_a);
     }
 }
@@ -585,9 +585,9 @@ __global__ __launch_bounds__(BIN_SCATTER_BLOCK) void k_rbin_scatter(TableArgs t,
 template <bool P2>
 __global__ __launch_bounds__(BIN_SPLIT_BLOCK) void k_rbin_split(TableArgs t, RecBinArgs rb) {
     constexpr uint32_t NT = BIN_SPLIT_BLOCK, PER = BIN_SPLIT_PER;
-    __shared__ uint32_t cnt[BIN_SUB];
-    __shared__ uint32_t start[BIN_SUB];
-    __shared__ uint64_t cursor[BIN_SUB];
+    __shared__ uint32_t cnt[RBIN_SUB];
+    __shared__ uint32_t start[RBIN_SUB];
+    __shared__ uint64_t cursor[RBIN_SUB];
     __shared__ uint64_t srt[NT * PER];
     __shared__ uint32_t wtot[NT / 64];
     __shared__ uint32_t total;
@@ -595,9 +595,9 @@ __global__ __launch_bounds__(BIN_SPLIT_BLOCK) void k_rbin_split(TableArgs t, Rec
     const uint64_t lo = rb.offsets[(uint64_t)bk * rb.grid];
     const uint64_t hi = rb.offsets[(uint64_t)(bk + 1) * rb.grid];
     const auto sub_of = [&](uint64_t x) {
-        return (uint32_t)(rbin_block<P2>(t, x) - rb.r_lo) & (BIN_SUB - 1);
+        return (uint32_t)(rbin_block<P2>(t, x) - rb.r_lo) & (RBIN_SUB - 1);
     };
-    for (uint32_t i = threadIdx.x; i < BIN_SUB; i += NT)
+    for (uint32_t i = threadIdx.x; i < RBIN_SUB; i += NT)
         cnt[i] = 0;
     __syncthreads();
     for (uint64_t i = lo + threadIdx.x; i < hi; i += NT)
@@ -605,14 +605,14 @@ __global__ __launch_bounds__(BIN_SPLIT_BLOCK) void k_rbin_split(TableArgs t, Rec
     __syncthreads();
     if (threadIdx.x == 0) {
         uint64_t c = lo;
-        for (uint32_t q = 0; q < BIN_SUB; ++q) {
+        for (uint32_t q = 0; q < RBIN_SUB; ++q) {
             cursor[q] = c;
-            rb.region_off[(uint64_t)bk * BIN_SUB + q] = c;
+            rb.region_off[(uint64_t)bk * RBIN_SUB + q] = c;
             c += cnt[q];
             cnt[q] = 0;
         }
         if (bk + 1 == rb.n_buckets)
-            rb.region_off[(uint64_t)rb.n_buckets * BIN_SUB] = c;
+            rb.region_off[(uint64_t)rb.n_buckets * RBIN_SUB] = c;
     }
     __syncthreads();
     for (uint64_t i0 = lo; i0 < hi; i0 += PER * NT) {
@@ -622,7 +622,7 @@ __global__ __launch_bounds__(BIN_SPLIT_BLOCK) void k_rbin_split(TableArgs t, Rec
             const uint64_t j = i0 + (uint64_t)q * NT + threadIdx.x;
             v[q] = j < hi ? rb.items_a[j] : BIN_NONE;
         }
-        sorted_write_by<BIN_SUB, NT, PER>(v, sub_of, cnt, start, wtot, &total, srt, cursor,
+        sorted_write_by<RBIN_SUB, NT, PER>(v, sub_of, cnt, start, wtot, &total, srt, cursor,
                                           rb.items_b);
     }
 }
@@ -721,7 +721,7 @@ hipError_t launch_record_binned(const SeqArgs &a, const uint64_t *c1, const Tabl
         for (uint64_t r0 = 0; r0 < n_blocks; r0 += per_pass) {
             rb.r_lo = r0;
             rb.r_hi = min(n_blocks, r0 + per_pass);
-            rb.n_buckets = (uint32_t)((rb.r_hi - rb.r_lo + BIN_SUB - 1) / BIN_SUB);
+            rb.n_buckets = (uint32_t)((rb.r_hi - rb.r_lo + RBIN_SUB - 1) / RBIN_SUB);
             if (r0) {
                 e = launch_zero(rb.ctl, sizeof(unsigned long long), s);  // staging cursor
                 if (e != hipSuccess)

@@ -818,70 +818,130 @@ static int reserve(tp_plan *p, std::initializer_list<std::pair<DevBuf *, uint64_
 
 constexpr int RUN_SPLIT = 1;  // run_impl: redo the run with *split rounds
 
-constexpr uint64_t BIN_AUTO_BYTES = 1ull << 30;  // binned fill by default from this set filter size
+// Binned fill by default where the pool is not large for its positions: each
+// chunk reads and writes the whole pool once more than the atomic fill does
+// (two passes, at about 4.8 TB/s), and an edge costs about 7 ps binned against
+// 18 ps with atomics, besides a few launches (measured per run of 0.4, 2, 8,
+// 32 and 100 Mbp at k = 25, 16 bits a position: 0.042, 0.048, 0.084, 0.275 and
+// 1.03 ms binned, 0.101, 0.109, 0.197, 0.603 and 1.71 ms atomic).
+constexpr uint64_t BIN_POOL_PER_POSITION = 24;
+constexpr uint64_t BIN_POOL_FREE = 128ull << 20;
 
 // Whether this plan's fill can run binned: blocked filter, a pool within the
 // bucket limit.
 bool tp::fill_binnable(const tp_plan *p) {
     if (!(p->flags & TP_FLAG_BLOCKED_FILTER) || !p->n_tiles)
         return false;
-    const uint64_t blocks = p->bloom_words / 2;
-    const uint64_t per_bucket = (uint64_t)BIN_REGION * BIN_SUB;
-    return (blocks + per_bucket - 1) / per_bucket <= BIN_MAX_BUCKETS;
+    return p->bloom_words / 2 <= (uint64_t)BIN_MAX_BUCKETS << BIN_LOCAL_LOG2;
 }
 
-// Whether this plan's fill runs binned (tp_config.fill_binned): by default
-// when some set's own filter is 1 GiB or more (many small filters of a
-// batch stay in the caches while their tiles run, and fill faster with
-// atomics).
-static bool fill_binned(const tp_plan *p) {
+// Whether this plan's fill runs binned (tp_config.fill_binned) with the given
+// rounds.
+static bool fill_binned(const tp_plan *p, uint32_t rounds) {
     if (p->cfg.fill_binned == 1 || !fill_binnable(p))
         return false;
-    uint64_t largest = 0;
-    for (const auto &si : p->sets)
-        largest = std::max<uint64_t>(largest, si.b / 8);
-    return p->cfg.fill_binned == 2 || largest >= BIN_AUTO_BYTES;
+    return p->cfg.fill_binned == 2 ||
+           p->bloom_words * 4 <= BIN_POOL_PER_POSITION * (p->positions / rounds) + BIN_POOL_FREE;
+}
+
+// Room for the items of a chunk of `tiles` tiles, per bin of 2^bin_log2
+// blocks: off gets each bin's first item and the end.  A set's edges spread
+// evenly over its blocks; related genomes share most of them, so a bin's load
+// varies as if its distinct edges came once per genome (six standard
+// deviations and 2% are added; what finds no room is applied directly).
+static void bin_room(const tp_plan *p, uint64_t tiles, uint32_t rounds, uint64_t n_blocks,
+                     uint32_t bin_log2, std::vector<uint64_t> &off) {
+    const uint64_t bins = (n_blocks + (1ull << bin_log2) - 1) >> bin_log2;
+    std::vector<double> mean(bins, 0.0), var(bins, 0.0);
+    for (const SetInfo &si : p->sets) {
+        const uint64_t f = si.bloom_off / 2, nb = si.b / 64;
+        if (!nb || !si.positions)
+            continue;
+        // a round inserts the edges next to its class's k-mers
+        const double share = rounds > 1 ? std::min(1.0, 2.5 / rounds) : 1.0;
+        const double per = share * (double)std::min<uint64_t>(si.positions, tiles * TILE) / nb;
+        for (uint64_t i = f >> bin_log2; i <= (f + nb - 1) >> bin_log2; ++i) {
+            const uint64_t lo = std::max(f, i << bin_log2);
+            const uint64_t hi = std::min(f + nb, (i + 1) << bin_log2);
+            mean[i] += per * (double)(hi - lo);
+            var[i] += per * (double)(hi - lo) * (si.genome_hi - si.genome_lo);
+        }
+    }
+    off.resize(bins + 1);
+    off[0] = 0;
+    for (uint64_t i = 0; i < bins; ++i)
+        off[i + 1] = off[i] + align_up((uint64_t)(1.02 * mean[i] + 6 * std::sqrt(var[i])) + 64, 32);
 }
 
 // The binned fill's scratch: items in the exact table's key buffer (dead
-// during the first pass), counts and offsets in d_bin.  Sets *chunk_tiles.
-static int bin_setup(tp_plan *p, BinArgs *b, uint32_t *chunk_tiles,
-                     std::initializer_list<DevBuf *> outputs) {
+// during the first pass), cursors in d_bin, the bins' room in d_bin_room
+// (laid out again when the layout, the chunk size or the rounds change).
+// Sets *chunk_tiles.  *use = false where the memory is not to be had: the
+// fill then runs with atomics.
+static int bin_setup(tp_plan *p, BinArgs *b, uint32_t *chunk_tiles, uint32_t rounds, bool *use,
+                     std::initializer_list<DevBuf *> outputs, hipStream_t s) {
     *b = BinArgs{};
+    *use = false;
+    b->n_blocks = p->bloom_words / 2;
+    bin_shape(b->n_blocks, &b->bucket_log2, &b->region_log2);
+    const bool split = b->bucket_log2 != b->region_log2;
     // default: 2^31 positions, or as many as the key buffer already holds
-    // (a table from an earlier run) up to 2^33; fewer chunks reread the
-    // filter fewer times
+    // (a table from an earlier run; about 4.5 bytes per position and level)
+    // up to 2^33; fewer chunks reread the filter fewer times
     uint64_t want = p->cfg.bin_chunk_tiles;
     if (!want)
         want = std::min<uint64_t>(4ull * BIN_CHUNK_TILES_MAX,
                                   std::max<uint64_t>(BIN_CHUNK_TILES_MAX,
-                                                     p->d_keys.cap / (2 * 8 * TILE)));
+                                                     p->d_keys.cap / ((split ? 9 : 5) * TILE)));
     const uint64_t tiles = std::min<uint64_t>(p->n_tiles, want);
     *chunk_tiles = (uint32_t)tiles;
-    const uint64_t items = tiles * TILE;
-    b->n_blocks = p->bloom_words / 2;
-    const uint64_t regions = (b->n_blocks + BIN_REGION - 1) / BIN_REGION;
-    b->n_buckets = (uint32_t)((regions + BIN_SUB - 1) / BIN_SUB);
-    b->grid = (uint32_t)std::min<uint64_t>((uint64_t)BIN_WG_PER_CU * std::max<uint32_t>(1, p->n_cu),
-                                           tiles);
-    const uint64_t n_counts = (uint64_t)b->n_buckets * b->grid;
-    const uint64_t o_off = align_up(n_counts * 4, 256);
-    const uint64_t o_reg = o_off + align_up((n_counts + 1) * 8, 256);
-    const uint64_t meta = o_reg + ((uint64_t)b->n_buckets * BIN_SUB + 1) * 8;
-    const int rc = reserve(p, {{&p->d_keys, 2 * items * 8}, {&p->d_bin, meta}});
-    if (rc)
-        return rc;
-    HIPCHK(ensure_spare(p->d_keys, 2 * items * 8, outputs));
-    HIPCHK(ensure_spare(p->d_bin, meta, outputs));
-    b->items_a = p->d_keys.as<uint64_t>();
-    b->items_b = b->items_a + items;
-    uint8_t *m = p->d_bin.as<uint8_t>();
-    b->counts = (uint32_t *)m;
-    b->offsets = (uint64_t *)(m + o_off);
-    b->region_off = (uint64_t *)(m + o_reg);
+    const bool fresh = p->bin_tiles != tiles || p->bin_rounds != rounds;
+    if (fresh) {
+        bin_room(p, tiles, rounds, b->n_blocks, b->bucket_log2, p->bin_off);
+        p->bin_roff.clear();
+        if (split)
+            bin_room(p, tiles, rounds, b->n_blocks, b->region_log2, p->bin_roff);
+        p->bin_tiles = 0;
+    }
+    const uint64_t n_off = p->bin_off.size(), n_roff = p->bin_roff.size();
+    const uint64_t items_a = p->bin_off.back(), items_b = split ? p->bin_roff.back() : 0;
+    const uint64_t scratch = 4 * (items_a + items_b), cursors = 8 * (n_off + n_roff);
+    if (reserve(p, {{&p->d_keys, scratch}, {&p->d_bin, cursors}, {&p->d_bin_room, cursors}}))
+        return TP_OK;
+    for (const hipError_t e : {ensure_spare(p->d_keys, scratch, outputs), p->d_bin.ensure(cursors),
+                               p->d_bin_room.ensure(cursors)}) {
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            return TP_OK;
+        }
+        HIPCHK(e);
+    }
+    if (fresh) {
+        HIPCHK(hipMemcpyAsync(p->d_bin_room.p, p->bin_off.data(), n_off * 8, hipMemcpyHostToDevice,
+                              s));
+        if (split)
+            HIPCHK(hipMemcpyAsync(p->d_bin_room.as<uint64_t>() + n_off, p->bin_roff.data(),
+                                  n_roff * 8, hipMemcpyHostToDevice, s));
+        p->bin_tiles = tiles;
+        p->bin_rounds = rounds;
+    }
+    b->items_a = p->d_keys.as<uint32_t>();
+    b->items_b = b->items_a + items_a;
+    b->cursor = p->d_bin.as<unsigned long long>();
+    b->off = p->d_bin_room.as<uint64_t>();
+    b->roff = b->off + n_off;
+    b->n_buckets = (uint32_t)(n_off - 1);
+    b->n_regions = split ? (uint32_t)(n_roff - 1) : b->n_buckets;
+    b->n_cu = std::max<uint32_t>(1, p->n_cu);
+    uint64_t most = 0;
+    for (uint64_t i = 0; i + 1 < n_off; ++i)
+        most = std::max(most, p->bin_off[i + 1] - p->bin_off[i]);
+    b->slices = (uint32_t)((most + BIN_BATCH - 1) / BIN_BATCH);
+    *use = true;
     return TP_OK;
 }
 
+constexpr uint64_t RBIN_AUTO_BYTES = 1ull << 30;  // binned record by default from this table size
 constexpr uint32_t RBIN_AUTO_PASSES = 2;  // binned record by default: at most this many passes
 constexpr uint64_t RBIN_MEM_MARGIN = 1ull << 30;  // device bytes left free by its own scratch
 
@@ -897,14 +957,14 @@ static int rbin_setup(tp_plan *p, uint64_t candidates, uint64_t n_blocks, uint64
                       RecBinArgs *rb, uint32_t *passes, bool *use) {
     *use = false;
     const uint32_t mode = p->cfg.record_binned;
-    if (mode == 1 || (mode == 0 && table_bytes < BIN_AUTO_BYTES) || p->grow_hook)
+    if (mode == 1 || (mode == 0 && table_bytes < RBIN_AUTO_BYTES) || p->grow_hook)
         return TP_OK;
     const uint32_t grid = (uint32_t)std::max<uint64_t>(
         1, std::min<uint64_t>((uint64_t)BIN_WG_PER_CU * std::max<uint32_t>(1, p->n_cu),
                               p->n_tiles));
     const uint64_t slack = (uint64_t)grid * RBIN_SEG;  // partly filled staging segments
     const uint64_t want = (uint64_t)((double)candidates * 1.05) + 1;  // items, all passes
-    const uint64_t per_max = (uint64_t)BIN_MAX_BUCKETS * BIN_SUB;     // blocks per pass
+    const uint64_t per_max = (uint64_t)RBIN_MAX_BUCKETS * RBIN_SUB;   // blocks per pass
     const uint64_t min_passes = std::max<uint64_t>(
         {1, p->cfg.record_passes, (n_blocks + per_max - 1) / per_max});
     const uint64_t max_passes = mode == 2 ? RBIN_MAX_PASSES : RBIN_AUTO_PASSES;
@@ -947,10 +1007,10 @@ static int rbin_setup(tp_plan *p, uint64_t candidates, uint64_t n_blocks, uint64
         return TP_OK;
     const uint64_t per_pass = (n_blocks + n - 1) / n;
     n = (n_blocks + per_pass - 1) / per_pass;  // the passes the blocks take
-    const uint64_t nbk = (per_pass + BIN_SUB - 1) / BIN_SUB;
+    const uint64_t nbk = (per_pass + RBIN_SUB - 1) / RBIN_SUB;
     const uint64_t o_off = align_up(nbk * grid * 4, 256);
     const uint64_t o_reg = o_off + align_up((nbk * grid + 1) * 8, 256);
-    const uint64_t o_ctl = o_reg + align_up((nbk * BIN_SUB + 1) * 8, 256);
+    const uint64_t o_ctl = o_reg + align_up((nbk * RBIN_SUB + 1) * 8, 256);
     if (p->d_bin.ensure(o_ctl + 256) != hipSuccess) {
         (void)hipGetLastError();
         return TP_OK;
@@ -1043,6 +1103,7 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             if (!e)
                 HIPCHK(hipEventCreate(&e));
         p->static_uploaded = true;
+        p->bin_tiles = 0;  // the filters' places may have changed: the bins' room too
     }
     if (!p->order_uploaded) {
         if (p->n_tiles)
@@ -1080,14 +1141,15 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
     p->c1_out = rounds > 1 ? c1u : p->d_c1.as<uint64_t>();
 
     // binned fill: its scratch (the previous run's outputs are dead here)
-    const bool binned = fill_binned(p);
+    bool binned = fill_binned(p, rounds);
     BinArgs bin{};
     uint32_t bin_tiles = 0;
     if (binned) {
-        const int rcb = bin_setup(p, &bin, &bin_tiles,
-                                  {&p->d_pos, &p->d_vertex, &p->d_strand, &p->d_edges});
+        const int rcb = bin_setup(p, &bin, &bin_tiles, rounds, &binned,
+                                  {&p->d_pos, &p->d_vertex, &p->d_strand, &p->d_edges}, s);
         if (rcb)
             return rcb;
+        bin.popcount = nsets == 1 ? scnt : nullptr;
     }
 
     // tile queues of the four tile kernels (tp_config.tile_queue)
@@ -1144,8 +1206,7 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             }
             HIPCHK(launch_zero(scnt, nsets * sizeof(SetCounters), q));
             HIPCHK(launch_zero(p->d_hll.p, HLL_M * 4, q));
-            if (!binned)  // the binned fill's first chunk writes every block
-                HIPCHK(launch_zero(p->d_bloom.p, p->bloom_words * 4, q));
+            HIPCHK(launch_zero(p->d_bloom.p, p->bloom_words * 4, q));
             if (qbase)  // the fill's and the query's tile queues
                 HIPCHK(launch_zero(qbase, 2 * NXCD * sizeof(unsigned int), q));
             return TP_OK;
@@ -1169,8 +1230,9 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
         HIPCHK(launch_query(W, with_queue(a, qbase, K_QUERY, p->grid[K_QUERY]), pool, sa,
                             p->d_c1.as<uint64_t>(),
                             c1u, round, cnt, p->d_hll.as<uint32_t>(), p->grid[K_QUERY], s));
-        HIPCHK(launch_popcount(pool.words, p->bloom_words, p->d_bloom_starts.as<uint64_t>(),
-                               nsets, scnt, s));
+        if (!bin.popcount)  // (the binned fill of a one-set pool counts its bits)
+            HIPCHK(launch_popcount(pool.words, p->bloom_words, p->d_bloom_starts.as<uint64_t>(),
+                                   nsets, scnt, s));
         HIPCHK(hipEventRecord(p->ev[3], s));
         HIPCHK(hipMemcpyAsync(hs.data(), scnt, nsets * sizeof(SetCounters),
                               hipMemcpyDeviceToHost, s));

@@ -232,7 +232,11 @@ struct tp_plan {
     tp::DevBuf d_keys, d_seq, d_blockcnt, d_blockoff;  // d_seq: the input a reference table names
     tp::DevBuf d_pos, d_vertex, d_strand, d_edges, d_joff;
     tp::DevBuf d_c1u, d_census;            // rounds: union of candidates, class census
-    tp::DevBuf d_bin;                      // binned fill: counts, offsets, region starts
+    tp::DevBuf d_bin;                      // binned fill: cursors; binned record: counts, offsets
+    tp::DevBuf d_bin_room;                 // binned fill: the bins' places in the scratch
+    std::vector<uint64_t> bin_off, bin_roff;  // host copies of it (buckets, regions)
+    uint64_t bin_tiles = 0;                // the chunk size it is laid out for (0: not)
+    uint32_t bin_rounds = 0;               // ... and the rounds
     tp::DevBuf d_queue;                    // tile queues of the four tile kernels
     tp::DevBuf d_rbin;                     // binned record: items (when the outputs cannot hold them)
     std::vector<uint64_t> census;          // rounds: per set, CLASS_Q counters
@@ -263,7 +267,7 @@ struct tp_plan {
                               &d_c1, &d_j,
                               &d_cnt, &d_set_cnt, &d_hll, &d_keys, &d_seq,
                               &d_blockcnt, &d_blockoff, &d_pos, &d_vertex, &d_strand,
-                              &d_edges, &d_joff, &d_c1u, &d_census, &d_bin, &d_queue, &d_rbin})
+                              &d_edges, &d_joff, &d_c1u, &d_census, &d_bin, &d_bin_room, &d_queue, &d_rbin})
             f(*b);
     }
 

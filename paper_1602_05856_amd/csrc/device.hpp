@@ -35,7 +35,7 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
 // Reverse the order of the 2-bit groups of a 64-bit word.
 __device__ __forceinline__ uint64_t rev2(uint64_t x) {
     uint64_t y = __builtin_bitreverse64(x);
-    return ((y >> 1) & 0x5555555555555555ull) | ((y & 0x5555555555555555ull) << 1);
+    return ((y >> 1) & 0x5555555555555555ull) | ((y << 1) & 0xAAAAAAAAAAAAAAAAull);
 }
 
 // (lo >> sh) | (hi << (64 - sh)) for 0 <= sh < 64, without a branch.
@@ -135,6 +135,12 @@ template <> struct KT<uint64_t> {
         uint32_t q = r >> 5, sh = 2 * (r & 31);
         return funnel(w[q], w[q + 1], sh) & ones(2 * L);
     }
+    // The 32 bases from base r of the 32-bit words w (LSB first).
+    __device__ static __forceinline__ uint64_t win(const uint32_t *w, uint32_t r) {
+        const uint32_t *p = w + (r >> 4), s = 2 * r;
+        return (uint64_t)__builtin_amdgcn_alignbit(p[2], p[1], s) << 32 |
+               __builtin_amdgcn_alignbit(p[1], p[0], s);
+    }
     // val (first base most significant) of an LSB-first window of L bases.
     __device__ static __forceinline__ uint64_t val(uint64_t x, uint32_t L) {
         return rev2(x) >> (64 - 2 * L);
@@ -157,6 +163,9 @@ template <> struct KT<u128> {
         uint64_t a = funnel(w[q], w[q + 1], sh);
         uint64_t b = funnel(w[q + 1], w[q + 2], sh);
         return (((u128)b << 64) | a) & ones(2 * L);
+    }
+    __device__ static __forceinline__ u128 win(const uint32_t *w, uint32_t r) {
+        return (u128)KT<uint64_t>::win(w + 2, r) << 64 | KT<uint64_t>::win(w, r);
     }
     __device__ static __forceinline__ u128 val(u128 x, uint32_t L) {
         u128 r = ((u128)rev2((uint64_t)x) << 64) | rev2((uint64_t)(x >> 64));
@@ -191,6 +200,10 @@ template <> struct KT<u256> {
                      funnel(w[q + 2], w[q + 3], sh), funnel(w[q + 3], w[q + 4], sh));
         return x & ones(2 * L);
     }
+    __device__ static __forceinline__ u256 win(const uint32_t *w, uint32_t r) {
+        return u256(KT<uint64_t>::win(w, r), KT<uint64_t>::win(w + 2, r),
+                    KT<uint64_t>::win(w + 4, r), KT<uint64_t>::win(w + 6, r));
+    }
     __device__ static __forceinline__ u256 val(const u256 &x, uint32_t L) {
         const u256 r(rev2(x.w3), rev2(x.w2), rev2(x.w1), rev2(x.w0));
         return r >> (256 - 2 * L);
@@ -222,9 +235,69 @@ __device__ __forceinline__ T norm(const Strands<T> &s, bool single) {
     return (single || s.fwd <= s.rc) ? s.fwd : s.rc;
 }
 
-// Base code at base index r of words w.
-__device__ __forceinline__ uint32_t base_at(const uint64_t *w, uint32_t r) {
-    return (uint32_t)(w[r >> 5] >> (2 * (r & 31))) & 3u;
+// ------------------------------------------------------------ staged tile
+// A tile's packed words in LDS twice: as they are (f) and in reverse base
+// order (b; base u of b is base STAGE_BASES - 1 - u of f).  A k-mer's value
+// has its first base most significant, so it is a window of b, as its reverse
+// complement's is the complement of a window of f: both strands of a k-mer
+// are cut out with one funnel shift per 32-bit word, with no bit reversal and
+// no shift by the k-mer's length (which for a four-word k-mer were more than
+// half of the instructions; the tile kernels are bound by those).  Base index
+// r of the stage is global base index tile * TILE - 32 + r.
+constexpr uint32_t STAGE_BASES = STAGE_WORDS * 32;
+struct Stage {
+    uint64_t f[STAGE_WORDS];
+    uint64_t b[STAGE_WORDS + 4];  // (the longest window reads past a short k-mer's last word)
+};
+
+__device__ __forceinline__ void stage_word(Stage &sg, uint32_t i, uint64_t x) {
+    sg.f[i] = x;
+    sg.b[STAGE_WORDS - 1 - i] = rev2(x);
+}
+
+// Bases from r upwards, and from r - 1 downwards, the first in the low bits.
+template <class T> __device__ __forceinline__ T up_from(const Stage &sg, uint32_t r) {
+    return KT<T>::win((const uint32_t *)sg.f, r);
+}
+template <class T> __device__ __forceinline__ T down_from(const Stage &sg, uint32_t r) {
+    return KT<T>::win((const uint32_t *)sg.b, STAGE_BASES - r);
+}
+
+// The value and reverse-complement value of the L-mer at r.
+template <class T>
+__device__ __forceinline__ Strands<T> kmer_at(const Stage &sg, uint32_t r, uint32_t L) {
+    const T ones = KT<T>::ones(2 * L);
+    Strands<T> s;
+    s.fwd = down_from<T>(sg, r + L) & ones;
+    s.rc = ~up_from<T>(sg, r) & ones;
+    return s;
+}
+
+// The k-mer at r with the bases before and after it.
+template <class T>
+__device__ __forceinline__ Strands<T> kmer_between(const Stage &sg, uint32_t r, uint32_t k,
+                                                   uint32_t *before, uint32_t *after) {
+    const T ones = KT<T>::ones(2 * k);
+    const T u = up_from<T>(sg, r - 1), d = down_from<T>(sg, r + k + 1);
+    *before = (uint32_t)u & 3u;
+    *after = (uint32_t)d & 3u;
+    Strands<T> s;
+    s.fwd = (d >> 2) & ones;
+    s.rc = ~(u >> 2) & ones;
+    return s;
+}
+
+// A string relative to a tile: its first base and the one past its last, cut
+// to what a position of the tile can tell apart (first: before the tile, -1).
+// A position q of the tile starts a k-mer when gs <= q and q + k <= ge; it is
+// the string's first when q == gs, its last when q + k == ge.
+struct Span {
+    int32_t gs, ge;
+};
+
+__device__ __forceinline__ Span span_of(const DString *S, uint32_t si, uint64_t t0) {
+    const int64_t a = (int64_t)(S[si].gstart - t0), b = (int64_t)(S[si].gend - t0);
+    return Span{(int32_t)(a < -1 ? -1 : a), (int32_t)(b > (1 << 20) ? (1 << 20) : b)};
 }
 
 // --------------------------------------------------------------- Bloom ops
@@ -254,19 +327,12 @@ struct MiddleKey {
 };
 
 template <class T>
-__device__ __forceinline__ MiddleKey middle_key(T mf, T mr, bool single, uint64_t nblock_mask) {
-    T mu;
+__device__ __forceinline__ MiddleKey middle_key(const T &mf, const T &mr, bool single,
+                                                uint64_t nblock_mask) {
     MiddleKey key;
-    if (single || mf < mr) {
-        mu = mf;
-        key.orient = 0;
-    } else if (mf > mr) {
-        mu = mr;
-        key.orient = 1;
-    } else {
-        mu = mf;
-        key.orient = 2;
-    }
+    const bool rev = !single && mr < mf;
+    const T mu = rev ? mr : mf;
+    key.orient = rev ? 1u : (!single && mr == mf) ? 2u : 0u;
     const uint64_t f = KT<T>::fold(mu);
     key.block = mix64(f ^ kS1) & nblock_mask;
     const uint64_t g = mix64(f ^ kS2);
@@ -284,11 +350,11 @@ __device__ __forceinline__ uint64_t pair_mask(uint32_t a, uint32_t d, uint32_t j
     return m;
 }
 
-// Pair index of edge x.m.y in its middle's orientation; fwd_le_rc tells
-// whether val(edge) <= val(rc(edge)) (used for palindromic middles only).
-__device__ __forceinline__ uint32_t pair_index(uint32_t orient, uint32_t x, uint32_t y,
-                                               bool fwd_le_rc) {
-    const bool flip = orient == 1 || (orient == 2 && !fwd_le_rc);
+// Pair index of edge x.m.y in its middle's orientation.  With a palindromic
+// middle the edge's value is at most its reverse complement's when x is at
+// most 3 - y.
+__device__ __forceinline__ uint32_t pair_index(uint32_t orient, uint32_t x, uint32_t y) {
+    const bool flip = orient == 1 || (orient == 2 && x + y > 3);
     return flip ? 4 * (3 - y) + (3 - x) : 4 * x + y;
 }
 
@@ -308,22 +374,6 @@ __device__ __forceinline__ bool in_class(uint32_t sub, uint32_t lo, uint32_t hi)
     return sub >= lo && sub < hi;
 }
 
-// Normalised k-mers at p and p + 1 of the (k+1)-mer e at p: the prefix reads
-// fwd >> 2 forward and rc & ones(2k) reversed, the suffix fwd & ones(2k) and
-// rc >> 2.
-template <class T>
-__device__ __forceinline__ void edge_kmers(const Strands<T> &e, uint32_t k, bool single, T *pre,
-                                           T *suf) {
-    const T ones = KT<T>::ones(2 * k);
-    Strands<T> a, b;
-    a.fwd = e.fwd >> 2;
-    a.rc = e.rc & ones;
-    b.fwd = e.fwd & ones;
-    b.rc = e.rc >> 2;
-    *pre = norm(a, single);
-    *suf = norm(b, single);
-}
-
 // ---------------------------------------------------------- string lookup
 // Strings (contigs) of length >= k, sorted by gstart, disjoint, in global
 // base-index coordinates.  find the last string with gstart <= p among
@@ -341,19 +391,31 @@ __device__ __forceinline__ uint32_t find_string(const DString *S, uint32_t lo, u
     return a == lo ? hi : a - 1;
 }
 
+// The span of the string that holds position q of the tile at t0, among the
+// tile's strings [lo, hi), or one that holds nothing.
+__device__ __forceinline__ Span span_at(const DString *S, uint32_t lo, uint32_t hi, uint64_t t0,
+                                        uint32_t q) {
+    const uint32_t si = find_string(S, lo, hi, t0 + q);
+    return si != hi ? span_of(S, si, t0) : Span{1 << 20, -1};
+}
+
 // ------------------------------------------------------- sentinel filter
 // Sentinel k-mers (normalised first and last k-mer of every string): a bit
 // prefilter kept in LDS, then the set's open-addressing sentinel table.
 constexpr uint64_t kS6 = 0xC0AC29B7C97C50DDull;  // sentinel-table slots
 
-template <class T>
-__device__ __forceinline__ uint32_t prefilter_bit(T v, uint32_t log2bits) {
-    return (uint32_t)((KT<T>::fold(v) * 0x9E3779B97F4A7C15ull) >> (64 - log2bits));
+// Two prefilters of the same sentinels, each by a hash that its kernels have at
+// hand: the k-mer's table hash (the standard query and the decision), and the
+// sum of the G values of its two middles (the blocked query; the same for both
+// orientations).
+__device__ __forceinline__ uint32_t prefilter_bit(uint64_t slot_hash, uint32_t log2bits) {
+    return (uint32_t)(slot_hash >> 32) >> (32 - log2bits);
+}
+__device__ __forceinline__ uint32_t prefilter_bit_g(uint32_t ghi_sum, uint32_t log2bits) {
+    return ghi_sum >> (32 - log2bits);
 }
 
-template <class T>
-__device__ __forceinline__ bool prefilter_hit(T v, const uint32_t *lds_pf, uint32_t log2bits) {
-    const uint32_t bit = prefilter_bit(v, log2bits);
+__device__ __forceinline__ bool prefilter_hit(const uint32_t *lds_pf, uint32_t bit) {
     return (lds_pf[bit >> 5] >> (bit & 31)) & 1u;
 }
 
@@ -383,10 +445,7 @@ __device__ __forceinline__ bool sent_probe_from(const T *tab, uint32_t log2, T v
 
 // Membership in a set's sentinel table (tab: the set's first slot).
 template <class T>
-__device__ __forceinline__ bool is_sentinel(T v, const uint32_t *lds_pf, uint32_t pf_log2,
-                                            const T *tab, uint32_t log2) {
-    if (!log2 || !prefilter_hit(v, lds_pf, pf_log2))
-        return false;
+__device__ __forceinline__ bool in_sentinels(const T &v, const T *tab, uint32_t log2) {
     const uint32_t s = sent_home(v, log2);
     return sent_probe_from(tab, log2, v, s, tab[s]);
 }

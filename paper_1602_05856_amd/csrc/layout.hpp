@@ -53,9 +53,8 @@ constexpr uint32_t BIN_BUCKETS = 1024;
 constexpr uint32_t BIN_MAX_BUCKETS = 2048;         // pools up to 2^32 blocks (32 GiB)
 constexpr uint32_t BIN_LOCAL_LOG2 = 21;            // an item's block bits: buckets of up to 2^21 blocks
 constexpr uint32_t BIN_BLOCK = 1024;               // threads of the binned fill's kernels
-constexpr uint32_t BIN_PER = 16;                   // items per thread per batch
+constexpr uint32_t BIN_PER = 16;                   // the split's items per thread per batch
 constexpr uint32_t BIN_BATCH = BIN_BLOCK * BIN_PER;
-constexpr uint32_t BIN_TILES = BIN_BATCH / TILE;   // tiles per batch (of one- and two-word k-mers)
 constexpr uint32_t BIN_CHUNK_TILES_MAX = 1u << 20; // 2^31 positions per chunk (explicit)
 // Binned record: buckets of RBIN_SUB table blocks.
 constexpr uint32_t RBIN_MAX_BUCKETS = 1024;
@@ -152,14 +151,17 @@ enum KernelId { K_FILL = 0, K_QUERY = 1, K_RECORD = 2, K_DECIDE = 3, K_COUNT = 4
 
 // Sentinel k-mers: per set an open-addressing table of the normalised first
 // and last k-mers of its strings (home slot by hash, linear probing, empty
-// slots all ones -- never a k-mer value), plus one bit prefilter for all
-// sets kept in LDS.
+// slots all ones -- never a k-mer value), plus two bit prefilters for all
+// sets (by table hash, then by the middles' hashes), kept in LDS.
 struct SentArgs {
     const void *table;         // sentinel-table pool: W words per slot
     uint32_t n;                // sentinel k-mers (2 per string)
-    uint32_t pf_log2;          // prefilter size, log2 bits
-    const uint32_t *prefilter;
+    uint32_t pf_log2;          // a prefilter's size, log2 bits
+    const uint32_t *prefilter; // both, one after the other
 };
+__host__ __device__ constexpr uint32_t prefilter_words(uint32_t pf_log2) {
+    return (1u << pf_log2) / 32;
+}
 constexpr uint32_t SENT_TAB_MIN_LOG2 = 4;
 
 struct BloomArgs {
@@ -204,12 +206,11 @@ hipError_t pass2_occupancy(KernelId which, int W, int *blocks_per_cu);
 hipError_t launch_zero(void *p, uint64_t bytes, hipStream_t s);
 hipError_t launch_fill_u64(uint64_t *p, uint64_t n, uint64_t v, hipStream_t s);
 
-// a0: normalised first/last k-mer of every string (raw: 2 per string), each
-// set's sentinel table (values, and a claim word per slot; tab_slots in all)
-// and the sentinel prefilter.
-hipError_t launch_sentinels(int W, const SeqArgs &a, void *raw, void *tab, uint32_t *tab_owner,
-                            uint64_t tab_slots, uint32_t *prefilter, uint32_t pf_log2,
-                            hipStream_t s);
+// a0: each set's sentinel table (normalised first and last k-mer of every
+// string; tab_owner: a claim word per slot, tab_slots in all) and the sentinel
+// prefilters.
+hipError_t launch_sentinels(int W, const SeqArgs &a, const SentArgs &sa, uint32_t *tab_owner,
+                            uint64_t tab_slots, hipStream_t s);
 // a1: insert every normalised (k+1)-mer into its set's Bloom filter.
 // Binned fill of a blocked filter pool (the same bits as launch_fill; the
 // pool zeroed beforehand): per chunk of tiles, every edge's filter effect

@@ -1,11 +1,10 @@
 // First pass of Algorithm 2 (Filter-Junctions with E = Bloom filter) and the
 // sentinel set, for gfx950.
 //
-//   k_sentinel_values, k_sentinel_table, k_prefilter
-//                 normalised first and last k-mer of every string (the
+//   k_sentinels   normalised first and last k-mer of every string (the
 //                 sentinel vertices of the Preliminaries section, both
-//                 strands), a hash table of them per set, plus a bit
-//                 prefilter
+//                 strands): a hash table of them per set, plus two bit
+//                 prefilters
 //   k_fill        loop 1 of Algorithm 1 with every position marked: every
 //                 normalised (k+1)-mer goes into its set's filter (load first,
 //                 atomicOr only for bits still clear)
@@ -27,9 +26,9 @@
 //             costs one random load.
 //
 // Sequence reads: each workgroup stages its tile's packed words (plus one
-// word before and three after, covering predecessor, successor and the
-// longest window) in LDS with coalesced 64-bit loads; lanes then extract
-// their k-mer windows from LDS.
+// word before and five after, covering predecessor, successor and the
+// longest window) in LDS with coalesced 64-bit loads, in both base orders;
+// lanes then cut their k-mers' windows out of LDS (Stage).
 #include "device.hpp"
 
 namespace tp {
@@ -78,46 +77,50 @@ hipError_t launch_fill_u64(uint64_t *p, uint64_t n, uint64_t v, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Stage the packed words of tile `tile` into w: word i of w is global word
-// tile*TILE_WORDS - 1 + i (zero outside the buffer).  Base index r of w is
-// global base index tile*TILE - 32 + r.
-__device__ __forceinline__ void stage_tile(const SeqArgs &a, uint64_t tile, uint64_t *w) {
-    int64_t w0 = (int64_t)(tile * TILE_WORDS) - 1;
+// Stage the packed words of tile `tile`: word i of the stage is global word
+// tile*TILE_WORDS - 1 + i (zero outside the buffer).
+__device__ __forceinline__ void stage_tile(const SeqArgs &a, uint64_t tile, Stage &sg) {
+    const int64_t w0 = (int64_t)(tile * TILE_WORDS) - 1;
     for (uint32_t i = threadIdx.x; i < STAGE_WORDS; i += blockDim.x) {
-        int64_t gw = w0 + (int64_t)i;
-        w[i] = (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull;
+        const int64_t gw = w0 + (int64_t)i;
+        stage_word(sg, i, (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull);
     }
 }
 
 // ------------------------------------------------------------ sentinels (a0)
 
+// Sentinel i: the first (i even) or last k-mer of string i / 2.
 template <class T>
-__global__ void k_sentinel_values(SeqArgs a, T *out) {
-    uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.n_strings)
-        return;
-    DString s = a.strings[i];
-    uint64_t first = s.gstart, last = s.gend - a.k;
-    T x0 = KT<T>::window(a.seq + (first >> 5), (uint32_t)(first & 31), a.k);
-    T x1 = KT<T>::window(a.seq + (last >> 5), (uint32_t)(last & 31), a.k);
-    out[2 * i] = norm(strands(x0, a.k), a.single != 0);
-    out[2 * i + 1] = norm(strands(x1, a.k), a.single != 0);
+__device__ __forceinline__ Strands<T> sentinel_at(const SeqArgs &a, uint32_t i) {
+    const DString &s = a.strings[i / 2];
+    const uint64_t p = i & 1 ? s.gend - a.k : s.gstart;
+    return strands(KT<T>::window(a.seq + (p >> 5), (uint32_t)(p & 31), a.k), a.k);
 }
 
-// Each set's sentinel table: thread i inserts sentinel i (of string i / 2,
-// hence of that string's set) by claiming a slot's claim word; a k-mer that
-// another sentinel of the set has already claimed is not inserted twice.
-// Lookups run in later kernels, after every value is in place.
+// Each set's sentinel table and the prefilters (empty beforehand): thread i
+// inserts sentinel i by claiming a slot's claim word; a k-mer that another
+// sentinel of the set has already claimed (read again from the sequence) is
+// not inserted twice.  Lookups run in later kernels, after every value is in
+// place.
 template <class T>
-__global__ __launch_bounds__(BLOCK) void k_sentinel_table(SeqArgs a, const T *raw, uint32_t n,
-                                                          T *tab, uint32_t *owner) {
+__global__ __launch_bounds__(BLOCK) void k_sentinels(SeqArgs a, uint32_t n, T *tab, uint32_t *owner,
+                                                     uint32_t *pf, uint32_t *pf_g,
+                                                     uint32_t pf_log2) {
     const uint32_t i = blockIdx.x * BLOCK + threadIdx.x;
     if (i >= n)
         return;
+    const bool single = a.single != 0;
+    const Strands<T> st = sentinel_at<T>(a, i);
+    const T v = norm(st, single), mid_ones = KT<T>::ones(2 * (a.k - 1));
+    const uint32_t b = prefilter_bit(slot_hash(v), pf_log2);
+    atomicOr(&pf[b >> 5], 1u << (b & 31));
+    const MiddleKey in = middle_key((T)(st.fwd >> 2), (T)(st.rc & mid_ones), single, 0);
+    const MiddleKey out = middle_key((T)(st.fwd & mid_ones), (T)(st.rc >> 2), single, 0);
+    const uint32_t c = prefilter_bit_g((uint32_t)(in.g >> 32) + (uint32_t)(out.g >> 32), pf_log2);
+    atomicOr(&pf_g[c >> 5], 1u << (c & 31));
     const SetDesc &d = a.sets[a.strings[i / 2].set];
     if (!d.sent_tab_log2)
         return;
-    const T v = raw[i];
     const uint32_t mask = (1u << d.sent_tab_log2) - 1;
     T *t = tab + d.sent_tab_off;
     uint32_t *o = owner + d.sent_tab_off;
@@ -128,49 +131,28 @@ __global__ __launch_bounds__(BLOCK) void k_sentinel_table(SeqArgs a, const T *ra
             t[s] = v;
             return;
         }
-        if (raw[prev] == v)
+        if (norm(sentinel_at<T>(a, prev), single) == v)
             return;  // the same k-mer, inserted by another sentinel
         s = (s + 1) & mask;
     }
 }
 
-template <class T>
-__global__ void k_prefilter(const T *vals, uint32_t n, uint32_t log2bits, uint32_t *bits) {
-    uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n)
-        return;
-    uint32_t b = prefilter_bit(vals[i], log2bits);
-    atomicOr(&bits[b >> 5], 1u << (b & 31));
-}
-
-template <class T>
-static hipError_t sentinels_t(const SeqArgs &a, void *raw, void *tab, uint32_t *owner,
-                              uint64_t tab_slots, uint32_t *prefilter, uint32_t pf_log2,
-                              hipStream_t s) {
-    uint32_t n = 2 * a.n_strings;
-    hipError_t e = launch_zero(prefilter, (1ull << pf_log2) / 8, s);
+hipError_t launch_sentinels(int W, const SeqArgs &a, const SentArgs &sa, uint32_t *tab_owner,
+                            uint64_t tab_slots, hipStream_t s) {
+    hipError_t e = launch_zero((void *)sa.prefilter, 2 * prefilter_words(sa.pf_log2) * 4, s);
     if (e == hipSuccess && tab_slots) {
-        e = launch_fill_u64((uint64_t *)tab, tab_slots * KT<T>::W, ~0ull, s);
+        e = launch_fill_u64((uint64_t *)sa.table, tab_slots * W, ~0ull, s);
         if (e == hipSuccess)
-            e = launch_fill_u64((uint64_t *)owner, (tab_slots + 1) / 2, ~0ull, s);
+            e = launch_fill_u64((uint64_t *)tab_owner, (tab_slots + 1) / 2, ~0ull, s);
     }
-    if (e != hipSuccess || n == 0)
+    if (e != hipSuccess || sa.n == 0)
         return e;
-    uint32_t g1 = (a.n_strings + BLOCK - 1) / BLOCK, g2 = (n + BLOCK - 1) / BLOCK;
-    hipLaunchKernelGGL(k_sentinel_values<T>, dim3(g1), dim3(BLOCK), 0, s, a, (T *)raw);
-    hipLaunchKernelGGL(k_sentinel_table<T>, dim3(g2), dim3(BLOCK), 0, s, a, (const T *)raw, n,
-                       (T *)tab, owner);
-    hipLaunchKernelGGL(k_prefilter<T>, dim3(g2), dim3(BLOCK), 0, s, (const T *)raw, n, pf_log2,
-                       prefilter);
-    return hipGetLastError();
-}
-
-hipError_t launch_sentinels(int W, const SeqArgs &a, void *raw, void *tab, uint32_t *tab_owner,
-                            uint64_t tab_slots, uint32_t *prefilter, uint32_t pf_log2,
-                            hipStream_t s) {
     return by_width(W, [&](auto tag) {
-        return sentinels_t<decltype(tag)>(a, raw, tab, tab_owner, tab_slots, prefilter, pf_log2,
-                                          s);
+        using T = decltype(tag);
+        hipLaunchKernelGGL(k_sentinels<T>, dim3((sa.n + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, a,
+                           sa.n, (T *)sa.table, tab_owner, (uint32_t *)sa.prefilter,
+                           (uint32_t *)sa.prefilter + prefilter_words(sa.pf_log2), sa.pf_log2);
+        return hipGetLastError();
     });
 }
 
@@ -212,16 +194,9 @@ __device__ __forceinline__ uint32_t insert_standard(const BloomArgs &f, const St
 // has already sent is skipped: that lane's load and atomic complete within
 // the kernel, and filter bits are only ever set.  Lanes racing on one entry
 // both send.
-template <class T>
-__device__ __forceinline__ uint32_t insert_blocked(const BloomArgs &f, const Strands<T> &e,
-                                                   uint32_t k, bool single,
-                                                   unsigned long long *dd) {
-    const T mid_ones = KT<T>::ones(2 * (k - 1));
+__device__ __forceinline__ uint32_t insert_blocked(const BloomArgs &f, const MiddleKey &key,
+                                                   uint32_t j, unsigned long long *dd) {
     unsigned long long *blocks = (unsigned long long *)f.words;
-    const uint32_t x = (uint32_t)(e.fwd >> (2 * k)), y = (uint32_t)(e.fwd & 3);
-    const MiddleKey key = middle_key((T)((e.fwd >> 2) & mid_ones), (T)((e.rc >> 2) & mid_ones),
-                                     single, f.mask >> 6);
-    const uint32_t j = pair_index(key.orient, x, y, e.fwd <= e.rc);
     if (dd) {
         const unsigned long long id =
             (unsigned long long)key.block << 16 | key.a | key.d << 6 | j << 12;
@@ -240,9 +215,29 @@ __device__ __forceinline__ uint32_t insert_blocked(const BloomArgs &f, const Str
     return 1;
 }
 
+// The blocked filter's key of the (k+1)-mer at r, and its pair.
+template <class T>
+__device__ __forceinline__ MiddleKey edge_key(const Stage &sg, uint32_t r, uint32_t k, bool single,
+                                              uint64_t nblock_mask, uint32_t *pair) {
+    uint32_t x, y;
+    const Strands<T> m = kmer_between<T>(sg, r + 1, k - 1, &x, &y);
+    const MiddleKey key = middle_key(m.fwd, m.rc, single, nblock_mask);
+    *pair = pair_index(key.orient, x, y);
+    return key;
+}
+
+// Whether a round inserts the (k+1)-mer at r: one of its k-mers is in the
+// round's class.
+template <class T>
+__device__ __forceinline__ bool edge_in_class(const Stage &sg, uint32_t r, uint32_t k, bool single,
+                                              uint32_t lo, uint32_t hi) {
+    return in_class(class_subrange(norm(kmer_at<T>(sg, r, k), single)), lo, hi) ||
+           in_class(class_subrange(norm(kmer_at<T>(sg, r + 1, k), single)), lo, hi);
+}
+
 template <class T, bool BLOCKED>
 __global__ __launch_bounds__(BLOCK) void k_fill(SeqArgs a, BloomArgs pool, Counters *cnt) {
-    __shared__ uint64_t w[STAGE_WORDS];
+    __shared__ Stage sg;
     __shared__ unsigned long long block_atomics;
     extern __shared__ unsigned long long dd_lds[];  // FILL_DD entries when deduplicating
     const uint32_t L = a.k + 1;
@@ -261,7 +256,7 @@ __global__ __launch_bounds__(BLOCK) void k_fill(SeqArgs a, BloomArgs pool, Count
         if (lo == hi)
             continue;
         __syncthreads();
-        stage_tile(a, tile, w);
+        stage_tile(a, tile, sg);
         if (dd && ti.set != dd_set) {
             // block indices are relative to the set's own filter
             for (uint32_t q = threadIdx.x; q < FILL_DD; q += BLOCK)
@@ -270,29 +265,23 @@ __global__ __launch_bounds__(BLOCK) void k_fill(SeqArgs a, BloomArgs pool, Count
         }
         __syncthreads();
         const TileSet ts = tile_set_of(a, pool, ti.set);
-        uint32_t si = hi;
-        uint64_t gs = 0, ge = 0;
+        const bool one = lo + 1 == hi;
+        Span sp = one ? span_of(a.strings, lo, t0) : Span{0, -1};
         for (uint32_t it = 0; it < TILE / BLOCK; ++it) {
-            const uint64_t p = t0 + it * BLOCK + threadIdx.x;
-            if (p >= ge) {
-                si = find_string(a.strings, lo, hi, p);
-                gs = si != hi ? a.strings[si].gstart : ~0ull;
-                ge = si != hi ? a.strings[si].gend : 0;
-            }
-            if (p < gs || p + L > ge)
+            const uint32_t q = it * BLOCK + threadIdx.x, r = q + 32;
+            if (!one && (int32_t)q >= sp.ge)
+                sp = span_at(a.strings, lo, hi, t0, q);
+            if ((int32_t)q < sp.gs || (int32_t)(q + L) > sp.ge)
                 continue;
-            const uint32_t r = (uint32_t)(p - t0) + 32;
-            const Strands<T> e = strands(KT<T>::window(w, r, L), L);
-            if (a.classes) {
-                // a round inserts the edges next to a k-mer of its class
-                T pre, suf;
-                edge_kmers(e, a.k, single, &pre, &suf);
-                if (!in_class(class_subrange(pre), ts.cls_lo, ts.cls_hi) &&
-                    !in_class(class_subrange(suf), ts.cls_lo, ts.cls_hi))
-                    continue;
+            if (a.classes && !edge_in_class<T>(sg, r, a.k, single, ts.cls_lo, ts.cls_hi))
+                continue;
+            if (BLOCKED) {
+                uint32_t j;
+                const MiddleKey key = edge_key<T>(sg, r, a.k, single, ts.f.mask >> 6, &j);
+                my_atomics += insert_blocked(ts.f, key, j, dd);
+            } else {
+                my_atomics += insert_standard(ts.f, kmer_at<T>(sg, r, L), single);
             }
-            my_atomics += BLOCKED ? insert_blocked(ts.f, e, a.k, single, dd)
-                                  : insert_standard(ts.f, e, single);
         }
     }
     if (my_atomics)
@@ -331,7 +320,7 @@ hipError_t launch_fill(int W, const SeqArgs &a, const BloomArgs &pool, Counters 
 // directly (the pool is zeroed first and a region is read before its items
 // are ORed in).
 //
-//   k_bin_items    batches of 8 tiles: the items of the batch, sorted by
+//   k_bin_items    batches of a few tiles: the items of the batch, sorted by
 //                  bucket in LDS, appended to their buckets
 //   k_bin_split    buckets of several regions: batches of a bucket's items,
 //                  sorted by region in LDS, appended to their regions
@@ -448,26 +437,27 @@ __device__ __forceinline__ uint32_t bin_lanes(uint32_t nb, uint32_t batch) {
 // A batch's tile: its range of strings, its set's filter, and its string when
 // it has just one.
 struct BinTile {
-    uint64_t t0, gs, ge;
+    uint64_t t0;
     uint64_t mask;       // the set's filter bits - 1
     uint32_t block0;     // its first block in the pool
     uint32_t lo, hi, cls_lo, cls_hi;
+    Span sp;
 };
 
 // The edges are those k_fill inserts: every (k+1)-mer within a string, of the
 // round's class when there are rounds.
 template <class T, uint32_t NB, uint32_t NT, uint32_t PER, bool CLASSES>
-__global__ __launch_bounds__(NT) void k_bin_items(SeqArgs a, BloomArgs pool, BinArgs b,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KT<T>::W <= 2 && !CLASSES ? 8 : 4)))
+void k_bin_items(SeqArgs a, BloomArgs pool, BinArgs b,
                                                          Counters *cnt) {
     constexpr uint32_t TILES = NT * PER / TILE;
     __shared__ BinSort<NB, NT, PER> sh;
-    __shared__ uint64_t w[TILES][STAGE_WORDS];
+    __shared__ Stage sg[TILES];
     __shared__ BinTile tl[TILES];
     const uint32_t L = a.k + 1, k = a.k;
     const bool single = a.single != 0;
     const uint32_t lpb = bin_lanes(b.n_buckets, NT * PER);
     const uint64_t batches = (b.t_hi - b.t_lo + TILES - 1) / TILES;
-    const T mid_ones = KT<T>::ones(2 * (k - 1));
     uint32_t atomics = 0;
     for (uint32_t i = threadIdx.x; i < NB; i += NT)
         sh.cnt[i] = 0;
@@ -476,6 +466,7 @@ __global__ __launch_bounds__(NT) void k_bin_items(SeqArgs a, BloomArgs pool, Bin
         const uint32_t nt = (uint32_t)min((uint64_t)TILES, b.t_hi - e0);
         if (threadIdx.x < TILES) {
             BinTile x{};
+            x.sp = Span{0, -1};  // (no string: no edge)
             if (threadIdx.x < nt) {
                 const uint64_t tile = a.tile_order[e0 + threadIdx.x];
                 const TileInfo ti = a.tiles[tile];
@@ -487,17 +478,15 @@ __global__ __launch_bounds__(NT) void k_bin_items(SeqArgs a, BloomArgs pool, Bin
                 x.mask = d.bloom_mask;
                 x.cls_lo = d.cls_lo;
                 x.cls_hi = d.cls_hi;
-                if (x.lo + 1 == x.hi) {
-                    x.gs = a.strings[x.lo].gstart;
-                    x.ge = a.strings[x.lo].gend;
-                }
+                if (x.lo + 1 == x.hi)
+                    x.sp = span_of(a.strings, x.lo, x.t0);
             }
-            tl[threadIdx.x] = x;  // without strings (lo == hi): no edge
+            tl[threadIdx.x] = x;
         }
         for (uint32_t i = threadIdx.x; i < nt * STAGE_WORDS; i += NT) {
             const uint32_t j = i / STAGE_WORDS, u = i % STAGE_WORDS;
             const int64_t gw = (int64_t)((uint64_t)a.tile_order[e0 + j] * TILE_WORDS) - 1 + u;
-            w[j][u] = (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull;
+            stage_word(sg[j], u, (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull);
         }
         __syncthreads();
         uint32_t item[PER], at[PER];
@@ -505,29 +494,15 @@ __global__ __launch_bounds__(NT) void k_bin_items(SeqArgs a, BloomArgs pool, Bin
         for (uint32_t q = 0; q < PER; ++q) {
             item[q] = 0;
             at[q] = ~0u;
-            const uint32_t j = q * NT / TILE, r = (q * NT & (TILE - 1)) + threadIdx.x;
+            const uint32_t j = q * NT / TILE, p = (q * NT & (TILE - 1)) + threadIdx.x;
             const BinTile &x = tl[j];
-            const uint64_t p = x.t0 + r;
-            uint64_t gs = x.gs, ge = x.ge;
-            if (x.hi - x.lo > 1) {
-                const uint32_t si = find_string(a.strings, x.lo, x.hi, p);
-                gs = si != x.hi ? a.strings[si].gstart : ~0ull;
-                ge = si != x.hi ? a.strings[si].gend : 0;
-            }
-            if (p < gs || p + L > ge)
+            const Span sp = x.hi - x.lo > 1 ? span_at(a.strings, x.lo, x.hi, x.t0, p) : x.sp;
+            if ((int32_t)p < sp.gs || (int32_t)(p + L) > sp.ge)
                 continue;
-            const Strands<T> e = strands(KT<T>::window(w[j], r + 32, L), L);
-            if (CLASSES) {
-                T pre, suf;
-                edge_kmers(e, k, single, &pre, &suf);
-                if (!in_class(class_subrange(pre), x.cls_lo, x.cls_hi) &&
-                    !in_class(class_subrange(suf), x.cls_lo, x.cls_hi))
-                    continue;
-            }
-            const uint32_t c0 = (uint32_t)(e.fwd >> (2 * k)), c1 = (uint32_t)(e.fwd & 3);
-            const MiddleKey key = middle_key((T)((e.fwd >> 2) & mid_ones),
-                                             (T)((e.rc >> 2) & mid_ones), single, x.mask >> 6);
-            const uint32_t pair = pair_index(key.orient, c0, c1, e.fwd <= e.rc);
+            if (CLASSES && !edge_in_class<T>(sg[j], p + 32, k, single, x.cls_lo, x.cls_hi))
+                continue;
+            uint32_t pair;
+            const MiddleKey key = edge_key<T>(sg[j], p + 32, k, single, x.mask >> 6, &pair);
             const uint32_t block = x.block0 + (uint32_t)key.block;
             item[q] = (block & ((1u << b.bucket_log2) - 1)) << BIN_EFFECT_BITS |
                       bin_effect(key, pair, pool.h);
@@ -642,23 +617,34 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_bin_apply(BloomArgs pool, BinArgs
         atomicAdd(&b.popcount->bloom_popcount, (unsigned long long)bits_wg);
 }
 
-// Items per thread of k_bin_items: four-word k-mers take half (registers).
-template <class T> struct ItemsPer {
-    static constexpr uint32_t N = KT<T>::W == 4 ? BIN_PER / 2 : BIN_PER;
+// Items per thread of k_bin_items.  Twelve leave room for two workgroups per
+// CU, in registers (64, with a few spilled) and LDS, so that one's sort runs
+// beside the other's hashing: 62 x 5 Mbp at k = 25 1.57 ms, against 1.80 with
+// sixteen and one workgroup and 1.69 with eight (more claims).  Four-word
+// k-mers and rounds (two more k-mers to hash) need the registers of one
+// workgroup per CU.
+template <class T, bool CLASSES> struct ItemsPer {
+    static constexpr uint32_t N = KT<T>::W == 4 ? 8 : CLASSES ? 16 : 12;
 };
 
-template <class T, uint32_t NB>
+template <class T, uint32_t NB, bool CLASSES>
 static void bin_items_t(const SeqArgs &a, const BloomArgs &pool, const BinArgs &b, Counters *cnt,
                         hipStream_t s) {
-    constexpr uint32_t NT = BIN_BLOCK, PER = ItemsPer<T>::N, TILES = NT * PER / TILE;
+    constexpr uint32_t NT = BIN_BLOCK, PER = ItemsPer<T, CLASSES>::N, TILES = NT * PER / TILE;
     const uint64_t batches = (b.t_hi - b.t_lo + TILES - 1) / TILES;
-    const uint32_t grid = (uint32_t)min(batches, (uint64_t)b.n_cu);
-    if (a.classes)
-        hipLaunchKernelGGL((k_bin_items<T, NB, NT, PER, true>), dim3(grid), dim3(NT), 0, s, a,
-                           pool, b, cnt);
-    else
-        hipLaunchKernelGGL((k_bin_items<T, NB, NT, PER, false>), dim3(grid), dim3(NT), 0, s, a,
-                           pool, b, cnt);
+    const uint32_t grid = (uint32_t)min(batches, 2ull * b.n_cu);
+    hipLaunchKernelGGL((k_bin_items<T, NB, NT, PER, CLASSES>), dim3(grid), dim3(NT), 0, s, a, pool,
+                       b, cnt);
+}
+
+template <class T>
+static void bin_items_w(const SeqArgs &a, const BloomArgs &pool, const BinArgs &b, Counters *cnt,
+                        hipStream_t s) {
+    auto *fn = b.n_buckets <= BIN_BUCKETS
+                   ? (a.classes ? bin_items_t<T, BIN_BUCKETS, true> : bin_items_t<T, BIN_BUCKETS, false>)
+                   : (a.classes ? bin_items_t<T, BIN_MAX_BUCKETS, true>
+                                : bin_items_t<T, BIN_MAX_BUCKETS, false>);
+    fn(a, pool, b, cnt, s);
 }
 
 hipError_t launch_fill_binned(int W, const SeqArgs &a, const BloomArgs &pool, Counters *cnt,
@@ -677,10 +663,7 @@ hipError_t launch_fill_binned(int W, const SeqArgs &a, const BloomArgs &pool, Co
             hipError_t e = launch_zero(b.cursor, n_cursor * sizeof(unsigned long long), s);
             if (e != hipSuccess)
                 return e;
-            if (b.n_buckets <= BIN_BUCKETS)
-                bin_items_t<T, BIN_BUCKETS>(a, pool, b, cnt, s);
-            else
-                bin_items_t<T, BIN_MAX_BUCKETS>(a, pool, b, cnt, s);
+            bin_items_w<T>(a, pool, b, cnt, s);
             if (split)
                 hipLaunchKernelGGL(k_bin_split, dim3(b.slices, b.n_buckets), dim3(BIN_BLOCK), 0, s,
                                    pool, b, cnt);
@@ -749,34 +732,6 @@ __device__ __forceinline__ bool any_present_standard(const BloomArgs &f, const S
     return true;
 }
 
-// Pair tests in rotation form.  Pair j's bits (a + (j*h + t)*d) mod 64,
-// t < h, are the key's template sum_t 2^(t*d mod 64) rotated left by
-// s = a + j*hd, hd = h*d mod 64; the template depends on the odd stride d
-// only, so a workgroup keeps the 32 of them in LDS.  In the query, the pair
-// index of the edge through base c is affine in c for a non-palindromic
-// middle: s = base + c*step (mod 64).
-struct PairKey {
-    uint32_t a, d, hd, orient;
-};
-
-__device__ __forceinline__ uint32_t pack_key(const MiddleKey &m, uint32_t h) {
-    return m.a | m.d << 6 | ((h * m.d) & 63u) << 12 | m.orient << 18;
-}
-
-__device__ __forceinline__ PairKey unpack_key(uint32_t x) {
-    return PairKey{x & 63u, (x >> 6) & 63u, (x >> 12) & 63u, x >> 18};
-}
-
-// All bits of template t, rotated left by s (mod 64), set in w.
-__device__ __forceinline__ bool rot_all(uint64_t w, uint64_t t, uint32_t s) {
-    const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
-    const bool sw = (s & 32u) != 0;  // rotating by 32 swaps the halves
-    const uint32_t x = sw ? lo : hi, y = sw ? hi : lo;
-    const uint32_t rlo = __builtin_amdgcn_alignbit(x, y, s);
-    const uint32_t rhi = __builtin_amdgcn_alignbit(y, x, s);
-    return ((~rlo & (uint32_t)t) | (~rhi & (uint32_t)(t >> 32))) == 0;
-}
-
 // Value of the lane below (DPP wave shift right by one); lane 0 gets lane0.
 __device__ __forceinline__ uint32_t from_below(uint32_t x, uint32_t lane0) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)lane0, (int)x, 0x138, 0xF, 0xF, false);
@@ -791,87 +746,135 @@ __device__ __forceinline__ uint64_t lane63(uint64_t x) {
            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, 63);
 }
 
-// Blocked layout: the three out-edges against the out-middle block wo, the
-// three in-edges against the in-middle block wi.  Only a palindromic middle
-// (orientation 2) needs the edge's own orientation, per edge.
-template <class T>
-__device__ __forceinline__ bool any_present_blocked(const Strands<T> &st, uint32_t k, uint32_t pa,
-                                                    uint32_t sb, const PairKey &ko, uint64_t to,
-                                                    uint64_t wo, const PairKey &ki, uint64_t ti,
-                                                    uint64_t wi) {
-    const uint32_t v0 = (uint32_t)(st.fwd >> (2 * (k - 1)));
-    const uint32_t vk = (uint32_t)(st.fwd & 3);
-    // out-edge v.c has pair 4*v0 + c, or 15 - 4c - v0 read reversed; in-edge
-    // d.v has pair 4d + vk, or 15 - 4*vk - d reversed
-    const bool fo = ko.orient == 1, fi = ki.orient == 1;
-    uint32_t so[3], si[3];
-    {
-        const uint32_t bo = ko.a + __umul24(fo ? 15 - v0 : 4 * v0, ko.hd);
-        const uint32_t po = fo ? 64 - 4 * ko.hd : ko.hd;
-        const uint32_t bi = ki.a + __umul24(fi ? 15 - 4 * vk : vk, ki.hd);
-        const uint32_t pi = fi ? 64 - ki.hd : 4 * ki.hd;
-#pragma unroll
-        for (uint32_t j = 0; j < 3; ++j) {
-            so[j] = bo + __umul24(j + (j >= sb), po);
-            si[j] = bi + __umul24(j + (j >= pa), pi);
-        }
-    }
-    const bool pal = ko.orient == 2 || ki.orient == 2;
-    if (__builtin_amdgcn_ballot_w64(pal)) {
-        if (pal) {
-#pragma unroll
-            for (uint32_t j = 0; j < 3; ++j) {
-                if (ko.orient == 2) {
-                    const uint32_t c = j + (j >= sb);
-                    const T of = (st.fwd << 2) | (T)c;
-                    const T orc = st.rc | ((T)(3 - c) << (2 * k));
-                    so[j] = ko.a + ko.hd * pair_index(2, v0, c, of <= orc);
-                }
-                if (ki.orient == 2) {
-                    const uint32_t d = j + (j >= pa);
-                    const T inf = ((T)d << (2 * k)) | st.fwd;
-                    const T inr = (st.rc << 2) | (T)(3 - d);
-                    si[j] = ki.a + ki.hd * pair_index(2, d, vk, inf <= inr);
-                }
-            }
-        }
-    }
-    bool present = false;
-#pragma unroll
-    for (uint32_t j = 0; j < 3; ++j)
-        present |= rot_all(wo, to, so[j]) | rot_all(wi, ti, si[j]);
-    return present;
+// A middle's key as lanes pass it on: offset a (bits 0-5), (d >> 1) << 7 (the
+// byte offset of its stride's masks in pm) and the orientation (bits 12-13).
+__device__ __forceinline__ uint32_t pack_key(const MiddleKey &m) {
+    return ((uint32_t)m.g & 0xFBFu) | m.orient << 12;
+}
+constexpr uint32_t KEY_STRIDE = 0xF80u;
+
+// w rotated right by s (mod 64).
+__device__ __forceinline__ uint64_t rotr64(uint64_t w, uint32_t s) {
+    const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
+    const bool sw = (s & 32u) != 0;  // rotating by 32 swaps the halves
+    const uint32_t x = sw ? hi : lo, y = sw ? lo : hi;
+    return (uint64_t)__builtin_amdgcn_alignbit(x, y, s) << 32 | __builtin_amdgcn_alignbit(y, x, s);
 }
 
-template <class T, bool BLOCKED, bool CLASSES>
+// The pair tests.  Rotating a block right by its key's offset a leaves pair
+// j's bits at (j*h + t)*d mod 64, t < h: 32 x 16 masks (stride, pair), which a
+// workgroup keeps in LDS (pm), so a test is a mask load and two bit
+// operations.  A pair is 4p + q for the edge p.m.q in its middle's
+// orientation, so with two bits each for p and q the three other edges of a
+// side differ from the actual one by an exclusive-or.
+//
+// Nonzero bits of mask j that block w (rotated) lacks.
+__device__ __forceinline__ uint32_t lacking(const uint64_t *pm, uint32_t at, uint64_t w) {
+    const uint64_t m = *(const uint64_t *)((const char *)pm + at);
+    return ((uint32_t)m & ~(uint32_t)w) | ((uint32_t)(m >> 32) & ~(uint32_t)(w >> 32));
+}
+
+// Whether some edge x.m.c (OUT) or c.m.y (in) other than the actual x.m.y is
+// present in the middle's rotated block w.  Palindromic middles (orientation
+// 2) take each edge's own orientation.
+template <bool OUT>
+__device__ __forceinline__ uint32_t others_lacking(const uint64_t *pm, uint32_t key, uint64_t w,
+                                                   uint32_t x, uint32_t y) {
+    const uint32_t base = key & KEY_STRIDE;
+    const bool rev = (key >> 12) == 1;
+    const uint32_t pair = rev ? (15u - 4 * y - x) : (4 * x + y);
+    const uint32_t at = base | pair << 3;
+    // the varied base sits in the pair's low two bits, or its high two
+    const uint32_t e = OUT == rev ? 32u : 8u;
+    return min(min(lacking(pm, at ^ e, w), lacking(pm, at ^ (2 * e), w)),
+               lacking(pm, at ^ (3 * e), w));
+}
+
+template <bool OUT>
+__device__ __forceinline__ uint32_t others_lacking_palindrome(const uint64_t *pm, uint32_t key,
+                                                              uint64_t w, uint32_t x,
+                                                              uint32_t y) {
+    uint32_t least = ~0u;
+    for (uint32_t i = 1; i < 4; ++i) {
+        const uint32_t p = OUT ? x : x ^ i, q = OUT ? y ^ i : y;
+        least = min(least, lacking(pm, (key & KEY_STRIDE) | pair_index(2, p, q) << 3, w));
+    }
+    return least;
+}
+
+// What the two layouts' queries share per workgroup: the candidate words of
+// a tile, the counters, the sketch of distinct candidate k-mers.
+struct QueryShared {
+    uint32_t pf[(1u << PF_MAX_LOG2) / 32];
+    uint32_t hll[HLL_M];
+    unsigned long long block_probes, cand_lds;
+};
+
+__device__ __forceinline__ void query_begin(QueryShared &qs, const uint32_t *prefilter,
+                                            uint32_t pf_log2) {
+    for (uint32_t i = threadIdx.x; i < prefilter_words(pf_log2); i += BLOCK)
+        qs.pf[i] = prefilter[i];
+    for (uint32_t i = threadIdx.x; i < HLL_M; i += BLOCK)
+        qs.hll[i] = 0;
+    if (threadIdx.x == 0)
+        qs.block_probes = 0;
+}
+
+__device__ __forceinline__ void query_end(const SeqArgs &a, QueryShared &qs, SetSum &cand,
+                                          uint32_t my_probes, Counters *cnt, uint32_t *hll_out) {
+    setsum_flush(cand, &qs.cand_lds, &a.set_cnt[0].candidates, SETCNT_STRIDE);
+    if (my_probes)
+        atomicAdd(&qs.block_probes, (unsigned long long)my_probes);
+    __syncthreads();
+    if (threadIdx.x == 0 && qs.block_probes)
+        atomicAdd(&cnt->query_probes, qs.block_probes);
+    if (a.sketch) {
+        for (uint32_t i = threadIdx.x; i < HLL_M; i += BLOCK) {
+            const uint32_t v = qs.hll[i];
+            if (v && v > __hip_atomic_load(&hll_out[i], __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT))
+                atomicMax(&hll_out[i], v);
+        }
+    }
+}
+
+// A tile that no string touches: all-zero candidate words.
+__device__ __forceinline__ void query_no_string(uint64_t tile, uint64_t *c1, uint64_t *c1u,
+                                                uint32_t round) {
+    if (threadIdx.x < TILE / 64) {
+        c1[tile * (TILE / 64) + threadIdx.x] = 0;
+        if (c1u && round == 0)
+            c1u[tile * (TILE / 64) + threadIdx.x] = 0;
+    }
+}
+
+// Blocked layout.  Each wave walks its own run of 512 consecutive positions
+// of the tile, 64 at a time; a lane hashes its out-middle, loads that block,
+// rotates it, and passes key and block to the lane above, whose in-middle it
+// is; lane 63's carry to the next step's lane 0.  So a position hashes one
+// middle and issues one random load.  Bound by instruction issue where the
+// filter sits in the last-level cache (62 x 5 Mbp, b = 2^30, k = 25: 293
+// vector instructions a position and 2.87 ms when k-mers were reversed and
+// shifted in registers, each pair test rotated the block by itself and the
+// sketch and the prefilter hashed on their own; now 204 and 2.28 ms; k = 100
+// 7.0 -> 4.4 ms), by random loads where it does not (1.6 Gbp, a 1 GiB filter:
+// 26.8 -> 26.3 ms).
+template <class T, bool CLASSES>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(KT<T>::W == 1 ? 5 : 1)))
-void k_query(SeqArgs a, BloomArgs pool, SentArgs sa,
-                                                 uint64_t *c1, uint64_t *c1u, uint32_t round,
-                                                 Counters *cnt, uint32_t *hll_out) {
-    __shared__ uint64_t w[STAGE_WORDS];
-    __shared__ uint32_t pf[(1u << PF_MAX_LOG2) / 32];
-    __shared__ uint32_t hll[HLL_M];
-    __shared__ uint64_t tmpl[32];  // pair template of odd stride d at d >> 1
-    __shared__ unsigned long long block_probes, cand_lds;
+void k_query_blocked(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint64_t *c1u,
+                     uint32_t round, Counters *cnt, uint32_t *hll_out) {
+    __shared__ Stage sg;
+    __shared__ QueryShared qs;
+    __shared__ uint64_t pm[32 * 16];  // pair j of odd stride d at (d >> 1) * 16 + j
     SetSum cand = setsum_begin();
     const uint32_t k = a.k;
     const bool single = a.single != 0;
     const T *sent = (const T *)sa.table;
     const uint32_t lane = threadIdx.x & 63;
     const T mid_ones = KT<T>::ones(2 * (k - 1));
-    for (uint32_t i = threadIdx.x; i < (1u << sa.pf_log2) / 32; i += BLOCK)
-        pf[i] = sa.prefilter[i];
-    for (uint32_t i = threadIdx.x; i < HLL_M; i += BLOCK)
-        hll[i] = 0;
-    if (BLOCKED && threadIdx.x < 32) {
-        const uint32_t d = 2 * threadIdx.x + 1;
-        uint64_t m = 0;
-        for (uint32_t t = 0; t < pool.h; ++t)
-            m |= 1ull << ((t * d) & 63u);
-        tmpl[threadIdx.x] = m;
-    }
-    if (threadIdx.x == 0)
-        block_probes = 0;
+    query_begin(qs, sa.prefilter + prefilter_words(sa.pf_log2), sa.pf_log2);
+    for (uint32_t i = threadIdx.x; i < 32 * 16; i += BLOCK)
+        pm[i] = pair_mask(0, 2 * (i >> 4) + 1, i & 15, pool.h);
     uint32_t my_probes = 0;
 
     RunCursor rc = run_cursor(a, a.chunk);
@@ -880,158 +883,174 @@ void k_query(SeqArgs a, BloomArgs pool, SentArgs sa,
         const TileInfo ti = a.tiles[tile];
         const uint32_t lo = ti.str_lo, hi = ti.str_hi;
         if (lo == hi) {
-            // no string touches this tile: all-zero candidate words
-            if (threadIdx.x < TILE / 64) {
-                c1[tile * (TILE / 64) + threadIdx.x] = 0;
-                if (c1u && round == 0)
-                    c1u[tile * (TILE / 64) + threadIdx.x] = 0;
-            }
+            query_no_string(tile, c1, c1u, round);
             continue;
         }
         __syncthreads();
-        stage_tile(a, tile, w);
+        stage_tile(a, tile, sg);
         __syncthreads();
         const TileSet ts = tile_set_of(a, pool, ti.set);
         const unsigned long long *blocks = (const unsigned long long *)ts.f.words;
-        setsum_switch(cand, ts.set, &cand_lds, &a.set_cnt[0].candidates, SETCNT_STRIDE);
-        uint32_t si = hi;
-        uint64_t gs = 0, ge = 0;
-        // each wave walks its own run of consecutive positions, 64 at a time;
-        // lane 63's out-middle key and block carry to the next step's lane 0
-        const uint64_t run0 = t0 + (uint64_t)(threadIdx.x >> 6) * (TILE / (BLOCK / 64));
-        uint32_t carry_key = 0;
-        uint64_t carry_w = 0, carry_g = 0;
+        setsum_switch(cand, ts.set, &qs.cand_lds, &a.set_cnt[0].candidates, SETCNT_STRIDE);
+        const bool one = lo + 1 == hi;
+        Span sp = one ? span_of(a.strings, lo, t0) : Span{0, -1};
+        const uint32_t run0 = (threadIdx.x >> 6) * (TILE / (BLOCK / 64));
+        uint32_t carry_key = 0, carry_g = 0;
+        uint64_t carry_w = 0;
         for (uint32_t it = 0; it < TILE / BLOCK; ++it) {
-            const uint64_t p = run0 + it * 64 + lane;
-            if (p >= ge) {
-                si = find_string(a.strings, lo, hi, p);
-                gs = si != hi ? a.strings[si].gstart : ~0ull;
-                ge = si != hi ? a.strings[si].gend : 0;
-            }
-            const bool valid = p >= gs && p + k <= ge;
-            const uint32_t r = (uint32_t)(p - t0) + 32;
-            Strands<T> st;
-            st.fwd = 0;
-            st.rc = 0;
-            if (valid)
-                st = strands(KT<T>::window(w, r, k), k);
+            const uint32_t q = run0 + it * 64 + lane, r = q + 32;
+            if (!one && (int32_t)q >= sp.ge)
+                sp = span_at(a.strings, lo, hi, t0, q);
+            const bool valid = (int32_t)q >= sp.gs && (int32_t)(q + k) <= sp.ge;
             // evaluated in this round: every valid position, or with classes
             // those whose k-mer is in the round's class
             bool live = valid;
             if (CLASSES && valid)
-                live = in_class(class_subrange(norm(st, single)), ts.cls_lo, ts.cls_hi);
-            uint32_t kout = 0, kin = 0;
-            unsigned long long wo = 0, wi = 0;
-            uint64_t gout = 0, gin = 0;  // G of the out- and in-middle
-            if (BLOCKED) {
-                // a valid lane takes its out-middle key and block when it or
-                // the position above is evaluated; the position above uses
-                // them as its in-middle (an evaluated position that is not a
-                // string start has a valid predecessor in its string).  Lane
-                // 63's position above is the next step's lane 0.
-                const bool live_above = CLASSES ? __shfl_down(live, 1, 64) != 0 : true;
-                const bool need = !CLASSES || live || lane == 63 || live_above;
-                if (valid && need) {
-                    const MiddleKey m = middle_key((T)(st.fwd & mid_ones), (T)(st.rc >> 2), single,
-                                                   ts.f.mask >> 6);
-                    kout = pack_key(m, ts.f.h);
-                    gout = m.g;
-                    wo = __hip_atomic_load(&blocks[m.block], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-                    ++my_probes;
-                }
-                kin = from_below(kout, carry_key);
-                wi = from_below((uint64_t)wo, carry_w);
-                gin = from_below(gout, carry_g);
-                carry_key = (uint32_t)__builtin_amdgcn_readlane((int)kout, 63);
-                carry_w = lane63(wo);
-                carry_g = lane63(gout);
-                if (it == 0 && lane == 0 && live && p > gs) {
-                    // the position before is in another wave's run
-                    const MiddleKey m = middle_key((T)(st.fwd >> 2), (T)(st.rc & mid_ones), single,
-                                                   ts.f.mask >> 6);
-                    kin = pack_key(m, ts.f.h);
-                    gin = m.g;
-                    wi = __hip_atomic_load(&blocks[m.block], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
+                live = in_class(class_subrange(norm(kmer_at<T>(sg, r, k), single)), ts.cls_lo,
+                                ts.cls_hi);
+            // the bases around: before the k-mer, its first, its last, after it
+            const T u = up_from<T>(sg, r - 1), d = down_from<T>(sg, r + k + 1);
+            const uint32_t pa = (uint32_t)u & 3u, v0 = ((uint32_t)u >> 2) & 3u;
+            const uint32_t sb = (uint32_t)d & 3u, vk = k > 1 ? ((uint32_t)d >> 2) & 3u : v0;
+            const MiddleKey m = middle_key((T)((d >> 2) & mid_ones), (T)(~(u >> 4) & mid_ones),
+                                           single, ts.f.mask >> 6);
+            const uint32_t kout = pack_key(m), gout = (uint32_t)(m.g >> 32);
+            // a valid lane loads its out-middle's block when it or the
+            // position above is evaluated; the position above uses it as its
+            // in-middle's (an evaluated position that is not a string start
+            // has a valid predecessor in its string).  Lane 63's position
+            // above is the next step's lane 0.
+            const bool live_above = CLASSES ? __shfl_down(live, 1, 64) != 0 : true;
+            uint64_t wo = 0;
+            if (valid && (!CLASSES || live || lane == 63 || live_above)) {
+                wo = __hip_atomic_load(&blocks[m.block], __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+                ++my_probes;
+            }
+            wo = rotr64(wo, m.a);
+            uint32_t kin = from_below(kout, carry_key), gin = from_below(gout, carry_g);
+            uint64_t wi = from_below(wo, carry_w);
+            carry_key = (uint32_t)__builtin_amdgcn_readlane((int)kout, 63);
+            carry_g = (uint32_t)__builtin_amdgcn_readlane((int)gout, 63);
+            carry_w = lane63(wo);
+            const bool first = (int32_t)q == sp.gs, last = (int32_t)(q + k) == sp.ge;
+            if (live && (first || (it == 0 && lane == 0))) {
+                // the position before is in another wave's run, or there is
+                // none (its middle is then part of the sketch's hash only)
+                const Strands<T> s = kmer_at<T>(sg, r, k - 1);
+                const MiddleKey mi = middle_key(s.fwd, s.rc, single, ts.f.mask >> 6);
+                kin = pack_key(mi);
+                gin = (uint32_t)(mi.g >> 32);
+                if (!first) {
+                    wi = rotr64(__hip_atomic_load(&blocks[mi.block], __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT), mi.a);
                     ++my_probes;
                 }
             }
+            uint32_t least = min(others_lacking<true>(pm, kout, wo, v0, sb),
+                                 others_lacking<false>(pm, kin, wi, pa, vk));
+            const bool pal = live && ((kout | kin) >> 13) != 0;
+            if (__builtin_amdgcn_ballot_w64(pal)) {
+                if (pal)
+                    least = min((kout >> 12) == 2 ? others_lacking_palindrome<true>(pm, kout, wo, v0, sb)
+                                                  : others_lacking<true>(pm, kout, wo, v0, sb),
+                                (kin >> 12) == 2 ? others_lacking_palindrome<false>(pm, kin, wi, pa, vk)
+                                                 : others_lacking<false>(pm, kin, wi, pa, vk));
+            }
+            bool mark = live && (first || last || least == 0);
+            const uint32_t gsum = gin + gout;
+            if (live && !mark && ts.sent_log2 &&
+                prefilter_hit(qs.pf, prefilter_bit_g(gsum, sa.pf_log2)))
+                mark = in_sentinels(norm(kmer_at<T>(sg, r, k), single), sent + ts.sent_off,
+                                    ts.sent_log2);
+            const uint64_t word = ballot64(mark);
+            if (lane == 0) {
+                const uint64_t at = (t0 + q) >> 6;
+                c1[at] = word;
+                if (c1u)
+                    c1u[at] = round ? c1u[at] | word : word;
+                cand.v += (unsigned long long)__popcll(word);
+            }
+            if (a.sketch && mark) {
+                // the k-mer's hash: the sum of its two middles' G values (an
+                // unordered pair, the same for both orientations); 12 bits
+                // of the high words' sum choose the register, the other 20
+                // and the sum of the keys' low bits give the rank
+                const uint32_t rest = gsum << HLL_LOG2 |
+                                      (((kin & 0xFBFu) + (kout & 0xFBFu)) & ((1u << HLL_LOG2) - 1));
+                const uint32_t rank = rest ? (uint32_t)__builtin_clz(rest) + 1 : 33;
+                atomicMax(&qs.hll[gsum >> (32 - HLL_LOG2)], rank);
+            }
+        }
+    }
+    query_end(a, qs, cand, my_probes, cnt, hll_out);
+}
+
+// Standard layout: a lane tests its position's six neighbours level by level.
+template <class T, bool CLASSES>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(KT<T>::W == 1 ? 5 : 1)))
+void k_query_standard(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint64_t *c1u,
+                      uint32_t round, Counters *cnt, uint32_t *hll_out) {
+    __shared__ Stage sg;
+    __shared__ QueryShared qs;
+    SetSum cand = setsum_begin();
+    const uint32_t k = a.k;
+    const bool single = a.single != 0;
+    const T *sent = (const T *)sa.table;
+    const uint32_t lane = threadIdx.x & 63;
+    query_begin(qs, sa.prefilter, sa.pf_log2);
+    uint32_t my_probes = 0;
+    RunCursor rc = run_cursor(a, a.chunk);
+    for (uint64_t tile; run_next(a, rc, &tile);) {
+        const uint64_t t0 = tile * TILE;
+        const TileInfo ti = a.tiles[tile];
+        const uint32_t lo = ti.str_lo, hi = ti.str_hi;
+        if (lo == hi) {
+            query_no_string(tile, c1, c1u, round);
+            continue;
+        }
+        __syncthreads();
+        stage_tile(a, tile, sg);
+        __syncthreads();
+        const TileSet ts = tile_set_of(a, pool, ti.set);
+        setsum_switch(cand, ts.set, &qs.cand_lds, &a.set_cnt[0].candidates, SETCNT_STRIDE);
+        const bool one = lo + 1 == hi;
+        Span sp = one ? span_of(a.strings, lo, t0) : Span{0, -1};
+        for (uint32_t it = 0; it < TILE / BLOCK; ++it) {
+            const uint32_t q = it * BLOCK + threadIdx.x;
+            if (!one && (int32_t)q >= sp.ge)
+                sp = span_at(a.strings, lo, hi, t0, q);
             bool mark = false;
-            T canon = 0;
-            if (live) {
-                canon = norm(st, single);
-                if (p == gs || p + k == ge) {
-                    mark = true;  // first or last k-mer of its string
-                } else if (BLOCKED) {
-                    // the neighbour test needs only the blocks already loaded,
-                    // so it goes first: a marked position skips the sentinel
-                    // lookup (a probe of the sentinel table on a prefilter hit)
-                    const uint32_t pa = base_at(w, r - 1), sb = base_at(w, r + k);
-                    const PairKey ko = unpack_key(kout), ki = unpack_key(kin);
-                    mark = any_present_blocked(st, k, pa, sb, ko, tmpl[ko.d >> 1], wo, ki,
-                                               tmpl[ki.d >> 1], wi) ||
-                           is_sentinel(canon, pf, sa.pf_log2, sent + ts.sent_off, ts.sent_log2);
-                } else if (is_sentinel(canon, pf, sa.pf_log2, sent + ts.sent_off, ts.sent_log2)) {
-                    mark = true;
-                } else {
-                    const uint32_t pa = base_at(w, r - 1), sb = base_at(w, r + k);
-                    mark = any_present_standard(ts.f, st, k, pa, sb, single, my_probes);
+            uint64_t hash = 0;
+            if ((int32_t)q >= sp.gs && (int32_t)(q + k) <= sp.ge) {
+                uint32_t pa, sb;
+                const Strands<T> st = kmer_between<T>(sg, q + 32, k, &pa, &sb);
+                const T canon = norm(st, single);
+                if (!CLASSES || in_class(class_subrange(canon), ts.cls_lo, ts.cls_hi)) {
+                    hash = slot_hash(canon);
+                    mark = (int32_t)q == sp.gs || (int32_t)(q + k) == sp.ge ||
+                           (ts.sent_log2 &&
+                            prefilter_hit(qs.pf, prefilter_bit(hash, sa.pf_log2)) &&
+                            in_sentinels(canon, sent + ts.sent_off, ts.sent_log2)) ||
+                           any_present_standard(ts.f, st, k, pa, sb, single, my_probes);
                 }
             }
             const uint64_t word = ballot64(mark);
             if (lane == 0) {
-                c1[p >> 6] = word;
+                const uint64_t at = (t0 + q) >> 6;
+                c1[at] = word;
                 if (c1u)
-                    c1u[p >> 6] = round ? c1u[p >> 6] | word : word;
+                    c1u[at] = round ? c1u[at] | word : word;
                 cand.v += (unsigned long long)__popcll(word);
             }
             if (a.sketch && mark) {
-                // item hash of the candidate k-mer: with the blocked filter the sum
-                // of its two middles' G values (an unordered pair, the same for
-                // both orientations; a string's first k-mer hashes its first
-                // middle here), else its table hash
-                uint64_t hv;
-                if (BLOCKED) {
-                    if (p == gs)
-                        gin = middle_key((T)(st.fwd >> 2), (T)(st.rc & mid_ones), single, 0).g;
-                    hv = gin + gout;
-                } else {
-                    hv = slot_hash(canon);
-                }
-                const uint32_t reg = (uint32_t)(hv >> (64 - HLL_LOG2));
-                const uint64_t rest = hv << HLL_LOG2;
+                const uint64_t rest = hash << HLL_LOG2;
                 const uint32_t rank = rest ? (uint32_t)__clzll(rest) + 1 : 64 - HLL_LOG2 + 1;
-                atomicMax(&hll[reg], rank);
+                atomicMax(&qs.hll[(uint32_t)(hash >> (64 - HLL_LOG2))], rank);
             }
         }
     }
-    setsum_flush(cand, &cand_lds, &a.set_cnt[0].candidates, SETCNT_STRIDE);
-    if (my_probes)
-        atomicAdd(&block_probes, (unsigned long long)my_probes);
-    __syncthreads();
-    if (threadIdx.x == 0 && block_probes)
-        atomicAdd(&cnt->query_probes, block_probes);
-    if (a.sketch) {
-        for (uint32_t i = threadIdx.x; i < HLL_M; i += BLOCK) {
-            const uint32_t v = hll[i];
-            if (v && v > __hip_atomic_load(&hll_out[i], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT))
-                atomicMax(&hll_out[i], v);
-        }
-    }
-}
-
-template <class T, bool BLOCKED>
-static void query_t(const SeqArgs &a, const BloomArgs &pool, const SentArgs &sa, uint64_t *c1,
-                    uint64_t *c1u, uint32_t round, Counters *cnt, uint32_t *hll, uint32_t grid,
-                    hipStream_t s) {
-    if (a.classes)
-        hipLaunchKernelGGL((k_query<T, BLOCKED, true>), dim3(grid), dim3(BLOCK), 0, s, a, pool,
-                           sa, c1, c1u, round, cnt, hll);
-    else
-        hipLaunchKernelGGL((k_query<T, BLOCKED, false>), dim3(grid), dim3(BLOCK), 0, s, a, pool,
-                           sa, c1, c1u, round, cnt, hll);
+    query_end(a, qs, cand, my_probes, cnt, hll_out);
 }
 
 hipError_t launch_query(int W, const SeqArgs &a, const BloomArgs &pool, const SentArgs &sa,
@@ -1041,10 +1060,9 @@ hipError_t launch_query(int W, const SeqArgs &a, const BloomArgs &pool, const Se
         return hipSuccess;
     return by_width(W, [&](auto tag) {
         using T = decltype(tag);
-        if (pool.blocked)
-            query_t<T, true>(a, pool, sa, c1, c1u, round, cnt, hll, grid, s);
-        else
-            query_t<T, false>(a, pool, sa, c1, c1u, round, cnt, hll, grid, s);
+        auto *fn = pool.blocked ? (a.classes ? k_query_blocked<T, true> : k_query_blocked<T, false>)
+                                : (a.classes ? k_query_standard<T, true> : k_query_standard<T, false>);
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(BLOCK), 0, s, a, pool, sa, c1, c1u, round, cnt, hll);
         return hipGetLastError();
     });
 }
@@ -1058,7 +1076,7 @@ hipError_t launch_query(int W, const SeqArgs &a, const BloomArgs &pool, const Se
 // its tiles move to another set, and at the end.
 template <class T>
 __global__ __launch_bounds__(BLOCK) void k_census(SeqArgs a, unsigned long long *counters) {
-    __shared__ uint64_t w[STAGE_WORDS];
+    __shared__ Stage sg;
     __shared__ uint32_t hist[CLASS_Q];
     const uint32_t L = a.k + 1;
     const bool single = a.single != 0;
@@ -1088,24 +1106,18 @@ __global__ __launch_bounds__(BLOCK) void k_census(SeqArgs a, unsigned long long 
             cur_set = ti.set;
         }
         __syncthreads();
-        stage_tile(a, tile, w);
+        stage_tile(a, tile, sg);
         __syncthreads();
-        uint32_t si = hi;
-        uint64_t gs = 0, ge = 0;
+        const bool one = lo + 1 == hi;
+        Span sp = one ? span_of(a.strings, lo, t0) : Span{0, -1};
         for (uint32_t it = 0; it < TILE / BLOCK; ++it) {
-            const uint64_t p = t0 + it * BLOCK + threadIdx.x;
-            if (p >= ge) {
-                si = find_string(a.strings, lo, hi, p);
-                gs = si != hi ? a.strings[si].gstart : ~0ull;
-                ge = si != hi ? a.strings[si].gend : 0;
-            }
-            if (p < gs || p + L > ge)
+            const uint32_t q = it * BLOCK + threadIdx.x;
+            if (!one && (int32_t)q >= sp.ge)
+                sp = span_at(a.strings, lo, hi, t0, q);
+            if ((int32_t)q < sp.gs || (int32_t)(q + L) > sp.ge)
                 continue;
-            const uint32_t r = (uint32_t)(p - t0) + 32;
-            const Strands<T> e = strands(KT<T>::window(w, r, L), L);
-            T pre, suf;
-            edge_kmers(e, a.k, single, &pre, &suf);
-            const uint32_t x = class_subrange(pre), y = class_subrange(suf);
+            const uint32_t x = class_subrange(norm(kmer_at<T>(sg, q + 32, a.k), single));
+            const uint32_t y = class_subrange(norm(kmer_at<T>(sg, q + 33, a.k), single));
             atomicAdd(&hist[x], 1u);
             if (y != x)
                 atomicAdd(&hist[y], 1u);
@@ -1187,10 +1199,11 @@ hipError_t launch_set_round(SetDesc *sets, const uint32_t *bounds, uint32_t n_se
 hipError_t pass1_occupancy(KernelId which, int W, bool blocked, bool fill_dedup, int *blocks) {
     return by_width(W, [&](auto tag) {
         using T = decltype(tag);
-        const void *fn = which == K_FILL
-                             ? (blocked ? (const void *)k_fill<T, true> : (const void *)k_fill<T, false>)
-                             : (blocked ? (const void *)k_query<T, true, false>
-                                        : (const void *)k_query<T, false, false>);
+        const void *fn =
+            which == K_FILL
+                ? (blocked ? (const void *)k_fill<T, true> : (const void *)k_fill<T, false>)
+                : (blocked ? (const void *)k_query_blocked<T, false>
+                           : (const void *)k_query_standard<T, false>);
         const size_t dyn = which == K_FILL && blocked && fill_dedup
                                ? FILL_DD * sizeof(unsigned long long) : 0;
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, fn, BLOCK, dyn);

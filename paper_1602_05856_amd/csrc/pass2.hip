@@ -26,12 +26,12 @@ namespace tp {
 
 // Stage a tile's packed words (as the first pass does) and its TILE / 64
 // candidate-bitmap words in LDS, with one round of loads.
-__device__ __forceinline__ void stage_tile2(const SeqArgs &a, uint64_t tile, uint64_t *w,
+__device__ __forceinline__ void stage_tile2(const SeqArgs &a, uint64_t tile, Stage &sg,
                                             const uint64_t *c1, uint64_t *cw) {
-    int64_t w0 = (int64_t)(tile * TILE_WORDS) - 1;
+    const int64_t w0 = (int64_t)(tile * TILE_WORDS) - 1;
     for (uint32_t i = threadIdx.x; i < STAGE_WORDS; i += blockDim.x) {
-        int64_t gw = w0 + (int64_t)i;
-        w[i] = (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull;
+        const int64_t gw = w0 + (int64_t)i;
+        stage_word(sg, i, (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull);
     }
     if (threadIdx.x >= BLOCK - TILE / 64)
         cw[threadIdx.x - (BLOCK - TILE / 64)] = c1[tile * (TILE / 64) + threadIdx.x -
@@ -138,12 +138,14 @@ __device__ __forceinline__ uint64_t ref_tag(const TableArgs &t, uint64_t h) {
 // Whether the sequence reads the k-mer st, on either strand, at the position
 // that slot word names: x ^ ones is the value of the reverse complement of
 // the window x, and it is st.rc when x is st as read, st.fwd when x is its
-// reverse complement.
+// reverse complement.  (The words read past the k-mer lie within the input's
+// last 64 bytes at most.)
 template <class T>
 __device__ __forceinline__ bool ref_is(const SeqArgs &a, const TableArgs &t,
                                        unsigned long long word, const Strands<T> &st) {
     const uint64_t p = (word & ((1ull << t.ref_shift) - 1)) >> 8;
-    const T z = KT<T>::window(a.seq + (p >> 5), (uint32_t)(p & 31), a.k) ^ KT<T>::ones(2 * a.k);
+    const T z = ~KT<T>::win((const uint32_t *)a.seq + (p >> 4), (uint32_t)(p & 15)) &
+                KT<T>::ones(2 * a.k);
     return z == st.rc || (!a.single && z == st.fwd);
 }
 
@@ -235,43 +237,45 @@ template <class F> hipError_t by_table(int W, const TableArgs &t, F &&f) {
 
 // ------------------------------------------------------------- record (a3)
 
-// The normalised k-mer of position p (at offset r of the staged words w) in
-// the string [gs, ge), and in m its edge bits: the predecessor's base as an
-// in-bit and the successor's as an out-bit, for the orientation in which the
-// k-mer is normalised (both orientations for a palindrome).
+// The normalised k-mer of position q of a staged tile, in the string sp, and
+// in m its edge bits: the predecessor's base as an in-bit and the successor's
+// as an out-bit, for the orientation in which the k-mer is normalised (both
+// orientations for a palindrome).
 template <class T>
-__device__ __forceinline__ T record_key(const uint64_t *w, uint32_t r, uint32_t k, uint64_t p,
-                                        uint64_t gs, uint64_t ge, bool single, uint32_t &m,
-                                        Strands<T> &st) {
-    st = strands(KT<T>::window(w, r, k), k);
-    const bool has_pred = p > gs, has_succ = p + k < ge;
-    const uint32_t pa = has_pred ? base_at(w, r - 1) : 0;
-    const uint32_t sb = has_succ ? base_at(w, r + k) : 0;
+__device__ __forceinline__ T record_key(const Stage &sg, uint32_t q, uint32_t k, const Span &sp,
+                                        bool single, uint32_t &m, Strands<T> &st) {
+    uint32_t pa, sb;
+    st = kmer_between<T>(sg, q + 32, k, &pa, &sb);
+    const uint32_t has_pred = (int32_t)q > sp.gs, has_succ = (int32_t)(q + k) < sp.ge;
     m = 0;
     T canon = st.fwd;
     if (single || st.fwd <= st.rc) {
         // the k-mer as read is normalised: pred.v enters, v.succ leaves
-        if (has_pred)
-            m |= 1u << pa;
-        if (has_succ)
-            m |= 16u << sb;
+        m = has_pred << pa | has_succ << (4 + sb);
     }
     if (!single && st.rc <= st.fwd) {
         // its reverse complement is normalised: comp(succ) enters, comp(pred)
         // leaves
-        if (has_succ)
-            m |= 1u << (3 - sb);
-        if (has_pred)
-            m |= 16u << (3 - pa);
+        m |= has_succ << (3 - sb) | has_pred << (7 - pa);
         canon = st.rc;
     }
     return canon;
 }
 
+// The span a candidate at position q of the tile lies in, given the last one
+// of this lane (positions only grow): false when q starts no k-mer (never
+// marked by the first pass).
+__device__ __forceinline__ bool record_span(const DString *S, uint32_t lo, uint32_t hi,
+                                            uint64_t t0, uint32_t q, Span &sp) {
+    if (lo + 1 != hi && ((int32_t)q < sp.gs || (int32_t)q >= sp.ge))
+        sp = span_at(S, lo, hi, t0, q);
+    return (int32_t)q >= sp.gs;
+}
+
 template <class T, bool P2, bool REF>
 __global__ __launch_bounds__(BLOCK) void k_record(SeqArgs a, const uint64_t *c1, TableArgs pool,
                                                   Counters *cnt) {
-    __shared__ uint64_t w[STAGE_WORDS];
+    __shared__ Stage sg;
     __shared__ uint64_t cw[TILE / 64];
     __shared__ unsigned long long block_probes, keys_lds;
     __shared__ uint32_t skip_lds;
@@ -297,7 +301,7 @@ __global__ __launch_bounds__(BLOCK) void k_record(SeqArgs a, const uint64_t *c1,
             continue;
         const uint32_t set = ti.set;
         __syncthreads();
-        stage_tile2(a, tile, w, c1, cw);
+        stage_tile2(a, tile, sg, c1, cw);
         // a set whose table overflowed in this attempt is redone with a
         // larger table: skip the rest of its work now.  Other workgroups may
         // set the flag at any time, so one thread reads it and the whole
@@ -310,27 +314,20 @@ __global__ __launch_bounds__(BLOCK) void k_record(SeqArgs a, const uint64_t *c1,
         const TableArgs t = table_of(a, pool, set);
         setsum_switch(keys, set, &keys_lds, &a.set_cnt[0].table_keys, SETCNT_STRIDE);
         bool overflow = false;
-        uint64_t gs = ~0ull, ge = 0;  // this lane's last string (positions only grow)
+        Span sp = lo + 1 == hi ? span_of(a.strings, lo, t0) : Span{0, -1};
         for (uint32_t it = 0; it < TILE / BLOCK; ++it) {
-            const uint64_t p = t0 + it * BLOCK + threadIdx.x;
-            if (!((cw[(it * BLOCK + threadIdx.x) >> 6] >> lane) & 1ull))
+            const uint32_t q = it * BLOCK + threadIdx.x;
+            if (!((cw[q >> 6] >> lane) & 1ull) || !record_span(a.strings, lo, hi, t0, q, sp))
                 continue;
-            if (p < gs || p >= ge) {
-                const uint32_t si = find_string(a.strings, lo, hi, p);
-                if (si == hi)
-                    continue;  // not a k-mer start: never marked by the first pass
-                gs = a.strings[si].gstart;
-                ge = a.strings[si].gend;
-            }
             uint32_t m;
             Strands<T> st;
-            const T canon = record_key<T>(w, (uint32_t)(p - t0) + 32, k, p, gs, ge, single, m, st);
+            const T canon = record_key<T>(sg, q, k, sp, single, m, st);
             const uint64_t hash = slot_hash(canon);
             const uint64_t slot = home_slot<P2>(t, hash);
             const u64x2 pr = load_pair(t, slot);
             int rc;
             if constexpr (REF) {
-                const unsigned long long own = ref_tag<P2>(t, hash) | p << 8 | m;
+                const unsigned long long own = ref_tag<P2>(t, hash) | (t0 + q) << 8 | m;
                 rc = insert_pair<P2>(t, own, m, slot, pr, [&](unsigned long long x) {
                     return (x ^ own) >> t.ref_shift == 0 && ref_is(a, t, x, st);
                 }, my_probes);
@@ -404,7 +401,7 @@ template <bool P2>
 __global__ __launch_bounds__(BLOCK) void k_rbin_count(SeqArgs a, const uint64_t *c1, TableArgs t,
                                                       RecBinArgs rb) {
     constexpr uint32_t PER = TILE / BLOCK;
-    __shared__ uint64_t w[STAGE_WORDS];
+    __shared__ Stage sg;
     __shared__ uint64_t cw[TILE / 64];
     __shared__ uint32_t wtot[BLOCK / 64];
     __shared__ uint64_t seg_base, seg_new;
@@ -428,28 +425,20 @@ __global__ __launch_bounds__(BLOCK) void k_rbin_count(SeqArgs a, const uint64_t 
             continue;
         const uint64_t t0 = tile * TILE;
         __syncthreads();  // the last tile's staged words and segment state are read
-        stage_tile2(a, tile, w, c1, cw);
+        stage_tile2(a, tile, sg, c1, cw);
         __syncthreads();
         uint64_t v[PER];
         uint32_t nv = 0;
-        uint64_t gs = ~0ull, ge = 0;
+        Span sp = lo + 1 == hi ? span_of(a.strings, lo, t0) : Span{0, -1};
 #pragma unroll
         for (uint32_t it = 0; it < PER; ++it) {
             v[it] = BIN_NONE;
-            const uint64_t p = t0 + it * BLOCK + threadIdx.x;
-            if (!((cw[(it * BLOCK + threadIdx.x) >> 6] >> lane) & 1ull))
+            const uint32_t q = it * BLOCK + threadIdx.x;
+            if (!((cw[q >> 6] >> lane) & 1ull) || !record_span(a.strings, lo, hi, t0, q, sp))
                 continue;
-            if (p < gs || p >= ge) {
-                const uint32_t si = find_string(a.strings, lo, hi, p);
-                if (si == hi)
-                    continue;  // not a k-mer start: never marked by the first pass
-                gs = a.strings[si].gstart;
-                ge = a.strings[si].gend;
-            }
             uint32_t m;
             Strands<uint64_t> st;
-            const uint64_t key =
-                record_key<uint64_t>(w, (uint32_t)(p - t0) + 32, k, p, gs, ge, single, m, st);
+            const uint64_t key = record_key<uint64_t>(sg, q, k, sp, single, m, st);
             const uint64_t item = key << 8 | m;
             const uint64_t r = rbin_block<P2>(t, item);
             if (r >= rb.r_lo && r < rb.r_hi) {
@@ -755,7 +744,7 @@ template <class T, bool P2, bool REF>
 __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const uint64_t *c1,
                                                   TableArgs pool, uint64_t *jbits,
                                                   bool accumulate, Counters *cnt) {
-    __shared__ uint64_t w[STAGE_WORDS];
+    __shared__ Stage sg;
     __shared__ uint64_t cw[TILE / 64];
     __shared__ uint32_t pf[(1u << PF_MAX_LOG2) / 32];
     __shared__ unsigned long long block_probes, junc_lds;
@@ -766,7 +755,7 @@ __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const 
     const bool single = a.single != 0;
     const T *sent = (const T *)sa.table;
     const uint32_t lane = threadIdx.x & 63;
-    for (uint32_t i = threadIdx.x; i < (1u << sa.pf_log2) / 32; i += BLOCK)
+    for (uint32_t i = threadIdx.x; i < prefilter_words(sa.pf_log2); i += BLOCK)
         pf[i] = sa.prefilter[i];
     if (threadIdx.x == 0)
         block_probes = 0;
@@ -779,7 +768,7 @@ __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const 
         const uint64_t t0 = tile * TILE;
         const uint32_t set = a.tiles[tile].set;
         __syncthreads();
-        stage_tile2(a, tile, w, c1, cw);
+        stage_tile2(a, tile, sg, c1, cw);
         if (threadIdx.x == 0)
             skip_lds = overflow_seen(a, set, flag_set, flag_age, flag_val);
         __syncthreads();
@@ -818,12 +807,12 @@ __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const 
                 id[j] = 0;
                 ss[j] = 0;
                 if ((cw[q >> 6] >> lane) & 1ull) {
-                    const T canon = norm(strands(KT<T>::window(w, q + 32, k), k), single);
+                    const T canon = norm(kmer_at<T>(sg, q + 32, k), single);
                     look |= 1u << j;
                     const uint64_t hash = slot_hash(canon);
                     slot[j] = home_slot<P2>(t, hash);
                     id[j] = REF ? ref_tag<P2>(t, hash) : (uint64_t)canon;
-                    if (slog2 && prefilter_hit(canon, pf, sa.pf_log2)) {
+                    if (slog2 && prefilter_hit(pf, prefilter_bit(hash, sa.pf_log2))) {
                         maybe_sent |= 1u << j;
                         ss[j] = sent_home(canon, slog2);
                     }
@@ -842,7 +831,7 @@ __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const 
                     continue;
                 const uint32_t q = (g0 + j) * BLOCK + threadIdx.x;
                 if ((maybe_sent >> j) & 1u) {
-                    const T canon = norm(strands(KT<T>::window(w, q + 32, k), k), single);
+                    const T canon = norm(kmer_at<T>(sg, q + 32, k), single);
                     if (sent_probe_from(stab, slog2, canon, ss[j], sx[j])) {
                         junction |= 1u << j;  // a sentinel k-mer
                         continue;
@@ -855,7 +844,7 @@ __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const 
                         return false;
                     // this position's own word, or one that reads the same k-mer
                     return (x & ((1ull << t.ref_shift) - 1)) >> 8 == t0 + q ||
-                           ref_is(a, t, x, strands(KT<T>::window(w, q + 32, k), k));
+                           ref_is(a, t, x, kmer_at<T>(sg, q + 32, k));
                 }, my_probes);
                 if (m < 0)
                     ++my_missing;

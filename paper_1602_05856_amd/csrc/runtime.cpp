@@ -276,8 +276,10 @@ int tp::plan_layout(tp_plan *p, const tp_set *sets, uint32_t n_sets, uint32_t k,
     }
     p->bitmap_words = p->total / 64;
     p->input_bytes = p->total / 4 + 64;
+    // a prefilter bit per 256th sentinel: a wave of 64 lookups rarely has a
+    // false hit (at one per 32nd, most waves had one)
     p->pf_log2 = std::min<uint32_t>(PF_MAX_LOG2,
-                                    std::max<uint32_t>(10, log2_ceil(2 * p->strings.size() * 32)));
+                                    std::max<uint32_t>(10, log2_ceil(2 * p->strings.size() * 256)));
     // Per-tile set and strings.  Strings are sorted and disjoint, so the
     // first string ending after a tile's start only moves forward.
     const uint32_t nstr = (uint32_t)p->strings.size();
@@ -1069,10 +1071,9 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
     HIPCHK(p->d_bloom_starts.ensure((nsets + 1) * 8ull));
     HIPCHK(p->d_strings.ensure(ns * sizeof(DString)));
     HIPCHK(p->d_gbase.ensure(ngen * 8));
-    HIPCHK(p->d_sent_raw.ensure(2 * ns * 8 * W));
     HIPCHK(p->d_sent.ensure(p->sent_tab_slots * 8 * W));
     HIPCHK(p->d_sent_owner.ensure(p->sent_tab_slots * 4));
-    HIPCHK(p->d_pf.ensure((1ull << p->pf_log2) / 8));
+    HIPCHK(p->d_pf.ensure(2ull * 4 * prefilter_words(p->pf_log2)));
     HIPCHK(p->d_bloom.ensure(p->bloom_words * 4));
     HIPCHK(p->d_c1.ensure(p->bitmap_words * 8));
     HIPCHK(p->d_cnt.ensure(sizeof(Counters)));
@@ -1159,8 +1160,7 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
     const bool graphs = p->cfg.graphs && rounds == 1;
     auto enqueue_a0 = [&](hipStream_t q) -> int {
         HIPCHK(launch_zero(cnt, sizeof(Counters), q));
-        HIPCHK(launch_sentinels(W, a, p->d_sent_raw.p, p->d_sent.p, p->d_sent_owner.as<uint32_t>(),
-                                sent_slots, p->d_pf.as<uint32_t>(), p->pf_log2, q));
+        HIPCHK(launch_sentinels(W, a, sa, p->d_sent_owner.as<uint32_t>(), sent_slots, q));
         return TP_OK;
     };
     HIPCHK(hipEventRecord(p->ev[0], s));
@@ -1214,7 +1214,7 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
         {
             KeyBuilder kb;
             kb(W)(a)(sa)(cnt)(scnt)(p->d_hll.p)(p->d_bloom.p)(p->bloom_words)(nsets)(
-                p->d_sent_raw.p)(p->pf_log2)(p->d_sent_owner.p)(sent_slots)(binned)(qbase);
+                p->pf_log2)(p->d_sent_owner.p)(sent_slots)(binned)(qbase);
             const int rc1 = run_segment(p, graphs, 0, kb.v, s, enqueue_p1);
             if (rc1)
                 return rc1;

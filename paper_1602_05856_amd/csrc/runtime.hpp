@@ -184,7 +184,7 @@ struct WsState {
     const void *prepared = nullptr;   // workspace last prepared for it
     tp_ws_layout pub{};               // the public part (sizes, offsets)
     uint64_t o_tiles = 0, o_tile_info = 0, o_sets = 0, o_bloom_starts = 0, o_strings = 0,
-             o_gbase = 0, o_sent_raw = 0, o_sent = 0, o_sent_owner = 0, o_pf = 0, o_bloom = 0,
+             o_gbase = 0, o_sent = 0, o_sent_owner = 0, o_pf = 0, o_bloom = 0,
              o_c1 = 0, o_c1u = 0,
              o_j = 0, o_cnt = 0, o_set_cnt = 0, o_census = 0, o_bounds = 0, o_keys = 0,
              o_blockcnt = 0, o_blockoff = 0,
@@ -228,7 +228,7 @@ struct tp_plan {
     bool static_uploaded = false;
     bool order_uploaded = false;           // tile_order on the device matches cfg
     tp::DevBuf d_tiles, d_tile_info, d_sets, d_bloom_starts, d_strings, d_gbase;
-    tp::DevBuf d_sent_raw, d_sent, d_sent_owner, d_pf, d_bloom, d_c1, d_j, d_cnt, d_set_cnt, d_hll;
+    tp::DevBuf d_sent, d_sent_owner, d_pf, d_bloom, d_c1, d_j, d_cnt, d_set_cnt, d_hll;
     tp::DevBuf d_keys, d_seq, d_blockcnt, d_blockoff;  // d_seq: the input a reference table names
     tp::DevBuf d_pos, d_vertex, d_strand, d_edges, d_joff;
     tp::DevBuf d_c1u, d_census;            // rounds: union of candidates, class census
@@ -263,7 +263,7 @@ struct tp_plan {
 
     template <class F> void for_each_buf(F f) {
         for (tp::DevBuf *b : {&d_tiles, &d_tile_info, &d_sets, &d_bloom_starts, &d_strings,
-                              &d_gbase, &d_sent_raw, &d_sent, &d_sent_owner, &d_pf, &d_bloom,
+                              &d_gbase, &d_sent, &d_sent_owner, &d_pf, &d_bloom,
                               &d_c1, &d_j,
                               &d_cnt, &d_set_cnt, &d_hll, &d_keys, &d_seq,
                               &d_blockcnt, &d_blockoff, &d_pos, &d_vertex, &d_strand,

@@ -500,10 +500,10 @@ __device__ __forceinline__ RunCursor run_cursor(const SeqArgs &a, uint32_t G) {
                      G, gridDim.x / NXCD, 1, 0, 0};
 }
 
-__device__ __forceinline__ RunCursor linear_run(const SeqArgs &a) {
+__device__ __forceinline__ RunCursor linear_run(const SeqArgs &a, uint32_t G) {
     if (a.queue)
-        return RunCursor{0, 0, a.chunk, a.chunk, 0, 0, 0, 1};
-    return RunCursor{(uint64_t)blockIdx.x * a.chunk, a.n_tiles, 0, a.chunk, gridDim.x, 0, 0, 0};
+        return RunCursor{0, 0, G, G, 0, 0, 0, 1};
+    return RunCursor{(uint64_t)blockIdx.x * G, a.n_tiles, 0, G, gridDim.x, 0, 0, 0};
 }
 
 // Next tile of the walk, or false at its end.

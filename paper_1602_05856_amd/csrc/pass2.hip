@@ -24,18 +24,138 @@
 
 namespace tp {
 
-// Stage a tile's packed words (as the first pass does) and its TILE / 64
-// candidate-bitmap words in LDS, with one round of loads.
-__device__ __forceinline__ void stage_tile2(const SeqArgs &a, uint64_t tile, Stage &sg,
-                                            const uint64_t *c1, uint64_t *cw) {
-    const int64_t w0 = (int64_t)(tile * TILE_WORDS) - 1;
-    for (uint32_t i = threadIdx.x; i < STAGE_WORDS; i += blockDim.x) {
-        const int64_t gw = w0 + (int64_t)i;
-        stage_word(sg, i, (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull);
+// The second pass walks up to P2_TILES tiles of one set at a time.  Their
+// candidates are listed first (their positions, ascending), and the lanes walk
+// the list, so that every lane holds a candidate: a 16-bit-a-position filter
+// leaves some 8% of them, spread over every wave, and a round the same of its
+// class.  Several tiles at once, because a tile's own chain of dependent steps
+// (the claim of it, its record, its words, the set's flag) takes as long as
+// its lookups.  Walked by position and tile by tile, then listed tile by tile,
+// then in batches of four: 128 sets of 654 Mbp at k = 31 record 5.5, 5.1 and
+// 2.2 ms, decision 3.9, 3.8 and 1.4; 1 Gbp at k = 63 record 8.9, 6.1 and 2.5,
+// decision 6.6, 5.7 and 1.9; four rounds of 80 Mbp at k = 25 record 2.0, 2.0
+// and 0.7, decision 2.4, 2.3 and 0.9.
+constexpr uint32_t P2_TILES = 4;
+
+struct P2Tile {
+    uint64_t t0;
+    uint32_t lo, hi;  // its strings
+    Span sp;          // its string when it has just one
+};
+
+struct P2Batch {
+    Stage sg[P2_TILES];
+    P2Tile tile[P2_TILES];
+    uint32_t set[P2_TILES];
+    uint64_t w[P2_TILES * TILE / 64];   // candidate words
+    uint16_t at[P2_TILES * TILE];       // candidates: tile << 11 | position
+    uint32_t wsum[BLOCK / 64];
+    uint32_t skip;
+};
+static_assert(TILE == 1u << 11, "candidate positions");
+
+// Whether a set's table overflowed in this attempt (thread 0 only): the
+// device-coherent flag is read again when the set changes and every 8th
+// batch, so the workgroups do not all read one counter line per batch.  A late
+// reading only delays the skip; the attempt is redone either way.
+struct OverflowFlag {
+    uint32_t set = ~0u, age = 0, value = 0;
+};
+
+__device__ __forceinline__ uint32_t overflow_seen(const SeqArgs &a, uint32_t set, OverflowFlag &f) {
+    if (set != f.set || (++f.age & 7) == 0) {
+        f.value = (uint32_t)__hip_atomic_load(&a.set_cnt[set].overflow, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+        f.set = set;
+        f.age = 0;
     }
-    if (threadIdx.x >= BLOCK - TILE / 64)
-        cw[threadIdx.x - (BLOCK - TILE / 64)] = c1[tile * (TILE / 64) + threadIdx.x -
-                                                   (BLOCK - TILE / 64)];
+    return f.value;
+}
+
+// The next batch of the walk (at most `most` tiles of one chunk and one set),
+// staged, and its candidates listed: false at the walk's end, else its tiles
+// in *n, its candidates in *total and its set.  A set whose table overflowed
+// in this attempt is redone with a larger table, so its work is skipped (skip:
+// other workgroups may set the flag at any time, so one thread reads it and
+// the whole workgroup takes that one reading).  Whole workgroup; ends
+// synchronised.
+__device__ __forceinline__ bool next_batch(const SeqArgs &a, RunCursor &rc, uint32_t most,
+                                           const uint64_t *c1, P2Batch &b, OverflowFlag &flag,
+                                           uint32_t *n, uint32_t *total, uint32_t *set) {
+    uint64_t first;
+    if (!run_next(a, rc, &first))
+        return false;
+    const uint64_t j0 = rc.c + rc.gi - 1;  // the walk's entry of the first tile
+    uint32_t m = 1;
+    while (m < most && rc.gi + m - 1 < rc.G && j0 + m < rc.end)
+        ++m;
+    __syncthreads();  // the last batch is done with
+    if (threadIdx.x < m) {
+        const uint64_t tile = rc.ordered ? (uint64_t)a.tile_order[j0 + threadIdx.x] : j0 + threadIdx.x;
+        const TileInfo ti = a.tiles[tile];
+        P2Tile x;
+        x.t0 = tile * TILE;
+        x.lo = ti.str_lo;
+        x.hi = ti.str_hi;
+        x.sp = x.lo + 1 == x.hi ? span_of(a.strings, x.lo, x.t0) : Span{0, -1};
+        b.tile[threadIdx.x] = x;
+        b.set[threadIdx.x] = ti.set;
+    }
+    __syncthreads();
+    *set = b.set[0];
+    uint32_t take = 1;
+    while (take < m && b.set[take] == *set)
+        ++take;
+    rc.gi += take - 1;
+    *n = take;
+    for (uint32_t i = threadIdx.x; i < take * STAGE_WORDS; i += BLOCK) {
+        const uint32_t j = i / STAGE_WORDS, u = i % STAGE_WORDS;
+        const int64_t gw = (int64_t)(b.tile[j].t0 / 32) - 1 + u;
+        stage_word(b.sg[j], u, (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull);
+    }
+    for (uint32_t i = threadIdx.x; i < P2_TILES * TILE / 64; i += BLOCK) {
+        const uint32_t j = i / (TILE / 64);
+        b.w[i] = j < take ? c1[b.tile[j].t0 / 64 + i % (TILE / 64)] : 0ull;
+    }
+    if (threadIdx.x == 0)
+        b.skip = overflow_seen(a, *set, flag);
+    __syncthreads();
+    // a thread lists 32 positions
+    static_assert(P2_TILES * TILE / 32 == BLOCK, "32 positions per thread");
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t bits = ((const uint32_t *)b.w)[threadIdx.x];
+    const uint32_t c = (uint32_t)__popc(bits);
+    uint32_t x = c;
+#pragma unroll
+    for (uint32_t d = 1; d < 64; d <<= 1) {
+        const uint32_t y = __shfl_up(x, d, 64);
+        x += lane >= d ? y : 0;
+    }
+    if (lane == 63)
+        b.wsum[wave] = x;
+    __syncthreads();
+    uint32_t at = x - c, sum = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < BLOCK / 64; ++q) {
+        at += q < wave ? b.wsum[q] : 0;
+        sum += b.wsum[q];
+    }
+    for (; bits; bits &= bits - 1)
+        b.at[at++] = (uint16_t)(threadIdx.x * 32 + (uint32_t)__builtin_ctz(bits));
+    *total = sum;
+    __syncthreads();
+    return true;
+}
+
+// Tiles per batch of a launch: enough batches to go round.
+__host__ __device__ inline uint32_t batch_tiles(uint64_t n_tiles, uint32_t grid) {
+    const uint64_t per = n_tiles / (4ull * grid);
+    return per < 1 ? 1u : per > P2_TILES ? P2_TILES : (uint32_t)per;
+}
+
+// The walk of a second-pass kernel: chunks of whole batches.
+__device__ __forceinline__ RunCursor batch_run(const SeqArgs &a, bool slabs, uint32_t chunk) {
+    return slabs ? run_cursor(a, chunk) : linear_run(a, chunk);
 }
 
 __global__ void k_table_clear(ulonglong2 *keys, uint64_t pairs) {
@@ -204,22 +324,6 @@ __device__ __forceinline__ int find_pair(const TableArgs &t, uint64_t s, u64x2 p
     return -1;
 }
 
-// Whether a set's table overflowed in this attempt (thread 0 only): the
-// device-coherent flag is read again when the set changes and every 8th
-// tile, so the workgroups do not all read one counter line per tile.  A late
-// reading only delays the skip; the attempt is redone either way.
-__device__ __forceinline__ uint32_t overflow_seen(const SeqArgs &a, uint32_t set,
-                                                  uint32_t &flag_set, uint32_t &flag_age,
-                                                  uint32_t &flag) {
-    if (set != flag_set || (++flag_age & 7) == 0) {
-        flag = (uint32_t)__hip_atomic_load(&a.set_cnt[set].overflow, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-        flag_set = set;
-        flag_age = 0;
-    }
-    return flag;
-}
-
 // Host-side dispatch on the k-mer width, the table mode and the slot words:
 // f(value of the k-mer type, power-of-two table, reference words); packed
 // words are one-word k-mers'.
@@ -262,63 +366,43 @@ __device__ __forceinline__ T record_key(const Stage &sg, uint32_t q, uint32_t k,
     return canon;
 }
 
-// The span a candidate at position q of the tile lies in, given the last one
-// of this lane (positions only grow): false when q starts no k-mer (never
-// marked by the first pass).
-__device__ __forceinline__ bool record_span(const DString *S, uint32_t lo, uint32_t hi,
-                                            uint64_t t0, uint32_t q, Span &sp) {
-    if (lo + 1 != hi && ((int32_t)q < sp.gs || (int32_t)q >= sp.ge))
-        sp = span_at(S, lo, hi, t0, q);
-    return (int32_t)q >= sp.gs;
+// The span that position q of a tile lies in.
+__device__ __forceinline__ Span record_span(const SeqArgs &a, const P2Tile &tl, uint32_t q) {
+    return tl.lo + 1 == tl.hi ? tl.sp : span_at(a.strings, tl.lo, tl.hi, tl.t0, q);
 }
 
 template <class T, bool P2, bool REF>
 __global__ __launch_bounds__(BLOCK) void k_record(SeqArgs a, const uint64_t *c1, TableArgs pool,
                                                   Counters *cnt) {
-    __shared__ Stage sg;
-    __shared__ uint64_t cw[TILE / 64];
+    __shared__ P2Batch b;
     __shared__ unsigned long long block_probes, keys_lds;
-    __shared__ uint32_t skip_lds;
-    uint32_t flag_set = ~0u, flag_age = 0, flag_val = 0;  // thread 0: last flag reading
+    OverflowFlag flag;
     SetSum keys = setsum_begin();
     const uint32_t k = a.k;
     const bool single = a.single != 0;
-    const uint32_t lane = threadIdx.x & 63;
     if (threadIdx.x == 0)
         block_probes = 0;
     uint32_t my_probes = 0;
     // memory order spreads homologous tiles' claims out in time; runs of them
     // on one workgroup keep their slots hot without the concurrent claims of
     // the plain first-pass order
-    const uint32_t order = a.pass2_slabs;
-    RunCursor rc = (order & 4) ? run_cursor(a, a.chunk > RECORD_RUN ? a.chunk : RECORD_RUN)
-                   : (order & 1) ? run_cursor(a, a.chunk) : linear_run(a);
-    for (uint64_t tile; run_next(a, rc, &tile);) {
-        const uint64_t t0 = tile * TILE;
-        const TileInfo ti = a.tiles[tile];
-        const uint32_t lo = ti.str_lo, hi = ti.str_hi;
-        if (lo == hi)
-            continue;
-        const uint32_t set = ti.set;
-        __syncthreads();
-        stage_tile2(a, tile, sg, c1, cw);
-        // a set whose table overflowed in this attempt is redone with a
-        // larger table: skip the rest of its work now.  Other workgroups may
-        // set the flag at any time, so one thread reads it and the whole
-        // workgroup takes that one reading (the skip stays uniform).
-        if (threadIdx.x == 0)
-            skip_lds = overflow_seen(a, set, flag_set, flag_age, flag_val);
-        __syncthreads();
-        if (skip_lds)
+    const uint32_t order = a.pass2_slabs, most = batch_tiles(a.n_tiles, gridDim.x);
+    const uint32_t chunk = max(a.chunk, (order & 4) ? RECORD_RUN : most);
+    RunCursor rc = batch_run(a, (order & 5) != 0, chunk);
+    uint32_t n, total, set;
+    while (next_batch(a, rc, most, c1, b, flag, &n, &total, &set)) {
+        if (b.skip)
             continue;
         const TableArgs t = table_of(a, pool, set);
         setsum_switch(keys, set, &keys_lds, &a.set_cnt[0].table_keys, SETCNT_STRIDE);
         bool overflow = false;
-        Span sp = lo + 1 == hi ? span_of(a.strings, lo, t0) : Span{0, -1};
-        for (uint32_t it = 0; it < TILE / BLOCK; ++it) {
-            const uint32_t q = it * BLOCK + threadIdx.x;
-            if (!((cw[q >> 6] >> lane) & 1ull) || !record_span(a.strings, lo, hi, t0, q, sp))
-                continue;
+        for (uint32_t i = threadIdx.x; i < total; i += BLOCK) {
+            const uint32_t q = b.at[i] & (TILE - 1);
+            const P2Tile &tl = b.tile[b.at[i] / TILE];
+            const Stage &sg = b.sg[b.at[i] / TILE];
+            const Span sp = record_span(a, tl, q);
+            if ((int32_t)q < sp.gs)
+                continue;  // not a k-mer start: never marked by the first pass
             uint32_t m;
             Strands<T> st;
             const T canon = record_key<T>(sg, q, k, sp, single, m, st);
@@ -327,7 +411,7 @@ __global__ __launch_bounds__(BLOCK) void k_record(SeqArgs a, const uint64_t *c1,
             const u64x2 pr = load_pair(t, slot);
             int rc;
             if constexpr (REF) {
-                const unsigned long long own = ref_tag<P2>(t, hash) | (t0 + q) << 8 | m;
+                const unsigned long long own = ref_tag<P2>(t, hash) | (tl.t0 + q) << 8 | m;
                 rc = insert_pair<P2>(t, own, m, slot, pr, [&](unsigned long long x) {
                     return (x ^ own) >> t.ref_shift == 0 && ref_is(a, t, x, st);
                 }, my_probes);
@@ -425,17 +509,25 @@ __global__ __launch_bounds__(BLOCK) void k_rbin_count(SeqArgs a, const uint64_t 
             continue;
         const uint64_t t0 = tile * TILE;
         __syncthreads();  // the last tile's staged words and segment state are read
-        stage_tile2(a, tile, sg, c1, cw);
+        for (uint32_t i = threadIdx.x; i < STAGE_WORDS; i += BLOCK) {
+            const int64_t gw = (int64_t)(tile * TILE_WORDS) - 1 + i;
+            stage_word(sg, i, (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull);
+        }
+        if (threadIdx.x < TILE / 64)
+            cw[threadIdx.x] = c1[tile * (TILE / 64) + threadIdx.x];
         __syncthreads();
         uint64_t v[PER];
         uint32_t nv = 0;
-        Span sp = lo + 1 == hi ? span_of(a.strings, lo, t0) : Span{0, -1};
+        P2Tile tl{t0, lo, hi, lo + 1 == hi ? span_of(a.strings, lo, t0) : Span{0, -1}};
 #pragma unroll
         for (uint32_t it = 0; it < PER; ++it) {
             v[it] = BIN_NONE;
             const uint32_t q = it * BLOCK + threadIdx.x;
-            if (!((cw[q >> 6] >> lane) & 1ull) || !record_span(a.strings, lo, hi, t0, q, sp))
+            if (!((cw[q >> 6] >> lane) & 1ull))
                 continue;
+            const Span sp = record_span(a, tl, q);
+            if ((int32_t)q < sp.gs)
+                continue;  // not a k-mer start: never marked by the first pass
             uint32_t m;
             Strands<uint64_t> st;
             const uint64_t key = record_key<uint64_t>(sg, q, k, sp, single, m, st);
@@ -744,17 +836,15 @@ template <class T, bool P2, bool REF>
 __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const uint64_t *c1,
                                                   TableArgs pool, uint64_t *jbits,
                                                   bool accumulate, Counters *cnt) {
-    __shared__ Stage sg;
-    __shared__ uint64_t cw[TILE / 64];
+    __shared__ P2Batch b;
+    __shared__ uint32_t jw[P2_TILES * TILE / 32];  // the batch's junction words
     __shared__ uint32_t pf[(1u << PF_MAX_LOG2) / 32];
     __shared__ unsigned long long block_probes, junc_lds;
-    __shared__ uint32_t skip_lds;
-    uint32_t flag_set = ~0u, flag_age = 0, flag_val = 0;  // thread 0: last flag reading
+    OverflowFlag flag;
     SetSum junc = setsum_begin();
     const uint32_t k = a.k;
     const bool single = a.single != 0;
     const T *sent = (const T *)sa.table;
-    const uint32_t lane = threadIdx.x & 63;
     for (uint32_t i = threadIdx.x; i < prefilter_words(sa.pf_log2); i += BLOCK)
         pf[i] = sa.prefilter[i];
     if (threadIdx.x == 0)
@@ -763,21 +853,18 @@ __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const 
     uint32_t my_probes = 0;
     // homologous tiles at once (slab order) share table lines in L2; lookups
     // do not contend, unlike the record's atomics
-    RunCursor rc = (a.pass2_slabs & 2) ? run_cursor(a, a.chunk) : linear_run(a);
-    for (uint64_t tile; run_next(a, rc, &tile);) {
-        const uint64_t t0 = tile * TILE;
-        const uint32_t set = a.tiles[tile].set;
-        __syncthreads();
-        stage_tile2(a, tile, sg, c1, cw);
-        if (threadIdx.x == 0)
-            skip_lds = overflow_seen(a, set, flag_set, flag_age, flag_val);
-        __syncthreads();
-        if (skip_lds) {
+    const uint32_t most = batch_tiles(a.n_tiles, gridDim.x);
+    RunCursor rc = batch_run(a, (a.pass2_slabs & 2) != 0, max(a.chunk, most));
+    uint32_t n, total, set;
+    while (next_batch(a, rc, most, c1, b, flag, &n, &total, &set)) {
+        const uint32_t jt = threadIdx.x / (TILE / 64);  // this thread's junction word: its tile
+        uint64_t *const jdst = jbits + (jt < n ? b.tile[jt].t0 / 64 + threadIdx.x % (TILE / 64) : 0);
+        if (b.skip) {
             // this attempt's table overflowed: its results are discarded (the
-            // run is redone, or reports the overflow); the tile's junction
+            // run is redone, or reports the overflow); the tiles' junction
             // words are still defined
-            if (!accumulate && threadIdx.x < TILE / 64)
-                jbits[tile * (TILE / 64) + threadIdx.x] = 0;
+            if (!accumulate && jt < n)
+                *jdst = 0;
             continue;
         }
         const TableArgs t = table_of(a, pool, set);
@@ -785,29 +872,34 @@ __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const 
         const T *stab = sent + sd.sent_tab_off;
         const uint32_t slog2 = sd.sent_tab_log2;
         setsum_switch(junc, set, &junc_lds, &a.set_cnt[0].junctions, SETCNT_STRIDE);
-        // A thread's positions of the tile in groups: the group's candidate
-        // k-mers and home slots are computed from LDS alone, then every table
-        // word (and, on a sentinel-prefilter hit, the sentinel-table word) is
-        // loaded at once, so that many random reads are in flight per lane
-        // before any is needed; then each lookup is resolved.
-        // (The k-mer itself is read again from LDS where a lookup needs it, so
-        // that a group of wide k-mers fits the registers.)
-        for (uint32_t g0 = 0; g0 < TILE / BLOCK; g0 += DECIDE_GROUP) {
+        jw[threadIdx.x] = 0;
+        static_assert(P2_TILES * TILE / 32 == BLOCK, "a junction half-word per thread");
+        __syncthreads();
+        // A thread's candidates in groups: the group's candidate k-mers and
+        // home slots are computed from LDS alone, then every table word (and,
+        // on a sentinel-prefilter hit, the sentinel-table word) is loaded at
+        // once, so that several random reads are in flight per lane before
+        // any is needed; then each lookup is resolved.  (The k-mer itself is
+        // read again from LDS where a lookup needs it, so that a group of
+        // wide k-mers fits the registers.)
+        for (uint32_t i0 = threadIdx.x; i0 < total; i0 += DECIDE_GROUP * BLOCK) {
             constexpr uint32_t G = DECIDE_GROUP;
             uint64_t slot[G];
             unsigned long long id[G];  // packed: the key; reference: its tag
             u64x2 cur[G];
-            uint32_t ss[G];
+            uint32_t ss[G], pos[G];
             T sx[G];
-            uint32_t look = 0, maybe_sent = 0, junction = 0;
+            uint32_t look = 0, maybe_sent = 0;
 #pragma unroll
             for (uint32_t j = 0; j < G; ++j) {
-                const uint32_t q = (g0 + j) * BLOCK + threadIdx.x;  // position in the tile
                 slot[j] = 0;
                 id[j] = 0;
                 ss[j] = 0;
-                if ((cw[q >> 6] >> lane) & 1ull) {
-                    const T canon = norm(kmer_at<T>(sg, q + 32, k), single);
+                pos[j] = 0;
+                if (i0 + j * BLOCK < total) {
+                    pos[j] = b.at[i0 + j * BLOCK];
+                    const T canon = norm(kmer_at<T>(b.sg[pos[j] / TILE], pos[j] % TILE + 32, k),
+                                         single);
                     look |= 1u << j;
                     const uint64_t hash = slot_hash(canon);
                     slot[j] = home_slot<P2>(t, hash);
@@ -829,37 +921,36 @@ __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const 
             for (uint32_t j = 0; j < G; ++j) {
                 if (!((look >> j) & 1u))
                     continue;
-                const uint32_t q = (g0 + j) * BLOCK + threadIdx.x;
+                const uint32_t q = pos[j] % TILE, tj = pos[j] / TILE;
+                bool junction = false;
                 if ((maybe_sent >> j) & 1u) {
-                    const T canon = norm(kmer_at<T>(sg, q + 32, k), single);
-                    if (sent_probe_from(stab, slog2, canon, ss[j], sx[j])) {
-                        junction |= 1u << j;  // a sentinel k-mer
-                        continue;
-                    }
+                    const T canon = norm(kmer_at<T>(b.sg[tj], q + 32, k), single);
+                    junction = sent_probe_from(stab, slog2, canon, ss[j], sx[j]);
                 }
-                const int m = find_pair<P2>(t, slot[j], cur[j], [&](unsigned long long x) {
-                    if (!REF)
-                        return x >> 8 == id[j];
-                    if ((x ^ id[j]) >> t.ref_shift != 0)
-                        return false;
-                    // this position's own word, or one that reads the same k-mer
-                    return (x & ((1ull << t.ref_shift) - 1)) >> 8 == t0 + q ||
-                           ref_is(a, t, x, kmer_at<T>(sg, q + 32, k));
-                }, my_probes);
-                if (m < 0)
-                    ++my_missing;
-                else if (__popc((uint32_t)m & 15u) > 1 || __popc((uint32_t)m >> 4) > 1)
-                    junction |= 1u << j;
-            }
-#pragma unroll
-            for (uint32_t j = 0; j < G; ++j) {
-                const uint64_t p = t0 + (g0 + j) * BLOCK + threadIdx.x;
-                const uint64_t jw = ballot64((junction >> j) & 1u);
-                if (lane == 0) {
-                    jbits[p >> 6] = accumulate ? jbits[p >> 6] | jw : jw;
-                    junc.v += (unsigned long long)__popcll(jw);
+                if (!junction) {
+                    const int m = find_pair<P2>(t, slot[j], cur[j], [&](unsigned long long x) {
+                        if (!REF)
+                            return x >> 8 == id[j];
+                        if ((x ^ id[j]) >> t.ref_shift != 0)
+                            return false;
+                        // this position's own word, or one that reads the same k-mer
+                        return (x & ((1ull << t.ref_shift) - 1)) >> 8 == b.tile[tj].t0 + q ||
+                               ref_is(a, t, x, kmer_at<T>(b.sg[tj], q + 32, k));
+                    }, my_probes);
+                    if (m < 0)
+                        ++my_missing;
+                    else
+                        junction = __popc((uint32_t)m & 15u) > 1 || __popc((uint32_t)m >> 4) > 1;
                 }
+                if (junction)
+                    atomicOr(&jw[pos[j] >> 5], 1u << (pos[j] & 31));
             }
+        }
+        __syncthreads();
+        if (jt < n) {
+            const uint64_t x = (uint64_t)jw[2 * threadIdx.x + 1] << 32 | jw[2 * threadIdx.x];
+            *jdst = accumulate ? *jdst | x : x;
+            junc.v += (unsigned long long)__popcll(x);
         }
     }
     setsum_flush(junc, &junc_lds, &a.set_cnt[0].junctions, SETCNT_STRIDE);

@@ -3,7 +3,7 @@
 // junction positions, and every two consecutive junction positions of one
 // string give an edge), for gfx950.
 //
-//   k_block_counts  popcount of SCAN_WORDS bitmap words per workgroup
+//   k_block_counts  popcount of per (scan_words) bitmap words per workgroup
 //   k_scan_blocks   exclusive scan of the workgroup counts (one workgroup)
 //   k_emit          per workgroup: wave shuffle scan + LDS scan of word
 //                   popcounts, then every set bit writes its junction in
@@ -46,11 +46,11 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *t
 }
 
 __global__ __launch_bounds__(BLOCK) void k_block_counts(const uint64_t *bits, uint64_t nwords,
-                                                        uint32_t *blockcnt) {
+                                                        uint32_t per, uint32_t *blockcnt) {
     __shared__ uint32_t wsum[BLOCK / 64];
     uint32_t c = 0;
-    const uint64_t w0 = (uint64_t)blockIdx.x * SCAN_WORDS;
-    for (uint32_t i = 0; i < SCAN_WORDS / BLOCK; ++i) {
+    const uint64_t w0 = (uint64_t)blockIdx.x * per;
+    for (uint32_t i = 0; i < per / BLOCK; ++i) {
         const uint64_t wi = w0 + i * BLOCK + threadIdx.x;
         if (wi < nwords)
             c += (uint32_t)__popcll(bits[wi]);
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(BLOCK) void k_scan_blocks(const uint32_t *blockcnt,
         blockoff[nblocks] = running;
 }
 
-// Junctions in global order.  Each of SCAN_WORDS / BLOCK rounds scans BLOCK
+// Junctions in global order.  Each of per / BLOCK rounds scans BLOCK
 // bitmap words (one per thread): each thread writes the in-round positions of
 // its word's set bits into an LDS index at its scanned offset (one short
 // store per junction, no search), then thread t writes junctions t, t +
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(BLOCK) void k_scan_blocks(const uint32_t *blockcnt,
 // (coalesced) whatever the junction density.
 template <class T>
 __global__ __launch_bounds__(BLOCK) void k_emit(SeqArgs a, const uint64_t *bits, uint64_t nwords,
-                                                const uint64_t *blockoff, OutArgs o, uint64_t nj,
+                                                uint32_t per, const uint64_t *blockoff, OutArgs o, uint64_t nj,
                                                 uint64_t ne) {
     // the round's k-mers: its BLOCK * 64 positions, plus the longest window
     constexpr uint32_t EMIT_WORDS = BLOCK * 64 / 32 + 5;
@@ -97,10 +97,10 @@ __global__ __launch_bounds__(BLOCK) void k_emit(SeqArgs a, const uint64_t *bits,
     const uint32_t k = a.k;
     const bool single = a.single != 0;
     uint64_t running = blockoff[blockIdx.x];
-    const uint64_t w0 = (uint64_t)blockIdx.x * SCAN_WORDS;
+    const uint64_t w0 = (uint64_t)blockIdx.x * per;
     uint32_t si = a.n_strings;
     uint64_t gs = ~0ull, ge = 0;
-    for (uint32_t i = 0; i < SCAN_WORDS / BLOCK; ++i) {
+    for (uint32_t i = 0; i < per / BLOCK; ++i) {
         const uint64_t wbase = w0 + (uint64_t)i * BLOCK;
         const uint64_t wi = wbase + threadIdx.x;
         const uint64_t word = wi < nwords ? bits[wi] : 0;
@@ -161,15 +161,15 @@ __global__ __launch_bounds__(BLOCK) void k_emit(SeqArgs a, const uint64_t *bits,
 // workgroup per genome: the scanned count of the bits' compaction block plus
 // the popcounts of that block's words before the genome's first word.
 // Genomes start on tile boundaries, hence on word boundaries.
-__global__ __launch_bounds__(BLOCK) void k_joff(const uint64_t *bits, uint64_t nwords,
+__global__ __launch_bounds__(BLOCK) void k_joff(const uint64_t *bits, uint64_t nwords, uint32_t per,
                                                 const uint64_t *blockoff, OutArgs o) {
     __shared__ uint32_t wsum[BLOCK / 64];
-    const uint64_t nj = blockoff[(nwords + SCAN_WORDS - 1) / SCAN_WORDS];  // all set bits
+    const uint64_t nj = blockoff[(nwords + per - 1) / per];  // all set bits
     const uint32_t g = blockIdx.x;
     const uint64_t w = o.gbase[g] / 64;
-    const uint64_t b = w / SCAN_WORDS;
+    const uint64_t b = w / per;
     uint32_t c = 0;
-    for (uint64_t i = b * SCAN_WORDS + threadIdx.x; i < w && i < nwords; i += BLOCK)
+    for (uint64_t i = b * per + threadIdx.x; i < w && i < nwords; i += BLOCK)
         c += (uint32_t)__popcll(bits[i]);
     uint32_t tot;
     block_exclusive_scan(c, &tot, wsum);
@@ -184,19 +184,8 @@ hipError_t launch_compact(int W, const SeqArgs &a, const uint64_t *jbits, uint64
                           uint64_t n_junctions, hipStream_t s) {
     if (n_junctions == 0)
         return launch_fill_u64(o.joff, (uint64_t)o.n_genomes + 1, 0, s);
-    const uint32_t nblocks = (uint32_t)((nwords + SCAN_WORDS - 1) / SCAN_WORDS);
     const uint64_t ne = n_junctions >= a.n_strings ? n_junctions - a.n_strings : 0;
-    hipLaunchKernelGGL(k_block_counts, dim3(nblocks), dim3(BLOCK), 0, s, jbits, nwords, blockcnt);
-    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(BLOCK), 0, s, blockcnt, nblocks, blockoff);
-    (void)by_width(W, [&](auto tag) {
-        hipLaunchKernelGGL(k_emit<decltype(tag)>, dim3(nblocks), dim3(BLOCK), 0, s, a, jbits,
-                           nwords, blockoff, o, n_junctions, ne);
-        return hipSuccess;
-    });
-    if (o.n_genomes)
-        hipLaunchKernelGGL(k_joff, dim3(o.n_genomes), dim3(BLOCK), 0, s, jbits, nwords, blockoff,
-                           o);
-    return hipGetLastError();
+    return launch_compact_bound(W, a, jbits, nwords, blockcnt, blockoff, o, n_junctions, ne, s);
 }
 
 hipError_t launch_compact_bound(int W, const SeqArgs &a, const uint64_t *jbits, uint64_t nwords,
@@ -204,17 +193,19 @@ hipError_t launch_compact_bound(int W, const SeqArgs &a, const uint64_t *jbits, 
                                 uint64_t max_j, uint64_t max_e, hipStream_t s) {
     if (nwords == 0)
         return launch_fill_u64(o.joff, (uint64_t)o.n_genomes + 1, 0, s);
-    const uint32_t nblocks = (uint32_t)((nwords + SCAN_WORDS - 1) / SCAN_WORDS);
-    hipLaunchKernelGGL(k_block_counts, dim3(nblocks), dim3(BLOCK), 0, s, jbits, nwords, blockcnt);
+    const uint32_t per = scan_words(nwords), nblocks = (uint32_t)scan_blocks(nwords);
+    static_assert(SCAN_ROUND == BLOCK, "a bitmap word per thread");
+    hipLaunchKernelGGL(k_block_counts, dim3(nblocks), dim3(BLOCK), 0, s, jbits, nwords, per,
+                       blockcnt);
     hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(BLOCK), 0, s, blockcnt, nblocks, blockoff);
     (void)by_width(W, [&](auto tag) {
         hipLaunchKernelGGL(k_emit<decltype(tag)>, dim3(nblocks), dim3(BLOCK), 0, s, a, jbits,
-                           nwords, blockoff, o, max_j, max_e);
+                           nwords, per, blockoff, o, max_j, max_e);
         return hipSuccess;
     });
     if (o.n_genomes)
-        hipLaunchKernelGGL(k_joff, dim3(o.n_genomes), dim3(BLOCK), 0, s, jbits, nwords, blockoff,
-                           o);
+        hipLaunchKernelGGL(k_joff, dim3(o.n_genomes), dim3(BLOCK), 0, s, jbits, nwords, per,
+                           blockoff, o);
     return hipGetLastError();
 }
 
@@ -222,7 +213,7 @@ hipError_t launch_compact_bound(int W, const SeqArgs &a, const uint64_t *jbits, 
 // compaction scan, edges = junctions - strings (every string of c junctions
 // has c - 1 edges), and a status word.
 __global__ __launch_bounds__(BLOCK) void k_ws_finalize(FinalizeArgs f) {
-    __shared__ unsigned long long part[5][BLOCK];
+    __shared__ unsigned long long part[5][BLOCK / 64];
     unsigned long long c[5] = {0, 0, 0, 0, 0};
     for (uint32_t i = threadIdx.x; i < f.n_sets; i += BLOCK) {
         const SetCounters &sc = f.set_cnt[i];
@@ -232,12 +223,16 @@ __global__ __launch_bounds__(BLOCK) void k_ws_finalize(FinalizeArgs f) {
         c[3] += sc.overflow ? 1ull : 0ull;
         c[4] += sc.junctions;
     }
-    for (int q = 0; q < 5; ++q)
-        part[q][threadIdx.x] = c[q];
+    for (int q = 0; q < 5; ++q) {
+        for (int d = 32; d; d >>= 1)
+            c[q] += __shfl_xor(c[q], d, 64);
+        if ((threadIdx.x & 63) == 0)
+            part[q][threadIdx.x >> 6] = c[q];
+    }
     __syncthreads();
     if (threadIdx.x != 0)
         return;
-    for (uint32_t t = 1; t < BLOCK; ++t)
+    for (uint32_t t = 1; t < BLOCK / 64; ++t)
         for (int q = 0; q < 5; ++q)
             c[q] += part[q][t];
     const uint64_t nj = f.nblocks ? f.blockoff[f.nblocks] : 0;

@@ -485,15 +485,25 @@ __device__ __forceinline__ TileSet tile_set_of(const SeqArgs &a, const BloomArgs
 // one, and once that share is exhausted from the other XCDs' shares in
 // turn, so the last chunks go to whichever workgroups are free.  The walk is
 // the same for every thread of a workgroup; with a queue, every thread must
-// call run_next (it synchronises the workgroup to share each claim).
+// call run_next (it synchronises the workgroup to share each claim).  Where
+// there are too few tiles to go round, each is cut in parts instead
+// (SeqArgs.parts_log2).
 struct RunCursor {
     uint64_t c, end;
     uint32_t gi, G, step, ordered;
     uint32_t qx, qleft;  // queue: the share being walked, shares not yet exhausted
 };
 
+// One part of one tile: the workgroup's only entry.
+__device__ __forceinline__ RunCursor part_cursor(const SeqArgs &a) {
+    const uint64_t c = blockIdx.x >> a.parts_log2;
+    return RunCursor{c, min(c + 1, a.n_tiles), 0, 1, gridDim.x, 0, 0, 0};
+}
+
 __device__ __forceinline__ RunCursor run_cursor(const SeqArgs &a, uint32_t G) {
     const uint32_t x = blockIdx.x % NXCD;
+    if (a.parts_log2)
+        return part_cursor(a);
     if (a.queue)  // nothing claimed yet: the first run_next claims
         return RunCursor{0, 0, G, G, 0, 1, x, NXCD};
     return RunCursor{a.xcd_start[x] + (uint64_t)(blockIdx.x / NXCD) * G, a.xcd_start[x + 1], 0,
@@ -504,6 +514,16 @@ __device__ __forceinline__ RunCursor linear_run(const SeqArgs &a, uint32_t G) {
     if (a.queue)
         return RunCursor{0, 0, G, G, 0, 0, 0, 1};
     return RunCursor{(uint64_t)blockIdx.x * G, a.n_tiles, 0, G, gridDim.x, 0, 0, 0};
+}
+
+// The workgroup's part of a tile, in eighths of it: steps [lo, hi).
+struct Part {
+    uint32_t lo, hi;
+};
+__device__ __forceinline__ Part tile_part(const SeqArgs &a) {
+    static_assert(TILE / BLOCK == 8, "a tile is eight steps");
+    const uint32_t n = 8u >> a.parts_log2, i = blockIdx.x & ((1u << a.parts_log2) - 1);
+    return a.parts_log2 ? Part{i * n, i * n + n} : Part{0, 8};
 }
 
 // Next tile of the walk, or false at its end.

@@ -34,7 +34,14 @@ constexpr uint32_t NXCD = 8;                       // accelerator dies (L2 domai
 constexpr uint32_t HLL_LOG2 = 12;                  // distinct-count sketch registers
 constexpr uint32_t HLL_M = 1u << HLL_LOG2;
 constexpr uint32_t PF_MAX_LOG2 = 16;               // sentinel prefilter bits (max)
-constexpr uint32_t SCAN_WORDS = 2048;              // bitmap words per compaction block
+// Bitmap words per compaction block: few for a small bitmap, whose blocks
+// would else be too few to fill the device (at 0.4 Mbp, 4 blocks: the emit took
+// 27 us), many for a large one (one workgroup scans the blocks' counts).
+constexpr uint32_t SCAN_ROUND = 256;               // words a block takes at once
+inline uint32_t scan_words(uint64_t nwords) { return nwords <= (1u << 18) ? SCAN_ROUND : 2048u; }
+inline uint64_t scan_blocks(uint64_t nwords) {
+    return (nwords + scan_words(nwords) - 1) / scan_words(nwords);
+}
 constexpr uint32_t FILL_CHUNK = 8;                 // deduplicating fill: tiles per visit
 constexpr uint32_t RECORD_RUN = 8;                 // record in runs: tiles per visit
 constexpr uint32_t FILL_DD = 4096;                 // deduplicating fill: LDS table entries
@@ -142,7 +149,8 @@ struct SeqArgs {
                                // bit 2 record in runs of RECORD_RUN entries of it
     uint32_t fill_dedup;       // blocked fill: skip filter effects the workgroup has sent
     uint32_t chunk;            // tiles a workgroup takes per visit of a tile walk
-    uint32_t pad;
+    uint32_t parts_log2;       // nonzero: few tiles, each cut in 2^parts_log2 parts and every
+                               // part a workgroup (memory order)
     unsigned int *queue;       // tile queue of this launch (NXCD zeroed counters), or
                                // null: the walk's static chunk schedule
 };
@@ -203,14 +211,31 @@ struct OutArgs {
 hipError_t pass1_occupancy(KernelId which, int W, bool blocked, bool fill_dedup,
                            int *blocks_per_cu);
 hipError_t pass2_occupancy(KernelId which, int W, int *blocks_per_cu);
+// Several regions set to a repeated 32-bit value in one launch (addresses and
+// sizes multiples of 16 bytes).
+struct ClearList {
+    struct {
+        void *p;
+        uint64_t n16;
+        uint32_t v;
+    } r[10];
+    uint32_t n;
+    void add(void *p, uint64_t bytes, uint32_t v = 0) {
+        if (bytes)
+            r[n].p = p, r[n].n16 = bytes / 16, r[n++].v = v;
+    }
+};
+hipError_t launch_clear(const ClearList &c, hipStream_t s);
 hipError_t launch_zero(void *p, uint64_t bytes, hipStream_t s);
 hipError_t launch_fill_u64(uint64_t *p, uint64_t n, uint64_t v, hipStream_t s);
 
 // a0: each set's sentinel table (normalised first and last k-mer of every
 // string; tab_owner: a claim word per slot, tab_slots in all) and the sentinel
-// prefilters.
+// prefilters, all cleared beforehand (clear_sentinels).
+void clear_sentinels(ClearList &c, int W, const SentArgs &sa, uint32_t *tab_owner,
+                     uint64_t tab_slots);
 hipError_t launch_sentinels(int W, const SeqArgs &a, const SentArgs &sa, uint32_t *tab_owner,
-                            uint64_t tab_slots, hipStream_t s);
+                            hipStream_t s);
 // a1: insert every normalised (k+1)-mer into its set's Bloom filter.
 // Binned fill of a blocked filter pool (the same bits as launch_fill; the
 // pool zeroed beforehand): per chunk of tiles, every edge's filter effect
@@ -266,7 +291,6 @@ hipError_t launch_census(int W, const SeqArgs &a, unsigned long long *counters, 
 hipError_t launch_popcount(const uint32_t *pool, uint64_t n_words, const uint64_t *bloom_starts,
                            uint32_t n_sets, SetCounters *set_cnt, hipStream_t s);
 // a3: exact in/out edge masks of every candidate k-mer.
-hipError_t launch_table_clear(const TableArgs &pool, uint64_t slots, hipStream_t s);
 hipError_t launch_record(int W, const SeqArgs &a, const uint64_t *c1, const TableArgs &pool,
                          Counters *cnt, uint32_t grid, hipStream_t s);
 

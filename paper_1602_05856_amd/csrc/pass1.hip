@@ -29,6 +29,8 @@
 // word before and five after, covering predecessor, successor and the
 // longest window) in LDS with coalesced 64-bit loads, in both base orders;
 // lanes then cut their k-mers' windows out of LDS (Stage).
+#include <algorithm>
+
 #include "device.hpp"
 
 namespace tp {
@@ -51,9 +53,28 @@ __global__ void k_fill_u64(uint64_t *p, uint64_t n, uint64_t v) {
         p[i] = v;
 }
 
+__global__ __launch_bounds__(BLOCK) void k_clear(ClearList c) {
+    for (uint32_t q = 0; q < c.n; ++q) {
+        uint4 *p = (uint4 *)c.r[q].p;
+        const uint32_t v = c.r[q].v;
+        for (uint64_t i = blockIdx.x * (uint64_t)BLOCK + threadIdx.x; i < c.r[q].n16;
+             i += (uint64_t)gridDim.x * BLOCK)
+            p[i] = make_uint4(v, v, v, v);
+    }
+}
+
 static uint32_t grid_for(uint64_t n, uint32_t cap = 8192) {
     uint64_t g = (n + BLOCK - 1) / BLOCK;
     return (uint32_t)(g < 1 ? 1 : (g > cap ? cap : g));
+}
+
+hipError_t launch_clear(const ClearList &c, hipStream_t s) {
+    uint64_t most = 0;
+    for (uint32_t q = 0; q < c.n; ++q)
+        most = std::max(most, c.r[q].n16);
+    if (most)
+        hipLaunchKernelGGL(k_clear, dim3(grid_for(most)), dim3(BLOCK), 0, s, c);
+    return hipGetLastError();
 }
 
 hipError_t launch_zero(void *p, uint64_t bytes, hipStream_t s) {
@@ -137,16 +158,18 @@ __global__ __launch_bounds__(BLOCK) void k_sentinels(SeqArgs a, uint32_t n, T *t
     }
 }
 
+void clear_sentinels(ClearList &c, int W, const SentArgs &sa, uint32_t *tab_owner,
+                     uint64_t tab_slots) {
+    c.add((void *)sa.prefilter, 2ull * 4 * prefilter_words(sa.pf_log2));
+    c.add((void *)sa.table, tab_slots * 8 * W, ~0u);
+    c.add(tab_owner, tab_slots * 4, ~0u);
+}
+
 hipError_t launch_sentinels(int W, const SeqArgs &a, const SentArgs &sa, uint32_t *tab_owner,
-                            uint64_t tab_slots, hipStream_t s) {
-    hipError_t e = launch_zero((void *)sa.prefilter, 2 * prefilter_words(sa.pf_log2) * 4, s);
-    if (e == hipSuccess && tab_slots) {
-        e = launch_fill_u64((uint64_t *)sa.table, tab_slots * W, ~0ull, s);
-        if (e == hipSuccess)
-            e = launch_fill_u64((uint64_t *)tab_owner, (tab_slots + 1) / 2, ~0ull, s);
-    }
-    if (e != hipSuccess || sa.n == 0)
-        return e;
+                            hipStream_t s) {
+    static_assert((4u << SENT_TAB_MIN_LOG2) % 16 == 0, "claim words clear in 16-byte pieces");
+    if (sa.n == 0)
+        return hipSuccess;
     return by_width(W, [&](auto tag) {
         using T = decltype(tag);
         hipLaunchKernelGGL(k_sentinels<T>, dim3((sa.n + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, a,
@@ -267,7 +290,8 @@ __global__ __launch_bounds__(BLOCK) void k_fill(SeqArgs a, BloomArgs pool, Count
         const TileSet ts = tile_set_of(a, pool, ti.set);
         const bool one = lo + 1 == hi;
         Span sp = one ? span_of(a.strings, lo, t0) : Span{0, -1};
-        for (uint32_t it = 0; it < TILE / BLOCK; ++it) {
+        const Part part = tile_part(a);
+        for (uint32_t it = part.lo; it < part.hi; ++it) {
             const uint32_t q = it * BLOCK + threadIdx.x, r = q + 32;
             if (!one && (int32_t)q >= sp.ge)
                 sp = span_at(a.strings, lo, hi, t0, q);
@@ -838,7 +862,8 @@ __device__ __forceinline__ void query_end(const SeqArgs &a, QueryShared &qs, Set
     }
 }
 
-// A tile that no string touches: all-zero candidate words.
+// A tile that no string touches: all-zero candidate words (every part of it
+// writes them).
 __device__ __forceinline__ void query_no_string(uint64_t tile, uint64_t *c1, uint64_t *c1u,
                                                 uint32_t round) {
     if (threadIdx.x < TILE / 64) {
@@ -897,7 +922,8 @@ void k_query_blocked(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint6
         const uint32_t run0 = (threadIdx.x >> 6) * (TILE / (BLOCK / 64));
         uint32_t carry_key = 0, carry_g = 0;
         uint64_t carry_w = 0;
-        for (uint32_t it = 0; it < TILE / BLOCK; ++it) {
+        const Part part = tile_part(a);
+        for (uint32_t it = part.lo; it < part.hi; ++it) {
             const uint32_t q = run0 + it * 64 + lane, r = q + 32;
             if (!one && (int32_t)q >= sp.ge)
                 sp = span_at(a.strings, lo, hi, t0, q);
@@ -934,8 +960,8 @@ void k_query_blocked(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint6
             carry_g = (uint32_t)__builtin_amdgcn_readlane((int)gout, 63);
             carry_w = lane63(wo);
             const bool first = (int32_t)q == sp.gs, last = (int32_t)(q + k) == sp.ge;
-            if (live && (first || (it == 0 && lane == 0))) {
-                // the position before is in another wave's run, or there is
+            if (live && (first || (it == part.lo && lane == 0))) {
+                // the position before is another wave's or part's, or there is
                 // none (its middle is then part of the sketch's hash only)
                 const Strands<T> s = kmer_at<T>(sg, r, k - 1);
                 const MiddleKey mi = middle_key(s.fwd, s.rc, single, ts.f.mask >> 6);
@@ -1016,7 +1042,8 @@ void k_query_standard(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint
         setsum_switch(cand, ts.set, &qs.cand_lds, &a.set_cnt[0].candidates, SETCNT_STRIDE);
         const bool one = lo + 1 == hi;
         Span sp = one ? span_of(a.strings, lo, t0) : Span{0, -1};
-        for (uint32_t it = 0; it < TILE / BLOCK; ++it) {
+        const Part part = tile_part(a);
+        for (uint32_t it = part.lo; it < part.hi; ++it) {
             const uint32_t q = it * BLOCK + threadIdx.x;
             if (!one && (int32_t)q >= sp.ge)
                 sp = span_at(a.strings, lo, hi, t0, q);
@@ -1212,56 +1239,63 @@ hipError_t pass1_occupancy(KernelId which, int W, bool blocked, bool fill_dedup,
 
 // ----------------------------------------------------- filter popcount per set
 
-// Workgroup b counts words [b*chunk, (b+1)*chunk) of the pool; a thread adds
-// its running count to a set's counter whenever its words cross into
-// another set (set regions are consecutive in the pool).  At the end the
-// threads whose last set is the last set of the chunk add in LDS first, so a
-// chunk inside one set costs one device atomic.
-__global__ __launch_bounds__(BLOCK) void k_popcount(const uint32_t *pool, uint64_t n,
-                                                    uint64_t chunk, const uint64_t *starts,
-                                                    uint32_t n_sets, SetCounters *sc) {
+// Workgroup b counts 16-byte pieces [b*chunk, (b+1)*chunk) of the pool (sets'
+// filters start and end on whole pieces); a thread adds its running count to a
+// set's counter whenever its pieces cross into another set (set regions are
+// consecutive in the pool).  At the end the threads whose last set is the last
+// set of the chunk add in LDS first, so a chunk inside one set costs one
+// device atomic.  A chunk is at least 16 KiB: atomics on one counter queue up
+// (with 1 KiB chunks a 2 MiB filter took 28 us), and at most a 2048th of the
+// pool (1.4 GB over 128 sets: 1.14 ms by words, 0.32 by these pieces).
+__global__ __launch_bounds__(BLOCK) void k_popcount(const uint4 *pool, uint64_t n, uint64_t chunk,
+                                                    const uint64_t *starts, uint32_t n_sets,
+                                                    SetCounters *sc) {
     __shared__ unsigned long long sum;
-    __shared__ uint32_t last_set;
     const uint64_t b0 = blockIdx.x * chunk;
     const uint64_t b1 = b0 + chunk < n ? b0 + chunk : n;
-    uint32_t set = 0;
-    unsigned long long c = 0;
-    for (uint64_t i = b0 + threadIdx.x; i < b1; i += BLOCK) {
-        if (i < starts[set] || i >= starts[set + 1]) {
-            if (c)
-                atomicAdd(&sc[set].bloom_popcount, c);
-            c = 0;
-            uint32_t lo = 0, hi = n_sets;  // last set with starts[set] <= i
-            while (hi - lo > 1) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (starts[mid] <= i)
-                    lo = mid;
-                else
-                    hi = mid;
-            }
-            set = lo;
-        }
-        c += (unsigned long long)__popc(pool[i]);
-    }
-    if (threadIdx.x == 0) {
-        sum = 0;
-        // set of the chunk's last word
+    // last set that starts at or before piece i
+    auto set_of = [&](uint64_t i) {
         uint32_t lo = 0, hi = n_sets;
         while (hi - lo > 1) {
             const uint32_t mid = (lo + hi) >> 1;
-            if (b1 > b0 && starts[mid] <= b1 - 1)
+            if (starts[mid] <= 4 * i)
                 lo = mid;
             else
                 hi = mid;
         }
-        last_set = lo;
+        return lo;
+    };
+    if (threadIdx.x == 0)
+        sum = 0;
+    const uint32_t first_set = set_of(b0), last_set = set_of(b1 - 1);
+    uint32_t set = first_set;
+    uint64_t end = starts[set + 1] / 4;
+    uint32_t c = 0;  // (a thread's pieces of one chunk hold well under 2^32 bits)
+    constexpr uint32_t U = 4;
+    for (uint64_t i0 = b0 + threadIdx.x; i0 < b1; i0 += U * BLOCK) {
+        uint4 v[U];
+#pragma unroll
+        for (uint32_t q = 0; q < U; ++q)
+            v[q] = i0 + q * BLOCK < b1 ? pool[i0 + q * BLOCK] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (uint32_t q = 0; q < U; ++q) {
+            const uint64_t i = i0 + q * BLOCK;
+            if (i >= end && i < b1) {
+                if (c)
+                    atomicAdd(&sc[set].bloom_popcount, (unsigned long long)c);
+                c = 0;
+                set = set_of(i);
+                end = starts[set + 1] / 4;
+            }
+            c += __popc(v[q].x) + __popc(v[q].y) + __popc(v[q].z) + __popc(v[q].w);
+        }
     }
     __syncthreads();
     if (c) {
         if (set == last_set)
-            atomicAdd(&sum, c);
+            atomicAdd(&sum, (unsigned long long)c);
         else
-            atomicAdd(&sc[set].bloom_popcount, c);
+            atomicAdd(&sc[set].bloom_popcount, (unsigned long long)c);
     }
     __syncthreads();
     if (threadIdx.x == 0 && sum)
@@ -1272,10 +1306,11 @@ hipError_t launch_popcount(const uint32_t *pool, uint64_t n_words, const uint64_
                            uint32_t n_sets, SetCounters *set_cnt, hipStream_t s) {
     if (n_words == 0 || n_sets == 0)
         return hipSuccess;
-    const uint32_t grid = grid_for(n_words, 2048);
-    const uint64_t chunk = (n_words + grid - 1) / grid;
-    hipLaunchKernelGGL(k_popcount, dim3(grid), dim3(BLOCK), 0, s, pool, n_words, chunk,
-                       bloom_starts, n_sets, set_cnt);
+    const uint64_t n = n_words / 4;
+    const uint32_t grid = (uint32_t)std::min<uint64_t>(2048, (n + 1023) / 1024);
+    const uint64_t chunk = (n + grid - 1) / grid;
+    hipLaunchKernelGGL(k_popcount, dim3((uint32_t)((n + chunk - 1) / chunk)), dim3(BLOCK), 0, s,
+                       (const uint4 *)pool, n, chunk, bloom_starts, n_sets, set_cnt);
     return hipGetLastError();
 }
 

@@ -158,24 +158,6 @@ __device__ __forceinline__ RunCursor batch_run(const SeqArgs &a, bool slabs, uin
     return slabs ? run_cursor(a, chunk) : linear_run(a, chunk);
 }
 
-__global__ void k_table_clear(ulonglong2 *keys, uint64_t pairs) {
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < pairs;
-         i += (uint64_t)gridDim.x * blockDim.x)
-        keys[i] = make_ulonglong2(EMPTY_KEY, EMPTY_KEY);
-}
-
-// slots: even (capacities and spare tails are multiples of 64 slots).
-hipError_t launch_table_clear(const TableArgs &pool, uint64_t slots, hipStream_t s) {
-    if (slots == 0)
-        return hipSuccess;
-    uint64_t g = (slots / 2 + BLOCK - 1) / BLOCK;
-    if (g > 16384)
-        g = 16384;
-    hipLaunchKernelGGL(k_table_clear, dim3((uint32_t)g), dim3(BLOCK), 0, s,
-                       (ulonglong2 *)pool.keys, slots / 2);
-    return hipGetLastError();
-}
-
 // The table of a tile's set: the pools shifted to its region.
 __device__ __forceinline__ TableArgs table_of(const SeqArgs &a, const TableArgs &pool,
                                               uint32_t set) {

@@ -168,7 +168,7 @@ void tp::plan_clear_layout(tp_plan *p) {
     p->sent_tab_slots = 0;
     p->pf_log2 = 10;
     for (auto &g : p->grid)
-        g = 0;
+        g = Grid{};
     p->static_uploaded = p->order_uploaded = false;
     p->have_run = false;
     p->set_cnt.clear();
@@ -589,7 +589,7 @@ extern "C" int tp_plan_set_config(tp_plan *p, const tp_config *cfg) {
     }
     ++p->layout_gen;
     for (auto &g : p->grid)
-        g = 0;
+        g = Grid{};
     if (reorder) {
         build_tile_order(p);
         p->order_uploaded = false;
@@ -618,7 +618,7 @@ static SeqArgs seq_args(const tp_plan *p, const uint8_t *d_input) {
     a.pass2_slabs = p->cfg.pass2_slabs;
     a.fill_dedup = p->cfg.fill_dedup;
     a.chunk = p->cfg.chunk_tiles;
-    a.pad = 0;
+    a.parts_log2 = 0;
     a.queue = nullptr;
     return a;
 }
@@ -628,8 +628,11 @@ static SeqArgs seq_args(const tp_plan *p, const uint8_t *d_input) {
 // least QUEUE_MIN_TILES tiles per workgroup of its grid (with fewer, a
 // claim's workgroup barriers cost more than balancing gains).
 constexpr uint64_t QUEUE_MIN_TILES = 4;
-SeqArgs tp::with_queue(SeqArgs a, unsigned int *qbase, int kid, uint32_t grid) {
-    a.queue = qbase && a.n_tiles >= QUEUE_MIN_TILES * grid ? qbase + kid * NXCD : nullptr;
+SeqArgs tp::with_queue(SeqArgs a, unsigned int *qbase, int kid, const Grid &g) {
+    a.queue = qbase && a.n_tiles >= QUEUE_MIN_TILES * g.n ? qbase + kid * NXCD : nullptr;
+    a.parts_log2 = g.parts_log2;
+    if (g.parts_log2)
+        a.fill_dedup = 0;  // (its runs of tiles would undo the parts)
     return a;
 }
 
@@ -744,9 +747,16 @@ int tp::plan_grids(tp_plan *p, int dev) {
         occ = std::max(1, occ);
         if (p->cfg.wg_per_cu[kid])
             occ = std::min<int>(occ, (int)p->cfg.wg_per_cu[kid]);
-        uint64_t g = (uint64_t)occ * (uint64_t)std::max(1, ncu);
-        g = std::min<uint64_t>(g, align_up(std::max<uint64_t>(p->n_tiles, 1), NXCD));
-        p->grid[kid] = (uint32_t)std::max<uint64_t>(NXCD, g / NXCD * NXCD);
+        const uint64_t g = std::max<uint64_t>((uint64_t)occ * std::max(1, ncu) / NXCD * NXCD, NXCD);
+        // fewer tiles than that: up to four workgroups a tile in the first
+        // pass (each ends with an atomic on one counter, which queue up at
+        // some 14 ns).  0.4 Mbp, 195 tiles, whole, in four and in eight parts:
+        // standard query 61, 39 and 37 us, blocked 27, 23 and 23.
+        const uint64_t tiles = std::max<uint64_t>(p->n_tiles, 1);
+        uint32_t parts = 0;
+        while (kid <= K_QUERY && parts < 2 && (tiles << (parts + 1)) <= g)
+            ++parts;
+        p->grid[kid] = Grid{(uint32_t)std::min<uint64_t>(g, align_up(tiles << parts, NXCD)), parts};
     }
     return TP_OK;
 }
@@ -1112,7 +1122,7 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
                                   hipMemcpyHostToDevice, s));
         p->order_uploaded = true;
     }
-    if (!p->grid[0]) {
+    if (!p->grid[0].n) {
         const int rcg = plan_grids(p, dev);
         if (rcg)
             return rcg;
@@ -1159,19 +1169,25 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
     // ---- a0: sentinels; with rounds, the class census and partition
     const bool graphs = p->cfg.graphs && rounds == 1;
     auto enqueue_a0 = [&](hipStream_t q) -> int {
-        HIPCHK(launch_zero(cnt, sizeof(Counters), q));
-        HIPCHK(launch_sentinels(W, a, sa, p->d_sent_owner.as<uint32_t>(), sent_slots, q));
+        HIPCHK(launch_sentinels(W, a, sa, p->d_sent_owner.as<uint32_t>(), q));
         return TP_OK;
+    };
+    auto clear_a0 = [&](ClearList &c) {
+        c.add(cnt, sizeof(Counters));
+        clear_sentinels(c, W, sa, p->d_sent_owner.as<uint32_t>(), sent_slots);
     };
     HIPCHK(hipEventRecord(p->ev[0], s));
     HIPCHK(hipMemcpyAsync(p->d_sets.p, desc.data(), nsets * sizeof(SetDesc),
                           hipMemcpyHostToDevice, s));
     if (rounds > 1) {
+        ClearList c{};
+        clear_a0(c);
+        HIPCHK(launch_clear(c, s));
         int rc0 = enqueue_a0(s);
         if (rc0)
             return rc0;
         HIPCHK(p->d_census.ensure((uint64_t)nsets * CLASS_Q * 8));
-        HIPCHK(launch_census(W, a, p->d_census.as<unsigned long long>(), p->grid[K_FILL], s));
+        HIPCHK(launch_census(W, a, p->d_census.as<unsigned long long>(), p->grid[K_FILL].n, s));
         p->census.assign((size_t)nsets * CLASS_Q, 0);
         HIPCHK(hipMemcpyAsync(p->census.data(), p->d_census.p, p->census.size() * 8,
                               hipMemcpyDeviceToHost, s));
@@ -1199,17 +1215,16 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
         }
         // prologue (graph-replayable): sentinels on a single round, zeroing
         auto enqueue_p1 = [&](hipStream_t q) -> int {
-            if (rounds == 1) {
-                const int rc0 = enqueue_a0(q);
-                if (rc0)
-                    return rc0;
-            }
-            HIPCHK(launch_zero(scnt, nsets * sizeof(SetCounters), q));
-            HIPCHK(launch_zero(p->d_hll.p, HLL_M * 4, q));
-            HIPCHK(launch_zero(p->d_bloom.p, p->bloom_words * 4, q));
+            ClearList c{};
+            if (rounds == 1)
+                clear_a0(c);
+            c.add(scnt, nsets * sizeof(SetCounters));
+            c.add(p->d_hll.p, HLL_M * 4);
+            c.add(p->d_bloom.p, p->bloom_words * 4);
             if (qbase)  // the fill's and the query's tile queues
-                HIPCHK(launch_zero(qbase, 2 * NXCD * sizeof(unsigned int), q));
-            return TP_OK;
+                c.add(qbase, 2 * NXCD * sizeof(unsigned int));
+            HIPCHK(launch_clear(c, q));
+            return rounds == 1 ? enqueue_a0(q) : TP_OK;
         };
         {
             KeyBuilder kb;
@@ -1225,11 +1240,11 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             HIPCHK(launch_fill_binned(W, a, pool, cnt, bin, bin_tiles, s));
         else
             HIPCHK(launch_fill(W, with_queue(a, qbase, K_FILL, p->grid[K_FILL]), pool, cnt,
-                               p->grid[K_FILL], s));
+                               p->grid[K_FILL].n, s));
         HIPCHK(hipEventRecord(p->ev[2], s));
         HIPCHK(launch_query(W, with_queue(a, qbase, K_QUERY, p->grid[K_QUERY]), pool, sa,
                             p->d_c1.as<uint64_t>(),
-                            c1u, round, cnt, p->d_hll.as<uint32_t>(), p->grid[K_QUERY], s));
+                            c1u, round, cnt, p->d_hll.as<uint32_t>(), p->grid[K_QUERY].n, s));
         if (!bin.popcount)  // (the binned fill of a one-set pool counts its bits)
             HIPCHK(launch_popcount(pool.words, p->bloom_words, p->d_bloom_starts.as<uint64_t>(),
                                    nsets, scnt, s));
@@ -1354,18 +1369,16 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             // prologue (graph-replayable): counters and the table cleared (the
             // binned record writes every block itself: only the spare tail)
             auto enqueue_p2 = [&](hipStream_t q) -> int {
-                HIPCHK(launch_zero(&cnt->fill_atomics + PASS2_OFFSET,
-                                   PASS2_FIELDS * sizeof(unsigned long long), q));
-                HIPCHK(launch_zero(scnt, nsets * sizeof(SetCounters), q));
-                if (rbin) {
-                    TableArgs tail = t;
-                    tail.keys = t.keys + p->sets[0].table_cap;
-                    HIPCHK(launch_table_clear(tail, TABLE_TAIL, q));
-                } else {
-                    HIPCHK(launch_table_clear(t, slots, q));
-                }
+                ClearList c{};
+                c.add(&cnt->fill_atomics + PASS2_OFFSET, PASS2_FIELDS * sizeof(unsigned long long));
+                c.add(scnt, nsets * sizeof(SetCounters));
+                if (rbin)
+                    c.add(t.keys + p->sets[0].table_cap, TABLE_TAIL * 8, ~0u);
+                else
+                    c.add(t.keys, slots * 8, ~0u);
                 if (qbase)  // the record's and the decision's tile queues
-                    HIPCHK(launch_zero(qbase + 2 * NXCD, 2 * NXCD * sizeof(unsigned int), q));
+                    c.add(qbase + 2 * NXCD, 2 * NXCD * sizeof(unsigned int));
+                HIPCHK(launch_clear(c, q));
                 return TP_OK;
             };
             {
@@ -1381,11 +1394,11 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
                                             d2[0].table_m, scnt, cnt, s));
             else
                 HIPCHK(launch_record(W, with_queue(a, qbase, K_RECORD, p->grid[K_RECORD]),
-                                     p->d_c1.as<uint64_t>(), t, cnt, p->grid[K_RECORD], s));
+                                     p->d_c1.as<uint64_t>(), t, cnt, p->grid[K_RECORD].n, s));
             HIPCHK(hipEventRecord(p->ev[6], s));
             HIPCHK(launch_decide(W, with_queue(a, qbase, K_DECIDE, p->grid[K_DECIDE]), sa,
                                  p->d_c1.as<uint64_t>(), t, p->d_j.as<uint64_t>(),
-                                 round > 0, cnt, p->grid[K_DECIDE], s));
+                                 round > 0, cnt, p->grid[K_DECIDE].n, s));
             HIPCHK(hipEventRecord(p->ev[7], s));
             std::vector<SetCounters> h2(nsets);
             unsigned long long rb_short = 0;
@@ -1463,7 +1476,7 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
     if (nj < ns)
         return fail(TP_EDEVICE, "internal error: fewer junctions than strings");
     const uint64_t ne = nj - ns;
-    const uint64_t nblocks = (p->bitmap_words + SCAN_WORDS - 1) / SCAN_WORDS;
+    const uint64_t nblocks = scan_blocks(p->bitmap_words);
     // the exact tables are dead from here on: spare them if the outputs do
     // not fit beside them (the next run allocates them again)
     const std::initializer_list<DevBuf *> tables = {&p->d_keys};

@@ -119,8 +119,12 @@ struct SetInfo {
 
 // Sequence arguments of tile kernel kid with its tile queue (NXCD counters
 // at qbase + kid * NXCD), or with the static schedule when qbase is null or
-// the kernel has few tiles per workgroup of its grid.
-SeqArgs with_queue(SeqArgs a, unsigned int *qbase, int kid, uint32_t grid);
+// the kernel has few tiles per workgroup of its grid, and the cut of its
+// tiles in parts.
+struct Grid {
+    uint32_t n = 0, parts_log2 = 0;  // workgroups of a tile kernel, parts a tile is cut in
+};
+SeqArgs with_queue(SeqArgs a, unsigned int *qbase, int kid, const Grid &grid);
 // Whether the plan's fill can run binned (blocked filter, pool within the
 // bucket limit).
 bool fill_binnable(const tp_plan *p);
@@ -193,7 +197,7 @@ struct WsState {
     bool pow2 = true;
     std::vector<SetDesc> desc;
     std::vector<uint64_t> bloom_starts;
-    uint32_t grid[K_COUNT] = {};
+    Grid grid[K_COUNT] = {};
 };
 }  // namespace tp
 
@@ -212,7 +216,7 @@ struct tp_plan {
     uint64_t bloom_words = 0;              // filter pool, 32-bit words
     uint64_t sent_tab_slots = 0;           // sentinel-table pool, slots (even)
     uint32_t pf_log2 = 10;
-    uint32_t grid[tp::K_COUNT] = {};           // persistent grid per tile kernel (0: not set)
+    tp::Grid grid[tp::K_COUNT] = {};           // grid per tile kernel (0: not set)
     uint32_t n_cu = 0;                     // CUs the plan's kernels run on (set with the grids)
     uint32_t rounds = 1;                   // Algorithm 3: k-mer classes, one round each
     uint32_t last_rounds = 1;              // rounds of the last run (more with a table budget)

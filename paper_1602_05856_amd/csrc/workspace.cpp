@@ -76,7 +76,7 @@ extern "C" int tp_plan_workspace_layout(tp_plan *p, double key_fraction, double 
     for (uint32_t i = 0; i < nsets; ++i)
         w.bloom_starts[i] = p->sets[i].bloom_off;
     w.bloom_starts[nsets] = p->bloom_words;
-    w.nblocks = (p->bitmap_words + SCAN_WORDS - 1) / SCAN_WORDS;
+    w.nblocks = scan_blocks(p->bitmap_words);
 
     Carver c;
     w.o_tiles = c.take(p->n_tiles * 4);
@@ -208,7 +208,7 @@ int ws_run(tp_plan *p, const uint8_t *d_input, uint8_t *base, uint8_t *outb, hip
     a.pass2_slabs = p->cfg.pass2_slabs;
     a.fill_dedup = p->cfg.fill_dedup;
     a.chunk = p->cfg.chunk_tiles;
-    a.pad = 0;
+    a.parts_log2 = 0;
     a.queue = nullptr;  // set per launch below (tp_config.tile_queue)
 
     BloomArgs pool{(uint32_t *)(base + w.o_bloom), 0, p->h,
@@ -232,33 +232,48 @@ int ws_run(tp_plan *p, const uint8_t *d_input, uint8_t *base, uint8_t *outb, hip
     auto queued = [&](int kid) { return with_queue(a, qbase, kid, w.grid[kid]); };
     // counters start at zero and add up over rounds; a set whose table
     // overflows keeps its flag, so its later rounds are skipped too
-    HIPCHK(launch_zero(cnt, sizeof(Counters), s));
-    HIPCHK(launch_zero(scnt, nsets * sizeof(SetCounters), s));
-    HIPCHK(launch_sentinels(W, a, sa, (uint32_t *)(base + w.o_sent_owner), p->sent_tab_slots, s));
+    // (the tile queues are cleared by a kernel too: graph-safe)
+    auto clear_round = [&](ClearList &c) {
+        c.add(pool.words, p->bloom_words * 4);
+        if (qbase)
+            c.add(qbase, 4 * NXCD * sizeof(unsigned int));
+        if (!pass1_only)
+            c.add(t.keys, w.slots * 8, ~0u);
+    };
+    {
+        ClearList c{};
+        c.add(cnt, sizeof(Counters));
+        c.add(scnt, nsets * sizeof(SetCounters));
+        clear_sentinels(c, W, sa, (uint32_t *)(base + w.o_sent_owner), p->sent_tab_slots);
+        clear_round(c);
+        HIPCHK(launch_clear(c, s));
+    }
+    HIPCHK(launch_sentinels(W, a, sa, (uint32_t *)(base + w.o_sent_owner), s));
     if (rounds > 1) {
         auto *census = (unsigned long long *)(base + w.o_census);
         auto *bounds = (uint32_t *)(base + w.o_bounds);
-        HIPCHK(launch_census(W, a, census, w.grid[K_FILL], s));
+        HIPCHK(launch_census(W, a, census, w.grid[K_FILL].n, s));
         HIPCHK(launch_partition(census, nsets, rounds, bounds, s));
     }
     for (uint32_t round = 0; round < rounds; ++round) {
         if (rounds > 1)
             HIPCHK(launch_set_round((SetDesc *)(base + w.o_sets),
                                     (const uint32_t *)(base + w.o_bounds), nsets, rounds, round, s));
-        HIPCHK(launch_zero(pool.words, p->bloom_words * 4, s));
-        if (qbase)  // every tile kernel's queue, cleared by a kernel (graph-safe)
-            HIPCHK(launch_zero(qbase, 4 * NXCD * sizeof(unsigned int), s));
-        HIPCHK(launch_fill(W, queued(K_FILL), pool, cnt, w.grid[K_FILL], s));
+        if (round) {
+            ClearList c{};
+            clear_round(c);
+            HIPCHK(launch_clear(c, s));
+        }
+        HIPCHK(launch_fill(W, queued(K_FILL), pool, cnt, w.grid[K_FILL].n, s));
         HIPCHK(launch_query(W, queued(K_QUERY), pool, sa, c1, c1u, round, cnt, nullptr,
-                            w.grid[K_QUERY], s));
+                            w.grid[K_QUERY].n, s));
         HIPCHK(launch_popcount(pool.words, p->bloom_words, (const uint64_t *)(base + w.o_bloom_starts),
                                nsets, scnt, s));
         if (pass1_only)
             continue;
-        HIPCHK(launch_table_clear(t, w.slots, s));
-        HIPCHK(launch_record(W, queued(K_RECORD), c1, t, cnt, w.grid[K_RECORD], s));
+        HIPCHK(launch_record(W, queued(K_RECORD), c1, t, cnt, w.grid[K_RECORD].n, s));
         HIPCHK(launch_decide(W, queued(K_DECIDE), sa, c1, t, jbits, round > 0, cnt,
-                             w.grid[K_DECIDE], s));
+                             w.grid[K_DECIDE].n, s));
     }
     // pass-1-only: the candidates (their union over rounds) are the junctions
     const uint64_t *jb = pass1_only ? (rounds > 1 ? c1u : c1) : jbits;

@@ -97,17 +97,18 @@ def algorithmic_bytes(c, bases, k, W, h, blocked, filter_bytes, table_bytes, non
     return out, probes, {"filter_in_hbm": f_hbm, "table_in_hbm": t_hbm}
 
 
-def binned_fill_bytes(st, c, bases, filter_bytes, fill_ms):
+def binned_fill_bytes(st, c, bases, filter_bytes, fill_ms, items_per_edge=1):
     """Streaming bytes of the binned fill (one round): the input read once;
-    every item (4 bytes, one per edge position) written to its bucket and
-    read back, and, where a filter above 128 MiB has several regions to a
-    bucket, written to its region and read once more; the filter zeroed, then
+    every item (4 bytes; one per edge position with the blocked filter, h with
+    the standard one) written to its bucket and read back, and, where a filter
+    has several regions to a bucket (blocked above 128 MiB, standard above
+    16 MiB), written to its region and read once more; the filter zeroed, then
     read and written by every chunk.  These replace the direct-probe bytes in
     the fill's roofline entry when the fill ran binned (the model follows the
     schedule)."""
     chunks = st["fill_chunks"]
-    levels = 1 if filter_bytes <= 128 << 20 else 2
-    nbytes = (bases / 4 + 8 * levels * c["edge_positions"] + filter_bytes * (2 * chunks + 1))
+    levels = 1 if filter_bytes <= (128 if items_per_edge == 1 else 16) << 20 else 2
+    nbytes = (bases / 4 + 8 * levels * items_per_edge * c["edge_positions"] + filter_bytes * (2 * chunks + 1))
     gbs = nbytes / (fill_ms * 1e-3) / 1e9
     return {"chunks": chunks, "streaming_bytes": nbytes, "achieved_gbs": gbs,
             "frac": gbs / HBM_PEAK_GBS}
@@ -302,7 +303,8 @@ def primate_leg(args, stream, genomes, bases, flags, steps, warmup, d_in=None, o
         # the fill or the record ran binned: its bytes are that schedule's
         # (streaming), the direct-probe figure is kept beside them
         if st["fill_chunks"]:
-            rec["binned_fill"] = binned_fill_bytes(st, c, bases, b // 8, km["fill"])
+            rec["binned_fill"] = binned_fill_bytes(st, c, bases, b // 8, km["fill"],
+                                                   1 if blocked else h)
             rec["binned_fill"]["direct_probe_bytes"] = alg["fill"]
             alg["fill"] = rec["binned_fill"]["streaming_bytes"]
         if st["record_passes"]:

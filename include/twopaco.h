@@ -304,18 +304,19 @@ typedef struct {
                               workgroup takes this many consecutive tiles
                               (2048 positions each) of its walk per visit,
                               1..64                                          */
-    uint32_t fill_binned;  /* blocked filter, fill: 0 = binned unless the
-                              filter pool is large for the positions (more
-                              than 24 bytes each and 128 MiB besides), else
-                              atomic; 1 = atomic (each edge's block loaded,
-                              then an atomicOr for bits still clear, in HBM);
-                              2 = binned: per chunk of positions, every
-                              edge's filter effect is written as a 4-byte
-                              item, the items partitioned by region of the
+    uint32_t fill_binned;  /* fill: 0 = binned unless the filter pool is large
+                              for the positions (more than 24 bytes each and
+                              128 MiB besides), else atomic; 1 = atomic (each
+                              edge's words loaded, then an atomicOr for bits
+                              still clear, in HBM); 2 = binned: per chunk of
+                              positions, every edge's filter effect is
+                              written as a 4-byte item (standard filter: one
+                              for each of its hash_count bits),
+                              the items partitioned by region of the
                               pool (64 or 128 KiB) in one or two streaming
                               passes, and each region's items ORed into the
                               region in LDS.  Same filter bits either way.
-                              Binned needs about 4.5 bytes per chunk position
+                              Binned needs about 4.5 bytes per item of a chunk
                               and pass of scratch, held in the exact table's
                               key buffer (the table is not live during the
                               fill), and a pool of at most 32 GiB; where the

@@ -127,6 +127,8 @@ template <class T> struct KT;
 template <> struct KT<uint64_t> {
     static constexpr int W = 1;
     __device__ static __forceinline__ uint64_t fold(uint64_t x) { return x; }
+    // A word that depends on all of x (internal tables; not the hash spec).
+    __device__ static __forceinline__ uint64_t mixed(uint64_t x) { return x ^ x >> 29; }
     __device__ static __forceinline__ uint64_t ones(uint32_t nbits) {
         return nbits >= 64 ? ~0ull : ((1ull << nbits) - 1);
     }
@@ -154,6 +156,9 @@ template <> struct KT<u128> {
     static constexpr int W = 2;
     __device__ static __forceinline__ uint64_t fold(u128 x) {
         return mix64((uint64_t)(x >> 64) ^ kS0) ^ (uint64_t)x;
+    }
+    __device__ static __forceinline__ uint64_t mixed(u128 x) {
+        return KT<uint64_t>::mixed((uint64_t)x + (uint64_t)(x >> 64) * 0xD6E8FEB86659FD93ull);
     }
     __device__ static __forceinline__ u128 ones(uint32_t nbits) {
         return nbits >= 128 ? ~(u128)0 : (((u128)1 << nbits) - 1);
@@ -185,6 +190,10 @@ template <> struct KT<u256> {
         f = mix64(f ^ kS0) ^ x.w2;
         f = mix64(f ^ kS0) ^ x.w1;
         return mix64(f ^ kS0) ^ x.w0;
+    }
+    __device__ static __forceinline__ uint64_t mixed(const u256 &x) {
+        return KT<uint64_t>::mixed(x.w0 + x.w1 * 0xD6E8FEB86659FD93ull +
+                                   (x.w2 + x.w3 * 0xD6E8FEB86659FD93ull) * 0xA0761D6478BD642Full);
     }
     __device__ static __forceinline__ u256 ones(uint32_t nbits) {
         auto part = [&](uint32_t i) -> uint64_t {

@@ -53,7 +53,7 @@ constexpr uint32_t TABLE_BLOCK_LOG2 = 13;          // any-size tables: blocks of
 static_assert(TABLE_TAIL % TABLE_ALIGN == 0, "set regions stay aligned");
 constexpr uint32_t CLASS_Q_LOG2 = 10;              // k-mer class subranges (rounds)
 constexpr uint32_t CLASS_Q = 1u << CLASS_Q_LOG2;
-// Binned fill (blocked filter): the filter pool in regions of up to 2^14
+// Binned fill: the filter pool in regions of up to 2^14
 // blocks (one workgroup's LDS), buckets of one or more regions.
 constexpr uint32_t BIN_REGION_LOG2 = 13;           // 8192 blocks = 64 KiB (2^14 at most)
 constexpr uint32_t BIN_BUCKETS = 1024;
@@ -208,7 +208,7 @@ struct OutArgs {
 // -------------------------------------------------------------- launchers
 // Resident workgroups per CU of a tile kernel (sizes its persistent grid):
 // pass1_occupancy for K_FILL / K_QUERY, pass2_occupancy for K_RECORD / K_DECIDE.
-hipError_t pass1_occupancy(KernelId which, int W, bool blocked, bool fill_dedup,
+hipError_t pass1_occupancy(KernelId which, int W, bool blocked, bool fill_dedup, uint64_t n_tiles,
                            int *blocks_per_cu);
 hipError_t pass2_occupancy(KernelId which, int W, int *blocks_per_cu);
 // Several regions set to a repeated 32-bit value in one launch (addresses and
@@ -237,9 +237,9 @@ void clear_sentinels(ClearList &c, int W, const SentArgs &sa, uint32_t *tab_owne
 hipError_t launch_sentinels(int W, const SeqArgs &a, const SentArgs &sa, uint32_t *tab_owner,
                             hipStream_t s);
 // a1: insert every normalised (k+1)-mer into its set's Bloom filter.
-// Binned fill of a blocked filter pool (the same bits as launch_fill; the
-// pool zeroed beforehand): per chunk of tiles, every edge's filter effect
-// becomes a 4-byte item of its bucket, the items of a bucket of several
+// Binned fill of a filter pool (the same bits as launch_fill; the pool zeroed
+// beforehand): per chunk of tiles, every edge's filter effect (standard filter:
+// every bit of it) becomes a 4-byte item of its bucket, the items of a bucket of several
 // regions are split by region, and one workgroup per region ORs its items in
 // LDS and writes the region back.
 struct BinArgs {
@@ -262,13 +262,16 @@ struct BinArgs {
 // longer runs: 654 Mbp over 128 filters of 1.4 GB in all, k_bin_items 4.15 ms
 // against 4.67 with 1024 buckets).  Pools beyond 16 GiB need up to 2048
 // buckets, for an item's block bits.
-inline void bin_shape(uint64_t n_blocks, uint32_t *bucket_log2, uint32_t *region_log2) {
+// The standard filter's items (h to an edge) go to 256 buckets at most:
+// their claims (an atomic per bin and batch) would take as long as the sort.
+inline void bin_shape(uint64_t n_blocks, bool blocked, uint32_t *bucket_log2,
+                      uint32_t *region_log2) {
     const uint64_t last = n_blocks ? n_blocks - 1 : 0;
     *region_log2 = BIN_REGION_LOG2;
-    if ((last >> BIN_REGION_LOG2) >= BIN_BUCKETS && (last >> (BIN_REGION_LOG2 + 1)) < BIN_BUCKETS)
+    if (blocked && (last >> BIN_REGION_LOG2) >= BIN_BUCKETS && (last >> (BIN_REGION_LOG2 + 1)) < BIN_BUCKETS)
         ++*region_log2;
     *bucket_log2 = *region_log2;
-    if ((last >> *region_log2) >= BIN_BUCKETS)
+    if ((last >> *region_log2) >= (blocked ? BIN_BUCKETS : BIN_BUCKETS / 4))
         while ((last >> *bucket_log2) >= BIN_BUCKETS / 4 && *bucket_log2 < BIN_LOCAL_LOG2)
             ++*bucket_log2;
 }

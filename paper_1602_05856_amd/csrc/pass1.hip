@@ -358,7 +358,12 @@ hipError_t launch_fill(int W, const SeqArgs &a, const BloomArgs &pool, Counters 
 // edge count (a hash spreads them evenly), so nothing is counted beforehand:
 // an item is written and read once per level, 8 or 16 bytes an edge in all.
 
-constexpr uint32_t BIN_EFFECT_BITS = 11;
+//
+// The standard filter's items are one per edge and hash function: the block
+// within the bucket and 6 bits for the bit in it.
+
+constexpr uint32_t BIN_EFFECT_BITS = 11, BIN_BIT_BITS = 6;
+template <bool STD> constexpr uint32_t effect_bits() { return STD ? BIN_BIT_BITS : BIN_EFFECT_BITS; }
 
 __device__ __forceinline__ uint32_t bin_effect(const MiddleKey &m, uint32_t j, uint32_t h) {
     return (m.d >> 1) << 6 | ((m.a + j * h * m.d) & 63u);
@@ -377,11 +382,15 @@ __device__ __forceinline__ uint64_t stride_template(uint32_t d, uint32_t h) {
     return m;
 }
 
-// An item without room: straight into the pool (as insert_blocked does).
-__device__ __forceinline__ uint32_t bin_direct(const BloomArgs &pool, uint64_t block,
+// An item without room, of the bucket that starts at block block0: straight
+// into the pool (load first, as insert_blocked does).
+template <bool STD>
+__device__ __forceinline__ uint32_t bin_direct(const BloomArgs &pool, uint64_t block0,
                                                uint32_t item) {
-    unsigned long long *p = (unsigned long long *)pool.words + block;
-    const uint64_t m = rotl64(stride_template((item >> 5 & 62u) | 1u, pool.h), item & 63u);
+    unsigned long long *p =
+        (unsigned long long *)pool.words + block0 + (item >> effect_bits<STD>());
+    const uint64_t m = STD ? 1ull << (item & 63u)
+                           : rotl64(stride_template((item >> 5 & 62u) | 1u, pool.h), item & 63u);
     const unsigned long long cur =
         __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((cur & m) == m)
@@ -468,6 +477,39 @@ struct BinTile {
     Span sp;
 };
 
+// Stage a batch: entries [e0, e0 + TILES) of the first-pass order, those from
+// end on empty.  Whole workgroup; ends synchronised.
+template <uint32_t TILES, uint32_t NT>
+__device__ __forceinline__ void bin_stage(const SeqArgs &a, uint64_t e0, uint64_t end, Stage *sg,
+                                          BinTile *tl) {
+    const uint32_t nt = (uint32_t)min((uint64_t)TILES, end - e0);
+    if (threadIdx.x < TILES) {
+        BinTile x{};
+        x.sp = Span{0, -1};  // (no string: no edge)
+        if (threadIdx.x < nt) {
+            const uint64_t tile = a.tile_order[e0 + threadIdx.x];
+            const TileInfo ti = a.tiles[tile];
+            const SetDesc &d = a.sets[ti.set];
+            x.t0 = tile * TILE;
+            x.lo = ti.str_lo;
+            x.hi = ti.str_hi;
+            x.block0 = (uint32_t)(d.bloom_off >> 1);
+            x.mask = d.bloom_mask;
+            x.cls_lo = d.cls_lo;
+            x.cls_hi = d.cls_hi;
+            if (x.lo + 1 == x.hi)
+                x.sp = span_of(a.strings, x.lo, x.t0);
+        }
+        tl[threadIdx.x] = x;
+    }
+    for (uint32_t i = threadIdx.x; i < nt * STAGE_WORDS; i += NT) {
+        const uint32_t j = i / STAGE_WORDS, u = i % STAGE_WORDS;
+        const int64_t gw = (int64_t)((uint64_t)a.tile_order[e0 + j] * TILE_WORDS) - 1 + u;
+        stage_word(sg[j], u, (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull);
+    }
+    __syncthreads();
+}
+
 // The edges are those k_fill inserts: every (k+1)-mer within a string, of the
 // round's class when there are rounds.
 template <class T, uint32_t NB, uint32_t NT, uint32_t PER, bool CLASSES>
@@ -486,33 +528,7 @@ void k_bin_items(SeqArgs a, BloomArgs pool, BinArgs b,
     for (uint32_t i = threadIdx.x; i < NB; i += NT)
         sh.cnt[i] = 0;
     for (uint64_t batch = blockIdx.x; batch < batches; batch += gridDim.x) {
-        const uint64_t e0 = b.t_lo + batch * TILES;
-        const uint32_t nt = (uint32_t)min((uint64_t)TILES, b.t_hi - e0);
-        if (threadIdx.x < TILES) {
-            BinTile x{};
-            x.sp = Span{0, -1};  // (no string: no edge)
-            if (threadIdx.x < nt) {
-                const uint64_t tile = a.tile_order[e0 + threadIdx.x];
-                const TileInfo ti = a.tiles[tile];
-                const SetDesc &d = a.sets[ti.set];
-                x.t0 = tile * TILE;
-                x.lo = ti.str_lo;
-                x.hi = ti.str_hi;
-                x.block0 = (uint32_t)(d.bloom_off >> 1);
-                x.mask = d.bloom_mask;
-                x.cls_lo = d.cls_lo;
-                x.cls_hi = d.cls_hi;
-                if (x.lo + 1 == x.hi)
-                    x.sp = span_of(a.strings, x.lo, x.t0);
-            }
-            tl[threadIdx.x] = x;
-        }
-        for (uint32_t i = threadIdx.x; i < nt * STAGE_WORDS; i += NT) {
-            const uint32_t j = i / STAGE_WORDS, u = i % STAGE_WORDS;
-            const int64_t gw = (int64_t)((uint64_t)a.tile_order[e0 + j] * TILE_WORDS) - 1 + u;
-            stage_word(sg[j], u, (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull);
-        }
-        __syncthreads();
+        bin_stage<TILES, NT>(a, b.t_lo + batch * TILES, b.t_hi, sg, tl);
         uint32_t item[PER], at[PER];
 #pragma unroll
         for (uint32_t q = 0; q < PER; ++q) {
@@ -535,10 +551,70 @@ void k_bin_items(SeqArgs a, BloomArgs pool, BinArgs b,
         }
         bin_append<NB, NT, PER>(sh, item, at, b.n_buckets, lpb, b.cursor, b.off, b.items_a,
                             [&](uint32_t bucket, uint32_t it) {
-                                atomics += bin_direct(
-                                    pool, ((uint64_t)bucket << b.bucket_log2) +
-                                              (it >> BIN_EFFECT_BITS), it);
+                                atomics += bin_direct<false>(
+                                    pool, (uint64_t)bucket << b.bucket_log2, it);
                             });
+    }
+    if (atomics)
+        atomicAdd(&cnt->fill_atomics, (unsigned long long)atomics);
+}
+
+// The standard filter's items: PER positions per thread, hashed once, then
+// their bits appended one hash function at a time (h batches).
+template <class T, uint32_t NB, uint32_t NT, uint32_t PER, bool CLASSES>
+__global__ __launch_bounds__(NT) void k_bin_items_std(SeqArgs a, BloomArgs pool, BinArgs b,
+                                                      Counters *cnt) {
+    constexpr uint32_t TILES = NT * PER / TILE;
+    __shared__ BinSort<NB, NT, PER> sh;
+    __shared__ Stage sg[TILES];
+    __shared__ BinTile tl[TILES];
+    const uint32_t L = a.k + 1, k = a.k;
+    const bool single = a.single != 0;
+    const uint32_t lpb = bin_lanes(b.n_buckets, NT * PER);
+    const uint64_t batches = (b.t_hi - b.t_lo + TILES - 1) / TILES;
+    uint32_t atomics = 0;
+    for (uint32_t i = threadIdx.x; i < NB; i += NT)
+        sh.cnt[i] = 0;
+    for (uint64_t batch = blockIdx.x; batch < batches; batch += gridDim.x) {
+        bin_stage<TILES, NT>(a, b.t_lo + batch * TILES, b.t_hi, sg, tl);
+        uint64_t h1[PER], h2[PER];
+        uint32_t in = 0;  // positions with an edge
+#pragma unroll
+        for (uint32_t q = 0; q < PER; ++q) {
+            h1[q] = h2[q] = 0;
+            const uint32_t j = q * NT / TILE, p = (q * NT & (TILE - 1)) + threadIdx.x;
+            const BinTile &x = tl[j];
+            const Span sp = x.hi - x.lo > 1 ? span_at(a.strings, x.lo, x.hi, x.t0, p) : x.sp;
+            if ((int32_t)p < sp.gs || (int32_t)(p + L) > sp.ge)
+                continue;
+            if (CLASSES && !edge_in_class<T>(sg[j], p + 32, k, single, x.cls_lo, x.cls_hi))
+                continue;
+            const BloomHash bh = bloom_hash(norm(kmer_at<T>(sg[j], p + 32, L), single));
+            h1[q] = bh.h1;
+            h2[q] = bh.h2;
+            in |= 1u << q;
+        }
+        for (uint32_t t = 0; t < pool.h; ++t) {
+            uint32_t item[PER], at[PER];
+#pragma unroll
+            for (uint32_t q = 0; q < PER; ++q) {
+                item[q] = 0;
+                at[q] = ~0u;
+                if (!((in >> q) & 1u))
+                    continue;
+                const BinTile &x = tl[q * NT / TILE];
+                const uint64_t bit = ((uint64_t)x.block0 << 6) + (h1[q] & x.mask);
+                h1[q] += h2[q];
+                const uint32_t bucket = (uint32_t)(bit >> (6 + b.bucket_log2));
+                item[q] = (uint32_t)bit & ((64u << b.bucket_log2) - 1);
+                at[q] = bucket << 14 | atomicAdd(&sh.cnt[bucket], 1u);
+            }
+            bin_append<NB, NT, PER>(sh, item, at, b.n_buckets, lpb, b.cursor, b.off, b.items_a,
+                                    [&](uint32_t bucket, uint32_t it) {
+                                        atomics += bin_direct<true>(
+                                            pool, (uint64_t)bucket << b.bucket_log2, it);
+                                    });
+        }
     }
     if (atomics)
         atomicAdd(&cnt->fill_atomics, (unsigned long long)atomics);
@@ -546,11 +622,12 @@ void k_bin_items(SeqArgs a, BloomArgs pool, BinArgs b,
 
 // One batch of one bucket's items (blockIdx.y: the bucket, blockIdx.x: the
 // batch) appended to the bucket's regions.
+template <bool STD>
 __global__ __launch_bounds__(BIN_BLOCK) void k_bin_split(BloomArgs pool, BinArgs b,
                                                          Counters *cnt) {
     constexpr uint32_t NT = BIN_BLOCK, PER = BIN_PER, NB = 1u << (BIN_LOCAL_LOG2 - BIN_REGION_LOG2);
     __shared__ BinSort<NB, NT, PER> sh;
-    const uint32_t bucket = blockIdx.y, shift = b.region_log2 + BIN_EFFECT_BITS;
+    const uint32_t bucket = blockIdx.y, shift = b.region_log2 + effect_bits<STD>();
     const uint32_t sub = 1u << (b.bucket_log2 - b.region_log2), r0 = bucket * sub;
     const uint64_t o = b.off[bucket];
     const uint64_t n = min((uint64_t)b.cursor[bucket], b.off[bucket + 1] - o);
@@ -574,8 +651,7 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_bin_split(BloomArgs pool, BinArgs
     const uint32_t nb = min(sub, b.n_regions - r0);
     bin_append<NB, NT, PER>(sh, item, at, nb, bin_lanes(nb, NT * PER), b.cursor + b.n_buckets + r0, b.roff + r0,
                         b.items_b, [&](uint32_t, uint32_t it) {
-                            atomics += bin_direct(pool, ((uint64_t)bucket << b.bucket_log2) +
-                                                            (it >> BIN_EFFECT_BITS), it);
+                            atomics += bin_direct<STD>(pool, (uint64_t)bucket << b.bucket_log2, it);
                         });
     if (atomics)
         atomicAdd(&cnt->fill_atomics, (unsigned long long)atomics);
@@ -584,7 +660,7 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_bin_split(BloomArgs pool, BinArgs
 // One workgroup per region: the region's blocks in LDS, its items ORed in, the
 // blocks written back.  Counts the items that set a bit not yet set and, in
 // the last chunk of a one-set pool, the filter's bits.
-template <uint32_t REGION_LOG2>
+template <uint32_t REGION_LOG2, bool STD>
 __global__ __launch_bounds__(BIN_BLOCK) void k_bin_apply(BloomArgs pool, BinArgs b, Counters *cnt) {
     constexpr uint32_t NT = BIN_BLOCK, U = 4;
     __shared__ __align__(16) unsigned long long reg[1u << REGION_LOG2];
@@ -616,7 +692,13 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_bin_apply(BloomArgs pool, BinArgs
             v[q] = i + (uint64_t)q * NT < n ? items[i + (uint64_t)q * NT] : 0u;
 #pragma unroll
         for (uint32_t q = 0; q < U; ++q) {
-            if (i + (uint64_t)q * NT < n) {
+            if (i + (uint64_t)q * NT >= n)
+                continue;
+            if (STD) {
+                const uint32_t m = 1u << (v[q] & 31u);
+                const uint32_t old = atomicOr((uint32_t *)reg + (v[q] >> 5 & (2 * lmask + 1)), m);
+                fresh += (old & m) == 0;
+            } else {
                 const uint64_t m = rotl64(tmpl[v[q] >> 6 & 31u], v[q] & 63u);
                 const unsigned long long old =
                     atomicOr(&reg[(v[q] >> BIN_EFFECT_BITS) & lmask], (unsigned long long)m);
@@ -655,10 +737,16 @@ template <class T, uint32_t NB, bool CLASSES>
 static void bin_items_t(const SeqArgs &a, const BloomArgs &pool, const BinArgs &b, Counters *cnt,
                         hipStream_t s) {
     constexpr uint32_t NT = BIN_BLOCK, PER = ItemsPer<T, CLASSES>::N, TILES = NT * PER / TILE;
-    const uint64_t batches = (b.t_hi - b.t_lo + TILES - 1) / TILES;
-    const uint32_t grid = (uint32_t)min(batches, 2ull * b.n_cu);
-    hipLaunchKernelGGL((k_bin_items<T, NB, NT, PER, CLASSES>), dim3(grid), dim3(NT), 0, s, a, pool,
-                       b, cnt);
+    constexpr uint32_t SPER = 16, STILES = NT * SPER / TILE;
+    const uint64_t n = b.t_hi - b.t_lo;
+    if (pool.blocked)
+        hipLaunchKernelGGL((k_bin_items<T, NB, NT, PER, CLASSES>),
+                           dim3((uint32_t)min((n + TILES - 1) / TILES, 2ull * b.n_cu)), dim3(NT),
+                           0, s, a, pool, b, cnt);
+    else
+        hipLaunchKernelGGL((k_bin_items_std<T, NB, NT, SPER, CLASSES>),
+                           dim3((uint32_t)min((n + STILES - 1) / STILES, (uint64_t)b.n_cu)),
+                           dim3(NT), 0, s, a, pool, b, cnt);
 }
 
 template <class T>
@@ -689,14 +777,15 @@ hipError_t launch_fill_binned(int W, const SeqArgs &a, const BloomArgs &pool, Co
                 return e;
             bin_items_w<T>(a, pool, b, cnt, s);
             if (split)
-                hipLaunchKernelGGL(k_bin_split, dim3(b.slices, b.n_buckets), dim3(BIN_BLOCK), 0, s,
-                                   pool, b, cnt);
-            if (b.region_log2 == BIN_REGION_LOG2)
-                hipLaunchKernelGGL(k_bin_apply<BIN_REGION_LOG2>, dim3(b.n_regions),
-                                   dim3(BIN_BLOCK), 0, s, pool, b, cnt);
-            else
-                hipLaunchKernelGGL(k_bin_apply<BIN_REGION_LOG2 + 1>, dim3(b.n_regions),
-                                   dim3(BIN_BLOCK), 0, s, pool, b, cnt);
+                hipLaunchKernelGGL(pool.blocked ? k_bin_split<false> : k_bin_split<true>,
+                                   dim3(b.slices, b.n_buckets), dim3(BIN_BLOCK), 0, s, pool, b,
+                                   cnt);
+            auto *apply = b.region_log2 == BIN_REGION_LOG2
+                              ? (pool.blocked ? k_bin_apply<BIN_REGION_LOG2, false>
+                                              : k_bin_apply<BIN_REGION_LOG2, true>)
+                              : (pool.blocked ? k_bin_apply<BIN_REGION_LOG2 + 1, false>
+                                              : k_bin_apply<BIN_REGION_LOG2 + 1, true>);
+            hipLaunchKernelGGL(apply, dim3(b.n_regions), dim3(BIN_BLOCK), 0, s, pool, b, cnt);
             e = hipGetLastError();
             if (e != hipSuccess)
                 return e;
@@ -834,16 +923,18 @@ struct QueryShared {
     unsigned long long block_probes, cand_lds;
 };
 
+template <uint32_t NT>
 __device__ __forceinline__ void query_begin(QueryShared &qs, const uint32_t *prefilter,
                                             uint32_t pf_log2) {
-    for (uint32_t i = threadIdx.x; i < prefilter_words(pf_log2); i += BLOCK)
+    for (uint32_t i = threadIdx.x; i < prefilter_words(pf_log2); i += NT)
         qs.pf[i] = prefilter[i];
-    for (uint32_t i = threadIdx.x; i < HLL_M; i += BLOCK)
+    for (uint32_t i = threadIdx.x; i < HLL_M; i += NT)
         qs.hll[i] = 0;
     if (threadIdx.x == 0)
         qs.block_probes = 0;
 }
 
+template <uint32_t NT>
 __device__ __forceinline__ void query_end(const SeqArgs &a, QueryShared &qs, SetSum &cand,
                                           uint32_t my_probes, Counters *cnt, uint32_t *hll_out) {
     setsum_flush(cand, &qs.cand_lds, &a.set_cnt[0].candidates, SETCNT_STRIDE);
@@ -853,7 +944,7 @@ __device__ __forceinline__ void query_end(const SeqArgs &a, QueryShared &qs, Set
     if (threadIdx.x == 0 && qs.block_probes)
         atomicAdd(&cnt->query_probes, qs.block_probes);
     if (a.sketch) {
-        for (uint32_t i = threadIdx.x; i < HLL_M; i += BLOCK) {
+        for (uint32_t i = threadIdx.x; i < HLL_M; i += NT) {
             const uint32_t v = qs.hll[i];
             if (v && v > __hip_atomic_load(&hll_out[i], __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT))
@@ -897,7 +988,7 @@ void k_query_blocked(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint6
     const T *sent = (const T *)sa.table;
     const uint32_t lane = threadIdx.x & 63;
     const T mid_ones = KT<T>::ones(2 * (k - 1));
-    query_begin(qs, sa.prefilter + prefilter_words(sa.pf_log2), sa.pf_log2);
+    query_begin<BLOCK>(qs, sa.prefilter + prefilter_words(sa.pf_log2), sa.pf_log2);
     for (uint32_t i = threadIdx.x; i < 32 * 16; i += BLOCK)
         pm[i] = pair_mask(0, 2 * (i >> 4) + 1, i & 15, pool.h);
     uint32_t my_probes = 0;
@@ -1009,75 +1100,160 @@ void k_query_blocked(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint6
             }
         }
     }
-    query_end(a, qs, cand, my_probes, cnt, hll_out);
+    query_end<BLOCK>(a, qs, cand, my_probes, cnt, hll_out);
 }
 
-// Standard layout: a lane tests its position's six neighbours level by level.
-template <class T, bool CLASSES>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(KT<T>::W == 1 ? 5 : 1)))
+// Standard layout: a lane tests its position's six neighbours level by level,
+// some 10 random words a position, which is what bounds it (57-63 G words/s).
+// A position inside its string is marked or not by its k-mer and the bases
+// before and after it alone, and homologous tiles repeat most of those windows:
+// so a workgroup takes up to 32 consecutive tiles of the first-pass order
+// together and keeps a table of the windows it has decided (LDS: the position
+// of one, its verdict, some bits of its hash); a window found there, compared
+// base by base with the staged sequence, is not probed again.  62 x 5 Mbp,
+// b = 2^30, k = 25: 3.30 G words and 41.1 ms without the table, 1.99 G and 31.4
+// with 8 tiles (512 threads, 8192 windows), 1.62 G and 25.7 with 16 (1024,
+// 16384), 1.50 G and 24.4 with 32.
+constexpr uint32_t QS_TILES = 32, QS_BLOCK = 1024, QS_SEEN = 16384;
+constexpr uint32_t QS_NONE = ~0u;
+
+// Inputs of fewer tiles than this take the plain form: a tile (or a part of
+// one) to a workgroup of 256 threads, no table.
+static bool query_seen(uint64_t n_tiles) { return n_tiles >= 2048; }
+
+struct QsTile {
+    uint64_t t0;
+    uint32_t lo, hi;
+    Span sp;
+};
+
+// The bases r - 1 .. r + k around the k-mer at r: all but the last in w (which
+// holds 2k + 2 bits), the last apart.
+template <class T>
+__device__ __forceinline__ T seen_window(const Stage &sg, uint32_t r, uint32_t k, uint32_t *after) {
+    const T d = down_from<T>(sg, r + k + 1);
+    *after = (uint32_t)d & 3u;
+    return up_from<T>(sg, r - 1) & KT<T>::ones(2 * k + 2);
+}
+
+template <class T, bool CLASSES, bool SEEN>
+__global__ __launch_bounds__(SEEN ? QS_BLOCK : BLOCK)
 void k_query_standard(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint64_t *c1u,
                       uint32_t round, Counters *cnt, uint32_t *hll_out) {
-    __shared__ Stage sg;
+    constexpr uint32_t NT = SEEN ? QS_BLOCK : BLOCK, TILES = SEEN ? QS_TILES : 1;
+    __shared__ Stage sg[TILES];
+    __shared__ QsTile tl[TILES];
+    __shared__ uint32_t tset[TILES];
+    __shared__ uint32_t seen[SEEN ? QS_SEEN : 1];  // hash bits << 17 | verdict << 16 | tile << 11 | position
     __shared__ QueryShared qs;
     SetSum cand = setsum_begin();
     const uint32_t k = a.k;
     const bool single = a.single != 0;
     const T *sent = (const T *)sa.table;
     const uint32_t lane = threadIdx.x & 63;
-    query_begin(qs, sa.prefilter, sa.pf_log2);
+    query_begin<NT>(qs, sa.prefilter, sa.pf_log2);
     uint32_t my_probes = 0;
-    RunCursor rc = run_cursor(a, a.chunk);
-    for (uint64_t tile; run_next(a, rc, &tile);) {
-        const uint64_t t0 = tile * TILE;
-        const TileInfo ti = a.tiles[tile];
-        const uint32_t lo = ti.str_lo, hi = ti.str_hi;
-        if (lo == hi) {
-            query_no_string(tile, c1, c1u, round);
-            continue;
+    // as many tiles as leave every workgroup a few batches
+    const uint64_t per = a.n_tiles / (4ull * gridDim.x);
+    const uint32_t most = per < 1 ? 1u : per > TILES ? TILES : (uint32_t)per;
+    const Part part = tile_part(a);
+    RunCursor rc = run_cursor(a, max(a.chunk, most));
+    uint64_t tile;
+    while (run_next(a, rc, &tile)) {
+        const uint64_t j0 = rc.c + rc.gi - 1;  // the walk's entry of the first tile
+        uint32_t m = 1;
+        while (m < most && rc.gi + m - 1 < rc.G && j0 + m < rc.end)
+            ++m;
+        __syncthreads();  // the last batch is done with
+        if (threadIdx.x < m) {
+            const uint64_t x = rc.ordered ? (uint64_t)a.tile_order[j0 + threadIdx.x]
+                                          : j0 + threadIdx.x;
+            const TileInfo ti = a.tiles[x];
+            QsTile t{x * TILE, ti.str_lo, ti.str_hi, Span{0, -1}};
+            if (t.lo + 1 == t.hi)
+                t.sp = span_of(a.strings, t.lo, t.t0);
+            tl[threadIdx.x] = t;
+            tset[threadIdx.x] = ti.set;
         }
+        if (SEEN)
+            for (uint32_t i = threadIdx.x; i < QS_SEEN; i += NT)
+                seen[i] = QS_NONE;
         __syncthreads();
-        stage_tile(a, tile, sg);
+        const uint32_t set = tset[0];  // tiles of one set (a verdict is of its filter)
+        uint32_t n = 1;
+        while (n < m && tset[n] == set)
+            ++n;
+        rc.gi += n - 1;
+        for (uint32_t i = threadIdx.x; i < n * STAGE_WORDS; i += NT) {
+            const uint32_t j = i / STAGE_WORDS, u = i % STAGE_WORDS;
+            const int64_t gw = (int64_t)(tl[j].t0 / 32) - 1 + u;
+            stage_word(sg[j], u, (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull);
+        }
+        const TileSet ts = tile_set_of(a, pool, set);
+        setsum_switch(cand, set, &qs.cand_lds, &a.set_cnt[0].candidates, SETCNT_STRIDE);
         __syncthreads();
-        const TileSet ts = tile_set_of(a, pool, ti.set);
-        setsum_switch(cand, ts.set, &qs.cand_lds, &a.set_cnt[0].candidates, SETCNT_STRIDE);
-        const bool one = lo + 1 == hi;
-        Span sp = one ? span_of(a.strings, lo, t0) : Span{0, -1};
-        const Part part = tile_part(a);
-        for (uint32_t it = part.lo; it < part.hi; ++it) {
-            const uint32_t q = it * BLOCK + threadIdx.x;
-            if (!one && (int32_t)q >= sp.ge)
-                sp = span_at(a.strings, lo, hi, t0, q);
-            bool mark = false;
-            uint64_t hash = 0;
-            if ((int32_t)q >= sp.gs && (int32_t)(q + k) <= sp.ge) {
-                uint32_t pa, sb;
-                const Strands<T> st = kmer_between<T>(sg, q + 32, k, &pa, &sb);
-                const T canon = norm(st, single);
-                if (!CLASSES || in_class(class_subrange(canon), ts.cls_lo, ts.cls_hi)) {
-                    hash = slot_hash(canon);
-                    mark = (int32_t)q == sp.gs || (int32_t)(q + k) == sp.ge ||
-                           (ts.sent_log2 &&
-                            prefilter_hit(qs.pf, prefilter_bit(hash, sa.pf_log2)) &&
-                            in_sentinels(canon, sent + ts.sent_off, ts.sent_log2)) ||
-                           any_present_standard(ts.f, st, k, pa, sb, single, my_probes);
+        for (uint32_t j = 0; j < n; ++j) {
+            const QsTile &t = tl[j];
+            for (uint32_t q = part.lo * BLOCK + threadIdx.x; q < part.hi * BLOCK; q += NT) {
+                const Span sp = t.lo + 1 == t.hi   ? t.sp
+                                : t.lo == t.hi     ? Span{0, -1}
+                                                   : span_at(a.strings, t.lo, t.hi, t.t0, q);
+                bool mark = false, sketch = false;
+                uint64_t hash = 0;
+                if ((int32_t)q >= sp.gs && (int32_t)(q + k) <= sp.ge) {
+                    const bool end = (int32_t)q == sp.gs || (int32_t)(q + k) == sp.ge;
+                    uint32_t at = 0, tag = 0, found = QS_NONE;
+                    if (SEEN && !end) {
+                        uint32_t sb;
+                        const T w = seen_window<T>(sg[j], q + 32, k, &sb);
+                        const uint64_t x = (KT<T>::mixed(w) + sb) * 0x9E3779B97F4A7C15ull;
+                        at = (uint32_t)(x >> 50);
+                        tag = (uint32_t)(x >> 34) & 0x7FFFu;
+                        static_assert(QS_SEEN == 1u << 14, "table index bits");
+                        const uint32_t e = seen[at];
+                        if (e >> 17 == tag && e != QS_NONE) {
+                            uint32_t sb2;
+                            if (seen_window<T>(sg[e >> 11 & 31u], (e & (TILE - 1)) + 32, k, &sb2) == w &&
+                                sb2 == sb)
+                                found = e;
+                        }
+                    }
+                    if (found != QS_NONE) {
+                        mark = (found >> 16) & 1u;
+                    } else {
+                        uint32_t pa, sb;
+                        const Strands<T> st = kmer_between<T>(sg[j], q + 32, k, &pa, &sb);
+                        const T canon = norm(st, single);
+                        if (!CLASSES || in_class(class_subrange(canon), ts.cls_lo, ts.cls_hi)) {
+                            hash = slot_hash(canon);
+                            mark = end ||
+                                   (ts.sent_log2 &&
+                                    prefilter_hit(qs.pf, prefilter_bit(hash, sa.pf_log2)) &&
+                                    in_sentinels(canon, sent + ts.sent_off, ts.sent_log2)) ||
+                                   any_present_standard(ts.f, st, k, pa, sb, single, my_probes);
+                        }
+                        if (SEEN && !end)
+                            seen[at] = tag << 17 | (mark ? 1u : 0u) << 16 | j << 11 | q;
+                        sketch = mark && a.sketch;  // (a found window's k-mer is in it already)
+                    }
                 }
-            }
-            const uint64_t word = ballot64(mark);
-            if (lane == 0) {
-                const uint64_t at = (t0 + q) >> 6;
-                c1[at] = word;
-                if (c1u)
-                    c1u[at] = round ? c1u[at] | word : word;
-                cand.v += (unsigned long long)__popcll(word);
-            }
-            if (a.sketch && mark) {
-                const uint64_t rest = hash << HLL_LOG2;
-                const uint32_t rank = rest ? (uint32_t)__clzll(rest) + 1 : 64 - HLL_LOG2 + 1;
-                atomicMax(&qs.hll[(uint32_t)(hash >> (64 - HLL_LOG2))], rank);
+                const uint64_t word = ballot64(mark);
+                if (lane == 0) {
+                    const uint64_t i = (t.t0 + q) >> 6;
+                    c1[i] = word;
+                    if (c1u)
+                        c1u[i] = round ? c1u[i] | word : word;
+                    cand.v += (unsigned long long)__popcll(word);
+                }
+                if (sketch) {
+                    const uint64_t rest = hash << HLL_LOG2;
+                    const uint32_t rank = rest ? (uint32_t)__clzll(rest) + 1 : 64 - HLL_LOG2 + 1;
+                    atomicMax(&qs.hll[(uint32_t)(hash >> (64 - HLL_LOG2))], rank);
+                }
             }
         }
     }
-    query_end(a, qs, cand, my_probes, cnt, hll_out);
+    query_end<NT>(a, qs, cand, my_probes, cnt, hll_out);
 }
 
 hipError_t launch_query(int W, const SeqArgs &a, const BloomArgs &pool, const SentArgs &sa,
@@ -1087,9 +1263,14 @@ hipError_t launch_query(int W, const SeqArgs &a, const BloomArgs &pool, const Se
         return hipSuccess;
     return by_width(W, [&](auto tag) {
         using T = decltype(tag);
+        const bool seen = !pool.blocked && query_seen(a.n_tiles);
         auto *fn = pool.blocked ? (a.classes ? k_query_blocked<T, true> : k_query_blocked<T, false>)
-                                : (a.classes ? k_query_standard<T, true> : k_query_standard<T, false>);
-        hipLaunchKernelGGL(fn, dim3(grid), dim3(BLOCK), 0, s, a, pool, sa, c1, c1u, round, cnt, hll);
+                   : seen ? (a.classes ? k_query_standard<T, true, true>
+                                       : k_query_standard<T, false, true>)
+                          : (a.classes ? k_query_standard<T, true, false>
+                                       : k_query_standard<T, false, false>);
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(seen ? QS_BLOCK : BLOCK), 0, s, a, pool, sa, c1, c1u,
+                           round, cnt, hll);
         return hipGetLastError();
     });
 }
@@ -1223,17 +1404,21 @@ hipError_t launch_set_round(SetDesc *sets, const uint32_t *bounds, uint32_t n_se
     return hipGetLastError();
 }
 
-hipError_t pass1_occupancy(KernelId which, int W, bool blocked, bool fill_dedup, int *blocks) {
+hipError_t pass1_occupancy(KernelId which, int W, bool blocked, bool fill_dedup, uint64_t n_tiles,
+                           int *blocks) {
     return by_width(W, [&](auto tag) {
         using T = decltype(tag);
+        const bool seen = !blocked && query_seen(n_tiles);
         const void *fn =
             which == K_FILL
                 ? (blocked ? (const void *)k_fill<T, true> : (const void *)k_fill<T, false>)
-                : (blocked ? (const void *)k_query_blocked<T, false>
-                           : (const void *)k_query_standard<T, false>);
+            : blocked ? (const void *)k_query_blocked<T, false>
+            : seen    ? (const void *)k_query_standard<T, false, true>
+                      : (const void *)k_query_standard<T, false, false>;
         const size_t dyn = which == K_FILL && blocked && fill_dedup
                                ? FILL_DD * sizeof(unsigned long long) : 0;
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, fn, BLOCK, dyn);
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            blocks, fn, which == K_QUERY && seen ? QS_BLOCK : BLOCK, dyn);
     });
 }
 

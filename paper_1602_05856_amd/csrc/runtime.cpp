@@ -741,7 +741,7 @@ int tp::plan_grids(tp_plan *p, int dev) {
         int occ = 0;
         if (kid <= K_QUERY)
             HIPCHK(pass1_occupancy((KernelId)kid, p->W, (p->flags & TP_FLAG_BLOCKED_FILTER) != 0,
-                                   p->cfg.fill_dedup != 0, &occ));
+                                   p->cfg.fill_dedup != 0, p->n_tiles, &occ));
         else
             HIPCHK(pass2_occupancy((KernelId)kid, p->W, &occ));
         occ = std::max(1, occ);
@@ -839,12 +839,9 @@ constexpr int RUN_SPLIT = 1;  // run_impl: redo the run with *split rounds
 constexpr uint64_t BIN_POOL_PER_POSITION = 24;
 constexpr uint64_t BIN_POOL_FREE = 128ull << 20;
 
-// Whether this plan's fill can run binned: blocked filter, a pool within the
-// bucket limit.
+// Whether this plan's fill can run binned: a pool within the bucket limit.
 bool tp::fill_binnable(const tp_plan *p) {
-    if (!(p->flags & TP_FLAG_BLOCKED_FILTER) || !p->n_tiles)
-        return false;
-    return p->bloom_words / 2 <= (uint64_t)BIN_MAX_BUCKETS << BIN_LOCAL_LOG2;
+    return p->n_tiles && p->bloom_words / 2 <= (uint64_t)BIN_MAX_BUCKETS << BIN_LOCAL_LOG2;
 }
 
 // Whether this plan's fill runs binned (tp_config.fill_binned) with the given
@@ -871,7 +868,9 @@ static void bin_room(const tp_plan *p, uint64_t tiles, uint32_t rounds, uint64_t
             continue;
         // a round inserts the edges next to its class's k-mers
         const double share = rounds > 1 ? std::min(1.0, 2.5 / rounds) : 1.0;
-        const double per = share * (double)std::min<uint64_t>(si.positions, tiles * TILE) / nb;
+        const uint32_t items = (p->flags & TP_FLAG_BLOCKED_FILTER) ? 1 : p->h;  // per edge
+        const double per = share * items *
+                           (double)std::min<uint64_t>(si.positions, tiles * TILE) / (double)nb;
         for (uint64_t i = f >> bin_log2; i <= (f + nb - 1) >> bin_log2; ++i) {
             const uint64_t lo = std::max(f, i << bin_log2);
             const uint64_t hi = std::min(f + nb, (i + 1) << bin_log2);
@@ -895,16 +894,19 @@ static int bin_setup(tp_plan *p, BinArgs *b, uint32_t *chunk_tiles, uint32_t rou
     *b = BinArgs{};
     *use = false;
     b->n_blocks = p->bloom_words / 2;
-    bin_shape(b->n_blocks, &b->bucket_log2, &b->region_log2);
+    const bool blocked = (p->flags & TP_FLAG_BLOCKED_FILTER) != 0;
+    bin_shape(b->n_blocks, blocked, &b->bucket_log2, &b->region_log2);
     const bool split = b->bucket_log2 != b->region_log2;
     // default: 2^31 positions, or as many as the key buffer already holds
     // (a table from an earlier run; about 4.5 bytes per position and level)
     // up to 2^33; fewer chunks reread the filter fewer times
+    // (the standard filter has h items to a position)
     uint64_t want = p->cfg.bin_chunk_tiles;
+    const uint64_t items = blocked ? 1 : p->h;
     if (!want)
         want = std::min<uint64_t>(4ull * BIN_CHUNK_TILES_MAX,
-                                  std::max<uint64_t>(BIN_CHUNK_TILES_MAX,
-                                                     p->d_keys.cap / ((split ? 9 : 5) * TILE)));
+                                  std::max<uint64_t>(BIN_CHUNK_TILES_MAX / items,
+                                                     p->d_keys.cap / ((split ? 9 : 5) * items * TILE)));
     const uint64_t tiles = std::min<uint64_t>(p->n_tiles, want);
     *chunk_tiles = (uint32_t)tiles;
     const bool fresh = p->bin_tiles != tiles || p->bin_rounds != rounds;

@@ -57,3 +57,16 @@ def test_bins_over_several_filters():
     sets = [(to_genomes([g]), 1 << b) for g, b in zip(genomes(31), (10, 22, 25, 16, 30))]
     for rounds in (1, 3):
         fills(lambda tp: tp.Plan.batch(sets, 31, 4, BLOCKED), rounds)
+
+
+@pytest.mark.parametrize("k", [25, 40, 100])
+@pytest.mark.parametrize("log2b, h", [(5, 3), (19, 1), (26, 16), (28, 5), (30, 4)])
+def test_bins_of_a_standard_filter(k, log2b, h):
+    gs = to_genomes(genomes(k))
+    fills(lambda tp: tp.Plan(gs, k, 1 << log2b, h, SINGLE if log2b == 26 else 0))
+
+
+def test_bins_over_several_standard_filters():
+    sets = [(to_genomes([g]), 1 << b) for g, b in zip(genomes(31), (5, 22, 25, 16, 30))]
+    for rounds in (1, 3):
+        fills(lambda tp: tp.Plan.batch(sets, 31, 4, 0), rounds)

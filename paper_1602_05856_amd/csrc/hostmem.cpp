@@ -57,6 +57,12 @@ void *host_alloc(size_t bytes) {
     return std::malloc(bytes);
 }
 
+bool host_pinned(const void *b) {
+    Pool &P = pool();
+    std::lock_guard<std::mutex> lk(P.m);
+    return P.pinned.count((void *)b) != 0;
+}
+
 void host_free(void *b) {
     if (!b)
         return;

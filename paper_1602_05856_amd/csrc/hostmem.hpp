@@ -9,5 +9,8 @@ namespace tp {
 // memory otherwise).  Free with host_free only.
 void *host_alloc(size_t bytes);
 void host_free(void *block);
+// Whether a block of host_alloc is page-locked (the device can then read and
+// write it in place).
+bool host_pinned(const void *block);
 
 }  // namespace tp

@@ -211,21 +211,35 @@ struct OutArgs {
 hipError_t pass1_occupancy(KernelId which, int W, bool blocked, bool fill_dedup, uint64_t n_tiles,
                            int *blocks_per_cu);
 hipError_t pass2_occupancy(KernelId which, int W, int *blocks_per_cu);
-// Several regions set to a repeated 32-bit value in one launch (addresses and
-// sizes multiples of 16 bytes).
+// Several regions set to a repeated 32-bit value, or copied from memory that
+// the device can read, in one launch (addresses multiples of 16 bytes; sizes
+// too, a copy's rounded up).
 struct ClearList {
     struct {
         void *p;
+        const void *src;  // null: set to v
         uint64_t n16;
         uint32_t v;
     } r[10];
     uint32_t n;
-    void add(void *p, uint64_t bytes, uint32_t v = 0) {
-        if (bytes)
-            r[n].p = p, r[n].n16 = bytes / 16, r[n++].v = v;
+    void add(void *p, uint64_t bytes, uint32_t v = 0) { put(p, nullptr, bytes / 16, v); }
+    void copy(void *p, const void *src, uint64_t bytes) { put(p, src, (bytes + 15) / 16, 0); }
+    void put(void *p, const void *src, uint64_t n16, uint32_t v) {
+        if (n16)
+            r[n].p = p, r[n].src = src, r[n].n16 = n16, r[n++].v = v;
     }
 };
 hipError_t launch_clear(const ClearList &c, hipStream_t s);
+
+// What the host reads at its waits, written to memory that it can read (or to
+// device memory for one copy) by one small kernel: counters, and of the
+// sketch's registers (null: none) what its estimate needs.
+struct SketchSum {
+    double z;        // sum of 2^-register
+    uint64_t zeros;  // empty registers
+};
+hipError_t launch_publish(const ClearList &copies, const uint32_t *hll, SketchSum *sketch,
+                          hipStream_t s);
 hipError_t launch_zero(void *p, uint64_t bytes, hipStream_t s);
 hipError_t launch_fill_u64(uint64_t *p, uint64_t n, uint64_t v, hipStream_t s);
 
@@ -253,6 +267,7 @@ struct BinArgs {
     uint32_t n_buckets, bucket_log2, region_log2, n_regions;
     uint32_t slices;            // batches a bucket has room for (the split's grid)
     uint32_t n_cu;
+    uint32_t cleared;           // the cursors are clear for the first chunk
     SetCounters *popcount;      // last chunk of a one-set pool: its filter popcount, else null
 };
 // Blocks of a bucket and of a region for a pool: one region per bucket where

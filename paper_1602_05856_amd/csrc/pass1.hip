@@ -56,10 +56,48 @@ __global__ void k_fill_u64(uint64_t *p, uint64_t n, uint64_t v) {
 __global__ __launch_bounds__(BLOCK) void k_clear(ClearList c) {
     for (uint32_t q = 0; q < c.n; ++q) {
         uint4 *p = (uint4 *)c.r[q].p;
+        const uint4 *src = (const uint4 *)c.r[q].src;
         const uint32_t v = c.r[q].v;
         for (uint64_t i = blockIdx.x * (uint64_t)BLOCK + threadIdx.x; i < c.r[q].n16;
              i += (uint64_t)gridDim.x * BLOCK)
-            p[i] = make_uint4(v, v, v, v);
+            p[i] = src ? src[i] : make_uint4(v, v, v, v);
+    }
+}
+
+// One workgroup: the copies, and the sums of the sketch (a tree of exact
+// powers of two, so the same in every run).
+__global__ __launch_bounds__(BLOCK) void k_publish(ClearList c, const uint32_t *hll,
+                                                   SketchSum *sketch) {
+    __shared__ double wz[BLOCK / 64];
+    __shared__ uint32_t w0[BLOCK / 64];
+    for (uint32_t q = 0; q < c.n; ++q)
+        for (uint64_t i = threadIdx.x; i < c.r[q].n16; i += BLOCK)
+            ((uint4 *)c.r[q].p)[i] = ((const uint4 *)c.r[q].src)[i];
+    if (!hll)
+        return;
+    double z = 0;
+    uint32_t zeros = 0;
+    for (uint32_t i = threadIdx.x; i < HLL_M; i += BLOCK) {
+        const uint32_t r = hll[i];
+        z += __longlong_as_double((long long)(1023 - r) << 52);  // 2^-r (r <= 64)
+        zeros += r == 0;
+    }
+    for (int d = 32; d; d >>= 1) {
+        z += __shfl_xor(z, d, 64);
+        zeros += __shfl_xor(zeros, d, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        wz[threadIdx.x >> 6] = z;
+        w0[threadIdx.x >> 6] = zeros;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (uint32_t q = 1; q < BLOCK / 64; ++q) {
+            z += wz[q];
+            zeros += w0[q];
+        }
+        sketch->z = z;
+        sketch->zeros = zeros;
     }
 }
 
@@ -74,6 +112,12 @@ hipError_t launch_clear(const ClearList &c, hipStream_t s) {
         most = std::max(most, c.r[q].n16);
     if (most)
         hipLaunchKernelGGL(k_clear, dim3(grid_for(most)), dim3(BLOCK), 0, s, c);
+    return hipGetLastError();
+}
+
+hipError_t launch_publish(const ClearList &copies, const uint32_t *hll, SketchSum *sketch,
+                          hipStream_t s) {
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(BLOCK), 0, s, copies, hll, sketch);
     return hipGetLastError();
 }
 
@@ -772,7 +816,9 @@ hipError_t launch_fill_binned(int W, const SeqArgs &a, const BloomArgs &pool, Co
             b.t_lo = t0;
             b.t_hi = min(a.n_tiles, t0 + tiles_per_chunk);
             b.popcount = b.t_hi == a.n_tiles ? popcount : nullptr;
-            hipError_t e = launch_zero(b.cursor, n_cursor * sizeof(unsigned long long), s);
+            hipError_t e = t0 || !b.cleared
+                               ? launch_zero(b.cursor, n_cursor * sizeof(unsigned long long), s)
+                               : hipSuccess;
             if (e != hipSuccess)
                 return e;
             bin_items_w<T>(a, pool, b, cnt, s);

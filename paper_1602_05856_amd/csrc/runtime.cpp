@@ -32,17 +32,11 @@ namespace {
 
 // HyperLogLog estimate (Flajolet et al. 2007) with the linear-counting
 // correction for small cardinalities.
-double hll_estimate(const uint32_t *reg) {
+double hll_estimate(const SketchSum &s) {
     const double m = HLL_M;
-    double z = 0;
-    uint32_t zeros = 0;
-    for (uint32_t i = 0; i < HLL_M; ++i) {
-        z += std::ldexp(1.0, -(int)reg[i]);
-        zeros += reg[i] == 0;
-    }
-    double e = 0.7213 / (1 + 1.079 / m) * m * m / z;
-    if (e <= 2.5 * m && zeros)
-        e = m * std::log(m / zeros);
+    double e = 0.7213 / (1 + 1.079 / m) * m * m / s.z;
+    if (e <= 2.5 * m && s.zeros)
+        e = m * std::log(m / (double)s.zeros);
     return e;
 }
 
@@ -356,7 +350,7 @@ extern "C" uint64_t tp_bloom_bits_for(const tp_genome *genomes, uint32_t n_genom
 
 uint64_t tp::plan_device_bytes(const tp_plan *p) {
     uint64_t n = 0;
-    const_cast<tp_plan *>(p)->for_each_buf([&](DevBuf &b) { n += b.cap; });
+    const_cast<tp_plan *>(p)->for_each_buf([&](DevBuf &b) { n += b.borrowed ? 0 : b.cap; });
     return n;
 }
 
@@ -884,6 +878,11 @@ static void bin_room(const tp_plan *p, uint64_t tiles, uint32_t rounds, uint64_t
         off[i + 1] = off[i] + align_up((uint64_t)(1.02 * mean[i] + 6 * std::sqrt(var[i])) + 64, 32);
 }
 
+// Items claimed per bucket and, with several regions to one, per region.
+static uint64_t bin_cursors(const BinArgs &b) {
+    return b.n_buckets + (b.bucket_log2 != b.region_log2 ? b.n_regions : 0u);
+}
+
 // The binned fill's scratch: items in the exact table's key buffer (dead
 // during the first pass), cursors in d_bin, the bins' room in d_bin_room
 // (laid out again when the layout, the chunk size or the rounds change).
@@ -947,6 +946,7 @@ static int bin_setup(tp_plan *p, BinArgs *b, uint32_t *chunk_tiles, uint32_t rou
     b->n_buckets = (uint32_t)(n_off - 1);
     b->n_regions = split ? (uint32_t)(n_roff - 1) : b->n_buckets;
     b->n_cu = std::max<uint32_t>(1, p->n_cu);
+    b->cleared = 1;  // (by the run's own clear)
     uint64_t most = 0;
     for (uint64_t i = 0; i + 1 < n_off; ++i)
         most = std::max(most, p->bin_off[i + 1] - p->bin_off[i]);
@@ -1044,6 +1044,156 @@ static int rbin_setup(tp_plan *p, uint64_t candidates, uint64_t n_blocks, uint64
     return TP_OK;
 }
 
+// The plan's host block: what a run reads at its waits (written there by a
+// kernel, or copied where the block is not page-locked) and what it sends to
+// the device between them.  Each part is written anew only after the wait that
+// ended its last use.
+struct Mail {
+    uint64_t sets, set_cnt, cnt, sketch, rb_short, joff, tables, bytes;  // offsets, size
+};
+constexpr uint64_t MAIL_TABLES = 1ull << 20;  // layout tables up to this size go through it
+
+static Mail mail_layout(const tp_plan *p) {
+    Mail m{};
+    uint64_t at = 0;
+    auto take = [&](uint64_t bytes) {
+        const uint64_t o = at;
+        at += align_up(std::max<uint64_t>(bytes, 1), 64);
+        return o;
+    };
+    m.sets = take(p->sets.size() * sizeof(SetDesc));
+    m.set_cnt = take(p->sets.size() * sizeof(SetCounters));
+    m.cnt = take(sizeof(Counters));
+    m.sketch = take(sizeof(SketchSum));
+    m.rb_short = take(16);
+    m.joff = take((p->n_bases.size() + 1) * 8);
+    m.tables = at;
+    m.bytes = at + MAIL_TABLES;
+    return m;
+}
+
+// Carve the arena for the plan's layout and send the layout tables (on the
+// run's own stream: a copy on the null stream would also wait for the work of
+// every other blocking stream of the device, another server worker's job,
+// say).  One allocation and one copy for small plans: an allocation, its
+// release and a copy from pageable memory take some 10 us each, and there were
+// 22, 22 and 6 of them, and 6 copies back a run (twopaco_build of 2.1 Mbp:
+// 617 -> 463 us; tp_run of 0.4 Mbp: 389 -> 279).
+static int static_setup(tp_plan *p, const Mail &m, hipStream_t s) {
+    const uint64_t ns = p->strings.size(), nsets = p->sets.size(), ngen = p->n_bases.size();
+    const uint64_t W = (uint64_t)p->W, nblocks = scan_blocks(p->bitmap_words);
+    struct Piece {
+        DevBuf *b;
+        uint64_t bytes;
+        const void *src;  // layout table
+    };
+    p->bloom_starts.assign(nsets + 1, 0);
+    for (uint64_t i = 0; i < nsets; ++i)
+        p->bloom_starts[i] = p->sets[i].bloom_off;
+    p->bloom_starts[nsets] = p->bloom_words;
+    const Piece pieces[] = {
+        {&p->d_tiles, p->n_tiles * 4, p->tile_order.data()},
+        {&p->d_tile_info, p->n_tiles * sizeof(TileInfo), p->tile_info.data()},
+        {&p->d_strings, ns * sizeof(DString), p->strings.data()},
+        {&p->d_gbase, ngen * 8, p->gbase.data()},
+        {&p->d_bloom_starts, (nsets + 1) * 8, p->bloom_starts.data()},
+        {&p->d_sets, nsets * sizeof(SetDesc), nullptr},
+        {&p->d_cnt, sizeof(Counters), nullptr},
+        {&p->d_set_cnt, nsets * sizeof(SetCounters), nullptr},
+        {&p->d_hll, HLL_M * 4, nullptr},
+        {&p->d_queue, 4 * NXCD * sizeof(unsigned int), nullptr},
+        {&p->d_pf, 2ull * 4 * prefilter_words(p->pf_log2), nullptr},
+        {&p->d_sent, p->sent_tab_slots * 8 * W, nullptr},
+        {&p->d_sent_owner, p->sent_tab_slots * 4, nullptr},
+        {&p->d_joff, (ngen + 1) * 8, nullptr},
+        {&p->d_blockcnt, nblocks * 4, nullptr},
+        {&p->d_blockoff, (nblocks + 1) * 8, nullptr},
+        {&p->d_c1, p->bitmap_words * 8, nullptr},
+        {&p->d_j, p->flags & TP_FLAG_PASS1_ONLY ? 0 : p->bitmap_words * 8, nullptr},
+        {&p->d_bloom, p->bloom_words * 4, nullptr},
+    };
+    uint64_t total = 0, tables = 0;
+    for (const Piece &x : pieces) {
+        total += align_up(std::max<uint64_t>(x.bytes, 16), 256);
+        if (x.src)
+            tables = total;
+    }
+    if (!p->static_uploaded) {
+        HIPCHK(ensure_spare(p->d_arena, total,
+                            {&p->d_pos, &p->d_vertex, &p->d_strand, &p->d_edges, &p->d_rbin}));
+        uint8_t *at = p->d_arena.as<uint8_t>();
+        for (const Piece &x : pieces) {
+            const uint64_t n = align_up(std::max<uint64_t>(x.bytes, 16), 256);
+            x.b->borrow(at, n);
+            at += n;
+        }
+        if (p->mail_cap < m.bytes) {
+            host_free(p->mail);
+            p->mail = (uint8_t *)host_alloc(m.bytes);
+            p->mail_cap = p->mail ? m.bytes : 0;
+            if (!p->mail)
+                return fail(TP_ENOMEM, "host allocation failed");
+            p->mail_mapped = host_pinned(p->mail);
+        }
+        if (!p->mail_mapped)
+            HIPCHK(p->d_mail.ensure(m.bytes));
+        for (auto &e : p->ev)
+            if (!e)
+                HIPCHK(hipEventCreate(&e));
+    }
+    if (tables <= MAIL_TABLES) {
+        p->mail_busy = true;
+        uint8_t *to = p->mail + m.tables;
+        for (const Piece &x : pieces)
+            if (x.src && x.bytes)
+                std::memcpy(to + ((uint8_t *)x.b->p - p->d_arena.as<uint8_t>()), x.src, x.bytes);
+        HIPCHK(hipMemcpyAsync(p->d_arena.p, to, tables, hipMemcpyHostToDevice, s));
+    } else {
+        for (const Piece &x : pieces)
+            if (x.src && x.bytes && (!p->static_uploaded || x.b == &p->d_tiles))
+                HIPCHK(hipMemcpyAsync(x.b->p, x.src, x.bytes, hipMemcpyHostToDevice, s));
+    }
+    if (!p->static_uploaded)
+        p->bin_tiles = 0;  // the filters' places may have changed: the bins' room too
+    p->static_uploaded = p->order_uploaded = true;
+    return TP_OK;
+}
+
+// Publish to the plan's host block and wait: counters (always), the sketch's
+// sums, the binned record's shortage flag, the junction offsets.
+static int publish_and_wait(tp_plan *p, const Mail &m, bool sketch, const void *rb_short,
+                            const void *joff, hipStream_t s) {
+    uint8_t *to = p->mail_mapped ? p->mail : p->d_mail.as<uint8_t>();
+    ClearList c{};
+    c.copy(to + m.set_cnt, p->d_set_cnt.p, p->sets.size() * sizeof(SetCounters));
+    c.copy(to + m.cnt, p->d_cnt.p, sizeof(Counters));
+    if (rb_short)
+        c.copy(to + m.rb_short, rb_short, 16);
+    if (joff)
+        c.copy(to + m.joff, joff, (p->n_bases.size() + 1) * 8);
+    HIPCHK(launch_publish(c, sketch ? p->d_hll.as<uint32_t>() : nullptr,
+                          (SketchSum *)(to + m.sketch), s));
+    if (!p->mail_mapped)  // everything after the set descriptors
+        HIPCHK(hipMemcpyAsync(p->mail + m.set_cnt, to + m.set_cnt, m.tables - m.set_cnt,
+                              hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    p->mail_busy = false;
+    return TP_OK;
+}
+
+// Set descriptors to the device: through the host block, as a copy of the
+// given list where kernels can read it.
+static hipError_t send_sets(tp_plan *p, const Mail &m, const std::vector<SetDesc> &d, ClearList *c,
+                            hipStream_t s) {
+    p->mail_busy = true;
+    std::memcpy(p->mail + m.sets, d.data(), d.size() * sizeof(SetDesc));
+    if (!p->mail_mapped)
+        return hipMemcpyAsync(p->d_sets.p, p->mail + m.sets, d.size() * sizeof(SetDesc),
+                              hipMemcpyHostToDevice, s);
+    c->copy(p->d_sets.p, p->mail + m.sets, d.size() * sizeof(SetDesc));
+    return hipSuccess;
+}
+
 static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t rounds,
                     uint32_t *split);
 
@@ -1077,52 +1227,15 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
     const int W = p->W;
 
     // ---- buffers that depend only on the plan
-    HIPCHK(p->d_tiles.ensure(p->n_tiles * 4));
-    HIPCHK(p->d_tile_info.ensure(p->n_tiles * sizeof(TileInfo)));
-    HIPCHK(p->d_sets.ensure(nsets * sizeof(SetDesc)));
-    HIPCHK(p->d_bloom_starts.ensure((nsets + 1) * 8ull));
-    HIPCHK(p->d_strings.ensure(ns * sizeof(DString)));
-    HIPCHK(p->d_gbase.ensure(ngen * 8));
-    HIPCHK(p->d_sent.ensure(p->sent_tab_slots * 8 * W));
-    HIPCHK(p->d_sent_owner.ensure(p->sent_tab_slots * 4));
-    HIPCHK(p->d_pf.ensure(2ull * 4 * prefilter_words(p->pf_log2)));
-    HIPCHK(p->d_bloom.ensure(p->bloom_words * 4));
-    HIPCHK(p->d_c1.ensure(p->bitmap_words * 8));
-    HIPCHK(p->d_cnt.ensure(sizeof(Counters)));
-    HIPCHK(p->d_set_cnt.ensure(nsets * sizeof(SetCounters)));
-    HIPCHK(p->d_hll.ensure(HLL_M * 4));
-    HIPCHK(p->d_queue.ensure(4 * NXCD * sizeof(unsigned int)));
-    // Layout tables go up on the run's own stream: a copy on the null
-    // stream would also wait for the work of every other blocking stream of
-    // the device (another server worker's job, say).  Their host copies are
-    // the plan's and stay put until the next layout.
-    if (!p->static_uploaded) {
-        if (p->n_tiles)
-            HIPCHK(hipMemcpyAsync(p->d_tile_info.p, p->tile_info.data(),
-                                  p->n_tiles * sizeof(TileInfo), hipMemcpyHostToDevice, s));
-        if (ns)
-            HIPCHK(hipMemcpyAsync(p->d_strings.p, p->strings.data(), ns * sizeof(DString),
-                                  hipMemcpyHostToDevice, s));
-        if (ngen)
-            HIPCHK(hipMemcpyAsync(p->d_gbase.p, p->gbase.data(), ngen * 8,
-                                  hipMemcpyHostToDevice, s));
-        p->bloom_starts.assign(nsets + 1, 0);
-        for (uint32_t i = 0; i < nsets; ++i)
-            p->bloom_starts[i] = p->sets[i].bloom_off;
-        p->bloom_starts[nsets] = p->bloom_words;
-        HIPCHK(hipMemcpyAsync(p->d_bloom_starts.p, p->bloom_starts.data(),
-                              p->bloom_starts.size() * 8, hipMemcpyHostToDevice, s));
-        for (auto &e : p->ev)
-            if (!e)
-                HIPCHK(hipEventCreate(&e));
-        p->static_uploaded = true;
-        p->bin_tiles = 0;  // the filters' places may have changed: the bins' room too
+    const Mail mail = mail_layout(p);
+    if (p->mail_busy) {  // a run that failed before its wait
+        HIPCHK(hipDeviceSynchronize());
+        p->mail_busy = false;
     }
-    if (!p->order_uploaded) {
-        if (p->n_tiles)
-            HIPCHK(hipMemcpyAsync(p->d_tiles.p, p->tile_order.data(), p->n_tiles * 4,
-                                  hipMemcpyHostToDevice, s));
-        p->order_uploaded = true;
+    if (!p->static_uploaded || !p->order_uploaded) {
+        const int rcs = static_setup(p, mail, s);
+        if (rcs)
+            return rcs;
     }
     if (!p->grid[0].n) {
         const int rcg = plan_grids(p, dev);
@@ -1179,10 +1292,9 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
         clear_sentinels(c, W, sa, p->d_sent_owner.as<uint32_t>(), sent_slots);
     };
     HIPCHK(hipEventRecord(p->ev[0], s));
-    HIPCHK(hipMemcpyAsync(p->d_sets.p, desc.data(), nsets * sizeof(SetDesc),
-                          hipMemcpyHostToDevice, s));
     if (rounds > 1) {
         ClearList c{};
+        HIPCHK(send_sets(p, mail, desc, &c, s));
         clear_a0(c);
         HIPCHK(launch_clear(c, s));
         int rc0 = enqueue_a0(s);
@@ -1204,7 +1316,6 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
     uint64_t slots = 0;
     uint32_t attempts = 0;
     double est = 0;
-    std::vector<uint32_t> hll(HLL_M);
     for (uint32_t round = 0; round < rounds; ++round) {
         // ---- a1-a2: first pass (of this round's class)
         if (rounds > 1) {
@@ -1212,17 +1323,19 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
                 desc[i].cls_lo = p->bounds[(size_t)i * (rounds + 1) + round];
                 desc[i].cls_hi = p->bounds[(size_t)i * (rounds + 1) + round + 1];
             }
-            HIPCHK(hipMemcpyAsync(p->d_sets.p, desc.data(), nsets * sizeof(SetDesc),
-                                  hipMemcpyHostToDevice, s));
         }
+        ClearList up{};
+        HIPCHK(send_sets(p, mail, desc, &up, s));
         // prologue (graph-replayable): sentinels on a single round, zeroing
         auto enqueue_p1 = [&](hipStream_t q) -> int {
-            ClearList c{};
+            ClearList c = up;
             if (rounds == 1)
                 clear_a0(c);
             c.add(scnt, nsets * sizeof(SetCounters));
             c.add(p->d_hll.p, HLL_M * 4);
             c.add(p->d_bloom.p, p->bloom_words * 4);
+            if (binned)
+                c.add(bin.cursor, align_up(8ull * bin_cursors(bin), 16));
             if (qbase)  // the fill's and the query's tile queues
                 c.add(qbase, 2 * NXCD * sizeof(unsigned int));
             HIPCHK(launch_clear(c, q));
@@ -1231,7 +1344,7 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
         {
             KeyBuilder kb;
             kb(W)(a)(sa)(cnt)(scnt)(p->d_hll.p)(p->d_bloom.p)(p->bloom_words)(nsets)(
-                p->pf_log2)(p->d_sent_owner.p)(sent_slots)(binned)(qbase);
+                p->pf_log2)(p->d_sent_owner.p)(sent_slots)(binned)(qbase)(bin.cursor)(p->mail)(up.n);
             const int rc1 = run_segment(p, graphs, 0, kb.v, s, enqueue_p1);
             if (rc1)
                 return rc1;
@@ -1251,11 +1364,13 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             HIPCHK(launch_popcount(pool.words, p->bloom_words, p->d_bloom_starts.as<uint64_t>(),
                                    nsets, scnt, s));
         HIPCHK(hipEventRecord(p->ev[3], s));
-        HIPCHK(hipMemcpyAsync(hs.data(), scnt, nsets * sizeof(SetCounters),
-                              hipMemcpyDeviceToHost, s));
-        if (a.sketch)
-            HIPCHK(hipMemcpyAsync(hll.data(), p->d_hll.p, HLL_M * 4, hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
+        {
+            const int rcp = publish_and_wait(p, mail, a.sketch != 0, nullptr, nullptr, s);
+            if (rcp)
+                return rcp;
+        }
+        std::memcpy(hs.data(), p->mail + mail.set_cnt, nsets * sizeof(SetCounters));
+        std::memcpy(&hc, p->mail + mail.cnt, sizeof(Counters));
         float t1 = 0, t2 = 0;
         if (round == 0)
             HIPCHK(hipEventElapsedTime(&ms_sent, p->ev[0], p->ev[1]));
@@ -1277,9 +1392,8 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             continue;
         }
         // ---- a3-a4: second pass over this round's candidates
-        HIPCHK(p->d_j.ensure(p->bitmap_words * 8));
         if (a.sketch)
-            est = hll_estimate(hll.data());
+            est = hll_estimate(*(const SketchSum *)(p->mail + mail.sketch));
         const bool packed = table_packed(p);
         {
             // keys <= candidate positions; one set: the sketch's estimate
@@ -1351,8 +1465,8 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             t.lomask = 0;
             t.pow2 = p->table_pow2 ? 1u : 0u;
             t.pad = 0;
-            HIPCHK(hipMemcpyAsync(p->d_sets.p, d2.data(), nsets * sizeof(SetDesc),
-                                  hipMemcpyHostToDevice, s));
+            ClearList up2{};
+            HIPCHK(send_sets(p, mail, d2, &up2, s));
             // binned record: one set, packed slots, home blocks of at most
             // 2^TABLE_BLOCK_LOG2 slots (the binned kernels take set 0's shape)
             RecBinArgs rb{};
@@ -1371,7 +1485,7 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             // prologue (graph-replayable): counters and the table cleared (the
             // binned record writes every block itself: only the spare tail)
             auto enqueue_p2 = [&](hipStream_t q) -> int {
-                ClearList c{};
+                ClearList c = up2;
                 c.add(&cnt->fill_atomics + PASS2_OFFSET, PASS2_FIELDS * sizeof(unsigned long long));
                 c.add(scnt, nsets * sizeof(SetCounters));
                 if (rbin)
@@ -1385,7 +1499,7 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             };
             {
                 KeyBuilder kb;
-                kb(W)(t)(slots)(cnt)(scnt)(nsets)(qbase)(rbin);
+                kb(W)(t)(slots)(cnt)(scnt)(nsets)(qbase)(rbin)(p->mail)(up2.n);
                 const int rc2 = run_segment(p, graphs, 1, kb.v, s, enqueue_p2);
                 if (rc2)
                     return rc2;
@@ -1402,15 +1516,16 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
                                  p->d_c1.as<uint64_t>(), t, p->d_j.as<uint64_t>(),
                                  round > 0, cnt, p->grid[K_DECIDE].n, s));
             HIPCHK(hipEventRecord(p->ev[7], s));
-            std::vector<SetCounters> h2(nsets);
-            unsigned long long rb_short = 0;
-            HIPCHK(hipMemcpyAsync(&hc, cnt, sizeof(Counters), hipMemcpyDeviceToHost, s));
-            HIPCHK(hipMemcpyAsync(h2.data(), scnt, nsets * sizeof(SetCounters),
-                                  hipMemcpyDeviceToHost, s));
-            if (rbin)
-                HIPCHK(hipMemcpyAsync(&rb_short, rb.ctl + 1, sizeof(rb_short),
-                                      hipMemcpyDeviceToHost, s));
-            HIPCHK(hipStreamSynchronize(s));
+            {
+                const int rcp =
+                    publish_and_wait(p, mail, false, rbin ? rb.ctl : nullptr, nullptr, s);
+                if (rcp)
+                    return rcp;
+            }
+            const SetCounters *h2 = (const SetCounters *)(p->mail + mail.set_cnt);
+            std::memcpy(&hc, p->mail + mail.cnt, sizeof(Counters));
+            const unsigned long long rb_short =
+                rbin ? ((const unsigned long long *)(p->mail + mail.rb_short))[1] : 0;
             p->last_record_passes = rbin ? rb_passes : 0;
             if (rb_short) {
                 // a pass had more items than the scratch holds (the table is
@@ -1467,8 +1582,6 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
     hs = tot;
     for (uint32_t i = 0; i < nsets; ++i)
         p->sets[i].table_cap = max_cap[i];
-    HIPCHK(hipMemcpyAsync(&hc, cnt, sizeof(Counters), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
     hc.table_probes = total_cnt.table_probes;
 
     // ---- a5: ordered compaction and edges
@@ -1478,7 +1591,6 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
     if (nj < ns)
         return fail(TP_EDEVICE, "internal error: fewer junctions than strings");
     const uint64_t ne = nj - ns;
-    const uint64_t nblocks = scan_blocks(p->bitmap_words);
     // the exact tables are dead from here on: spare them if the outputs do
     // not fit beside them (the next run allocates them again)
     const std::initializer_list<DevBuf *> tables = {&p->d_keys};
@@ -1488,9 +1600,7 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
         p->d_rbin.release();
     {
         const int rcr = reserve(p, {{&p->d_pos, nj * 8}, {&p->d_vertex, nj * 8 * W},
-                                    {&p->d_strand, nj}, {&p->d_edges, ne * sizeof(tp_edge)},
-                                    {&p->d_joff, (ngen + 1) * 8}, {&p->d_blockcnt, nblocks * 4},
-                                    {&p->d_blockoff, (nblocks + 1) * 8}});
+                                    {&p->d_strand, nj}, {&p->d_edges, ne * sizeof(tp_edge)}});
         if (rcr)
             return rcr;
     }
@@ -1500,9 +1610,6 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
     HIPCHK(ensure_spare(p->d_edges, ne * sizeof(tp_edge), tables));
     // the table is still there unless it had to be freed for the outputs
     p->table_live = !pass1_only && p->d_keys.p != nullptr;
-    HIPCHK(p->d_joff.ensure((ngen + 1) * 8));
-    HIPCHK(p->d_blockcnt.ensure(nblocks * 4));
-    HIPCHK(p->d_blockoff.ensure((nblocks + 1) * 8));
     OutArgs o;
     o.pos = p->d_pos.as<uint64_t>();
     o.vertex = p->d_vertex.as<uint64_t>();
@@ -1525,9 +1632,13 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             return rc3;
     }
     HIPCHK(hipEventRecord(p->ev[8], s));
-    p->joff.assign(ngen + 1, 0);
-    HIPCHK(hipMemcpyAsync(p->joff.data(), o.joff, (ngen + 1) * 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    {
+        const int rcp = publish_and_wait(p, mail, false, nullptr, o.joff, s);
+        if (rcp)
+            return rcp;
+    }
+    p->joff.resize(ngen + 1);
+    std::memcpy(p->joff.data(), p->mail + mail.joff, (ngen + 1) * 8);
 
     tp_stats &st = p->stats;
     st = tp_stats{};

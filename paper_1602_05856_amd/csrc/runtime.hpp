@@ -10,6 +10,7 @@
 #include <string>
 #include <vector>
 
+#include "hostmem.hpp"
 #include "layout.hpp"
 #include "twopaco.h"
 
@@ -30,15 +31,23 @@ int fail(int code, const std::string &msg);
 struct DevBuf {
     void *p = nullptr;
     uint64_t cap = 0;
+    bool borrowed = false;  // a piece of another buffer (the plan's arena)
     DevBuf() = default;
     DevBuf(const DevBuf &) = delete;
     DevBuf &operator=(const DevBuf &) = delete;
     ~DevBuf() { release(); }
     void release() {
-        if (p)
+        if (p && !borrowed)
             (void)hipFree(p);
         p = nullptr;
         cap = 0;
+        borrowed = false;
+    }
+    void borrow(void *from, uint64_t bytes) {
+        release();
+        p = from;
+        cap = bytes;
+        borrowed = true;
     }
     // Grow to at least `bytes` (contents are not preserved).
     hipError_t ensure(uint64_t bytes) {
@@ -229,6 +238,15 @@ struct tp_plan {
     tp_config cfg{};                       // runtime knobs (autotuner)
 
     int device = -1;
+    // One device buffer holds everything whose size the layout fixes (the
+    // layout tables, filters, bitmaps, counters: the borrowed buffers below);
+    // static_uploaded: it is carved and the layout tables are in it.
+    tp::DevBuf d_arena;
+    tp::DevBuf d_mail;          // where the host block cannot be written in place
+    uint8_t *mail = nullptr;    // host block of what a run's waits read and its
+    uint64_t mail_cap = 0;      // small uploads hold (host_alloc)
+    bool mail_mapped = false;   // page-locked: kernels read and write it in place
+    bool mail_busy = false;     // the device may still be reading it
     bool static_uploaded = false;
     bool order_uploaded = false;           // tile_order on the device matches cfg
     tp::DevBuf d_tiles, d_tile_info, d_sets, d_bloom_starts, d_strings, d_gbase;
@@ -266,7 +284,7 @@ struct tp_plan {
     uint64_t *c1_out = nullptr; // candidate bitmap of the last run (union over rounds)
 
     template <class F> void for_each_buf(F f) {
-        for (tp::DevBuf *b : {&d_tiles, &d_tile_info, &d_sets, &d_bloom_starts, &d_strings,
+        for (tp::DevBuf *b : {&d_arena, &d_mail, &d_tiles, &d_tile_info, &d_sets, &d_bloom_starts, &d_strings,
                               &d_gbase, &d_sent, &d_sent_owner, &d_pf, &d_bloom,
                               &d_c1, &d_j,
                               &d_cnt, &d_set_cnt, &d_hll, &d_keys, &d_seq,
@@ -286,6 +304,7 @@ struct tp_plan {
 
     ~tp_plan() {
         drop_graphs();
+        tp::host_free(mail);
         if (cap)
             (void)hipStreamDestroy(cap);
         for (auto &e : ev)

@@ -56,6 +56,7 @@ constexpr uint32_t CLASS_Q = 1u << CLASS_Q_LOG2;
 // Binned fill: the filter pool in regions of up to 2^14
 // blocks (one workgroup's LDS), buckets of one or more regions.
 constexpr uint32_t BIN_REGION_LOG2 = 13;           // 8192 blocks = 64 KiB (2^14 at most)
+constexpr uint32_t BIN_MIN_REGION_LOG2 = 8;        // 2 KiB, of small pools
 constexpr uint32_t BIN_BUCKETS = 1024;
 constexpr uint32_t BIN_MAX_BUCKETS = 2048;         // pools up to 2^32 blocks (32 GiB)
 constexpr uint32_t BIN_LOCAL_LOG2 = 21;            // an item's block bits: buckets of up to 2^21 blocks
@@ -283,6 +284,10 @@ inline void bin_shape(uint64_t n_blocks, bool blocked, uint32_t *bucket_log2,
                       uint32_t *region_log2) {
     const uint64_t last = n_blocks ? n_blocks - 1 : 0;
     *region_log2 = BIN_REGION_LOG2;
+    // a small pool in smaller regions, up to one to a CU (2 MiB: 16.7 us in 32
+    // regions, 12.5 in 256)
+    while (*region_log2 > BIN_MIN_REGION_LOG2 && (last >> (*region_log2 - 1)) < BIN_BUCKETS / 4)
+        --*region_log2;
     if (blocked && (last >> BIN_REGION_LOG2) >= BIN_BUCKETS && (last >> (BIN_REGION_LOG2 + 1)) < BIN_BUCKETS)
         ++*region_log2;
     *bucket_log2 = *region_log2;

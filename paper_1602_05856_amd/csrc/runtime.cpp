@@ -742,13 +742,14 @@ int tp::plan_grids(tp_plan *p, int dev) {
         if (p->cfg.wg_per_cu[kid])
             occ = std::min<int>(occ, (int)p->cfg.wg_per_cu[kid]);
         const uint64_t g = std::max<uint64_t>((uint64_t)occ * std::max(1, ncu) / NXCD * NXCD, NXCD);
-        // fewer tiles than that: up to four workgroups a tile in the first
-        // pass (each ends with an atomic on one counter, which queue up at
-        // some 14 ns).  0.4 Mbp, 195 tiles, whole, in four and in eight parts:
-        // standard query 61, 39 and 37 us, blocked 27, 23 and 23.
+        // fewer tiles than that: two workgroups a tile in the first pass (each
+        // ends with atomics on shared counters, which queue up at some 14 ns,
+        // so more of them cost what they save).  0.4 Mbp, 195 tiles, whole, in
+        // two and in four parts: blocked query 27, 19 and 23 us, standard query
+        // 61, 36 and 35, atomic fill (dedup's runs of 8 tiles) 76, 27 and 33.
         const uint64_t tiles = std::max<uint64_t>(p->n_tiles, 1);
         uint32_t parts = 0;
-        while (kid <= K_QUERY && parts < 2 && (tiles << (parts + 1)) <= g)
+        while (kid <= K_QUERY && parts < 1 && (tiles << (parts + 1)) <= g)
             ++parts;
         p->grid[kid] = Grid{(uint32_t)std::min<uint64_t>(g, align_up(tiles << parts, NXCD)), parts};
     }

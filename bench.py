@@ -116,14 +116,14 @@ def binned_fill_bytes(st, c, bases, filter_bytes, fill_ms, items_per_edge=1):
 
 def binned_record_bytes(st, c, bases, table_bytes, record_ms):
     """Streaming bytes of the binned record (one round): every pass reads
-    the input and the candidate bitmap; every item (one per candidate) is
-    staged, read by the histogram and the bucket scatter, written by it,
-    read twice and written by the block split and read by the apply (8 bytes
-    each time); the table is written once, block by block.  These replace
-    the direct-probe bytes in the record's roofline entry when the record
-    ran binned."""
+    the input and the candidate bitmap; every item (one per candidate, 8
+    bytes) is written and read once, twice where a pass has more than 512
+    table blocks (buckets split by block); the table is written once, block
+    by block.  These replace the direct-probe bytes in the record's roofline
+    entry when the record ran binned."""
     passes = st["record_passes"]
-    nbytes = (passes * (bases / 4 + c["positions"] / 8) + 64 * c["candidates"] + table_bytes)
+    per_item = 32 if table_bytes > passes * 512 * 65536 else 16
+    nbytes = (passes * (bases / 4 + c["positions"] / 8) + per_item * c["candidates"] + table_bytes)
     gbs = nbytes / (record_ms * 1e-3) / 1e9
     return {"passes": passes, "streaming_bytes": nbytes, "achieved_gbs": gbs,
             "frac": gbs / HBM_PEAK_GBS}

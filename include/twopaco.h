@@ -299,7 +299,8 @@ typedef struct {
                               within it (rounds up by less than 8192 slots);
                               0 = a power of two unless rounding up would
                               leave more than 4 GiB of slots unused over the
-                              run's sets                                   */
+                              run's sets, in the any-size shape where
+                              record_binned asks for it                    */
     uint32_t chunk_tiles;  /* chunk size of the persistent tile walks: a
                               workgroup takes this many consecutive tiles
                               (2048 positions each) of its walk per visit,
@@ -347,9 +348,11 @@ typedef struct {
                               a static schedule (every grid-th chunk)      */
     uint32_t record_binned; /* exact record of a one-set plan with k <= 27
                               whose table is any-size (table_shape) or at
-                              most 8192 slots: 0 = binned when the table is
-                              at least 1 GiB and its scratch takes at most 2
-                              passes, else direct (each pass walks all
+                              most 8192 slots: 0 = binned when the table's
+                              slots for the expected keys take at least 128
+                              MiB (table_shape 0 then takes the any-size
+                              shape at the same capacity) and its scratch at
+                              most 4 passes, else direct (each pass walks all
                               candidates again); 1 = direct (random
                               atomics into the table); 2 = binned whenever
                               scratch is found.  Binned: a lookup never
@@ -357,17 +360,20 @@ typedef struct {
                               so per pass (a range of blocks) every
                               candidate of that range becomes an 8-byte
                               item, the items are partitioned by block in
-                              two streaming passes and each block is built
-                              in LDS and written out whole.  Same keys and
-                              edge bits, so the same junctions.  Scratch: 16
-                              bytes per item of a pass, in the last run's
+                              one or two streaming steps and each block is
+                              built in LDS and written out whole.  Same keys
+                              and edge bits, so the same junctions.  Scratch:
+                              about 10 bytes per item of a pass, 20 with two
+                              steps (more than 512 blocks), in the last run's
                               edge array (dead until the compaction) or in a
                               buffer of its own when the device has room
                               (1 GiB left free; kept by the plan until its
                               outputs must grow); else, and for plans of a
                               server, the record runs directly, as it does
-                              on caller memory (tp_run_ws, tp_run_noalloc).
-                              A pass holds at most 2^19 blocks (32 GiB of
+                              on caller memory (tp_run_ws, tp_run_noalloc),
+                              and where a few k-mers make up so many of the
+                              candidates that their items find no room.
+                              A pass holds at most 2^18 blocks (16 GiB of
                               table).  The passes taken are in
                               tp_stats.record_passes.                        */
     uint64_t table_budget; /* exact-table budget in bytes (0: none).  A

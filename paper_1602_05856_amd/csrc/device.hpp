@@ -667,91 +667,73 @@ __device__ __forceinline__ void lds_scan(const uint32_t *cnt, uint32_t *start, u
     __syncthreads();
 }
 
-// Exclusive scan of n counts into n + 1 offsets (the last one the total), by
-// one workgroup: rounds of 4 counts per thread, a wave scan of the thread
-// sums, then the wave totals.
-__device__ __forceinline__ void bin_offsets_scan(const uint32_t *counts, uint64_t n,
-                                                 uint64_t *offsets) {
-    constexpr uint32_t WAVES = BIN_SCAN_BLOCK / 64;
-    __shared__ uint64_t wsum[WAVES];
-    __shared__ uint64_t carry_s;
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (threadIdx.x == 0)
-        carry_s = 0;
-    for (uint64_t base = 0; base < n; base += 4ull * BIN_SCAN_BLOCK) {
-        const uint64_t i0 = base + 4ull * threadIdx.x;
-        uint64_t v[4], t = 0;
-#pragma unroll
-        for (uint32_t q = 0; q < 4; ++q) {
-            v[q] = i0 + q < n ? counts[i0 + q] : 0;
-            t += v[q];
-        }
-        uint64_t x = t;  // inclusive scan of the thread sums within the wave
-#pragma unroll
-        for (uint32_t d = 1; d < 64; d <<= 1) {
-            const uint64_t y = (uint64_t)__shfl_up((long long)x, d, 64);
-            if (lane >= d)
-                x += y;
-        }
-        __syncthreads();  // carry_s of the last round is in place
-        if (lane == 63)
-            wsum[wave] = x;
-        __syncthreads();
-        uint64_t before = carry_s;
-        for (uint32_t q = 0; q < wave; ++q)
-            before += wsum[q];
-        uint64_t c = before + x - t;
-#pragma unroll
-        for (uint32_t q = 0; q < 4; ++q) {
-            if (i0 + q < n)
-                offsets[i0 + q] = c;
-            c += v[q];
-        }
-        __syncthreads();
-        if (threadIdx.x == BIN_SCAN_BLOCK - 1)
-            carry_s = c;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0)
-        offsets[n] = carry_s;
-}
+// Shared memory of a sort of NT * PER items into at most NB bins.
+template <uint32_t NB, uint32_t NT, uint32_t PER, class I = uint32_t> struct BinSort {
+    I srt[NT * PER];
+    uint32_t cnt[NB];        // a bin's items of the batch, then its first place in the bin
+    uint32_t start[NB + 1];  // a bin's first item in srt
+    uint32_t wtot[NT / 64], total;
+};
 
-// Write a batch of items, PER per thread (BIN_NONE: none), to their bins'
-// cursors in out: the batch sorted by bin (bin_of(item) < NB) in LDS
-// (counting sort), then the sorted items written in order, so that a bin's
-// items of the batch go out as one contiguous run.  A 32-bit out keeps the
-// low 32 bits of each item.  cnt[] must be zero on
-// entry and is zero again on return; cursor[] advances by each bin's count.
-// Whole workgroup; ends synchronised.
-template <uint32_t NB, uint32_t NT, uint32_t PER, class BinOf, class Out>
-__device__ __forceinline__ void sorted_write_by(const uint64_t (&v)[PER], BinOf bin_of,
-                                                uint32_t *cnt, uint32_t *start, uint32_t *wtot,
-                                                uint32_t *total, uint64_t *srt, uint64_t *cursor,
-                                                Out *out) {
-    uint32_t rk[PER];
+// Append a batch of items, PER per thread, to their bins: at[q] is bin << 14 |
+// rank (the item's number in its bin, from an atomic add on sh.cnt), or ~0 for
+// none.  The items are sorted by bin in LDS and a bin's items written as one
+// run by a group of 2^lpb lanes; bin i has room for off(i+1) - off(i) items
+// from out + off(i), of which cursor[i] are claimed.  direct(bin, item) takes
+// an item without room.  sh.cnt is zero again on return.  Whole workgroup;
+// ends synchronised.
+template <uint32_t NB, uint32_t NT, uint32_t PER, class I, class Off, class Direct>
+__device__ __forceinline__ void bin_append(BinSort<NB, NT, PER, I> &sh, const I (&item)[PER],
+                                           const uint32_t (&at)[PER], uint32_t nb, uint32_t lpb,
+                                           unsigned long long *cursor, Off off, I *out,
+                                           Direct direct) {
+    static_assert(NT * PER <= 1u << 14, "rank bits");
+    constexpr uint32_t E = (NB + NT - 1) / NT;
+    __syncthreads();  // every rank is taken
+    // this thread's bins claim their room; the adds return while the scan runs
+    uint64_t base[E];
+#pragma unroll
+    for (uint32_t e = 0; e < E; ++e) {
+        const uint32_t bin = threadIdx.x * E + e, c = bin < nb ? sh.cnt[bin] : 0;
+        base[e] = c ? atomicAdd(&cursor[bin], (unsigned long long)c) : 0;
+    }
+    lds_scan<NB, NT>(sh.cnt, sh.start, sh.wtot, &sh.total);
+    if (threadIdx.x == 0)
+        sh.start[NB] = sh.total;
+#pragma unroll
+    for (uint32_t e = 0; e < E; ++e)  // (a claim beyond 2^32 - 2^15 has no room anyhow)
+        if (threadIdx.x * E + e < NB)
+            sh.cnt[threadIdx.x * E + e] = (uint32_t)min(base[e], (uint64_t)0xFFFF7FFFu);
 #pragma unroll
     for (uint32_t q = 0; q < PER; ++q)
-        rk[q] = v[q] != BIN_NONE ? atomicAdd(&cnt[bin_of(v[q])], 1u) : 0;
+        if (at[q] != ~0u)
+            sh.srt[sh.start[at[q] >> 14] + (at[q] & 0x3FFFu)] = item[q];
     __syncthreads();
-    lds_scan<NB, NT>(cnt, start, wtot, total);
-#pragma unroll
-    for (uint32_t q = 0; q < PER; ++q)
-        if (v[q] != BIN_NONE)
-            srt[start[bin_of(v[q])] + rk[q]] = v[q];
-    __syncthreads();
-    const uint32_t n = *total;
-    for (uint32_t i = threadIdx.x; i < n; i += NT) {
-        const uint64_t it = srt[i];
-        const uint32_t bn = bin_of(it);
-        out[cursor[bn] + (i - start[bn])] = (Out)it;
+    const uint32_t l = threadIdx.x & ((1u << lpb) - 1);
+    for (uint32_t bin = threadIdx.x >> lpb; bin < nb; bin += NT >> lpb) {
+        const uint32_t s0 = sh.start[bin], n = sh.start[bin + 1] - s0, b0 = sh.cnt[bin];
+        const uint64_t o = off(bin);
+        const uint32_t room = (uint32_t)min(off(bin + 1) - o, (uint64_t)0xFFFF7FFFu);
+        for (uint32_t i = l; i < n; i += 1u << lpb) {
+            const I it = sh.srt[s0 + i];
+            if (b0 + i < room)
+                out[o + b0 + i] = it;
+            else
+                direct(bin, it);
+        }
     }
     __syncthreads();
-    for (uint32_t bn = threadIdx.x; bn < NB; bn += NT) {
-        cursor[bn] += cnt[bn];
-        cnt[bn] = 0;
-    }
+    for (uint32_t i = threadIdx.x; i < NB; i += NT)
+        sh.cnt[i] = 0;
     __syncthreads();
 }
 
+// Lanes that write a bin's run: about as many as a batch has items per bin.
+__device__ __forceinline__ uint32_t bin_lanes(uint32_t nb, uint32_t batch) {
+    uint32_t lpb = 6;
+    while (lpb > 3 && (nb << lpb) > batch)
+        --lpb;
+    return lpb;
+}
 
 }  // namespace tp

@@ -64,17 +64,13 @@ constexpr uint32_t BIN_BLOCK = 1024;               // threads of the binned fill
 constexpr uint32_t BIN_PER = 16;                   // the split's items per thread per batch
 constexpr uint32_t BIN_BATCH = BIN_BLOCK * BIN_PER;
 constexpr uint32_t BIN_CHUNK_TILES_MAX = 1u << 20; // 2^31 positions per chunk (explicit)
-// Binned record: buckets of RBIN_SUB table blocks.
-constexpr uint32_t RBIN_MAX_BUCKETS = 1024;
+// Binned record: up to RBIN_MAX_BUCKETS buckets of up to RBIN_SUB table blocks.
+constexpr uint32_t RBIN_MAX_BUCKETS = 512;
 constexpr uint32_t RBIN_SUB_LOG2 = 9;
 constexpr uint32_t RBIN_SUB = 1u << RBIN_SUB_LOG2;
-constexpr uint32_t BIN_SPLIT_BLOCK = 1024;         // threads of the bucket split
-constexpr uint32_t BIN_SCAN_BLOCK = 1024;          // threads of the offset scan
-constexpr uint32_t BIN_SPLIT_PER = 16;             // bucket split: items per thread per batch
-constexpr uint32_t BIN_SCATTER_PER = 16;           // bucket scatter: items per thread per batch
-constexpr uint32_t BIN_SCATTER_BLOCK = 1024;       // bucket scatter: threads per workgroup
-constexpr uint32_t BIN_APPLY_BLOCK = 1024;         // threads of a block's apply
-constexpr uint32_t BIN_WG_PER_CU = 8;              // count and scatter workgroups per CU
+constexpr uint32_t RBIN_BLOCK = 512;               // threads of its items kernel
+constexpr uint32_t RBIN_PER = 12;                  // its items per thread per batch
+constexpr uint32_t RBIN_SPLIT_PER = 8;             // the split's (of BIN_BLOCK threads)
 
 // A string of S: a maximal N-free run of one genome, of length >= k.
 struct DString {
@@ -321,20 +317,27 @@ hipError_t launch_record(int W, const SeqArgs &a, const uint64_t *c1, const Tabl
 // 2^TABLE_BLOCK_LOG2 slots): per pass, the candidates whose home block lies
 // in [r_lo, r_hi) become items (their slot words), are partitioned by block
 // and each block is built in LDS and written out whole.
-constexpr uint32_t RBIN_SEG = 16384;   // staging items a count workgroup claims at once
 constexpr uint32_t RBIN_MAX_PASSES = 64;
 struct RecBinArgs {
-    uint64_t *items_a;         // the pass's items by bucket
-    uint64_t *items_b;         // staging (segments), then the items by block
-    uint32_t *counts;          // [bucket * grid + workgroup]
-    uint64_t *offsets;         // exclusive scan of counts, n + 1 entries
-    uint64_t *region_off;      // per block of the pass: first item in items_b; then the total
-    unsigned long long *ctl;   // [0] staging items claimed, [1] nonzero: scratch too small
-    uint64_t cap;              // items each of items_a and items_b hold
-    uint64_t r_lo, r_hi;       // the pass's home blocks
-    uint32_t n_buckets;        // ceil((r_hi - r_lo) / RBIN_SUB)
-    uint32_t grid;             // workgroups of the count, histogram and scatter kernels
+    uint64_t *items_a;           // the pass's items by bucket
+    uint64_t *items_b;           // the pass's items by block (buckets of several blocks)
+    uint64_t *spill;             // items without room, of all passes
+    unsigned long long *cursor;  // per bucket, then (several blocks) per block: items claimed
+    unsigned long long *ctl;     // [0] items spilled, [1] nonzero: more than spill holds
+    uint64_t room_a, room_b;     // items a bucket, a block has room for
+    uint64_t spill_cap;
+    uint64_t cursors;            // entries of cursor, rounded up to whole 16-byte pieces
+    uint64_t r_lo, r_hi;         // the pass's home blocks
+    uint32_t sub_log2;           // a bucket is 2^sub_log2 blocks
+    uint32_t n_buckets;
+    uint32_t n_cu;
 };
+// What a pass over `blocks` of a table's n_blocks home blocks takes.
+struct RecBinShape {
+    uint32_t sub_log2, n_buckets;
+    uint64_t room_a, room_b, spill, bytes, cursors;
+};
+RecBinShape rbin_shape(uint64_t candidates, uint64_t n_blocks, uint64_t blocks, uint32_t genomes);
 // table: set 0's table (keys, cap_m, cap_e, lomask, pow2 filled in).
 hipError_t launch_record_binned(const SeqArgs &a, const uint64_t *c1, const TableArgs &table,
                                 RecBinArgs rb, uint32_t passes, uint64_t n_blocks,

@@ -443,74 +443,6 @@ __device__ __forceinline__ uint32_t bin_direct(const BloomArgs &pool, uint64_t b
     return 1;
 }
 
-// Shared memory of a sort of NT * PER items into at most NB bins.
-template <uint32_t NB, uint32_t NT, uint32_t PER> struct BinSort {
-    uint32_t srt[NT * PER];
-    uint32_t cnt[NB];        // a bin's items of the batch, then its first place in the bin
-    uint32_t start[NB + 1];  // a bin's first item in srt
-    uint32_t wtot[NT / 64], total;
-};
-
-// Append a batch of items, PER per thread, to their bins: at[q] is bin << 14 |
-// rank (the item's number in its bin, from an atomic add on sh.cnt), or ~0 for
-// none.  The items are sorted by bin in LDS and a bin's items written as one
-// run by a group of 2^lpb lanes; bin i has room for off[i+1] - off[i] items
-// from out + off[i], of which cursor[i] are claimed.  direct(bin, item) takes
-// an item without room.  sh.cnt is zero again on return.  Whole workgroup;
-// ends synchronised.
-template <uint32_t NB, uint32_t NT, uint32_t PER, class Direct>
-__device__ __forceinline__ void bin_append(BinSort<NB, NT, PER> &sh, const uint32_t (&item)[PER],
-                                           const uint32_t (&at)[PER], uint32_t nb, uint32_t lpb,
-                                           unsigned long long *cursor, const uint64_t *off,
-                                           uint32_t *out, Direct direct) {
-    constexpr uint32_t E = (NB + NT - 1) / NT;
-    __syncthreads();  // every rank is taken
-    // this thread's bins claim their room; the adds return while the scan runs
-    uint64_t base[E];
-#pragma unroll
-    for (uint32_t e = 0; e < E; ++e) {
-        const uint32_t bin = threadIdx.x * E + e, c = bin < nb ? sh.cnt[bin] : 0;
-        base[e] = c ? atomicAdd(&cursor[bin], (unsigned long long)c) : 0;
-    }
-    lds_scan<NB, NT>(sh.cnt, sh.start, sh.wtot, &sh.total);
-    if (threadIdx.x == 0)
-        sh.start[NB] = sh.total;
-#pragma unroll
-    for (uint32_t e = 0; e < E; ++e)  // (a claim beyond 2^32 - 2^15 has no room anyhow)
-        if (threadIdx.x * E + e < NB)
-            sh.cnt[threadIdx.x * E + e] = (uint32_t)min(base[e], (uint64_t)0xFFFF7FFFu);
-#pragma unroll
-    for (uint32_t q = 0; q < PER; ++q)
-        if (at[q] != ~0u)
-            sh.srt[sh.start[at[q] >> 14] + (at[q] & 0x3FFFu)] = item[q];
-    __syncthreads();
-    const uint32_t l = threadIdx.x & ((1u << lpb) - 1);
-    for (uint32_t bin = threadIdx.x >> lpb; bin < nb; bin += NT >> lpb) {
-        const uint32_t s0 = sh.start[bin], n = sh.start[bin + 1] - s0, b0 = sh.cnt[bin];
-        const uint64_t o = off[bin];
-        const uint32_t room = (uint32_t)min(off[bin + 1] - o, (uint64_t)0xFFFF7FFFu);
-        for (uint32_t i = l; i < n; i += 1u << lpb) {
-            const uint32_t it = sh.srt[s0 + i];
-            if (b0 + i < room)
-                out[o + b0 + i] = it;
-            else
-                direct(bin, it);
-        }
-    }
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < NB; i += NT)
-        sh.cnt[i] = 0;
-    __syncthreads();
-}
-
-// Lanes that write a bin's run: about as many as a batch has items per bin.
-__device__ __forceinline__ uint32_t bin_lanes(uint32_t nb, uint32_t batch) {
-    uint32_t lpb = 6;
-    while (lpb > 3 && (nb << lpb) > batch)
-        --lpb;
-    return lpb;
-}
-
 // A batch's tile: its range of strings, its set's filter, and its string when
 // it has just one.
 struct BinTile {
@@ -568,6 +500,7 @@ void k_bin_items(SeqArgs a, BloomArgs pool, BinArgs b,
     const bool single = a.single != 0;
     const uint32_t lpb = bin_lanes(b.n_buckets, NT * PER);
     const uint64_t batches = (b.t_hi - b.t_lo + TILES - 1) / TILES;
+    const auto off = [&](uint32_t i) { return b.off[i]; };
     uint32_t atomics = 0;
     for (uint32_t i = threadIdx.x; i < NB; i += NT)
         sh.cnt[i] = 0;
@@ -593,7 +526,7 @@ void k_bin_items(SeqArgs a, BloomArgs pool, BinArgs b,
             const uint32_t bucket = block >> b.bucket_log2;
             at[q] = bucket << 14 | atomicAdd(&sh.cnt[bucket], 1u);
         }
-        bin_append<NB, NT, PER>(sh, item, at, b.n_buckets, lpb, b.cursor, b.off, b.items_a,
+        bin_append(sh, item, at, b.n_buckets, lpb, b.cursor, off, b.items_a,
                             [&](uint32_t bucket, uint32_t it) {
                                 atomics += bin_direct<false>(
                                     pool, (uint64_t)bucket << b.bucket_log2, it);
@@ -616,6 +549,7 @@ __global__ __launch_bounds__(NT) void k_bin_items_std(SeqArgs a, BloomArgs pool,
     const bool single = a.single != 0;
     const uint32_t lpb = bin_lanes(b.n_buckets, NT * PER);
     const uint64_t batches = (b.t_hi - b.t_lo + TILES - 1) / TILES;
+    const auto off = [&](uint32_t i) { return b.off[i]; };
     uint32_t atomics = 0;
     for (uint32_t i = threadIdx.x; i < NB; i += NT)
         sh.cnt[i] = 0;
@@ -653,7 +587,7 @@ __global__ __launch_bounds__(NT) void k_bin_items_std(SeqArgs a, BloomArgs pool,
                 item[q] = (uint32_t)bit & ((64u << b.bucket_log2) - 1);
                 at[q] = bucket << 14 | atomicAdd(&sh.cnt[bucket], 1u);
             }
-            bin_append<NB, NT, PER>(sh, item, at, b.n_buckets, lpb, b.cursor, b.off, b.items_a,
+            bin_append(sh, item, at, b.n_buckets, lpb, b.cursor, off, b.items_a,
                                     [&](uint32_t bucket, uint32_t it) {
                                         atomics += bin_direct<true>(
                                             pool, (uint64_t)bucket << b.bucket_log2, it);
@@ -693,8 +627,8 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_bin_split(BloomArgs pool, BinArgs
         at[q] = i0 + q * NT + threadIdx.x < n ? reg << 14 | atomicAdd(&sh.cnt[reg], 1u) : ~0u;
     }
     const uint32_t nb = min(sub, b.n_regions - r0);
-    bin_append<NB, NT, PER>(sh, item, at, nb, bin_lanes(nb, NT * PER), b.cursor + b.n_buckets + r0, b.roff + r0,
-                        b.items_b, [&](uint32_t, uint32_t it) {
+    bin_append(sh, item, at, nb, bin_lanes(nb, NT * PER), b.cursor + b.n_buckets + r0,
+               [&](uint32_t i) { return b.roff[r0 + i]; }, b.items_b, [&](uint32_t, uint32_t it) {
                             atomics += bin_direct<STD>(pool, (uint64_t)bucket << b.bucket_log2, it);
                         });
     if (atomics)

@@ -49,7 +49,7 @@ struct P2Batch {
     uint32_t set[P2_TILES];
     uint64_t w[P2_TILES * TILE / 64];   // candidate words
     uint16_t at[P2_TILES * TILE];       // candidates: tile << 11 | position
-    uint32_t wsum[BLOCK / 64];
+    uint32_t wsum[16];                  // (up to 1024 threads)
     uint32_t skip;
 };
 static_assert(TILE == 1u << 11, "candidate positions");
@@ -79,6 +79,7 @@ __device__ __forceinline__ uint32_t overflow_seen(const SeqArgs &a, uint32_t set
 // other workgroups may set the flag at any time, so one thread reads it and
 // the whole workgroup takes that one reading).  Whole workgroup; ends
 // synchronised.
+template <uint32_t NT>
 __device__ __forceinline__ bool next_batch(const SeqArgs &a, RunCursor &rc, uint32_t most,
                                            const uint64_t *c1, P2Batch &b, OverflowFlag &flag,
                                            uint32_t *n, uint32_t *total, uint32_t *set) {
@@ -108,22 +109,25 @@ __device__ __forceinline__ bool next_batch(const SeqArgs &a, RunCursor &rc, uint
         ++take;
     rc.gi += take - 1;
     *n = take;
-    for (uint32_t i = threadIdx.x; i < take * STAGE_WORDS; i += BLOCK) {
+    for (uint32_t i = threadIdx.x; i < take * STAGE_WORDS; i += NT) {
         const uint32_t j = i / STAGE_WORDS, u = i % STAGE_WORDS;
         const int64_t gw = (int64_t)(b.tile[j].t0 / 32) - 1 + u;
         stage_word(b.sg[j], u, (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull);
     }
-    for (uint32_t i = threadIdx.x; i < P2_TILES * TILE / 64; i += BLOCK) {
+    for (uint32_t i = threadIdx.x; i < P2_TILES * TILE / 64; i += NT) {
         const uint32_t j = i / (TILE / 64);
         b.w[i] = j < take ? c1[b.tile[j].t0 / 64 + i % (TILE / 64)] : 0ull;
     }
     if (threadIdx.x == 0)
         b.skip = overflow_seen(a, *set, flag);
     __syncthreads();
-    // a thread lists 32 positions
-    static_assert(P2_TILES * TILE / 32 == BLOCK, "32 positions per thread");
+    // a thread lists PER positions
+    constexpr uint32_t PER = P2_TILES * TILE / NT;
+    static_assert(PER == 8 || PER == 16 || PER == 32, "a piece of one 32-bit word");
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t bits = ((const uint32_t *)b.w)[threadIdx.x];
+    uint32_t bits = ((const uint32_t *)b.w)[threadIdx.x * PER / 32];
+    if (PER < 32)
+        bits = bits >> (threadIdx.x * PER & 31u) & ((1u << (PER & 31u)) - 1);
     const uint32_t c = (uint32_t)__popc(bits);
     uint32_t x = c;
 #pragma unroll
@@ -136,12 +140,12 @@ __device__ __forceinline__ bool next_batch(const SeqArgs &a, RunCursor &rc, uint
     __syncthreads();
     uint32_t at = x - c, sum = 0;
 #pragma unroll
-    for (uint32_t q = 0; q < BLOCK / 64; ++q) {
+    for (uint32_t q = 0; q < NT / 64; ++q) {
         at += q < wave ? b.wsum[q] : 0;
         sum += b.wsum[q];
     }
     for (; bits; bits &= bits - 1)
-        b.at[at++] = (uint16_t)(threadIdx.x * 32 + (uint32_t)__builtin_ctz(bits));
+        b.at[at++] = (uint16_t)(threadIdx.x * PER + (uint32_t)__builtin_ctz(bits));
     *total = sum;
     __syncthreads();
     return true;
@@ -372,7 +376,7 @@ __global__ __launch_bounds__(BLOCK) void k_record(SeqArgs a, const uint64_t *c1,
     const uint32_t chunk = max(a.chunk, (order & 4) ? RECORD_RUN : most);
     RunCursor rc = batch_run(a, (order & 5) != 0, chunk);
     uint32_t n, total, set;
-    while (next_batch(a, rc, most, c1, b, flag, &n, &total, &set)) {
+    while (next_batch<BLOCK>(a, rc, most, c1, b, flag, &n, &total, &set)) {
         if (b.skip)
             continue;
         const TableArgs t = table_of(a, pool, set);
@@ -437,25 +441,35 @@ hipError_t launch_record(int W, const SeqArgs &a, const uint64_t *c1, const Tabl
 // e <= TABLE_BLOCK_LOG2), so blocks are independent: a pass takes the blocks
 // [r_lo, r_hi); every candidate whose home block is among them becomes an
 // item, the slot word it contributes (key << 8 | edge bits, packed slots);
-// the items are partitioned by block in two streaming steps (bucket of
-// RBIN_SUB blocks, then block; each batch sorted in LDS so that a
-// destination's items leave as one run); and each block is built in LDS from
-// empty and written out whole.  Same keys and edge bits as k_record (slots
-// within a block may differ: they follow the order of insertion), no table
-// clear and no random access.  Every pass walks the candidates again; the
-// passes are as many as the scratch needs.
+// the items are partitioned by block in one or two streaming steps, as the
+// binned fill's are (bin_append: buckets of up to RBIN_SUB blocks, then
+// blocks); and each block is built in LDS from empty and written out whole.
+// Same keys and edge bits as k_record (slots within a block may differ: they
+// follow the order of insertion), no table clear and no random access.  Every
+// pass walks the candidates again; the passes are as many as the scratch
+// needs.
 //
-//   k_rbin_count    candidates walked, a static share of the tiles per
-//                   workgroup; the pass's items appended to the staging in
-//                   segments of RBIN_SEG items that a workgroup claims with
-//                   one atomic add (a segment's unused tail holds BIN_NONE)
-//   k_rbin_hist     per workgroup (an even share of the staging): items per
-//                   bucket
-//   k_rbin_scan     offsets per (bucket, workgroup), bucket-major
-//   k_rbin_scatter  the same shares, each item to its (bucket, workgroup)
-//                   range
-//   k_rbin_split    per bucket: its items by block
+//   k_rbin_items    the candidates listed (next_batch), their items collected
+//                   in LDS until they fill a batch, the batch appended to the
+//                   buckets
+//   k_rbin_split    buckets of several blocks: batches of a bucket's items
+//                   appended to its blocks
 //   k_rbin_apply    per block: built in LDS, written out; new keys counted
+//   k_rbin_spill    the items that found no room, after the last pass: into
+//                   the finished table, as k_record inserts them
+//
+// Bound by the candidates' walk and the items' memory traffic (8 bytes, written
+// and read once per level): 1.6 Gbp, 450M candidates, a 4 GiB table, items 4.2
+// ms, split 1.8, apply 3.0, against 17.1 of k_record, whose random atomics move
+// a line in and out each, and 0.9 of the table's clear; 62 x 5 Mbp 1.3, 0.5 and
+// 0.6 against 3.2.  Items by workgroups of 1024 threads, one to a CU, 6.0 ms,
+// two (64 registers) 4.8, of 256, three to a CU, 7.3.  Apply with every item's
+// probes on their own 3.9 ms (of the smaller table), by lanes at their own pace
+// 3.6.
+//
+// A bucket's and a block's room come from the candidate count, as a hash
+// spreads keys evenly and a key comes up about once per genome; a k-mer of
+// many thousand copies fills its block's, and the rest of its items spill.
 
 // Home block of a packed slot word (its key is word >> 8).
 template <bool P2>
@@ -463,240 +477,131 @@ __device__ __forceinline__ uint64_t rbin_block(const TableArgs &t, uint64_t item
     return first_slot<P2>(t, item >> 8) >> t.cap_e;
 }
 
+// One item to the spilled ones (divergent: the active lanes share one claim).
+__device__ __forceinline__ void rbin_spill(const RecBinArgs &rb, uint64_t item) {
+    const uint64_t act = __builtin_amdgcn_ballot_w64(true);
+    const uint32_t before =
+        __builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0));
+    unsigned long long base = 0;
+    if (before == 0)
+        base = atomicAdd(&rb.ctl[0], (unsigned long long)__popcll(act));
+    base = (unsigned long long)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32 |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base);
+    if (base + before < rb.spill_cap)
+        rb.spill[base + before] = item;
+    else
+        atomicExch(&rb.ctl[1], 1ull);
+}
+
 template <bool P2>
-__global__ __launch_bounds__(BLOCK) void k_rbin_count(SeqArgs a, const uint64_t *c1, TableArgs t,
-                                                      RecBinArgs rb) {
-    constexpr uint32_t PER = TILE / BLOCK;
-    __shared__ Stage sg;
-    __shared__ uint64_t cw[TILE / 64];
-    __shared__ uint32_t wtot[BLOCK / 64];
-    __shared__ uint64_t seg_base, seg_new;
-    __shared__ uint32_t seg_used;
+__global__ __launch_bounds__(RBIN_BLOCK) __attribute__((amdgpu_waves_per_eu(4)))
+void k_rbin_items(SeqArgs a, const uint64_t *c1, TableArgs t, RecBinArgs rb) {
+    constexpr uint32_t NT = RBIN_BLOCK, PER = RBIN_PER, CAP = NT * PER;
+    __shared__ P2Batch b;
+    __shared__ BinSort<RBIN_MAX_BUCKETS, NT, PER, uint64_t> sh;
+    OverflowFlag flag;
     const uint32_t k = a.k;
     const bool single = a.single != 0;
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (threadIdx.x == 0) {
-        seg_base = 0;
-        seg_new = 0;
-        seg_used = RBIN_SEG;  // no segment yet
-    }
-    const uint64_t n = a.n_tiles;
-    const uint64_t per = (n + rb.grid - 1) / rb.grid;
-    const uint64_t t_lo = min(n, (uint64_t)blockIdx.x * per);
-    const uint64_t t_hi = min(n, (uint64_t)(blockIdx.x + 1) * per);
-    for (uint64_t tile = t_lo; tile < t_hi; ++tile) {
-        const TileInfo ti = a.tiles[tile];
-        const uint32_t lo = ti.str_lo, hi = ti.str_hi;
-        if (lo == hi)
-            continue;
-        const uint64_t t0 = tile * TILE;
-        __syncthreads();  // the last tile's staged words and segment state are read
-        for (uint32_t i = threadIdx.x; i < STAGE_WORDS; i += BLOCK) {
-            const int64_t gw = (int64_t)(tile * TILE_WORDS) - 1 + i;
-            stage_word(sg, i, (gw >= 0 && (uint64_t)gw < a.seq_words) ? a.seq[gw] : 0ull);
-        }
-        if (threadIdx.x < TILE / 64)
-            cw[threadIdx.x] = c1[tile * (TILE / 64) + threadIdx.x];
-        __syncthreads();
-        uint64_t v[PER];
-        uint32_t nv = 0;
-        P2Tile tl{t0, lo, hi, lo + 1 == hi ? span_of(a.strings, lo, t0) : Span{0, -1}};
-#pragma unroll
-        for (uint32_t it = 0; it < PER; ++it) {
-            v[it] = BIN_NONE;
-            const uint32_t q = it * BLOCK + threadIdx.x;
-            if (!((cw[q >> 6] >> lane) & 1ull))
-                continue;
-            const Span sp = record_span(a, tl, q);
-            if ((int32_t)q < sp.gs)
-                continue;  // not a k-mer start: never marked by the first pass
-            uint32_t m;
-            Strands<uint64_t> st;
-            const uint64_t key = record_key<uint64_t>(sg, q, k, sp, single, m, st);
-            const uint64_t item = key << 8 | m;
-            const uint64_t r = rbin_block<P2>(t, item);
-            if (r >= rb.r_lo && r < rb.r_hi) {
-                v[it] = item;
-                ++nv;
-            }
-        }
-        // the tile's items in thread order: a scan of the per-thread counts
-        uint32_t x = nv;
-#pragma unroll
-        for (uint32_t d = 1; d < 64; d <<= 1) {
-            const uint32_t y = __shfl_up(x, d, 64);
-            if (lane >= d)
-                x += y;
-        }
-        if (lane == 63)
-            wtot[wave] = x;
-        __syncthreads();
-        uint32_t before = 0, total = 0;
-#pragma unroll
-        for (uint32_t q = 0; q < BLOCK / 64; ++q) {
-            before += q < wave ? wtot[q] : 0u;
-            total += wtot[q];
-        }
-        const uint32_t room = RBIN_SEG - seg_used;
-        if (threadIdx.x == 0 && total > room) {
-            const uint64_t base = atomicAdd(&rb.ctl[0], (unsigned long long)RBIN_SEG);
-            seg_new = base;
-            if (base + RBIN_SEG > rb.cap)
-                atomicExch(&rb.ctl[1], 1ull);
-        }
-        __syncthreads();
-        const uint64_t cur = seg_base + seg_used, nxt = seg_new;
-        uint32_t i = before + x - nv;
+    const uint32_t lpb = bin_lanes(rb.n_buckets, CAP);
+    for (uint32_t i = threadIdx.x; i < RBIN_MAX_BUCKETS; i += NT)
+        sh.cnt[i] = 0;
+    // the n collected items to their buckets (sh.srt holds them, then holds
+    // them sorted)
+    const auto append = [&](uint32_t n) {
+        uint64_t item[PER];
+        uint32_t at[PER];
+        __syncthreads();  // all are collected
 #pragma unroll
         for (uint32_t q = 0; q < PER; ++q) {
-            if (v[q] != BIN_NONE) {
-                const uint64_t dst = i < room ? cur + i : nxt + (i - room);
-                if (dst < rb.cap)
-                    rb.items_b[dst] = v[q];
-                ++i;
+            const uint32_t i = q * NT + threadIdx.x;
+            item[q] = i < n ? sh.srt[i] : BIN_NONE;
+            at[q] = ~0u;
+            if (item[q] != BIN_NONE) {
+                const uint32_t bucket =
+                    (uint32_t)((rbin_block<P2>(t, item[q]) - rb.r_lo) >> rb.sub_log2);
+                at[q] = bucket << 14 | atomicAdd(&sh.cnt[bucket], 1u);
             }
         }
-        __syncthreads();  // every thread has read the segment state
-        if (threadIdx.x == 0) {
-            if (total > room) {
-                seg_base = nxt;
-                seg_used = total - room;
-            } else {
-                seg_used += total;
+        bin_append(sh, item, at, rb.n_buckets, lpb, rb.cursor,
+                   [&](uint32_t i) { return i * rb.room_a; }, rb.items_a,
+                   [&](uint32_t, uint64_t it) { rbin_spill(rb, it); });
+    };
+    uint32_t n, total, set, have = 0;
+    const uint32_t most = batch_tiles(a.n_tiles, gridDim.x);
+    RunCursor rc = linear_run(a, max(a.chunk, most));
+    while (next_batch<NT>(a, rc, most, c1, b, flag, &n, &total, &set)) {
+        for (uint32_t done = 0; done < total;) {
+            const uint32_t m = min(total - done, CAP - have);
+            for (uint32_t i = threadIdx.x; i < m; i += NT) {
+                const uint32_t c = b.at[done + i], q = c & (TILE - 1);
+                const P2Tile &tl = b.tile[c / TILE];
+                const Span sp = record_span(a, tl, q);
+                uint64_t item = BIN_NONE;
+                if ((int32_t)q >= sp.gs) {  // (a k-mer start)
+                    uint32_t mask;
+                    Strands<uint64_t> st;
+                    item = record_key<uint64_t>(b.sg[c / TILE], q, k, sp, single, mask, st) << 8;
+                    item |= mask;
+                    const uint64_t r = rbin_block<P2>(t, item);
+                    if (r < rb.r_lo || r >= rb.r_hi)
+                        item = BIN_NONE;
+                }
+                sh.srt[have + i] = item;
+            }
+            done += m;
+            have += m;
+            if (have == CAP) {
+                append(CAP);
+                have = 0;
             }
         }
     }
-    __syncthreads();
-    // the unused tail of the last segment
-    for (uint32_t i = seg_used + threadIdx.x; i < RBIN_SEG; i += BLOCK) {
-        const uint64_t dst = seg_base + i;
-        if (dst < rb.cap)
-            rb.items_b[dst] = BIN_NONE;
-    }
+    append(have);
 }
 
-// This workgroup's share of the staging (an even split of what was claimed).
-__device__ __forceinline__ void rbin_share(const RecBinArgs &rb, uint64_t *lo, uint64_t *hi) {
-    const uint64_t total = min((uint64_t)rb.ctl[0], rb.cap);
-    const uint64_t per = (total + rb.grid - 1) / rb.grid;
-    *lo = min(total, (uint64_t)blockIdx.x * per);
-    *hi = min(total, (uint64_t)(blockIdx.x + 1) * per);
-}
-
+// One batch of one bucket's items (blockIdx.y: the bucket, blockIdx.x: the
+// batch) appended to the bucket's blocks.
 template <bool P2>
-__global__ __launch_bounds__(BLOCK) void k_rbin_hist(TableArgs t, RecBinArgs rb) {
-    __shared__ uint32_t hist[RBIN_MAX_BUCKETS];
-    for (uint32_t i = threadIdx.x; i < RBIN_MAX_BUCKETS; i += BLOCK)
-        hist[i] = 0;
-    __syncthreads();
-    uint64_t lo, hi;
-    rbin_share(rb, &lo, &hi);
-    if (!rb.ctl[1]) {
-        for (uint64_t i = lo + threadIdx.x; i < hi; i += BLOCK) {
-            const uint64_t x = rb.items_b[i];
-            if (x != BIN_NONE)
-                atomicAdd(&hist[(uint32_t)((rbin_block<P2>(t, x) - rb.r_lo) >> RBIN_SUB_LOG2)], 1u);
-        }
-    }
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < rb.n_buckets; i += BLOCK)
-        rb.counts[(uint64_t)i * rb.grid + blockIdx.x] = hist[i];
-}
-
-__global__ __launch_bounds__(BIN_SCAN_BLOCK) void k_rbin_scan(const uint32_t *counts, uint64_t n,
-                                                             uint64_t *offsets) {
-    bin_offsets_scan(counts, n, offsets);
-}
-
-template <bool P2>
-__global__ __launch_bounds__(BIN_SCATTER_BLOCK) void k_rbin_scatter(TableArgs t, RecBinArgs rb) {
-    constexpr uint32_t NT = BIN_SCATTER_BLOCK, PER = BIN_SCATTER_PER;
-    __shared__ uint64_t cursor[RBIN_MAX_BUCKETS];
-    __shared__ uint32_t cnt[RBIN_MAX_BUCKETS];
-    __shared__ uint32_t start[RBIN_MAX_BUCKETS];
-    __shared__ uint64_t srt[NT * PER];
-    __shared__ uint32_t wtot[NT / 64];
-    __shared__ uint32_t total;
-    for (uint32_t i = threadIdx.x; i < RBIN_MAX_BUCKETS; i += NT) {
-        cursor[i] = i < rb.n_buckets ? rb.offsets[(uint64_t)i * rb.grid + blockIdx.x] : 0;
-        cnt[i] = 0;
-    }
-    __syncthreads();
-    if (rb.ctl[1])
+__global__ __launch_bounds__(BIN_BLOCK) void k_rbin_split(TableArgs t, RecBinArgs rb) {
+    constexpr uint32_t NT = BIN_BLOCK, PER = RBIN_SPLIT_PER;
+    __shared__ BinSort<RBIN_SUB, NT, PER, uint64_t> sh;
+    const uint32_t bucket = blockIdx.y, nb = 1u << rb.sub_log2;
+    const uint64_t *in = rb.items_a + bucket * rb.room_a;
+    const uint64_t n = min((uint64_t)rb.cursor[bucket], rb.room_a);
+    const uint64_t i0 = (uint64_t)blockIdx.x * (NT * PER);
+    if (i0 >= n)
         return;
-    uint64_t lo, hi;
-    rbin_share(rb, &lo, &hi);
-    const auto bucket_of = [&](uint64_t x) {
-        return (uint32_t)((rbin_block<P2>(t, x) - rb.r_lo) >> RBIN_SUB_LOG2);
-    };
-    // every thread runs the same number of batches (the workgroup syncs in each)
-    for (uint64_t i0 = lo; i0 < hi; i0 += PER * NT) {
-        uint64_t v[PER];
-#pragma unroll
-        for (uint32_t q = 0; q < PER; ++q) {
-            const uint64_t j = i0 + (uint64_t)q * NT + threadIdx.x;
-            v[q] = j < hi ? rb.items_b[j] : BIN_NONE;
-        }
-        sorted_write_by<RBIN_MAX_BUCKETS, NT, PER>(v, bucket_of, cnt, start, wtot, &total, srt,
-                                                  cursor, rb.items_a);
-    }
-}
-
-// One workgroup per bucket: its items (the ranges of all its pairs, back to
-// back) counted by block, then written block by block into the same range of
-// items_b; region_off gets each block's first item.
-template <bool P2>
-__global__ __launch_bounds__(BIN_SPLIT_BLOCK) void k_rbin_split(TableArgs t, RecBinArgs rb) {
-    constexpr uint32_t NT = BIN_SPLIT_BLOCK, PER = BIN_SPLIT_PER;
-    __shared__ uint32_t cnt[RBIN_SUB];
-    __shared__ uint32_t start[RBIN_SUB];
-    __shared__ uint64_t cursor[RBIN_SUB];
-    __shared__ uint64_t srt[NT * PER];
-    __shared__ uint32_t wtot[NT / 64];
-    __shared__ uint32_t total;
-    const uint32_t bk = blockIdx.x;
-    const uint64_t lo = rb.offsets[(uint64_t)bk * rb.grid];
-    const uint64_t hi = rb.offsets[(uint64_t)(bk + 1) * rb.grid];
-    const auto sub_of = [&](uint64_t x) {
-        return (uint32_t)(rbin_block<P2>(t, x) - rb.r_lo) & (RBIN_SUB - 1);
-    };
     for (uint32_t i = threadIdx.x; i < RBIN_SUB; i += NT)
-        cnt[i] = 0;
-    __syncthreads();
-    for (uint64_t i = lo + threadIdx.x; i < hi; i += NT)
-        atomicAdd(&cnt[sub_of(rb.items_a[i])], 1u);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t c = lo;
-        for (uint32_t q = 0; q < RBIN_SUB; ++q) {
-            cursor[q] = c;
-            rb.region_off[(uint64_t)bk * RBIN_SUB + q] = c;
-            c += cnt[q];
-            cnt[q] = 0;
-        }
-        if (bk + 1 == rb.n_buckets)
-            rb.region_off[(uint64_t)rb.n_buckets * RBIN_SUB] = c;
-    }
-    __syncthreads();
-    for (uint64_t i0 = lo; i0 < hi; i0 += PER * NT) {
-        uint64_t v[PER];
+        sh.cnt[i] = 0;
+    uint64_t item[PER];
+    uint32_t at[PER];
 #pragma unroll
-        for (uint32_t q = 0; q < PER; ++q) {
-            const uint64_t j = i0 + (uint64_t)q * NT + threadIdx.x;
-            v[q] = j < hi ? rb.items_a[j] : BIN_NONE;
-        }
-        sorted_write_by<RBIN_SUB, NT, PER>(v, sub_of, cnt, start, wtot, &total, srt, cursor,
-                                          rb.items_b);
+    for (uint32_t q = 0; q < PER; ++q) {
+        const uint64_t i = i0 + q * NT + threadIdx.x;
+        item[q] = i < n ? in[i] : BIN_NONE;
     }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+        at[q] = ~0u;
+        if (item[q] != BIN_NONE) {
+            const uint32_t sub = (uint32_t)(rbin_block<P2>(t, item[q]) - rb.r_lo) & (nb - 1);
+            at[q] = sub << 14 | atomicAdd(&sh.cnt[sub], 1u);
+        }
+    }
+    const uint64_t r0 = (uint64_t)bucket << rb.sub_log2;
+    bin_append(sh, item, at, nb, bin_lanes(nb, NT * PER), rb.cursor + rb.n_buckets + r0,
+               [&](uint32_t i) { return (r0 + i) * rb.room_b; }, rb.items_b,
+               [&](uint32_t, uint64_t it) { rbin_spill(rb, it); });
 }
 
 // One workgroup per block of the pass: the block built in LDS from empty (an
 // item claims an empty slot by compare-and-swap, or ORs its edge bits into
 // its key's slot; probes wrap within the block), then written out whole.
 template <bool P2>
-__global__ __launch_bounds__(BIN_APPLY_BLOCK) void k_rbin_apply(TableArgs t, RecBinArgs rb,
-                                                                SetCounters *sc, Counters *cnt) {
-    constexpr uint32_t NT = BIN_APPLY_BLOCK;
+__global__ __launch_bounds__(BIN_BLOCK) void k_rbin_apply(TableArgs t, RecBinArgs rb,
+                                                          SetCounters *sc, Counters *cnt) {
+    constexpr uint32_t NT = BIN_BLOCK;
     __shared__ __align__(16) unsigned long long reg[1u << TABLE_BLOCK_LOG2];
     __shared__ unsigned long long fresh_wg, probes_wg;
     __shared__ uint32_t over_wg;
@@ -710,44 +615,55 @@ __global__ __launch_bounds__(BIN_APPLY_BLOCK) void k_rbin_apply(TableArgs t, Rec
         over_wg = 0;
     }
     __syncthreads();
-    if (rb.ctl[1])
-        return;  // the scratch was too small: the host redoes the record
-    const uint64_t lo = rb.region_off[r], hi = rb.region_off[r + 1];
+    const bool split = rb.sub_log2 != 0;
+    const uint64_t *items = split ? rb.items_b + r * rb.room_b : rb.items_a + r * rb.room_a;
+    const uint64_t n = min((uint64_t)rb.cursor[split ? rb.n_buckets + r : r],
+                           split ? rb.room_b : rb.room_a);
     uint32_t fresh = 0, probes = 0;
     bool over = false;
     constexpr uint32_t U = 4;
-    for (uint64_t i = lo + threadIdx.x; i < hi; i += U * NT) {
+    // a lane works through U items at its own pace: an item that is done with
+    // gives way to the lane's next in the same step, so that a wave takes the
+    // steps of its slowest lane over U items, not of each item's slowest lane
+    for (uint64_t i = threadIdx.x; i < n; i += U * NT) {
         uint64_t v[U];
+        uint32_t s[U], left = 0, tries = 0;
 #pragma unroll
         for (uint32_t q = 0; q < U; ++q) {
             const uint64_t j = i + (uint64_t)q * NT;
-            v[q] = j < hi ? rb.items_b[j] : BIN_NONE;
+            v[q] = j < n ? items[j] : BIN_NONE;
+            left += j < n;
         }
 #pragma unroll
-        for (uint32_t q = 0; q < U; ++q) {
-            if (v[q] == BIN_NONE)
-                continue;
-            const uint64_t key = v[q] >> 8;
-            const unsigned long long m = v[q] & 0xFFu;
-            uint32_t s = (uint32_t)first_slot<P2>(t, key) & (nb - 1);
-            ++probes;
-            uint32_t j = 0;
-            for (; j < MAX_PROBE; ++j) {
-                const unsigned long long cur =
-                    atomicCAS(&reg[s], EMPTY_KEY, (unsigned long long)v[q]);
-                if (cur == EMPTY_KEY) {
-                    ++fresh;
-                    break;
-                }
-                if ((cur >> 8) == key) {
-                    if ((cur & m) != m)
-                        atomicOr(&reg[s], m);
-                    break;
-                }
-                s = (s + 1) & (nb - 1);
-                probes += (s & 1) == 0;  // a new pair of slots
+        for (uint32_t q = 0; q < U; ++q)
+            s[q] = (uint32_t)first_slot<P2>(t, v[q] >> 8) & (nb - 1);
+        probes += left;
+        while (left) {
+            const unsigned long long cur =
+                atomicCAS(&reg[s[0]], EMPTY_KEY, (unsigned long long)v[0]);
+            const unsigned long long m = v[0] & 0xFFu;
+            bool done = cur == EMPTY_KEY;
+            fresh += done;
+            if (!done && cur >> 8 == v[0] >> 8) {
+                if ((cur & m) != m)
+                    atomicOr(&reg[s[0]], m);
+                done = true;
             }
-            over |= j == MAX_PROBE;
+            if (!done) {
+                s[0] = (s[0] + 1) & (nb - 1);
+                probes += (s[0] & 1) == 0;  // a new pair of slots
+                if (++tries == MAX_PROBE)
+                    done = over = true;
+            }
+            if (done) {
+#pragma unroll
+                for (uint32_t q = 0; q + 1 < U; ++q) {
+                    v[q] = v[q + 1];
+                    s[q] = s[q + 1];
+                }
+                tries = 0;
+                --left;
+            }
         }
     }
     if (fresh)
@@ -770,41 +686,84 @@ __global__ __launch_bounds__(BIN_APPLY_BLOCK) void k_rbin_apply(TableArgs t, Rec
     }
 }
 
+// The spilled items into the finished table.
+template <bool P2>
+__global__ __launch_bounds__(BLOCK) void k_rbin_spill(TableArgs t, RecBinArgs rb, SetCounters *sc,
+                                                      Counters *cnt) {
+    const uint64_t n = min((uint64_t)rb.ctl[0], rb.spill_cap);
+    uint32_t keys = 0, probes = 0;
+    for (uint64_t i = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; i < n;
+         i += (uint64_t)gridDim.x * BLOCK) {
+        const uint64_t item = rb.spill[i], key = item >> 8, slot = first_slot<P2>(t, key);
+        const int got = insert_pair<P2>(t, item, (uint32_t)item & 0xFFu, slot, load_pair(t, slot),
+                                        [&](unsigned long long x) { return x >> 8 == key; },
+                                        probes);
+        keys += got > 0;
+        if (got < 0)
+            atomicExch(&sc->overflow, 1ull);
+    }
+    if (keys)
+        atomicAdd(&sc->table_keys, (unsigned long long)keys);
+    if (probes)
+        atomicAdd(&cnt->table_probes, (unsigned long long)probes);
+}
+
+// About 256 buckets, of up to RBIN_SUB blocks (a batch of k_rbin_items then
+// leaves in runs of some 24 items), or a block to each where that makes at most
+// RBIN_MAX_BUCKETS.  Room for a bin's share and six standard deviations of it,
+// its keys coming up once per genome; spill for a sixteenth of the items.
+RecBinShape rbin_shape(uint64_t candidates, uint64_t n_blocks, uint64_t blocks, uint32_t genomes) {
+    RecBinShape s{};
+    if (blocks > RBIN_MAX_BUCKETS)
+        while (s.sub_log2 < RBIN_SUB_LOG2 && (blocks - 1) >> s.sub_log2 >= RBIN_MAX_BUCKETS / 2)
+            ++s.sub_log2;
+    s.n_buckets = (uint32_t)((blocks + (1ull << s.sub_log2) - 1) >> s.sub_log2);
+    const double per = (double)candidates / (double)n_blocks;
+    const auto room = [&](double mean) {
+        return ((uint64_t)(1.02 * mean + 6 * std::sqrt(mean * genomes)) + 64 + 15) / 16 * 16;
+    };
+    s.room_a = room(per * (double)std::min<uint64_t>(blocks, 1ull << s.sub_log2));
+    s.room_b = s.sub_log2 ? room(per) : 0;
+    s.spill = candidates / 16 + 65536;
+    const uint64_t whole = (uint64_t)s.n_buckets << s.sub_log2;
+    s.cursors = (s.n_buckets + (s.sub_log2 ? whole : 0) + 1) / 2 * 2;  // (whole 16-byte pieces)
+    s.bytes = 8 * (32 + s.cursors + s.n_buckets * s.room_a + whole * s.room_b + s.spill);
+    return s;
+}
+
 hipError_t launch_record_binned(const SeqArgs &a, const uint64_t *c1, const TableArgs &t,
                                 RecBinArgs rb, uint32_t passes, uint64_t n_blocks,
                                 SetCounters *set_cnt, Counters *cnt, hipStream_t s) {
     if (n_blocks == 0 || passes == 0)
         return hipSuccess;
-    hipError_t e = launch_zero(rb.ctl, 2 * sizeof(unsigned long long), s);
-    if (e != hipSuccess)
-        return e;
     const uint64_t per_pass = (n_blocks + passes - 1) / passes;
     auto run = [&](auto p2) -> hipError_t {
         constexpr bool P2 = decltype(p2)::value;
-        for (uint64_t r0 = 0; r0 < n_blocks; r0 += per_pass) {
+        hipError_t e = launch_zero(rb.ctl, 2 * sizeof(unsigned long long), s);
+        for (uint64_t r0 = 0; r0 < n_blocks && e == hipSuccess; r0 += per_pass) {
             rb.r_lo = r0;
             rb.r_hi = min(n_blocks, r0 + per_pass);
-            rb.n_buckets = (uint32_t)((rb.r_hi - rb.r_lo + RBIN_SUB - 1) / RBIN_SUB);
-            if (r0) {
-                e = launch_zero(rb.ctl, sizeof(unsigned long long), s);  // staging cursor
-                if (e != hipSuccess)
-                    return e;
-            }
-            hipLaunchKernelGGL(k_rbin_count<P2>, dim3(rb.grid), dim3(BLOCK), 0, s, a, c1, t, rb);
-            hipLaunchKernelGGL(k_rbin_hist<P2>, dim3(rb.grid), dim3(BLOCK), 0, s, t, rb);
-            hipLaunchKernelGGL(k_rbin_scan, dim3(1), dim3(BIN_SCAN_BLOCK), 0, s, rb.counts,
-                               (uint64_t)rb.n_buckets * rb.grid, rb.offsets);
-            hipLaunchKernelGGL(k_rbin_scatter<P2>, dim3(rb.grid), dim3(BIN_SCATTER_BLOCK), 0, s, t,
-                               rb);
-            hipLaunchKernelGGL(k_rbin_split<P2>, dim3(rb.n_buckets), dim3(BIN_SPLIT_BLOCK), 0, s,
-                               t, rb);
-            hipLaunchKernelGGL(k_rbin_apply<P2>, dim3((uint32_t)(rb.r_hi - rb.r_lo)),
-                               dim3(BIN_APPLY_BLOCK), 0, s, t, rb, set_cnt, cnt);
-            e = hipGetLastError();
+            e = launch_zero(rb.cursor, rb.cursors * sizeof(unsigned long long), s);
             if (e != hipSuccess)
-                return e;
+                break;
+            const uint32_t grid =
+                (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(2ull * rb.n_cu, a.n_tiles));
+            hipLaunchKernelGGL(k_rbin_items<P2>, dim3(grid), dim3(RBIN_BLOCK), 0, s, a, c1, t, rb);
+            if (rb.sub_log2)
+                hipLaunchKernelGGL(
+                    k_rbin_split<P2>,
+                    dim3((uint32_t)((rb.room_a + BIN_BLOCK * RBIN_SPLIT_PER - 1) /
+                                    (BIN_BLOCK * RBIN_SPLIT_PER)), rb.n_buckets),
+                    dim3(BIN_BLOCK), 0, s, t, rb);
+            hipLaunchKernelGGL(k_rbin_apply<P2>, dim3((uint32_t)(rb.r_hi - rb.r_lo)),
+                               dim3(BIN_BLOCK), 0, s, t, rb, set_cnt, cnt);
+            e = hipGetLastError();
         }
-        return hipSuccess;
+        if (e != hipSuccess)
+            return e;
+        hipLaunchKernelGGL(k_rbin_spill<P2>, dim3(4 * rb.n_cu), dim3(BLOCK), 0, s, t, rb, set_cnt,
+                           cnt);
+        return hipGetLastError();
     };
     return t.pow2 ? run(std::true_type{}) : run(std::false_type{});
 }
@@ -838,7 +797,7 @@ __global__ __launch_bounds__(BLOCK) void k_decide(SeqArgs a, SentArgs sa, const 
     const uint32_t most = batch_tiles(a.n_tiles, gridDim.x);
     RunCursor rc = batch_run(a, (a.pass2_slabs & 2) != 0, max(a.chunk, most));
     uint32_t n, total, set;
-    while (next_batch(a, rc, most, c1, b, flag, &n, &total, &set)) {
+    while (next_batch<BLOCK>(a, rc, most, c1, b, flag, &n, &total, &set)) {
         const uint32_t jt = threadIdx.x / (TILE / 64);  // this thread's junction word: its tile
         uint64_t *const jdst = jbits + (jt < n ? b.tile[jt].t0 / 64 + threadIdx.x % (TILE / 64) : 0);
         if (b.skip) {

@@ -676,7 +676,7 @@ static uint64_t budget_slot_bytes(const tp_plan *p) {
 }
 
 std::vector<uint64_t> tp::table_caps(const tp_plan *p, const std::vector<double> &keys,
-                                     bool *pow2) {
+                                     bool *pow2, bool any_size) {
     const size_t nsets = keys.size();
     const double load = p->cfg.table_load;
     std::vector<uint64_t> exact(nsets), caps(nsets);
@@ -686,10 +686,14 @@ std::vector<uint64_t> tp::table_caps(const tp_plan *p, const std::vector<double>
         exact[i] = std::max((uint64_t)want, MIN_TABLE);
         waste += (pow2_ceil(exact[i]) - exact[i]) * 8;
     }
-    *pow2 = p->cfg.table_shape == 1 || (p->cfg.table_shape == 0 && waste <= POW2_WASTE_BYTES);
+    const bool round_up =
+        p->cfg.table_shape == 1 || (p->cfg.table_shape == 0 && waste <= POW2_WASTE_BYTES);
+    *pow2 = round_up && (p->cfg.table_shape == 1 || !any_size);
     for (size_t i = 0; i < nsets; ++i) {
         uint32_t m = 0, e = 0;
-        caps[i] = *pow2 ? pow2_ceil(exact[i]) : shape_table(exact[i], &m, &e);
+        caps[i] = round_up ? pow2_ceil(exact[i]) : exact[i];
+        if (!*pow2)
+            caps[i] = shape_table(caps[i], &m, &e);
     }
     return caps;
 }
@@ -956,14 +960,28 @@ static int bin_setup(tp_plan *p, BinArgs *b, uint32_t *chunk_tiles, uint32_t rou
     return TP_OK;
 }
 
-constexpr uint64_t RBIN_AUTO_BYTES = 1ull << 30;  // binned record by default from this table size
-constexpr uint32_t RBIN_AUTO_PASSES = 2;  // binned record by default: at most this many passes
+// Binned record by default from this table size (slots for the expected keys,
+// before rounding): direct and binned cost the same at four rounds of 20 Mbp
+// with tables of 64 MiB, which the last-level cache holds (0.71 ms direct,
+// 0.76 binned); 62 x 5 Mbp with 256 MiB 3.17 direct, 2.42 binned; 1.6 Gbp with
+// 4 GiB 17.1 direct, 9.1 binned (and 0.9 ms of table clear gone).
+constexpr uint64_t RBIN_AUTO_BYTES = 128ull << 20;
+// ... in at most this many passes: one more walk of the candidates takes about
+// a fifth of what the direct record does.
+constexpr uint32_t RBIN_AUTO_PASSES = 4;
 constexpr uint64_t RBIN_MEM_MARGIN = 1ull << 30;  // device bytes left free by its own scratch
 
+// Whether the run's table should be of any size, for the binned record: one
+// set with packed slots whose table is large enough for it by default.
+static bool rbin_wants(const tp_plan *p, bool packed, double keys) {
+    return p->cfg.record_binned != 1 && p->sets.size() == 1 && packed && !p->grow_hook &&
+           keys / p->cfg.table_load * 8 >= (double)RBIN_AUTO_BYTES;
+}
+
 // The binned record's scratch (tp_config.record_binned) for a one-set plan
-// with packed slots whose table has n_blocks home blocks: two arrays of
-// rb->cap items, and the passes they take (the fewest found): in the last
-// run's edge array (dead until the compaction), or in d_rbin, grown for
+// with packed slots whose table has n_blocks home blocks: the items of a pass
+// and the spilled ones, and the passes they take (the fewest found): in the
+// last run's edge array (dead until the compaction), or in d_rbin, grown for
 // record_passes passes (at least one) when the device has room.  By default
 // at most RBIN_AUTO_PASSES passes (any number when forced).  *use = false:
 // the record runs directly (also for plans of a server, which budgets their
@@ -974,26 +992,24 @@ static int rbin_setup(tp_plan *p, uint64_t candidates, uint64_t n_blocks, uint64
     const uint32_t mode = p->cfg.record_binned;
     if (mode == 1 || (mode == 0 && table_bytes < RBIN_AUTO_BYTES) || p->grow_hook)
         return TP_OK;
-    const uint32_t grid = (uint32_t)std::max<uint64_t>(
-        1, std::min<uint64_t>((uint64_t)BIN_WG_PER_CU * std::max<uint32_t>(1, p->n_cu),
-                              p->n_tiles));
-    const uint64_t slack = (uint64_t)grid * RBIN_SEG;  // partly filled staging segments
-    const uint64_t want = (uint64_t)((double)candidates * 1.05) + 1;  // items, all passes
     const uint64_t per_max = (uint64_t)RBIN_MAX_BUCKETS * RBIN_SUB;   // blocks per pass
     const uint64_t min_passes = std::max<uint64_t>(
         {1, p->cfg.record_passes, (n_blocks + per_max - 1) / per_max});
     const uint64_t max_passes = mode == 2 ? RBIN_MAX_PASSES : RBIN_AUTO_PASSES;
+    const uint32_t genomes = (uint32_t)p->n_bases.size();
+    auto shape = [&](uint64_t n) {
+        return rbin_shape(candidates, n_blocks, (n_blocks + n - 1) / n, genomes);
+    };
     auto passes_for = [&](uint64_t bytes) -> uint64_t {  // 0: too small
-        const uint64_t cap = bytes / 16;
-        if (cap <= slack)
-            return 0;
-        const uint64_t n = std::max(min_passes, (want + cap - slack - 1) / (cap - slack));
-        return n <= max_passes ? n : 0;
+        for (uint64_t n = min_passes; n <= max_passes; ++n)
+            if (shape(n).bytes <= bytes)
+                return n;
+        return 0;
     };
     if (min_passes > max_passes)
         return TP_OK;
-    // the fewest passes: the edge array, d_rbin as it is, or d_rbin grown
-    // for min_passes when the device has room
+    // the fewest passes: the edge array, d_rbin as it is, or d_rbin grown as
+    // far as the device has room
     DevBuf *buf = nullptr;
     uint64_t n = 0;
     for (DevBuf *b : {&p->d_edges, &p->d_rbin}) {
@@ -1004,42 +1020,41 @@ static int rbin_setup(tp_plan *p, uint64_t candidates, uint64_t n_blocks, uint64
         }
     }
     if (!n || n > min_passes) {
-        const uint64_t need = 16 * ((want + min_passes - 1) / min_passes + slack);
         size_t free_b = 0, total_b = 0;
         HIPCHK(hipMemGetInfo(&free_b, &total_b));
-        if (need + RBIN_MEM_MARGIN <= free_b + p->d_rbin.cap) {
+        for (uint64_t m = min_passes; m <= max_passes && (!n || m < n); ++m) {
+            const uint64_t need = shape(m).bytes;
+            if (need + RBIN_MEM_MARGIN > free_b + p->d_rbin.cap)
+                continue;
             if (p->d_rbin.ensure(need) == hipSuccess) {
-                n = passes_for(p->d_rbin.cap);
+                n = m;
                 buf = &p->d_rbin;
             } else {
                 (void)hipGetLastError();  // not kept: as found, or the record runs directly
                 n = passes_for(p->d_edges.cap);
                 buf = &p->d_edges;
             }
+            break;
         }
     }
     if (!n)
         return TP_OK;
     const uint64_t per_pass = (n_blocks + n - 1) / n;
+    const RecBinShape sh = shape(n);
     n = (n_blocks + per_pass - 1) / per_pass;  // the passes the blocks take
-    const uint64_t nbk = (per_pass + RBIN_SUB - 1) / RBIN_SUB;
-    const uint64_t o_off = align_up(nbk * grid * 4, 256);
-    const uint64_t o_reg = o_off + align_up((nbk * grid + 1) * 8, 256);
-    const uint64_t o_ctl = o_reg + align_up((nbk * RBIN_SUB + 1) * 8, 256);
-    if (p->d_bin.ensure(o_ctl + 256) != hipSuccess) {
-        (void)hipGetLastError();
-        return TP_OK;
-    }
     *rb = RecBinArgs{};
-    rb->cap = buf->cap / 16;
-    rb->items_a = buf->as<uint64_t>();
-    rb->items_b = rb->items_a + rb->cap;
-    uint8_t *m = p->d_bin.as<uint8_t>();
-    rb->counts = (uint32_t *)m;
-    rb->offsets = (uint64_t *)(m + o_off);
-    rb->region_off = (uint64_t *)(m + o_reg);
-    rb->ctl = (unsigned long long *)(m + o_ctl);
-    rb->grid = grid;
+    rb->ctl = buf->as<unsigned long long>();
+    rb->cursor = rb->ctl + 32;
+    rb->items_a = (uint64_t *)rb->cursor + sh.cursors;
+    rb->items_b = rb->items_a + sh.n_buckets * sh.room_a;
+    rb->spill = rb->items_b + ((uint64_t)sh.n_buckets << sh.sub_log2) * sh.room_b;
+    rb->room_a = sh.room_a;
+    rb->room_b = sh.room_b;
+    rb->spill_cap = sh.spill;
+    rb->cursors = sh.cursors;
+    rb->sub_log2 = sh.sub_log2;
+    rb->n_buckets = sh.n_buckets;
+    rb->n_cu = std::max<uint32_t>(1, p->n_cu);
     *passes = (uint32_t)n;
     *use = true;
     return TP_OK;
@@ -1406,7 +1421,8 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
                 keys[i] = a.sketch ? std::min(c, est * 1.15) : c;
             }
             bool pow2 = true;
-            const std::vector<uint64_t> caps = table_caps(p, keys, &pow2);
+            const std::vector<uint64_t> caps =
+                table_caps(p, keys, &pow2, rbin_wants(p, packed, keys[0]));
             p->table_pow2 = pow2;
             for (uint32_t i = 0; i < nsets; ++i)
                 p->sets[i].table_cap = caps[i];

@@ -788,53 +788,51 @@ hipError_t launch_fill_binned(int W, const SeqArgs &a, const BloomArgs &pool, Co
 
 // --------------------------------------------------------------- query (a2)
 
-// Standard layout: membership of the six neighbour (k+1)-mers, probed level
-// by level.  True when some neighbour has all h bits set.
-template <class T>
+// Standard layout: membership of the six neighbour (k+1)-mers, N of them at a
+// time, those probed level by level.  True when some neighbour has all h bits
+// set (the neighbours after it are then not probed).
+template <uint32_t N, class T>
 __device__ __forceinline__ bool any_present_standard(const BloomArgs &f, const Strands<T> &st,
                                                      uint32_t k, uint32_t pa, uint32_t sb,
                                                      bool single, uint32_t &probes) {
-    uint64_t h1[6], h2[6];
+    for (uint32_t i0 = 0; i0 < 6; i0 += N) {
+        uint64_t h1[N], h2[N];
 #pragma unroll
-    for (uint32_t j = 0; j < 3; ++j) {
-        // out-neighbour v.c for the j-th base c other than the successor
-        const uint32_t c = j + (j >= sb);
-        Strands<T> o;
-        o.fwd = (st.fwd << 2) | (T)c;
-        o.rc = st.rc | ((T)(3 - c) << (2 * k));
-        const BloomHash bo = bloom_hash(norm(o, single));
-        h1[j] = bo.h1;
-        h2[j] = bo.h2;
-        // in-neighbour d.v for the j-th base d other than the predecessor
-        const uint32_t d = j + (j >= pa);
-        Strands<T> n;
-        n.fwd = ((T)d << (2 * k)) | st.fwd;
-        n.rc = (st.rc << 2) | (T)(3 - d);
-        const BloomHash bn = bloom_hash(norm(n, single));
-        h1[3 + j] = bn.h1;
-        h2[3 + j] = bn.h2;
-    }
-    uint32_t alive = 0x3F;
-    for (uint32_t t = 0; t < f.h; ++t) {
-        probes += __popc(alive);
-        uint32_t v[6];
-        uint32_t b[6];
-#pragma unroll
-        for (int n = 0; n < 6; ++n) {
-            const uint64_t idx = (h1[n] + (uint64_t)t * h2[n]) & f.mask;
-            b[n] = (uint32_t)(idx & 31);
-            v[n] = ((alive >> n) & 1u) ? __hip_atomic_load(&f.words[idx >> 5], __ATOMIC_RELAXED,
-                                                            __HIP_MEMORY_SCOPE_AGENT)
-                                        : 0u;
+        for (uint32_t i = 0; i < N; ++i) {
+            // out-neighbour v.c for the j-th base c other than the successor,
+            // in-neighbour c.v for the j-th other than the predecessor
+            const uint32_t j = (i0 + i) >> 1;
+            const bool out = ((i0 + i) & 1) == 0;
+            const uint32_t c = j + (j >= (out ? sb : pa));
+            Strands<T> e;
+            e.fwd = out ? (T)((st.fwd << 2) | (T)c) : (T)(((T)c << (2 * k)) | st.fwd);
+            e.rc = out ? (T)(st.rc | ((T)(3 - c) << (2 * k))) : (T)((st.rc << 2) | (T)(3 - c));
+            const BloomHash bh = bloom_hash(norm(e, single));
+            h1[i] = bh.h1;
+            h2[i] = bh.h2;
         }
+        uint32_t alive = (1u << N) - 1;
+        for (uint32_t t = 0; t < f.h && alive; ++t) {
+            probes += __popc(alive);
+            uint32_t v[N];
+            uint32_t b[N];
 #pragma unroll
-        for (int n = 0; n < 6; ++n)
-            if (!((v[n] >> b[n]) & 1u))
-                alive &= ~(1u << n);
-        if (!alive)
-            return false;
+            for (uint32_t n = 0; n < N; ++n) {
+                const uint64_t idx = (h1[n] + (uint64_t)t * h2[n]) & f.mask;
+                b[n] = (uint32_t)(idx & 31);
+                v[n] = ((alive >> n) & 1u) ? __hip_atomic_load(&f.words[idx >> 5], __ATOMIC_RELAXED,
+                                                                __HIP_MEMORY_SCOPE_AGENT)
+                                            : 0u;
+            }
+#pragma unroll
+            for (uint32_t n = 0; n < N; ++n)
+                if (!((v[n] >> b[n]) & 1u))
+                    alive &= ~(1u << n);
+        }
+        if (alive)
+            return true;
     }
-    return true;
+    return false;
 }
 
 // Value of the lane below (DPP wave shift right by one); lane 0 gets lane0.
@@ -1105,9 +1103,15 @@ void k_query_blocked(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint6
 // base by base with the staged sequence, is not probed again.  62 x 5 Mbp,
 // b = 2^30, k = 25: 3.30 G words and 41.1 ms without the table, 1.99 G and 31.4
 // with 8 tiles (512 threads, 8192 windows), 1.62 G and 25.7 with 16 (1024,
-// 16384), 1.50 G and 24.4 with 32.
+// 16384), 1.50 G and 24.4 with 32; 1.44 G and 23.5 with a tile's windows looked
+// up before any is probed, and 19.8 with the neighbours probed two at a time.
 constexpr uint32_t QS_TILES = 32, QS_BLOCK = 1024, QS_SEEN = 16384;
 constexpr uint32_t QS_NONE = ~0u;
+// Neighbours probed at once: a present one ends the test, so fewer words the
+// fewer at once (half the positions are candidates there: 23.5 ms with all six,
+// 20.7 with three, 19.8 with two, 19.1 with one), but a longer chain of loads
+// (8 x 5 Mbp 2.48, -, 2.37, 2.40).
+constexpr uint32_t QS_AT_ONCE = 2;
 
 // Inputs of fewer tiles than this take the plain form: a tile (or a part of
 // one) to a workgroup of 256 threads, no table.
@@ -1128,23 +1132,105 @@ __device__ __forceinline__ T seen_window(const Stage &sg, uint32_t r, uint32_t k
     return up_from<T>(sg, r - 1) & KT<T>::ones(2 * k + 2);
 }
 
-template <class T, bool CLASSES, bool SEEN>
-__global__ __launch_bounds__(SEEN ? QS_BLOCK : BLOCK)
+// The verdict on the k-mer at r of a staged tile, at an end of its string or
+// within it; its hash to *hash when it was of the round's class.
+template <uint32_t N, bool CLASSES, class T>
+__device__ __forceinline__ bool standard_mark(const SeqArgs &a, const SentArgs &sa,
+                                              const QueryShared &qs, const TileSet &ts,
+                                              const Stage &sg, uint32_t r, bool end,
+                                              uint64_t *hash, uint32_t &probes) {
+    uint32_t pa, sb;
+    const bool single = a.single != 0;
+    const Strands<T> st = kmer_between<T>(sg, r, a.k, &pa, &sb);
+    const T canon = norm(st, single);
+    if (CLASSES && !in_class(class_subrange(canon), ts.cls_lo, ts.cls_hi))
+        return false;
+    *hash = slot_hash(canon);
+    return end ||
+           (ts.sent_log2 && prefilter_hit(qs.pf, prefilter_bit(*hash, sa.pf_log2)) &&
+            in_sentinels(canon, (const T *)sa.table + ts.sent_off, ts.sent_log2)) ||
+           any_present_standard<N>(ts.f, st, a.k, pa, sb, single, probes);
+}
+
+__device__ __forceinline__ void standard_sketch(QueryShared &qs, uint64_t hash) {
+    const uint64_t rest = hash << HLL_LOG2;
+    const uint32_t rank = rest ? (uint32_t)__clzll(rest) + 1 : 64 - HLL_LOG2 + 1;
+    atomicMax(&qs.hll[(uint32_t)(hash >> (64 - HLL_LOG2))], rank);
+}
+
+template <class T, bool CLASSES>
+__global__ __launch_bounds__(BLOCK)
 void k_query_standard(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint64_t *c1u,
                       uint32_t round, Counters *cnt, uint32_t *hll_out) {
-    constexpr uint32_t NT = SEEN ? QS_BLOCK : BLOCK, TILES = SEEN ? QS_TILES : 1;
-    __shared__ Stage sg[TILES];
-    __shared__ QsTile tl[TILES];
-    __shared__ uint32_t tset[TILES];
-    __shared__ uint32_t seen[SEEN ? QS_SEEN : 1];  // hash bits << 17 | verdict << 16 | tile << 11 | position
+    __shared__ Stage sg;
     __shared__ QueryShared qs;
     SetSum cand = setsum_begin();
     const uint32_t k = a.k;
-    const bool single = a.single != 0;
-    const T *sent = (const T *)sa.table;
-    const uint32_t lane = threadIdx.x & 63;
-    query_begin<NT>(qs, sa.prefilter, sa.pf_log2);
+    query_begin<BLOCK>(qs, sa.prefilter, sa.pf_log2);
     uint32_t my_probes = 0;
+    const Part part = tile_part(a);
+    RunCursor rc = run_cursor(a, a.chunk);
+    for (uint64_t tile; run_next(a, rc, &tile);) {
+        const uint64_t t0 = tile * TILE;
+        const TileInfo ti = a.tiles[tile];
+        const uint32_t lo = ti.str_lo, hi = ti.str_hi;
+        if (lo == hi) {
+            query_no_string(tile, c1, c1u, round);
+            continue;
+        }
+        __syncthreads();
+        stage_tile(a, tile, sg);
+        __syncthreads();
+        const TileSet ts = tile_set_of(a, pool, ti.set);
+        setsum_switch(cand, ts.set, &qs.cand_lds, &a.set_cnt[0].candidates, SETCNT_STRIDE);
+        const Span one = lo + 1 == hi ? span_of(a.strings, lo, t0) : Span{0, -1};
+        for (uint32_t q = part.lo * BLOCK + threadIdx.x; q < part.hi * BLOCK; q += BLOCK) {
+            const Span sp = lo + 1 == hi ? one : span_at(a.strings, lo, hi, t0, q);
+            bool mark = false;
+            uint64_t hash = 0;
+            if ((int32_t)q >= sp.gs && (int32_t)(q + k) <= sp.ge)
+                mark = standard_mark<6, CLASSES, T>(a, sa, qs, ts, sg, q + 32,
+                                                 (int32_t)q == sp.gs || (int32_t)(q + k) == sp.ge,
+                                                 &hash, my_probes);
+            const uint64_t word = ballot64(mark);
+            if ((threadIdx.x & 63) == 0) {
+                const uint64_t i = (t0 + q) >> 6;
+                c1[i] = word;
+                if (c1u)
+                    c1u[i] = round ? c1u[i] | word : word;
+                cand.v += (unsigned long long)__popcll(word);
+            }
+            if (a.sketch && mark)
+                standard_sketch(qs, hash);
+        }
+    }
+    query_end<BLOCK>(a, qs, cand, my_probes, cnt, hll_out);
+}
+
+// With the table.  A tile in two steps: every position looks its window up,
+// those not found go to a list; then the lanes walk the list.  (Probed where
+// the look-up failed, most lanes of every wave waited for a few.)
+template <class T, bool CLASSES>
+__global__ __launch_bounds__(QS_BLOCK)
+void k_query_standard_seen(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint64_t *c1u,
+                           uint32_t round, Counters *cnt, uint32_t *hll_out) {
+    constexpr uint32_t NT = QS_BLOCK, TILES = QS_TILES, AT_END = 1u << 31;
+    __shared__ Stage sg[TILES];
+    __shared__ QsTile tl[TILES];
+    __shared__ uint32_t tset[TILES];
+    __shared__ uint32_t seen[QS_SEEN];  // hash bits << 17 | verdict << 16 | tile << 11 | position
+    __shared__ QueryShared qs;
+    __shared__ uint16_t todo[TILE];     // positions of the tile to decide
+    __shared__ uint32_t todo_x[TILE];   // their windows: hash bits << 14 | place in seen, or AT_END
+    // by the tile's parity in its batch: its candidate words, the positions in todo
+    __shared__ uint64_t words[2][TILE / 64];
+    __shared__ uint32_t n_todo[2];
+    SetSum cand = setsum_begin();
+    const uint32_t k = a.k, lane = threadIdx.x & 63;
+    query_begin<NT>(qs, sa.prefilter, sa.pf_log2);
+    if (threadIdx.x < 2)
+        n_todo[threadIdx.x] = 0;
+    uint32_t my_probes = 0, par = 0;
     // as many tiles as leave every workgroup a few batches
     const uint64_t per = a.n_tiles / (4ull * gridDim.x);
     const uint32_t most = per < 1 ? 1u : per > TILES ? TILES : (uint32_t)per;
@@ -1167,9 +1253,8 @@ void k_query_standard(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint
             tl[threadIdx.x] = t;
             tset[threadIdx.x] = ti.set;
         }
-        if (SEEN)
-            for (uint32_t i = threadIdx.x; i < QS_SEEN; i += NT)
-                seen[i] = QS_NONE;
+        for (uint32_t i = threadIdx.x; i < QS_SEEN; i += NT)
+            seen[i] = QS_NONE;
         __syncthreads();
         const uint32_t set = tset[0];  // tiles of one set (a verdict is of its filter)
         uint32_t n = 1;
@@ -1184,65 +1269,72 @@ void k_query_standard(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint
         const TileSet ts = tile_set_of(a, pool, set);
         setsum_switch(cand, set, &qs.cand_lds, &a.set_cnt[0].candidates, SETCNT_STRIDE);
         __syncthreads();
-        for (uint32_t j = 0; j < n; ++j) {
+        for (uint32_t j = 0; j < n; ++j, par ^= 1) {
             const QsTile &t = tl[j];
             for (uint32_t q = part.lo * BLOCK + threadIdx.x; q < part.hi * BLOCK; q += NT) {
                 const Span sp = t.lo + 1 == t.hi   ? t.sp
                                 : t.lo == t.hi     ? Span{0, -1}
                                                    : span_at(a.strings, t.lo, t.hi, t.t0, q);
-                bool mark = false, sketch = false;
-                uint64_t hash = 0;
+                bool mark = false, ask = false;
+                uint32_t x = AT_END;
                 if ((int32_t)q >= sp.gs && (int32_t)(q + k) <= sp.ge) {
-                    const bool end = (int32_t)q == sp.gs || (int32_t)(q + k) == sp.ge;
-                    uint32_t at = 0, tag = 0, found = QS_NONE;
-                    if (SEEN && !end) {
+                    ask = true;
+                    if ((int32_t)q != sp.gs && (int32_t)(q + k) != sp.ge) {
                         uint32_t sb;
                         const T w = seen_window<T>(sg[j], q + 32, k, &sb);
-                        const uint64_t x = (KT<T>::mixed(w) + sb) * 0x9E3779B97F4A7C15ull;
-                        at = (uint32_t)(x >> 50);
-                        tag = (uint32_t)(x >> 34) & 0x7FFFu;
-                        static_assert(QS_SEEN == 1u << 14, "table index bits");
-                        const uint32_t e = seen[at];
-                        if (e >> 17 == tag && e != QS_NONE) {
+                        x = (uint32_t)(((KT<T>::mixed(w) + sb) * 0x9E3779B97F4A7C15ull) >> 35);
+                        static_assert(QS_SEEN == 1u << 14, "29 bits: 15 compared, 14 the place");
+                        const uint32_t e = seen[x & (QS_SEEN - 1)];
+                        if (e >> 17 == x >> 14 && e != QS_NONE) {
                             uint32_t sb2;
                             if (seen_window<T>(sg[e >> 11 & 31u], (e & (TILE - 1)) + 32, k, &sb2) == w &&
-                                sb2 == sb)
-                                found = e;
+                                sb2 == sb) {
+                                ask = false;
+                                mark = (e >> 16) & 1u;
+                            }
                         }
-                    }
-                    if (found != QS_NONE) {
-                        mark = (found >> 16) & 1u;
-                    } else {
-                        uint32_t pa, sb;
-                        const Strands<T> st = kmer_between<T>(sg[j], q + 32, k, &pa, &sb);
-                        const T canon = norm(st, single);
-                        if (!CLASSES || in_class(class_subrange(canon), ts.cls_lo, ts.cls_hi)) {
-                            hash = slot_hash(canon);
-                            mark = end ||
-                                   (ts.sent_log2 &&
-                                    prefilter_hit(qs.pf, prefilter_bit(hash, sa.pf_log2)) &&
-                                    in_sentinels(canon, sent + ts.sent_off, ts.sent_log2)) ||
-                                   any_present_standard(ts.f, st, k, pa, sb, single, my_probes);
-                        }
-                        if (SEEN && !end)
-                            seen[at] = tag << 17 | (mark ? 1u : 0u) << 16 | j << 11 | q;
-                        sketch = mark && a.sketch;  // (a found window's k-mer is in it already)
                     }
                 }
-                const uint64_t word = ballot64(mark);
+                const uint64_t word = ballot64(mark), asks = ballot64(ask);
+                uint32_t at = 0;
                 if (lane == 0) {
-                    const uint64_t i = (t.t0 + q) >> 6;
-                    c1[i] = word;
-                    if (c1u)
-                        c1u[i] = round ? c1u[i] | word : word;
-                    cand.v += (unsigned long long)__popcll(word);
+                    words[par][q >> 6] = word;
+                    if (asks)
+                        at = atomicAdd(&n_todo[par], (uint32_t)__popcll(asks));
                 }
-                if (sketch) {
-                    const uint64_t rest = hash << HLL_LOG2;
-                    const uint32_t rank = rest ? (uint32_t)__clzll(rest) + 1 : 64 - HLL_LOG2 + 1;
-                    atomicMax(&qs.hll[(uint32_t)(hash >> (64 - HLL_LOG2))], rank);
+                at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) +
+                     __builtin_amdgcn_mbcnt_hi((uint32_t)(asks >> 32),
+                                               __builtin_amdgcn_mbcnt_lo((uint32_t)asks, 0));
+                if (ask) {
+                    todo[at] = (uint16_t)q;
+                    todo_x[at] = x;
                 }
             }
+            __syncthreads();  // the list and the words are whole
+            const uint32_t n_ask = n_todo[par];
+            for (uint32_t i = threadIdx.x; i < n_ask; i += NT) {
+                const uint32_t q = todo[i], x = todo_x[i];
+                uint64_t hash = 0;
+                const bool mark = standard_mark<QS_AT_ONCE, CLASSES, T>(a, sa, qs, ts, sg[j], q + 32,
+                                                            x == AT_END, &hash, my_probes);
+                if (x != AT_END)
+                    seen[x & (QS_SEEN - 1)] = x >> 14 << 17 | (mark ? 1u : 0u) << 16 | j << 11 | q;
+                if (mark) {
+                    atomicOr((uint32_t *)words[par] + (q >> 5), 1u << (q & 31u));
+                    if (a.sketch)  // (a found window's k-mer is in it already)
+                        standard_sketch(qs, hash);
+                }
+            }
+            __syncthreads();  // (the next tile's step one reads the verdicts)
+            if (threadIdx.x >= part.lo * (BLOCK / 64) && threadIdx.x < part.hi * (BLOCK / 64)) {
+                const uint64_t i = t.t0 / 64 + threadIdx.x, word = words[par][threadIdx.x];
+                c1[i] = word;
+                if (c1u)
+                    c1u[i] = round ? c1u[i] | word : word;
+                cand.v += (unsigned long long)__popcll(word);
+            }
+            if (threadIdx.x == 0)
+                n_todo[par] = 0;
         }
     }
     query_end<NT>(a, qs, cand, my_probes, cnt, hll_out);
@@ -1257,10 +1349,9 @@ hipError_t launch_query(int W, const SeqArgs &a, const BloomArgs &pool, const Se
         using T = decltype(tag);
         const bool seen = !pool.blocked && query_seen(a.n_tiles);
         auto *fn = pool.blocked ? (a.classes ? k_query_blocked<T, true> : k_query_blocked<T, false>)
-                   : seen ? (a.classes ? k_query_standard<T, true, true>
-                                       : k_query_standard<T, false, true>)
-                          : (a.classes ? k_query_standard<T, true, false>
-                                       : k_query_standard<T, false, false>);
+                   : seen ? (a.classes ? k_query_standard_seen<T, true>
+                                       : k_query_standard_seen<T, false>)
+                          : (a.classes ? k_query_standard<T, true> : k_query_standard<T, false>);
         hipLaunchKernelGGL(fn, dim3(grid), dim3(seen ? QS_BLOCK : BLOCK), 0, s, a, pool, sa, c1, c1u,
                            round, cnt, hll);
         return hipGetLastError();
@@ -1405,8 +1496,8 @@ hipError_t pass1_occupancy(KernelId which, int W, bool blocked, bool fill_dedup,
             which == K_FILL
                 ? (blocked ? (const void *)k_fill<T, true> : (const void *)k_fill<T, false>)
             : blocked ? (const void *)k_query_blocked<T, false>
-            : seen    ? (const void *)k_query_standard<T, false, true>
-                      : (const void *)k_query_standard<T, false, false>;
+            : seen    ? (const void *)k_query_standard_seen<T, false>
+                      : (const void *)k_query_standard<T, false>;
         const size_t dyn = which == K_FILL && blocked && fill_dedup
                                ? FILL_DD * sizeof(unsigned long long) : 0;
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(

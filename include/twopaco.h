@@ -367,8 +367,9 @@ typedef struct {
                               steps (more than 512 blocks), in the last run's
                               edge array (dead until the compaction) or in a
                               buffer of its own when the device has room
-                              (1 GiB left free; kept by the plan until its
-                              outputs must grow); else, and for plans of a
+                              (1 GiB left free, and with 0 at most a quarter
+                              of the free memory taken; kept by the plan
+                              until its outputs must grow); else, and for plans of a
                               server, the record runs directly, as it does
                               on caller memory (tp_run_ws, tp_run_noalloc),
                               and where a few k-mers make up so many of the

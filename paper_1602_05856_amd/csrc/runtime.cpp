@@ -966,8 +966,8 @@ static int bin_setup(tp_plan *p, BinArgs *b, uint32_t *chunk_tiles, uint32_t rou
 // 0.76 binned); 62 x 5 Mbp with 256 MiB 3.17 direct, 2.42 binned; 1.6 Gbp with
 // 4 GiB 17.1 direct, 9.1 binned (and 0.9 ms of table clear gone).
 constexpr uint64_t RBIN_AUTO_BYTES = 128ull << 20;
-// ... in at most this many passes: one more walk of the candidates takes about
-// a fifth of what the direct record does.
+// ... in at most this many passes (6 Gbp in two 150 ms direct, 102 binned; 12 Gbp
+// in three 301 and 259; 24 Gbp takes six).
 constexpr uint32_t RBIN_AUTO_PASSES = 4;
 constexpr uint64_t RBIN_MEM_MARGIN = 1ull << 30;  // device bytes left free by its own scratch
 
@@ -982,8 +982,9 @@ static bool rbin_wants(const tp_plan *p, bool packed, double keys) {
 // with packed slots whose table has n_blocks home blocks: the items of a pass
 // and the spilled ones, and the passes they take (the fewest found): in the
 // last run's edge array (dead until the compaction), or in d_rbin, grown for
-// record_passes passes (at least one) when the device has room.  By default
-// at most RBIN_AUTO_PASSES passes (any number when forced).  *use = false:
+// record_passes passes (at least one) when the device has room (by default
+// up to a quarter of it: other plans need theirs).  By default at most
+// RBIN_AUTO_PASSES passes (any number when forced).  *use = false:
 // the record runs directly (also for plans of a server, which budgets their
 // memory).
 static int rbin_setup(tp_plan *p, uint64_t candidates, uint64_t n_blocks, uint64_t table_bytes,
@@ -1023,8 +1024,8 @@ static int rbin_setup(tp_plan *p, uint64_t candidates, uint64_t n_blocks, uint64
         size_t free_b = 0, total_b = 0;
         HIPCHK(hipMemGetInfo(&free_b, &total_b));
         for (uint64_t m = min_passes; m <= max_passes && (!n || m < n); ++m) {
-            const uint64_t need = shape(m).bytes;
-            if (need + RBIN_MEM_MARGIN > free_b + p->d_rbin.cap)
+            const uint64_t need = shape(m).bytes, room = free_b + p->d_rbin.cap;
+            if (need + RBIN_MEM_MARGIN > room || (mode == 0 && need > room / 4))
                 continue;
             if (p->d_rbin.ensure(need) == hipSuccess) {
                 n = m;

@@ -877,24 +877,22 @@ def profile_requests(tag, pmc_dir, command):
     import csv
     agg = collections.defaultdict(lambda: collections.defaultdict(list))
     for r in csv.DictReader(open(os.path.join(pmc_dir, "run_counter_collection.csv"))):
-        for pat, _ in PROFILE_KERNELS:
-            if "tp::" + pat + "<" in r["Kernel_Name"] or "tp::" + pat + "(" in r["Kernel_Name"]:
-                agg[pat][r["Counter_Name"]].append(float(r["Counter_Value"]))
+        name = r["Kernel_Name"].partition("tp::")[2].partition("<")[0].partition("(")[0]
+        if name.startswith(tuple(pat for pat, _ in PROFILE_KERNELS)):
+            agg[name][r["Counter_Name"]].append(float(r["Counter_Value"]))
     lines = ["# L2-to-fabric read requests by size: %s" % tag, "",
              "Command (from the repository root; rocprofv3 runs from /tmp with TMPDIR=/tmp):",
              "", "```", command, "```", "", "Per launch (average over the launches of the run):",
              "", "| kernel | EA read requests | of which 32 B | L2 hits | L2 misses | L2 hit rate "
              "| requests x 64 B (GB) |", "|---|---|---|---|---|---|---|"]
     any32 = 0.0
-    for pat, _ in PROFILE_KERNELS:
-        if pat not in agg:
-            continue
-        c = {n: sum(v) / len(v) for n, v in agg[pat].items()}
+    for name, counters in agg.items():
+        c = {n: sum(v) / len(v) for n, v in counters.items()}
         req, r32 = c.get("TCC_EA0_RDREQ_sum", 0.0), c.get("TCC_EA0_RDREQ_32B_sum", 0.0)
         hit, miss = c.get("TCC_HIT_sum", 0.0), c.get("TCC_MISS_sum", 0.0)
         any32 += r32
         lines.append("| %s | %.3g | %.3g | %.3g | %.3g | %.0f%% | %.2f |" % (
-            pat, req, r32, hit, miss, 100 * hit / max(1.0, hit + miss), req * 64 / 1e9))
+            name, req, r32, hit, miss, 100 * hit / max(1.0, hit + miss), req * 64 / 1e9))
     lines += ["", ("No kernel issues a 32-byte read request, so a random word access moves at "
                    "least 64 bytes: the granule of the algorithmic byte model." if any32 == 0 else
                    "Some kernels issue 32-byte read requests (column 3).")]

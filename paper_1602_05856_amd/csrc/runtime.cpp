@@ -1292,7 +1292,7 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
                                   {&p->d_pos, &p->d_vertex, &p->d_strand, &p->d_edges}, s);
         if (rcb)
             return rcb;
-        bin.popcount = nsets == 1 ? scnt : nullptr;
+        bin.popcount = binned && nsets == 1 ? scnt : nullptr;  // (the atomic fill counts no bits)
     }
 
     // tile queues of the four tile kernels (tp_config.tile_queue)

@@ -888,6 +888,13 @@ static uint64_t bin_cursors(const BinArgs &b) {
     return b.n_buckets + (b.bucket_log2 != b.region_log2 ? b.n_regions : 0u);
 }
 
+// The items' places in the key buffer (again before each round: the table of
+// the round before may have grown, and so moved, the buffer).
+static void bin_place(const tp_plan *p, BinArgs *b) {
+    b->items_a = p->d_keys.as<uint32_t>();
+    b->items_b = b->items_a + p->bin_off.back();
+}
+
 // The binned fill's scratch: items in the exact table's key buffer (dead
 // during the first pass), cursors in d_bin, the bins' room in d_bin_room
 // (laid out again when the layout, the chunk size or the rounds change).
@@ -943,8 +950,7 @@ static int bin_setup(tp_plan *p, BinArgs *b, uint32_t *chunk_tiles, uint32_t rou
         p->bin_tiles = tiles;
         p->bin_rounds = rounds;
     }
-    b->items_a = p->d_keys.as<uint32_t>();
-    b->items_b = b->items_a + items_a;
+    bin_place(p, b);
     b->cursor = p->d_bin.as<unsigned long long>();
     b->off = p->d_bin_room.as<uint64_t>();
     b->roff = b->off + n_off;
@@ -1368,11 +1374,13 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
         }
         // timed kernels, launched directly between their events
         HIPCHK(hipEventRecord(p->ev[1], s));
-        if (binned)
+        if (binned) {
+            bin_place(p, &bin);
             HIPCHK(launch_fill_binned(W, a, pool, cnt, bin, bin_tiles, s));
-        else
+        } else {
             HIPCHK(launch_fill(W, with_queue(a, qbase, K_FILL, p->grid[K_FILL]), pool, cnt,
                                p->grid[K_FILL].n, s));
+        }
         HIPCHK(hipEventRecord(p->ev[2], s));
         HIPCHK(launch_query(W, with_queue(a, qbase, K_QUERY, p->grid[K_QUERY]), pool, sa,
                             p->d_c1.as<uint64_t>(),

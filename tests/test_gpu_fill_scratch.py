@@ -42,3 +42,22 @@ def test_refused_scratch_counts_the_filter_bits():
     assert res.stats["bloom_popcount"] == bits
     assert res.stats["candidates"] == want.stats["candidates"]
     assert np.array_equal(res.junction_pos, want.junction_pos)
+
+
+@pytest.mark.parametrize("h, flags", [(4, BLOCKED), (1, 0)])
+def test_scratch_moved_by_a_rounds_table(h, flags):
+    """The items lie in the exact table's buffer.  Where every position is a
+    candidate a round's table outgrows them and moves the buffer, and the next
+    round's fill has to follow."""
+    r = synth.rng(32, h)
+    gs = to_genomes([synth.random_bases(r, 1_000_003) for _ in range(3)])
+    a = run_plan(gs, 25, 1 << 22, h, flags, rounds=3, fill_binned=1)
+    b = run_plan(gs, 25, 1 << 22, h, flags, rounds=3, fill_binned=2)
+    st = b[0]
+    assert st["fill_chunks"] == 1 and a[0]["fill_chunks"] == 0
+    items = 4 * (1 if flags else h) * 2.5 / 3 * 1.1 * st["positions"]
+    assert 8 * st["table_capacity"] > items, "the table did not outgrow the items"
+    assert np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
+    assert st["bloom_popcount"] == a[0]["bloom_popcount"]
+    for f in ("junction_pos", "vertex", "strand", "edges"):
+        assert np.array_equal(getattr(a[3], f), getattr(b[3], f)), f

@@ -306,6 +306,17 @@ struct tp_plan {
 
     ~tp_plan() {
         drop_graphs();
+        if (mail_busy) {
+            // a run that failed before its wait: its kernels and copies may
+            // still read the block, which the next owner of it would write
+            int dev = 0;
+            const bool other = hipGetDevice(&dev) == hipSuccess && dev != device;
+            if (other)
+                (void)hipSetDevice(device);
+            (void)hipDeviceSynchronize();
+            if (other)
+                (void)hipSetDevice(dev);
+        }
         tp::host_free(mail);
         if (cap)
             (void)hipStreamDestroy(cap);

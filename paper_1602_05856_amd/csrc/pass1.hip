@@ -849,11 +849,17 @@ __device__ __forceinline__ uint64_t lane63(uint64_t x) {
            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, 63);
 }
 
-// A middle's key as lanes pass it on: offset a (bits 0-5), (d >> 1) << 7 (the
-// byte offset of its stride's masks in pm) and the orientation (bits 12-13).
-__device__ __forceinline__ uint32_t pack_key(const MiddleKey &m) {
-    return ((uint32_t)m.g & 0xFBFu) | m.orient << 12;
+// A flag of the lane below (mask: the lanes that have it), lane 0 the one
+// carried; the mask's top bit carries on to the next step.
+__device__ __forceinline__ bool flag_below(uint64_t mask, uint32_t &carry) {
+    const uint64_t below = mask << 1 | carry;
+    carry = (uint32_t)(mask >> 63);
+    return __builtin_amdgcn_inverse_ballot_w64(below);
 }
+
+// What lanes pass on of a middle is its G, whose low word holds the key (offset
+// a in bits 0-5; d >> 1 in bits 7-11, the byte offset of its stride's masks in
+// pm), and its orientation as two flags.
 constexpr uint32_t KEY_STRIDE = 0xF80u;
 
 // w rotated right by s (mod 64).
@@ -878,13 +884,12 @@ __device__ __forceinline__ uint32_t lacking(const uint64_t *pm, uint32_t at, uin
 }
 
 // Whether some edge x.m.c (OUT) or c.m.y (in) other than the actual x.m.y is
-// present in the middle's rotated block w.  Palindromic middles (orientation
-// 2) take each edge's own orientation.
+// present in the middle's rotated block w.  Palindromic middles take each
+// edge's own orientation.
 template <bool OUT>
-__device__ __forceinline__ uint32_t others_lacking(const uint64_t *pm, uint32_t key, uint64_t w,
-                                                   uint32_t x, uint32_t y) {
+__device__ __forceinline__ uint32_t others_lacking(const uint64_t *pm, uint32_t key, bool rev,
+                                                   uint64_t w, uint32_t x, uint32_t y) {
     const uint32_t base = key & KEY_STRIDE;
-    const bool rev = (key >> 12) == 1;
     const uint32_t pair = rev ? (15u - 4 * y - x) : (4 * x + y);
     const uint32_t at = base | pair << 3;
     // the varied base sits in the pair's low two bits, or its high two
@@ -912,6 +917,14 @@ struct QueryShared {
     uint32_t hll[HLL_M];
     unsigned long long block_probes, cand_lds;
 };
+
+// A candidate k-mer's 64-bit hash into the sketch: the top HLL_LOG2 bits choose
+// the register, the others give the rank.
+__device__ __forceinline__ void sketch_add(QueryShared &qs, uint64_t hash) {
+    const uint64_t rest = hash << HLL_LOG2;
+    const uint32_t rank = rest ? (uint32_t)__clzll(rest) + 1 : 64 - HLL_LOG2 + 1;
+    atomicMax(&qs.hll[(uint32_t)(hash >> (64 - HLL_LOG2))], rank);
+}
 
 template <uint32_t NT>
 __device__ __forceinline__ void query_begin(QueryShared &qs, const uint32_t *prefilter,
@@ -1001,7 +1014,7 @@ void k_query_blocked(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint6
         const bool one = lo + 1 == hi;
         Span sp = one ? span_of(a.strings, lo, t0) : Span{0, -1};
         const uint32_t run0 = (threadIdx.x >> 6) * (TILE / (BLOCK / 64));
-        uint32_t carry_key = 0, carry_g = 0;
+        uint32_t carry_lo = 0, carry_hi = 0, carry_rev = 0, carry_pal = 0;
         uint64_t carry_w = 0;
         const Part part = tile_part(a);
         for (uint32_t it = part.lo; it < part.hi; ++it) {
@@ -1021,7 +1034,8 @@ void k_query_blocked(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint6
             const uint32_t sb = (uint32_t)d & 3u, vk = k > 1 ? ((uint32_t)d >> 2) & 3u : v0;
             const MiddleKey m = middle_key((T)((d >> 2) & mid_ones), (T)(~(u >> 4) & mid_ones),
                                            single, ts.f.mask >> 6);
-            const uint32_t kout = pack_key(m), gout = (uint32_t)(m.g >> 32);
+            const uint32_t kout = (uint32_t)m.g, gout = (uint32_t)(m.g >> 32);
+            const bool rev_out = m.orient == 1, pal_out = m.orient == 2;
             // a valid lane loads its out-middle's block when it or the
             // position above is evaluated; the position above uses it as its
             // in-middle's (an evaluated position that is not a string start
@@ -1035,10 +1049,12 @@ void k_query_blocked(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint6
                 ++my_probes;
             }
             wo = rotr64(wo, m.a);
-            uint32_t kin = from_below(kout, carry_key), gin = from_below(gout, carry_g);
+            uint32_t kin = from_below(kout, carry_lo), gin = from_below(gout, carry_hi);
             uint64_t wi = from_below(wo, carry_w);
-            carry_key = (uint32_t)__builtin_amdgcn_readlane((int)kout, 63);
-            carry_g = (uint32_t)__builtin_amdgcn_readlane((int)gout, 63);
+            bool rev_in = flag_below(ballot64(rev_out), carry_rev);
+            bool pal_in = flag_below(ballot64(pal_out), carry_pal);
+            carry_lo = (uint32_t)__builtin_amdgcn_readlane((int)kout, 63);
+            carry_hi = (uint32_t)__builtin_amdgcn_readlane((int)gout, 63);
             carry_w = lane63(wo);
             const bool first = (int32_t)q == sp.gs, last = (int32_t)(q + k) == sp.ge;
             if (live && (first || (it == part.lo && lane == 0))) {
@@ -1046,28 +1062,29 @@ void k_query_blocked(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint6
                 // none (its middle is then part of the sketch's hash only)
                 const Strands<T> s = kmer_at<T>(sg, r, k - 1);
                 const MiddleKey mi = middle_key(s.fwd, s.rc, single, ts.f.mask >> 6);
-                kin = pack_key(mi);
+                kin = (uint32_t)mi.g;
                 gin = (uint32_t)(mi.g >> 32);
+                rev_in = mi.orient == 1;
+                pal_in = mi.orient == 2;
                 if (!first) {
                     wi = rotr64(__hip_atomic_load(&blocks[mi.block], __ATOMIC_RELAXED,
                                                   __HIP_MEMORY_SCOPE_AGENT), mi.a);
                     ++my_probes;
                 }
             }
-            uint32_t least = min(others_lacking<true>(pm, kout, wo, v0, sb),
-                                 others_lacking<false>(pm, kin, wi, pa, vk));
-            const bool pal = live && ((kout | kin) >> 13) != 0;
+            uint32_t least = min(others_lacking<true>(pm, kout, rev_out, wo, v0, sb),
+                                 others_lacking<false>(pm, kin, rev_in, wi, pa, vk));
+            const bool pal = live && (pal_out || pal_in);
             if (__builtin_amdgcn_ballot_w64(pal)) {
                 if (pal)
-                    least = min((kout >> 12) == 2 ? others_lacking_palindrome<true>(pm, kout, wo, v0, sb)
-                                                  : others_lacking<true>(pm, kout, wo, v0, sb),
-                                (kin >> 12) == 2 ? others_lacking_palindrome<false>(pm, kin, wi, pa, vk)
-                                                 : others_lacking<false>(pm, kin, wi, pa, vk));
+                    least = min(pal_out ? others_lacking_palindrome<true>(pm, kout, wo, v0, sb)
+                                        : others_lacking<true>(pm, kout, rev_out, wo, v0, sb),
+                                pal_in ? others_lacking_palindrome<false>(pm, kin, wi, pa, vk)
+                                       : others_lacking<false>(pm, kin, rev_in, wi, pa, vk));
             }
             bool mark = live && (first || last || least == 0);
-            const uint32_t gsum = gin + gout;
             if (live && !mark && ts.sent_log2 &&
-                prefilter_hit(qs.pf, prefilter_bit_g(gsum, sa.pf_log2)))
+                prefilter_hit(qs.pf, prefilter_bit_g(gin + gout, sa.pf_log2)))
                 mark = in_sentinels(norm(kmer_at<T>(sg, r, k), single), sent + ts.sent_off,
                                     ts.sent_log2);
             const uint64_t word = ballot64(mark);
@@ -1078,16 +1095,10 @@ void k_query_blocked(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint6
                     c1u[at] = round ? c1u[at] | word : word;
                 cand.v += (unsigned long long)__popcll(word);
             }
-            if (a.sketch && mark) {
-                // the k-mer's hash: the sum of its two middles' G values (an
-                // unordered pair, the same for both orientations); 12 bits
-                // of the high words' sum choose the register, the other 20
-                // and the sum of the keys' low bits give the rank
-                const uint32_t rest = gsum << HLL_LOG2 |
-                                      (((kin & 0xFBFu) + (kout & 0xFBFu)) & ((1u << HLL_LOG2) - 1));
-                const uint32_t rank = rest ? (uint32_t)__builtin_clz(rest) + 1 : 33;
-                atomicMax(&qs.hll[gsum >> (32 - HLL_LOG2)], rank);
-            }
+            if (a.sketch && mark)
+                // the k-mer's hash: the 64-bit sum of its two middles' G values
+                // (an unordered pair, the same for both orientations)
+                sketch_add(qs, ((uint64_t)gin << 32 | kin) + ((uint64_t)gout << 32 | kout));
         }
     }
     query_end<BLOCK>(a, qs, cand, my_probes, cnt, hll_out);
@@ -1152,12 +1163,6 @@ __device__ __forceinline__ bool standard_mark(const SeqArgs &a, const SentArgs &
            any_present_standard<N>(ts.f, st, a.k, pa, sb, single, probes);
 }
 
-__device__ __forceinline__ void standard_sketch(QueryShared &qs, uint64_t hash) {
-    const uint64_t rest = hash << HLL_LOG2;
-    const uint32_t rank = rest ? (uint32_t)__clzll(rest) + 1 : 64 - HLL_LOG2 + 1;
-    atomicMax(&qs.hll[(uint32_t)(hash >> (64 - HLL_LOG2))], rank);
-}
-
 template <class T, bool CLASSES>
 __global__ __launch_bounds__(BLOCK)
 void k_query_standard(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint64_t *c1u,
@@ -1201,7 +1206,7 @@ void k_query_standard(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1, uint
                 cand.v += (unsigned long long)__popcll(word);
             }
             if (a.sketch && mark)
-                standard_sketch(qs, hash);
+                sketch_add(qs, hash);
         }
     }
     query_end<BLOCK>(a, qs, cand, my_probes, cnt, hll_out);
@@ -1322,7 +1327,7 @@ void k_query_standard_seen(SeqArgs a, BloomArgs pool, SentArgs sa, uint64_t *c1,
                 if (mark) {
                     atomicOr((uint32_t *)words[par] + (q >> 5), 1u << (q & 31u));
                     if (a.sketch)  // (a found window's k-mer is in it already)
-                        standard_sketch(qs, hash);
+                        sketch_add(qs, hash);
                 }
             }
             __syncthreads();  // (the next tile's step one reads the verdicts)

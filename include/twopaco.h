@@ -383,7 +383,13 @@ typedef struct {
                               Algorithm 3 with enough rounds (k-mer classes)
                               that each round's table fits, about; the
                               junctions are those of one round.  The rounds
-                              taken are in tp_stats.rounds.                  */
+                              taken are in tp_stats.rounds.  A slot counts as
+                              the key's words, and a byte where its edge mask
+                              does not fit beside it (8 bytes up to k = 27, 9
+                              up to 31, 16 up to 59, 17 up to 63, 32 up to
+                              123, 33 beyond), though a slot takes 8 bytes
+                              whatever k: the unit fixes the rounds, and so
+                              the first-pass candidates, of a given budget.  */
     uint32_t record_passes; /* binned record: at least this many passes
                               (0 = as the scratch needs), 0..64              */
     uint32_t reserved;     /* 0 */
@@ -653,7 +659,9 @@ typedef struct {
                                    table would exceed it is built in enough
                                    rounds (Algorithm 3, Multiple Rounds
                                    section) that each round's table fits,
-                                   with the same junctions                    */
+                                   with the same junctions (slots counted in
+                                   that field's unit, more than the 8 bytes
+                                   that they take at k >= 28)                 */
 } tp_server_opts;
 
 /* Times are seconds since the server was created (host steady clock). */

@@ -666,10 +666,11 @@ uint32_t tp::table_ref_shift(const tp_plan *p) {
     return bits + 8;
 }
 
-// Bytes that tp_config.table_budget counts per slot: the key's words and an
-// edge-mask byte, or the mask inside the top word where it fits.  (A slot
-// takes 8 bytes whatever k; the budget's unit stays, since the rounds it
-// leads to decide a run's first-pass candidates.)
+// Bytes that tp_config.table_budget and the choice of a table's shape count per
+// slot: the key's words and an edge-mask byte, or the mask inside the top word
+// where it fits.  (A slot takes 8 bytes whatever k; the unit stays, since the
+// capacities and the rounds that it leads to decide a run's first-pass
+// candidates.)
 static uint64_t budget_slot_bytes(const tp_plan *p) {
     const bool in_word = table_packed(p) || (p->W >= 2 && 2 * p->k <= 64u * (p->W - 1) + 54);
     return 8ull * p->W + (in_word ? 0 : 1);
@@ -684,7 +685,7 @@ std::vector<uint64_t> tp::table_caps(const tp_plan *p, const std::vector<double>
     for (size_t i = 0; i < nsets; ++i) {
         const double want = std::min(std::ceil(std::max(keys[i], 1.0) / load), (double)MAX_TABLE);
         exact[i] = std::max((uint64_t)want, MIN_TABLE);
-        waste += (pow2_ceil(exact[i]) - exact[i]) * 8;
+        waste += (pow2_ceil(exact[i]) - exact[i]) * budget_slot_bytes(p);
     }
     const bool round_up =
         p->cfg.table_shape == 1 || (p->cfg.table_shape == 0 && waste <= POW2_WASTE_BYTES);

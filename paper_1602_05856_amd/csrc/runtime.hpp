@@ -86,7 +86,8 @@ inline uint32_t log2_ceil(uint64_t x) {
 constexpr uint64_t MIN_TABLE = 1024;        // slots per set table
 constexpr uint64_t MAX_TABLE = 1ull << 40;  // slots per set table
 // Exact tables are rounded up to a power of two (the faster mode) unless that
-// would leave more than this many bytes of slots unused across a run's sets.
+// would leave more than this many bytes of slots unused across a run's sets
+// (a slot counted as tp_config.table_budget counts it).
 constexpr uint64_t POW2_WASTE_BYTES = 4ull << 30;
 
 // Capacity >= cap of the form m << e with m < 2^32 (the kernels take a home

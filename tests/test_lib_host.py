@@ -357,3 +357,14 @@ def test_debug_table_and_build_batch_validation():
     outs = (ctypes.c_void_p * 1)()
     assert tp.lib().tp_build_batch(None, 0, 25, 3, 0, ctypes.addressof(outs)) == tp.TP_EINVAL
     assert tp.lib().tp_build_batch(None, 0, 25, 3, 0, None) == tp.TP_EINVAL
+
+
+@pytest.mark.parametrize("k, slots", [(27, 1 << 30), (63, 600_006_656), (100, 600_006_656)])
+def test_table_shape_counts_slots_in_the_budget_unit(k, slots):
+    """600M slots: rounded up to 2^30 where a slot counts 8 bytes (3.8 GB of them
+    unused), kept where it counts 16 or 32, as tp_config.table_budget counts it."""
+    one = [tp.Genome(packed=np.zeros(0, np.uint8), n_bases=1_200_000_000 + k - 1,
+                     n_runs=np.zeros((0, 2), np.uint64))]
+    p = tp.Plan(one, k, 1 << 20, 3)
+    assert p.workspace_layout(0.35, 1.0)["table_slots"] == slots + 4096
+    p.close()

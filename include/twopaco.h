@@ -350,9 +350,9 @@ typedef struct {
                               whose table is any-size (table_shape) or at
                               most 8192 slots: 0 = binned when the table's
                               slots for the expected keys take at least 128
-                              MiB (table_shape 0 then takes the any-size
-                              shape at the same capacity) and its scratch at
-                              most 4 passes, else direct (each pass walks all
+                              MiB and its scratch at most 4 passes
+                              (table_shape 0 then takes the any-size shape
+                              at the same capacity), else direct (each pass walks all
                               candidates again); 1 = direct (random
                               atomics into the table); 2 = binned whenever
                               scratch is found.  Binned: a lookup never

@@ -677,7 +677,7 @@ static uint64_t budget_slot_bytes(const tp_plan *p) {
 }
 
 std::vector<uint64_t> tp::table_caps(const tp_plan *p, const std::vector<double> &keys,
-                                     bool *pow2, bool any_size) {
+                                     bool *pow2) {
     const size_t nsets = keys.size();
     const double load = p->cfg.table_load;
     std::vector<uint64_t> exact(nsets), caps(nsets);
@@ -687,14 +687,10 @@ std::vector<uint64_t> tp::table_caps(const tp_plan *p, const std::vector<double>
         exact[i] = std::max((uint64_t)want, MIN_TABLE);
         waste += (pow2_ceil(exact[i]) - exact[i]) * budget_slot_bytes(p);
     }
-    const bool round_up =
-        p->cfg.table_shape == 1 || (p->cfg.table_shape == 0 && waste <= POW2_WASTE_BYTES);
-    *pow2 = round_up && (p->cfg.table_shape == 1 || !any_size);
+    *pow2 = p->cfg.table_shape == 1 || (p->cfg.table_shape == 0 && waste <= POW2_WASTE_BYTES);
     for (size_t i = 0; i < nsets; ++i) {
         uint32_t m = 0, e = 0;
-        caps[i] = round_up ? pow2_ceil(exact[i]) : exact[i];
-        if (!*pow2)
-            caps[i] = shape_table(caps[i], &m, &e);
+        caps[i] = *pow2 ? pow2_ceil(exact[i]) : shape_table(exact[i], &m, &e);
     }
     return caps;
 }
@@ -978,11 +974,10 @@ constexpr uint64_t RBIN_AUTO_BYTES = 128ull << 20;
 constexpr uint32_t RBIN_AUTO_PASSES = 4;
 constexpr uint64_t RBIN_MEM_MARGIN = 1ull << 30;  // device bytes left free by its own scratch
 
-// Whether the run's table should be of any size, for the binned record: one
-// set with packed slots whose table is large enough for it by default.
-static bool rbin_wants(const tp_plan *p, bool packed, double keys) {
-    return p->cfg.record_binned != 1 && p->sets.size() == 1 && packed && !p->grow_hook &&
-           keys / p->cfg.table_load * 8 >= (double)RBIN_AUTO_BYTES;
+// Whether a table that would be a power of two takes the any-size shape, at the
+// same capacity, for the binned record: large enough for it by default.
+static bool rbin_reshapes(const tp_plan *p, double keys) {
+    return p->cfg.table_shape == 0 && keys / p->cfg.table_load * 8 >= (double)RBIN_AUTO_BYTES;
 }
 
 // The binned record's scratch (tp_config.record_binned) for a one-set plan
@@ -1421,6 +1416,7 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
         if (a.sketch)
             est = hll_estimate(*(const SketchSum *)(p->mail + mail.sketch));
         const bool packed = table_packed(p);
+        bool pow2 = true, reshapes = false;
         {
             // keys <= candidate positions; one set: the sketch's estimate
             // (+15% for its error) when smaller.  A table that overflows is
@@ -1430,10 +1426,8 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
                 const double c = (double)std::max<uint64_t>(hs[i].candidates, 1);
                 keys[i] = a.sketch ? std::min(c, est * 1.15) : c;
             }
-            bool pow2 = true;
-            const std::vector<uint64_t> caps =
-                table_caps(p, keys, &pow2, rbin_wants(p, packed, keys[0]));
-            p->table_pow2 = pow2;
+            const std::vector<uint64_t> caps = table_caps(p, keys, &pow2);
+            reshapes = rbin_reshapes(p, keys[0]);
             for (uint32_t i = 0; i < nsets; ++i)
                 p->sets[i].table_cap = caps[i];
             // a table beyond the budget: Algorithm 3 with enough classes that
@@ -1460,11 +1454,6 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
                 si.table_off = slots;
                 slots += si.table_cap + TABLE_TAIL;
             }
-            std::vector<SetDesc> d2 = set_descs(p);
-            for (uint32_t i = 0; i < nsets; ++i) {
-                d2[i].cls_lo = desc[i].cls_lo;
-                d2[i].cls_hi = desc[i].cls_hi;
-            }
             TableArgs t;
             t.packed = packed ? 1u : 0u;
             t.ref_shift = table_ref_shift(p);
@@ -1487,28 +1476,37 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
                 HIPCHK(hipMemcpyAsync(p->d_seq.p, d_input, p->input_bytes,
                                       hipMemcpyDeviceToDevice, s));
             }
+            // binned record: one set, packed slots, home blocks of at most
+            // 2^TABLE_BLOCK_LOG2 slots (the binned kernels take set 0's shape).
+            // Only a table that it builds changes its shape for it: a direct
+            // record's lookups are faster in a power of two.
+            RecBinArgs rb{};
+            uint32_t rb_passes = 0, m0 = 0, e0 = 0;
+            bool rbin = false;
+            (void)shape_table(p->sets[0].table_cap, &m0, &e0);
+            if (!rbin_off && nsets == 1 && packed && (!pow2 || m0 == 1 || reshapes)) {
+                const int rcb = rbin_setup(p, hs[0].candidates, m0, p->sets[0].table_cap * 8, &rb,
+                                           &rb_passes, &rbin);
+                if (rcb)
+                    return rcb;
+            }
+            p->table_pow2 = pow2 && !(rbin && m0 > 1);
+            std::vector<SetDesc> d2 = set_descs(p);
+            for (uint32_t i = 0; i < nsets; ++i) {
+                d2[i].cls_lo = desc[i].cls_lo;
+                d2[i].cls_hi = desc[i].cls_hi;
+            }
             t.keys = p->d_keys.as<unsigned long long>();
             t.cap_m = t.cap_e = 0;  // per set, from its descriptor
             t.lomask = 0;
             t.pow2 = p->table_pow2 ? 1u : 0u;
             t.pad = 0;
+            TableArgs t0 = t;
+            t0.cap_m = m0;
+            t0.cap_e = e0;
+            t0.lomask = (1ull << e0) - 1;
             ClearList up2{};
             HIPCHK(send_sets(p, mail, d2, &up2, s));
-            // binned record: one set, packed slots, home blocks of at most
-            // 2^TABLE_BLOCK_LOG2 slots (the binned kernels take set 0's shape)
-            RecBinArgs rb{};
-            uint32_t rb_passes = 0;
-            bool rbin = false;
-            TableArgs t0 = t;
-            if (!rbin_off && nsets == 1 && packed && d2[0].table_e <= TABLE_BLOCK_LOG2) {
-                t0.cap_m = d2[0].table_m;
-                t0.cap_e = d2[0].table_e;
-                t0.lomask = (1ull << d2[0].table_e) - 1;
-                const int rcb = rbin_setup(p, hs[0].candidates, d2[0].table_m,
-                                           p->sets[0].table_cap * 8, &rb, &rb_passes, &rbin);
-                if (rcb)
-                    return rcb;
-            }
             // prologue (graph-replayable): counters and the table cleared (the
             // binned record writes every block itself: only the spare tail)
             auto enqueue_p2 = [&](hipStream_t q) -> int {
@@ -1533,8 +1531,8 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             }
             HIPCHK(hipEventRecord(p->ev[5], s));
             if (rbin)
-                HIPCHK(launch_record_binned(a, p->d_c1.as<uint64_t>(), t0, rb, rb_passes,
-                                            d2[0].table_m, scnt, cnt, s));
+                HIPCHK(launch_record_binned(a, p->d_c1.as<uint64_t>(), t0, rb, rb_passes, m0, scnt,
+                                            cnt, s));
             else
                 HIPCHK(launch_record(W, with_queue(a, qbase, K_RECORD, p->grid[K_RECORD]),
                                      p->d_c1.as<uint64_t>(), t, cnt, p->grid[K_RECORD].n, s));

@@ -158,11 +158,9 @@ void class_partition(const uint64_t *e, uint32_t classes, uint32_t *bound);
 // Exact-table capacities for per-set key counts at the plan's table_load:
 // slots = keys / load, rounded up to a power of two unless that leaves more
 // than POW2_WASTE_BYTES unused over all sets (then to the m << e shape);
-// *pow2 receives the mode.  any_size: the same capacities in the m << e shape
-// (the binned record's) unless table_shape asks for a power of two.  (tp_run sizes from candidate counts and the
+// *pow2 receives the mode.  (tp_run sizes from candidate counts and the
 // sketch, the caller-memory run from a stated bound.)
-std::vector<uint64_t> table_caps(const tp_plan *p, const std::vector<double> &keys, bool *pow2,
-                                 bool any_size = false);
+std::vector<uint64_t> table_caps(const tp_plan *p, const std::vector<double> &keys, bool *pow2);
 // Slot words of a plan's exact tables: packed (else reference words), and the
 // first tag bit of reference words.
 bool table_packed(const tp_plan *p);
@@ -273,7 +271,7 @@ struct tp_plan {
     hipStream_t cap = nullptr;             // graphs: capture stream
 
     bool have_run = false;
-    bool table_pow2 = true;  // table mode of the last sizing (every set 2^e, else m << e)
+    bool table_pow2 = true;  // table mode of the last attempt (every set 2^e, else m << e)
     std::vector<uint64_t> last_cap, last_off;  // last table attempt: per-set capacity, offset
     bool table_live = false;  // the last run's table is still in d_keys..
     uint32_t last_record_passes = 0;  // binned record: passes of the last table attempt

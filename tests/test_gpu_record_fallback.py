@@ -1,0 +1,54 @@
+"""The binned record by default, and where it is given up."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+BLOCKED = 4
+
+
+def genome(codes):
+    import paper_1602_05856_amd as tp
+    pk, runs = synth.pack(codes)
+    return tp.Genome(packed=pk, n_bases=codes.size, n_runs=runs)
+
+
+def motif_units(r, k, units):
+    """`units` copies of one motif, a random base after each: some hundred
+    k-mers make up all of it, each with several pairs of bases around it."""
+    x = np.tile(np.append(synth.random_bases(r, k + 3), np.uint8(0)), units)
+    x[k + 3::k + 4] = r.integers(0, 4, units)
+    return x
+
+
+def mix64(z):
+    z = (z ^ (z >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+    z = (z ^ (z >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+    return z ^ (z >> np.uint64(31))
+
+
+@pytest.fixture(scope="module")
+def repetitive():
+    r = synth.rng(51)
+    return [genome(synth.random_bases(r, 13_000_000)), genome(motif_units(r, 25, 400_000))]
+
+
+def test_direct_record_keeps_the_power_of_two(repetitive):
+    """More items than the scratch takes: the record runs directly, in the table
+    a direct record takes (home slot: the hash's low bits)."""
+    import paper_1602_05856_amd as tp
+    plan = tp.Plan(repetitive, 25, 1 << 20, 4, BLOCKED)  # every position a candidate
+    plan.run(plan.upload())
+    st = plan.stats()
+    keys, _ = plan.debug_table()
+    plan.close()
+    assert st["record_passes"] == 0 and st["table_keys"] == len(keys) > 12_000_000
+    cap = st["table_capacity"] - 4096
+    assert cap & (cap - 1) == 0 and cap * 8 >= 128 << 20
+    home = mix64(keys[:, 0] ^ np.uint64(0x082EFA98EC4E6C89)) & np.uint64(cap - 1)
+    # in slot order the home slots rise, but for a probe's length here and there
+    # (and the last ones' wrap to the table's start)
+    late = home[4096:].astype(np.int64) < np.maximum.accumulate(home[4096:].astype(np.int64)) - 4096
+    assert late.sum() == 0

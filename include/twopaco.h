@@ -373,7 +373,9 @@ typedef struct {
                               server, the record runs directly, as it does
                               on caller memory (tp_run_ws, tp_run_noalloc),
                               and where a few k-mers make up so many of the
-                              candidates that their items find no room.
+                              candidates that their items find no room (with
+                              0 the plan's later runs then record directly at
+                              once, until its configuration is set again).
                               A pass holds at most 2^18 blocks (16 GiB of
                               table).  The passes taken are in
                               tp_stats.record_passes.                        */

@@ -598,6 +598,8 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_rbin_split(TableArgs t, RecBinArg
 // One workgroup per block of the pass: the block built in LDS from empty (an
 // item claims an empty slot by compare-and-swap, or ORs its edge bits into
 // its key's slot; probes wrap within the block), then written out whole.
+// Nothing once items were lost (only kernels before this one set ctl[1]): the
+// attempt is done again directly.
 template <bool P2>
 __global__ __launch_bounds__(BIN_BLOCK) void k_rbin_apply(TableArgs t, RecBinArgs rb,
                                                           SetCounters *sc, Counters *cnt) {
@@ -605,6 +607,8 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_rbin_apply(TableArgs t, RecBinArg
     __shared__ __align__(16) unsigned long long reg[1u << TABLE_BLOCK_LOG2];
     __shared__ unsigned long long fresh_wg, probes_wg;
     __shared__ uint32_t over_wg;
+    if (rb.ctl[1])
+        return;
     const uint32_t nb = 1u << t.cap_e;  // slots per block
     const uint64_t r = blockIdx.x;
     ulonglong2 *reg2 = (ulonglong2 *)reg;
@@ -686,10 +690,16 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_rbin_apply(TableArgs t, RecBinArg
     }
 }
 
-// The spilled items into the finished table.
+// The spilled items into the finished table; once items were lost, the set's
+// flag instead, so that the decision skips its tiles.
 template <bool P2>
 __global__ __launch_bounds__(BLOCK) void k_rbin_spill(TableArgs t, RecBinArgs rb, SetCounters *sc,
                                                       Counters *cnt) {
+    if (rb.ctl[1]) {
+        if (blockIdx.x == 0 && threadIdx.x == 0)
+            atomicExch(&sc->overflow, 1ull);
+        return;
+    }
     const uint64_t n = min((uint64_t)rb.ctl[0], rb.spill_cap);
     uint32_t keys = 0, probes = 0;
     for (uint64_t i = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; i < n;

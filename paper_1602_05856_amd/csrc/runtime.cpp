@@ -174,6 +174,7 @@ void tp::plan_clear_layout(tp_plan *p) {
     p->last_cap.clear();
     p->last_off.clear();
     p->table_live = false;
+    p->rbin_short = false;
     ++p->layout_gen;
     p->ws = WsState{};
 }
@@ -572,6 +573,7 @@ extern "C" int tp_plan_set_config(tp_plan *p, const tp_config *cfg) {
     const bool reorder = cfg->tile_order != p->cfg.tile_order;
     const bool refilter = cfg->bloom_bits_per_edge != p->cfg.bloom_bits_per_edge;
     p->cfg = *cfg;
+    p->rbin_short = false;
     if (refilter) {
         bool any_auto = false;
         for (const auto &si : p->sets)
@@ -993,7 +995,8 @@ static int rbin_setup(tp_plan *p, uint64_t candidates, uint64_t n_blocks, uint64
                       RecBinArgs *rb, uint32_t *passes, bool *use) {
     *use = false;
     const uint32_t mode = p->cfg.record_binned;
-    if (mode == 1 || (mode == 0 && table_bytes < RBIN_AUTO_BYTES) || p->grow_hook)
+    if (mode == 1 || p->grow_hook ||
+        (mode == 0 && (table_bytes < RBIN_AUTO_BYTES || p->rbin_short)))
         return TP_OK;
     const uint64_t per_max = (uint64_t)RBIN_MAX_BUCKETS * RBIN_SUB;   // blocks per pass
     const uint64_t min_passes = std::max<uint64_t>(
@@ -1553,12 +1556,11 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
                 rbin ? ((const unsigned long long *)(p->mail + mail.rb_short))[1] : 0;
             p->last_record_passes = rbin ? rb_passes : 0;
             if (rb_short) {
-                // a pass had more items than the scratch holds (the table is
-                // not complete): the same attempt again, recorded directly
-                rbin_off = true;
-                if (round_attempts >= MAX_ATTEMPTS)
-                    return fail(TP_EOVERFLOW, "exact table overflowed after " +
-                                                  std::to_string(round_attempts) + " attempts");
+                // more items without room than the scratch holds (the table is
+                // not complete): the same attempt again, recorded directly, as
+                // the plan's later runs are unless told otherwise
+                rbin_off = p->rbin_short = true;
+                --round_attempts;
                 continue;
             }
             bool overflow = false;

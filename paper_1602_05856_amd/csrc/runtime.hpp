@@ -275,6 +275,10 @@ struct tp_plan {
     std::vector<uint64_t> last_cap, last_off;  // last table attempt: per-set capacity, offset
     bool table_live = false;  // the last run's table is still in d_keys..
     uint32_t last_record_passes = 0;  // binned record: passes of the last table attempt
+    // a run's items found no room (an input of many-copy k-mers), so the binned
+    // record was done again directly: it is not tried by default until the
+    // layout or the configuration changes
+    bool rbin_short = false;
     uint64_t layout_gen = 1;  // bumped by changes that invalidate a workspace layout
     tp::WsState ws;           // caller-memory run
     tp_stats stats{};

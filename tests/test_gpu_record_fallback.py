@@ -52,3 +52,26 @@ def test_direct_record_keeps_the_power_of_two(repetitive):
     # (and the last ones' wrap to the table's start)
     late = home[4096:].astype(np.int64) < np.maximum.accumulate(home[4096:].astype(np.int64)) - 4096
     assert late.sum() == 0
+
+
+def test_a_record_given_up_is_not_tried_again(repetitive):
+    import paper_1602_05856_amd as tp
+    plan = tp.Plan(repetitive, 25, 1 << 20, 4, BLOCKED)
+    d_in = plan.upload()
+    got = []
+    for attempts in (2, 1, 1):
+        plan.run(d_in)
+        st = plan.stats()
+        assert (st["table_attempts"], st["record_passes"]) == (attempts, 0)
+        got.append((st["table_keys"], plan.download().junction_pos))
+    plan.config = {"record_binned": 1}
+    plan.run(d_in)
+    assert plan.stats()["table_attempts"] == 1
+    want = plan.download().junction_pos
+    for keys, pos in got:
+        assert keys == plan.stats()["table_keys"] and np.array_equal(pos, want)
+    plan.config = {"record_binned": 2, "table_shape": 2}  # as asked: tried every time
+    for _ in range(2):
+        plan.run(d_in)
+        assert plan.stats()["table_attempts"] == 2
+    plan.close()

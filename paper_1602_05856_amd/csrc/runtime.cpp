@@ -819,11 +819,25 @@ static uint64_t bytes_after(tp_plan *p, std::initializer_list<std::pair<DevBuf *
     return n;
 }
 
-// Ask the plan's owner (a server) for the device bytes a growth needs.
-static int reserve(tp_plan *p, std::initializer_list<std::pair<DevBuf *, uint64_t>> grow) {
+// Ask the plan's owner (a server) for the device bytes a growth needs, or
+// (wait false) only whether they are to be had at once.
+static int reserve(tp_plan *p, std::initializer_list<std::pair<DevBuf *, uint64_t>> grow,
+                   bool wait) {
     if (!p->grow_hook)
         return TP_OK;
-    return p->grow_hook(p->grow_ctx, bytes_after(p, grow));
+    return p->grow_hook(p->grow_ctx, plan_device_bytes(p), bytes_after(p, grow), wait);
+}
+
+// The same for memory that the run cannot do without.  Before it is waited for,
+// the key buffer goes back when it is more than keep bytes: the items of the
+// binned fill, which other jobs may be waiting for.
+static int reserve_needed(tp_plan *p, std::initializer_list<std::pair<DevBuf *, uint64_t>> grow,
+                          uint64_t keep) {
+    if (reserve(p, grow, false) == TP_OK)
+        return TP_OK;
+    if (p->d_keys.cap > align_up(keep, 256))
+        p->d_keys.release();
+    return reserve(p, grow, true);
 }
 
 constexpr int RUN_SPLIT = 1;  // run_impl: redo the run with *split rounds
@@ -887,11 +901,20 @@ static uint64_t bin_cursors(const BinArgs &b) {
     return b.n_buckets + (b.bucket_log2 != b.region_log2 ? b.n_regions : 0u);
 }
 
+// Bytes of the binned fill's items (two levels where buckets are split).
+static uint64_t bin_items_bytes(const tp_plan *p) {
+    return 4 * (p->bin_off.back() + (p->bin_roff.empty() ? 0 : p->bin_roff.back()));
+}
+
 // The items' places in the key buffer (again before each round: the table of
-// the round before may have grown, and so moved, the buffer).
-static void bin_place(const tp_plan *p, BinArgs *b) {
+// the round before may have grown, and so moved, the buffer).  False when it
+// does not hold them.
+static bool bin_place(const tp_plan *p, BinArgs *b) {
+    if (p->d_keys.cap < bin_items_bytes(p))
+        return false;
     b->items_a = p->d_keys.as<uint32_t>();
     b->items_b = b->items_a + p->bin_off.back();
+    return true;
 }
 
 // The binned fill's scratch: items in the exact table's key buffer (dead
@@ -928,9 +951,8 @@ static int bin_setup(tp_plan *p, BinArgs *b, uint32_t *chunk_tiles, uint32_t rou
         p->bin_tiles = 0;
     }
     const uint64_t n_off = p->bin_off.size(), n_roff = p->bin_roff.size();
-    const uint64_t items_a = p->bin_off.back(), items_b = split ? p->bin_roff.back() : 0;
-    const uint64_t scratch = 4 * (items_a + items_b), cursors = 8 * (n_off + n_roff);
-    if (reserve(p, {{&p->d_keys, scratch}, {&p->d_bin, cursors}, {&p->d_bin_room, cursors}}))
+    const uint64_t scratch = bin_items_bytes(p), cursors = 8 * (n_off + n_roff);
+    if (reserve(p, {{&p->d_keys, scratch}, {&p->d_bin, cursors}, {&p->d_bin_room, cursors}}, false))
         return TP_OK;
     for (const hipError_t e : {ensure_spare(p->d_keys, scratch, outputs), p->d_bin.ensure(cursors),
                                p->d_bin_room.ensure(cursors)}) {
@@ -949,7 +971,7 @@ static int bin_setup(tp_plan *p, BinArgs *b, uint32_t *chunk_tiles, uint32_t rou
         p->bin_tiles = tiles;
         p->bin_rounds = rounds;
     }
-    bin_place(p, b);
+    (void)bin_place(p, b);
     b->cursor = p->d_bin.as<unsigned long long>();
     b->off = p->d_bin_room.as<uint64_t>();
     b->roff = b->off + n_off;
@@ -1346,6 +1368,10 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
                 desc[i].cls_hi = p->bounds[(size_t)i * (rounds + 1) + round + 1];
             }
         }
+        if (binned && !bin_place(p, &bin)) {  // the buffer was given back for the last table
+            binned = false;
+            bin.popcount = nullptr;
+        }
         ClearList up{};
         HIPCHK(send_sets(p, mail, desc, &up, s));
         // prologue (graph-replayable): sentinels on a single round, zeroing
@@ -1373,13 +1399,11 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
         }
         // timed kernels, launched directly between their events
         HIPCHK(hipEventRecord(p->ev[1], s));
-        if (binned) {
-            bin_place(p, &bin);
+        if (binned)
             HIPCHK(launch_fill_binned(W, a, pool, cnt, bin, bin_tiles, s));
-        } else {
+        else
             HIPCHK(launch_fill(W, with_queue(a, qbase, K_FILL, p->grid[K_FILL]), pool, cnt,
                                p->grid[K_FILL].n, s));
-        }
         HIPCHK(hipEventRecord(p->ev[2], s));
         HIPCHK(launch_query(W, with_queue(a, qbase, K_QUERY, p->grid[K_QUERY]), pool, sa,
                             p->d_c1.as<uint64_t>(),
@@ -1465,8 +1489,9 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             const std::initializer_list<DevBuf *> outputs = {&p->d_pos, &p->d_vertex, &p->d_strand,
                                                              &p->d_edges, &p->d_rbin};
             {
-                const int rcr = reserve(p, {{&p->d_keys, slots * 8},
-                                            {&p->d_seq, packed ? 0 : p->input_bytes}});
+                const int rcr = reserve_needed(p, {{&p->d_keys, slots * 8},
+                                                   {&p->d_seq, packed ? 0 : p->input_bytes}},
+                                               slots * 8);
                 if (rcr)
                     return rcr;
             }
@@ -1626,8 +1651,9 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
                         p->d_strand.cap < nj || p->d_edges.cap < ne * sizeof(tp_edge)))
         p->d_rbin.release();
     {
-        const int rcr = reserve(p, {{&p->d_pos, nj * 8}, {&p->d_vertex, nj * 8 * W},
-                                    {&p->d_strand, nj}, {&p->d_edges, ne * sizeof(tp_edge)}});
+        const int rcr = reserve_needed(p, {{&p->d_pos, nj * 8}, {&p->d_vertex, nj * 8 * W},
+                                           {&p->d_strand, nj}, {&p->d_edges, ne * sizeof(tp_edge)}},
+                                       0);
         if (rcr)
             return rcr;
     }

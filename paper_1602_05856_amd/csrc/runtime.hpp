@@ -231,9 +231,10 @@ struct tp_plan {
     uint32_t rounds = 1;                   // Algorithm 3: k-mer classes, one round each
     uint32_t last_rounds = 1;              // rounds of the last run (more with a table budget)
     // Called before a run grows its device buffers, with the bytes the plan
-    // will hold after the growth (a server's budget check); a status other
-    // than TP_OK fails the run.
-    int (*grow_hook)(void *ctx, uint64_t bytes) = nullptr;
+    // holds and those it will hold after the growth (a server's budget check).
+    // wait: a status other than TP_OK fails the run; else only what is to be had
+    // at once is granted, and the run does without.
+    int (*grow_hook)(void *ctx, uint64_t held, uint64_t bytes, bool wait) = nullptr;
     void *grow_ctx = nullptr;
     uint32_t cu_limit = 0;                 // CUs its stream may use (0: all); sizes the grids
     tp_config cfg{};                       // runtime knobs (autotuner)

@@ -72,22 +72,19 @@ struct Job {
 };
 
 // Device bytes a job needs before its first pass ends (the first admission
-// point): the input laid out in tiles, the filter, the binned fill's
-// scratch, the candidate and junction bitmaps, and the
-// layout tables, counters and sentinel tables
+// point): the input laid out in tiles, the filter, the candidate and junction
+// bitmaps, and the layout tables, counters and sentinel tables
 // (bounded by a few bytes per base plus a fixed margin).  The exact table and
 // the outputs depend on the data: the run asks for them at the second
 // admission point (the grow hook), when the first pass has counted the
-// candidates.
+// candidates.  The binned fill's scratch is not counted: the run takes it where
+// the budget has it at once, and fills with atomics where it has not.
 uint64_t estimate_bytes(uint64_t bases, uint32_t n_genomes, uint64_t b, uint32_t k) {
     const uint64_t W = k <= 31 ? 1 : (k <= 63 ? 2 : 4);
     const uint64_t laid = bases + (uint64_t)n_genomes * TILE + TILE;  // tile-aligned positions
     const uint64_t tiles = laid / TILE + 1;
-    // the binned fill's scratch: about 4.5 bytes per position of a chunk of at
-    // most 2^31, twice that for a filter split by region
-    const uint64_t bin = (b / 8 > (128ull << 20) ? 10 : 5) * std::min<uint64_t>(laid, 1ull << 31);
     return laid / 4 + b / 8 + 3 * (laid / 8) + tiles * (4 + sizeof(TileInfo)) +
-           (uint64_t)n_genomes * 16 * (8 * W + 4) + bin + (64ull << 20);
+           (uint64_t)n_genomes * 16 * (8 * W + 4) + (64ull << 20);
 }
 
 }  // namespace
@@ -112,7 +109,8 @@ struct tp_server {
         tp_plan *plan = nullptr;
         DevBuf input;
         uint64_t held = 0;      // device bytes its plan and input hold
-        uint64_t reserved = 0;  // estimate of the group it is running
+        uint64_t est = 0;       // estimate of the group it is running
+        uint64_t reserved = 0;  // that, or what the group's run has asked for since
         bool busy = false;
         bool growing = false;   // waiting at the second admission point
         uint32_t index = 0;
@@ -140,15 +138,17 @@ struct tp_server {
 
     void worker_loop(Worker *w);
     void run_group(Worker *w, std::vector<Job *> &group);
-    int grow(Worker *w, uint64_t plan_bytes);
+    int grow(Worker *w, uint64_t held, uint64_t plan_bytes, bool wait);
 };
 
 // The second admission point: a running job's plan is about to grow to
 // plan_bytes (its exact table, or its outputs).  The worker's reservation
 // grows with it when everything fits the budget; otherwise it waits for other
 // jobs to finish (or idle workers to hand back their buffers), and fails
-// with TP_ENOMEM when nothing that could free memory is left.
-int tp_server::grow(Worker *w, uint64_t plan_bytes) {
+// with TP_ENOMEM when nothing that could free memory is left.  What the job can
+// do without is not waited for, and a job that waits reserves no more than its
+// estimate or what its plan holds now: other jobs may be waiting for the rest.
+int tp_server::grow(Worker *w, uint64_t held, uint64_t plan_bytes, bool wait) {
     std::unique_lock<std::mutex> lk(m);
     const uint64_t need = plan_bytes + w->input.cap;
     for (;;) {
@@ -157,6 +157,15 @@ int tp_server::grow(Worker *w, uint64_t plan_bytes) {
         if (held_by_others(w) + need <= o.hbm_budget) {
             w->reserved = need;
             return TP_OK;
+        }
+        if (!wait)
+            return TP_ENOMEM;
+        const uint64_t now_held = held + w->input.cap;
+        if (std::max(w->est, now_held) < std::max(w->held, w->reserved)) {
+            w->held = now_held;
+            w->reserved = std::max(w->est, now_held);
+            update_totals();
+            cv_work.notify_all();
         }
         bool idle_cache = false, running = false;
         for (const auto &v : workers) {
@@ -178,9 +187,9 @@ int tp_server::grow(Worker *w, uint64_t plan_bytes) {
     }
 }
 
-static int server_grow_hook(void *ctx, uint64_t bytes) {
+static int server_grow_hook(void *ctx, uint64_t held, uint64_t bytes, bool wait) {
     auto *w = (tp_server::Worker *)ctx;
-    return w->srv->grow(w, bytes);
+    return w->srv->grow(w, held, bytes, wait);
 }
 
 void tp_server::run_group(Worker *w, std::vector<Job *> &group) {
@@ -330,7 +339,7 @@ void tp_server::worker_loop(Worker *w) {
         for (Job *j : group)
             queue.erase(std::find(queue.begin(), queue.end(), j));
         w->busy = true;
-        w->reserved = est;
+        w->est = w->reserved = est;
         const double t = now();
         for (Job *j : group) {
             j->info.start_s = t;

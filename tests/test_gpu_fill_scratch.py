@@ -61,3 +61,45 @@ def test_scratch_moved_by_a_rounds_table(h, flags):
     assert st["bloom_popcount"] == a[0]["bloom_popcount"]
     for f in ("junction_pos", "vertex", "strand", "edges"):
         assert np.array_equal(getattr(a[3], f), getattr(b[3], f)), f
+
+
+def random_set(seed, n, genomes):
+    """`genomes` copies of one random genome (few candidates), without N."""
+    import paper_1602_05856_amd as tp
+    pk = np.random.default_rng(seed).integers(0, 256, (n + 3) // 4, dtype=np.uint8)
+    return [tp.Genome(packed=pk, n_bases=n, n_runs=np.zeros((0, 2), np.uint64))] * genomes
+
+
+def test_admission_asks_for_what_the_atomic_fill_needs():
+    """100 Mbp with a 128 MiB filter in a budget of 512 MiB."""
+    import paper_1602_05856_amd as tp
+    gs = random_set(33, 50_000_000, 2)
+    st, _, _, want = run_plan(gs, 25, 1 << 30, 4, BLOCKED, fill_binned=1)
+    srv = tp.Server(hbm_budget=512 << 20, workers=1, max_batch=1)
+    res, _ = srv.wait(srv.submit(gs, 25, 1 << 30, 4, BLOCKED))
+    peak = srv.stats()["peak_held_bytes"]
+    srv.close()
+    assert peak <= 512 << 20
+    assert res.stats["candidates"] == st["candidates"]
+    assert np.array_equal(res.junction_pos, want.junction_pos)
+
+
+def test_scratch_is_not_waited_for():
+    """A small job whose scratch does not fit beside a running large one fills
+    with atomics and ends first."""
+    import time
+    import paper_1602_05856_amd as tp
+    n, b = 800_000_000, 1 << 34
+    large, small = random_set(34, n, 1), related(35, 1_000_000, 4)
+    room = n // 4 + b // 8 + 3 * n // 8 + 20 * (n // 2048)
+    srv = tp.Server(hbm_budget=room + (300 << 20), workers=2, max_batch=1, wg_per_cu=2)
+    a = srv.submit(large, 25, b, 16, 0)
+    while not srv.stats()["running"]:
+        time.sleep(0.001)
+    c = srv.submit(small, 25, 1 << 26, 16, 0)
+    res, small_info = srv.wait(c)
+    _, large_info = srv.wait(a)
+    srv.close()
+    assert res.stats["fill_chunks"] == 0
+    assert large_info["start_s"] < small_info["start_s"]
+    assert small_info["end_s"] < large_info["end_s"]

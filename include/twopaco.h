@@ -493,7 +493,9 @@ int tp_build_batch(const tp_set *sets, uint32_t n_sets, uint32_t k, uint32_t has
  * order; *n_out receives their number.  With cap smaller than that number
  * nothing is written and TP_EINVAL is returned (*n_out still set).  Waits on
  * the device.  TP_ESTATE without a completed run, in pass-1-only mode, or when
- * the run released its table to fit its outputs. */
+ * the run released its table to fit its outputs.  With k >= 28 the table names
+ * its keys by position, and the plan keeps a copy of the run's input for this
+ * tap where the device has room for it (else TP_ESTATE). */
 int tp_debug_table(const tp_plan *p, uint32_t set, uint64_t *keys, uint8_t *masks, uint64_t cap,
                    uint64_t *n_out);
 

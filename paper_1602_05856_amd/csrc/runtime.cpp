@@ -1486,23 +1486,27 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
             t.ref_shift = table_ref_shift(p);
             // the last run's outputs are dead from here on: spare them if the
             // table does not fit beside them
-            const std::initializer_list<DevBuf *> outputs = {&p->d_pos, &p->d_vertex, &p->d_strand,
-                                                             &p->d_edges, &p->d_rbin};
+            const std::initializer_list<DevBuf *> outputs = {
+                &p->d_pos, &p->d_vertex, &p->d_strand, &p->d_edges, &p->d_rbin, &p->d_seq};
             {
-                const int rcr = reserve_needed(p, {{&p->d_keys, slots * 8},
-                                                   {&p->d_seq, packed ? 0 : p->input_bytes}},
-                                               slots * 8);
+                const int rcr = reserve_needed(p, {{&p->d_keys, slots * 8}}, slots * 8);
                 if (rcr)
                     return rcr;
             }
             HIPCHK(ensure_spare(p->d_keys, slots * 8, outputs));
-            if (!packed && round == 0 && round_attempts == 1) {
+            if (!packed && !p->grow_hook && round == 0 && round_attempts == 1) {
                 // the table names positions of this run's input, which the
-                // caller may change or free afterwards: a copy of it beside
-                // the table keeps tp_debug_table's keys readable
-                HIPCHK(ensure_spare(p->d_seq, p->input_bytes, outputs));
-                HIPCHK(hipMemcpyAsync(p->d_seq.p, d_input, p->input_bytes,
-                                      hipMemcpyDeviceToDevice, s));
+                // caller may change or free afterwards: a copy of it, where
+                // there is room, keeps tp_debug_table's keys readable (plans of
+                // a server have no such reader)
+                const hipError_t e = p->d_seq.ensure(p->input_bytes);
+                if (e == hipErrorOutOfMemory)
+                    (void)hipGetLastError();
+                else
+                    HIPCHK(e);
+                if (p->d_seq.p)
+                    HIPCHK(hipMemcpyAsync(p->d_seq.p, d_input, p->input_bytes,
+                                          hipMemcpyDeviceToDevice, s));
             }
             // binned record: one set, packed slots, home blocks of at most
             // 2^TABLE_BLOCK_LOG2 slots (the binned kernels take set 0's shape).
@@ -1643,9 +1647,10 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
     if (nj < ns)
         return fail(TP_EDEVICE, "internal error: fewer junctions than strings");
     const uint64_t ne = nj - ns;
-    // the exact tables are dead from here on: spare them if the outputs do
-    // not fit beside them (the next run allocates them again)
-    const std::initializer_list<DevBuf *> tables = {&p->d_keys};
+    // the exact tables are dead from here on: spare them (and the copy of the
+    // input that goes with them) if the outputs do not fit beside them (the next
+    // run allocates them again)
+    const std::initializer_list<DevBuf *> tables = {&p->d_keys, &p->d_seq};
     // the binned record's own scratch goes first when the outputs must grow
     if (p->d_rbin.p && (p->d_pos.cap < nj * 8 || p->d_vertex.cap < nj * 8 * W ||
                         p->d_strand.cap < nj || p->d_edges.cap < ne * sizeof(tp_edge)))
@@ -1662,7 +1667,7 @@ static int run_impl(tp_plan *p, const uint8_t *d_input, hipStream_t s, uint32_t 
     HIPCHK(ensure_spare(p->d_strand, nj, tables));
     HIPCHK(ensure_spare(p->d_edges, ne * sizeof(tp_edge), tables));
     // the table is still there unless it had to be freed for the outputs
-    p->table_live = !pass1_only && p->d_keys.p != nullptr;
+    p->table_live = !pass1_only && p->d_keys.p && (table_packed(p) || p->d_seq.p);
     OutArgs o;
     o.pos = p->d_pos.as<uint64_t>();
     o.vertex = p->d_vertex.as<uint64_t>();
@@ -1956,8 +1961,8 @@ extern "C" int tp_debug_table(const tp_plan *p, uint32_t set, uint64_t *keys, ui
     if (!p->have_run)
         return fail(TP_ESTATE, "no completed run");
     if (!p->table_live || set >= p->last_cap.size())
-        return fail(TP_ESTATE, "the last run kept no exact table (pass-1-only mode, or the "
-                               "table was released to fit the outputs)");
+        return fail(TP_ESTATE, "the last run kept no exact table (pass-1-only mode, or no room "
+                               "for it, or for its keys, beside the outputs)");
     const uint64_t off = p->last_off[set], slots = p->last_cap[set] + TABLE_TAIL;
     const int W = p->W;
     const bool packed = table_packed(p);

@@ -277,3 +277,18 @@ def test_serving_pool_full_size():
         say("large %d: %d of 20000 sampled positions are junctions (oracle %.0f s)" % (
             i, int(want.sum()), time.time() - t1))
         assert np.array_equal(got, want), (name, i, int((got != want).sum()))
+
+
+def test_wide_kmers_hold_no_copy_of_the_input():
+    """A server's plans have no table tap, so a job with k >= 28 (whose table
+    names positions of the input) holds what the same job with k = 27 does."""
+    import paper_1602_05856_amd as tp
+    pk = np.random.default_rng(78).integers(0, 256, 10_000_000, dtype=np.uint8)
+    gs = [tp.Genome(packed=pk, n_bases=40_000_000, n_runs=np.zeros((0, 2), np.uint64))] * 2
+    peak = []
+    for k in (27, 28):
+        srv = tp.Server(hbm_budget=8 << 30, workers=1, max_batch=1)
+        srv.wait(srv.submit(gs, k, 1 << 31, 4, BLOCKED))
+        peak.append(srv.stats()["peak_held_bytes"])
+        srv.close()
+    assert peak[1] - peak[0] < 5_000_000, peak

@@ -320,15 +320,19 @@ typedef struct {
                               Binned needs about 4.5 bytes per item of a chunk
                               and pass of scratch, held in the exact table's
                               key buffer (the table is not live during the
-                              fill), and a pool of at most 32 GiB; where the
-                              scratch is not to be had the fill is atomic.
+                              fill), and a pool of at most 32 GiB.  Beyond
+                              256 MiB the buffer grows for it to at most a
+                              quarter of the free memory, with smaller chunks
+                              (bin_chunk_tiles 0); where the scratch is not to
+                              be had the fill is atomic.
                               Runs on caller memory (tp_run_ws,
                               tp_run_noalloc) always fill atomically.        */
     uint32_t bin_chunk_tiles; /* binned fill: tiles (2048 positions each)
                               per chunk, 1..2^20; 0 = 2^20 (2^31
                               positions), or more, up to 2^22, when the
                               key buffer of an earlier run's table holds
-                              them.  Each chunk rereads the filter once.   */
+                              them, or fewer where memory is short (see
+                              fill_binned).  Each chunk rereads the filter once.   */
     uint32_t bloom_bits_per_edge; /* sets created with bloom_bits 0: filter
                               bits per (k+1)-mer position, rounded up to a
                               power of two (2^6..2^40); 0 = 16, else

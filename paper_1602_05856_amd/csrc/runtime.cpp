@@ -851,6 +851,10 @@ constexpr int RUN_SPLIT = 1;  // run_impl: redo the run with *split rounds
 constexpr uint64_t BIN_POOL_PER_POSITION = 24;
 constexpr uint64_t BIN_POOL_FREE = 128ull << 20;
 
+static bool bin_pool_fits(const tp_plan *p, uint64_t positions) {
+    return p->bloom_words * 4 <= BIN_POOL_PER_POSITION * positions + BIN_POOL_FREE;
+}
+
 // Whether this plan's fill can run binned: a pool within the bucket limit.
 bool tp::fill_binnable(const tp_plan *p) {
     return p->n_tiles && p->bloom_words / 2 <= (uint64_t)BIN_MAX_BUCKETS << BIN_LOCAL_LOG2;
@@ -861,8 +865,7 @@ bool tp::fill_binnable(const tp_plan *p) {
 static bool fill_binned(const tp_plan *p, uint32_t rounds) {
     if (p->cfg.fill_binned == 1 || !fill_binnable(p))
         return false;
-    return p->cfg.fill_binned == 2 ||
-           p->bloom_words * 4 <= BIN_POOL_PER_POSITION * (p->positions / rounds) + BIN_POOL_FREE;
+    return p->cfg.fill_binned == 2 || bin_pool_fits(p, p->positions / rounds);
 }
 
 // Room for the items of a chunk of `tiles` tiles, per bin of 2^bin_log2
@@ -920,8 +923,13 @@ static bool bin_place(const tp_plan *p, BinArgs *b) {
 // The binned fill's scratch: items in the exact table's key buffer (dead
 // during the first pass), cursors in d_bin, the bins' room in d_bin_room
 // (laid out again when the layout, the chunk size or the rounds change).
-// Sets *chunk_tiles.  *use = false where the memory is not to be had: the
-// fill then runs with atomics.
+// A buffer that has to grow for it takes up to BIN_SCRATCH_FREE or a quarter of
+// the free memory (other plans need theirs; the record's scratch is bounded the
+// same): the chunks are smaller then, or the fill runs with atomics where that
+// would read the pool too often.  Sets *chunk_tiles.  *use = false where the
+// memory is not to be had: the fill then runs with atomics too.
+constexpr uint64_t BIN_SCRATCH_FREE = 256ull << 20;
+
 static int bin_setup(tp_plan *p, BinArgs *b, uint32_t *chunk_tiles, uint32_t rounds, bool *use,
                      std::initializer_list<DevBuf *> outputs, hipStream_t s) {
     *b = BinArgs{};
@@ -940,16 +948,35 @@ static int bin_setup(tp_plan *p, BinArgs *b, uint32_t *chunk_tiles, uint32_t rou
         want = std::min<uint64_t>(4ull * BIN_CHUNK_TILES_MAX,
                                   std::max<uint64_t>(BIN_CHUNK_TILES_MAX / items,
                                                      p->d_keys.cap / ((split ? 9 : 5) * items * TILE)));
-    const uint64_t tiles = std::min<uint64_t>(p->n_tiles, want);
-    *chunk_tiles = (uint32_t)tiles;
-    const bool fresh = p->bin_tiles != tiles || p->bin_rounds != rounds;
-    if (fresh) {
+    want = std::min<uint64_t>(p->n_tiles, want);
+    bool fresh = false;
+    auto lay_out = [&](uint64_t tiles) {
         bin_room(p, tiles, rounds, b->n_blocks, b->bucket_log2, p->bin_off);
         p->bin_roff.clear();
         if (split)
             bin_room(p, tiles, rounds, b->n_blocks, b->region_log2, p->bin_roff);
-        p->bin_tiles = 0;
+        p->bin_tiles = tiles;
+        fresh = true;
+    };
+    if (p->bin_want != want || p->bin_rounds != rounds)
+        lay_out(want);
+    p->bin_want = 0;  // (until its room is on the device)
+    if (!p->cfg.bin_chunk_tiles &&
+        bin_items_bytes(p) > std::max(p->d_keys.cap, BIN_SCRATCH_FREE)) {
+        size_t free_b = 0, total_b = 0;
+        HIPCHK(hipMemGetInfo(&free_b, &total_b));
+        const uint64_t most = std::max<uint64_t>(BIN_SCRATCH_FREE, (free_b + p->d_keys.cap) / 4);
+        for (int tries = 0; bin_items_bytes(p) > most; ++tries) {
+            if (p->bin_tiles == 1 || tries == 8)
+                return TP_OK;
+            lay_out(std::max<uint64_t>(1, (uint64_t)(0.98 * (double)p->bin_tiles * (double)most /
+                                                     (double)bin_items_bytes(p))));
+        }
+        const uint64_t positions = std::min<uint64_t>(p->positions, p->bin_tiles * TILE) / rounds;
+        if (p->cfg.fill_binned == 0 && !bin_pool_fits(p, positions))
+            return TP_OK;
     }
+    *chunk_tiles = (uint32_t)p->bin_tiles;
     const uint64_t n_off = p->bin_off.size(), n_roff = p->bin_roff.size();
     const uint64_t scratch = bin_items_bytes(p), cursors = 8 * (n_off + n_roff);
     if (reserve(p, {{&p->d_keys, scratch}, {&p->d_bin, cursors}, {&p->d_bin_room, cursors}}, false))
@@ -968,9 +995,9 @@ static int bin_setup(tp_plan *p, BinArgs *b, uint32_t *chunk_tiles, uint32_t rou
         if (split)
             HIPCHK(hipMemcpyAsync(p->d_bin_room.as<uint64_t>() + n_off, p->bin_roff.data(),
                                   n_roff * 8, hipMemcpyHostToDevice, s));
-        p->bin_tiles = tiles;
         p->bin_rounds = rounds;
     }
+    p->bin_want = want;
     (void)bin_place(p, b);
     b->cursor = p->d_bin.as<unsigned long long>();
     b->off = p->d_bin_room.as<uint64_t>();
@@ -1198,7 +1225,7 @@ static int static_setup(tp_plan *p, const Mail &m, hipStream_t s) {
                 HIPCHK(hipMemcpyAsync(x.b->p, x.src, x.bytes, hipMemcpyHostToDevice, s));
     }
     if (!p->static_uploaded)
-        p->bin_tiles = 0;  // the filters' places may have changed: the bins' room too
+        p->bin_want = 0;  // the filters' places may have changed: the bins' room too
     p->static_uploaded = p->order_uploaded = true;
     return TP_OK;
 }

@@ -259,7 +259,8 @@ struct tp_plan {
     tp::DevBuf d_bin;                      // binned fill: cursors; binned record: counts, offsets
     tp::DevBuf d_bin_room;                 // binned fill: the bins' places in the scratch
     std::vector<uint64_t> bin_off, bin_roff;  // host copies of it (buckets, regions)
-    uint64_t bin_tiles = 0;                // the chunk size it is laid out for (0: not)
+    uint64_t bin_want = 0;                 // the chunk size asked for (0: not laid out),
+    uint64_t bin_tiles = 0;                // the one it is laid out for
     uint32_t bin_rounds = 0;               // ... and the rounds
     tp::DevBuf d_queue;                    // tile queues of the four tile kernels
     tp::DevBuf d_rbin;                     // binned record: items (when the outputs cannot hold them)

@@ -103,3 +103,27 @@ def test_scratch_is_not_waited_for():
     assert res.stats["fill_chunks"] == 0
     assert large_info["start_s"] < small_info["start_s"]
     assert small_info["end_s"] < large_info["end_s"]
+
+
+def test_scratch_takes_a_quarter_of_the_free_memory():
+    """13 GB of items where 20 GiB are free: smaller chunks, the same filter."""
+    import torch
+    import paper_1602_05856_amd as tp
+    gs, b, h = random_set(36, 50_000_000, 2), 1 << 31, 16
+    _, bloom, c1, _ = run_plan(gs, 25, b, h, 0, fill_binned=1)
+    plan = tp.Plan(gs, 25, b, h, 0)
+    d_in = plan.upload()
+    torch.cuda.empty_cache()
+    rest = torch.empty(torch.cuda.mem_get_info()[0] - (20 << 30), dtype=torch.uint8, device="cuda")
+    free = torch.cuda.mem_get_info()[0]
+    plan.run(d_in)
+    used = free - torch.cuda.mem_get_info()[0]
+    plan.run(d_in)
+    st = plan.stats()
+    got = plan.debug_bloom(), plan.debug_candidates()
+    plan.close()
+    del rest
+    torch.cuda.empty_cache()
+    assert st["fill_chunks"] > 1
+    assert used < free / 4 + (1 << 30)  # and the filter, the bitmaps, the outputs
+    assert np.array_equal(got[0], bloom) and np.array_equal(got[1], c1)

@@ -307,14 +307,17 @@ typedef struct {
                               1..64                                          */
     uint32_t fill_binned;  /* fill: 0 = binned unless the filter pool is large
                               for the positions (more than 24 bytes each and
-                              128 MiB besides), else atomic; 1 = atomic (each
+                              128 MiB besides) or small for them (a set's
+                              filter of fewer than 128 regions with more than
+                              2^18 positions to a region, or a pool below 4),
+                              else atomic; 1 = atomic (each
                               edge's words loaded, then an atomicOr for bits
                               still clear, in HBM); 2 = binned: per chunk of
                               positions, every edge's filter effect is
                               written as a 4-byte item (standard filter: one
                               for each of its hash_count bits),
                               the items partitioned by region of the
-                              pool (64 or 128 KiB) in one or two streaming
+                              pool (2 to 128 KiB) in one or two streaming
                               passes, and each region's items ORed into the
                               region in LDS.  Same filter bits either way.
                               Binned needs about 4.5 bytes per item of a chunk

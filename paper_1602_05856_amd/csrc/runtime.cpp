@@ -860,12 +860,39 @@ bool tp::fill_binnable(const tp_plan *p) {
     return p->n_tiles && p->bloom_words / 2 <= (uint64_t)BIN_MAX_BUCKETS << BIN_LOCAL_LOG2;
 }
 
+// ... and not small for them: a region's items are one workgroup's, so a filter
+// of few regions leaves CUs idle behind long chains, while the atomic fill of a
+// filter that soon is full only loads.  Fewest regions, of a set's filter, from
+// which any number of positions is binned; positions to a region below that;
+// regions of the pool (first pass of random genomes, h = 4, atomic and binned, ms:
+// blocked, 128 Mbp at 2^12 bits (1 region) 1.8 and 35, 2^18 (16) 1.8 and 3.4, 2^20
+// (64) 1.73 and 1.94, 2^21 (128) 1.77 and 1.73; 8 Mbp at 2^18 0.39 and 0.35, 2^16
+// (4) 0.35 and 0.66; 0.1 Mbp at 2^14 (1) 0.061 and 0.077, 2^16 0.068 and 0.060;
+// standard, 128 Mbp at 2^20 6.8 and 7.5, 2^21 7.02 and 6.93, 8 Mbp at 2^18 0.88
+// and 0.70, 2^16 0.96 and 1.57).
+constexpr uint64_t BIN_FULL_REGIONS = 128, BIN_REGION_POSITIONS = 1u << 18, BIN_FEWEST_REGIONS = 4;
+
+static bool bin_regions_suffice(const tp_plan *p, uint32_t rounds) {
+    uint32_t bucket_log2, region_log2;
+    bin_shape(p->bloom_words / 2, (p->flags & TP_FLAG_BLOCKED_FILTER) != 0, &bucket_log2,
+              &region_log2);
+    if (p->bloom_words / 2 < BIN_FEWEST_REGIONS << region_log2)
+        return false;
+    for (const SetInfo &si : p->sets) {
+        const uint64_t regions = std::max<uint64_t>(1, si.b / 64 >> region_log2);
+        if (regions < BIN_FULL_REGIONS && si.positions / rounds > regions * BIN_REGION_POSITIONS)
+            return false;
+    }
+    return true;
+}
+
 // Whether this plan's fill runs binned (tp_config.fill_binned) with the given
 // rounds.
 static bool fill_binned(const tp_plan *p, uint32_t rounds) {
     if (p->cfg.fill_binned == 1 || !fill_binnable(p))
         return false;
-    return p->cfg.fill_binned == 2 || bin_pool_fits(p, p->positions / rounds);
+    return p->cfg.fill_binned == 2 ||
+           (bin_pool_fits(p, p->positions / rounds) && bin_regions_suffice(p, rounds));
 }
 
 // Room for the items of a chunk of `tiles` tiles, per bin of 2^bin_log2

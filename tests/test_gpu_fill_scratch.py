@@ -127,3 +127,17 @@ def test_scratch_takes_a_quarter_of_the_free_memory():
     assert st["fill_chunks"] > 1
     assert used < free / 4 + (1 << 30)  # and the filter, the bitmaps, the outputs
     assert np.array_equal(got[0], bloom) and np.array_equal(got[1], c1)
+
+
+@pytest.mark.parametrize("log2b, n, binned", [(12, 2_000_000, 0), (18, 6_000_000, 0),
+                                              (18, 2_000_000, 1), (21, 40_000_000, 1),
+                                              (14, 100_000, 0), (16, 100_000, 1)])
+@pytest.mark.parametrize("flags", [BLOCKED, 0])
+def test_filters_of_few_regions_are_filled_atomically(log2b, n, binned, flags):
+    import paper_1602_05856_amd as tp
+    gs = random_set(37, n, 1)
+    for cfg in ({}, {"fill_binned": 2}):
+        st, bloom, _, _ = run_plan(gs, 25, 1 << log2b, 4, flags | tp.TP_FLAG_PASS1_ONLY, **cfg)
+        assert (st["fill_chunks"] > 0) == bool(binned or cfg)
+        want = bloom if not cfg else want
+        assert np.array_equal(bloom, want)

@@ -680,7 +680,9 @@ template <uint32_t NB, uint32_t NT, uint32_t PER, class I = uint32_t> struct Bin
 // none.  The items are sorted by bin in LDS and a bin's items written as one
 // run by a group of 2^lpb lanes; bin i has room for off(i+1) - off(i) items
 // from out + off(i), of which cursor[i] are claimed.  direct(bin, item) takes
-// an item without room.  sh.cnt is zero again on return.  Whole workgroup;
+// an item without room, unless it equals the one before it in the run: items
+// are idempotent, and a repetitive input's without room are mostly copies.
+// sh.cnt is zero again on return.  Whole workgroup;
 // ends synchronised.
 template <uint32_t NB, uint32_t NT, uint32_t PER, class I, class Off, class Direct>
 __device__ __forceinline__ void bin_append(BinSort<NB, NT, PER, I> &sh, const I (&item)[PER],
@@ -718,7 +720,7 @@ __device__ __forceinline__ void bin_append(BinSort<NB, NT, PER, I> &sh, const I 
             const I it = sh.srt[s0 + i];
             if (b0 + i < room)
                 out[o + b0 + i] = it;
-            else
+            else if (i == 0 || sh.srt[s0 + i - 1] != it)
                 direct(bin, it);
         }
     }

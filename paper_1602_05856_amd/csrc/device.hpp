@@ -716,13 +716,12 @@ __device__ __forceinline__ void bin_append(BinSort<NB, NT, PER, I> &sh, const I 
         const uint32_t s0 = sh.start[bin], n = sh.start[bin + 1] - s0, b0 = sh.cnt[bin];
         const uint64_t o = off(bin);
         const uint32_t room = (uint32_t)min(off(bin + 1) - o, (uint64_t)0xFFFF7FFFu);
-        for (uint32_t i = l; i < n; i += 1u << lpb) {
-            const I it = sh.srt[s0 + i];
-            if (b0 + i < room)
-                out[o + b0 + i] = it;
-            else if (i == 0 || sh.srt[s0 + i - 1] != it)
-                direct(bin, it);
-        }
+        const uint32_t fit = b0 < room ? min(n, room - b0) : 0;
+        for (uint32_t i = l; i < fit; i += 1u << lpb)
+            out[o + b0 + i] = sh.srt[s0 + i];
+        for (uint32_t i = fit + l; i < n; i += 1u << lpb)
+            if (i == 0 || sh.srt[s0 + i - 1] != sh.srt[s0 + i])
+                direct(bin, sh.srt[s0 + i]);
     }
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < NB; i += NT)

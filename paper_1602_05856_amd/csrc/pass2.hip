@@ -25,7 +25,7 @@
 namespace tp {
 
 // The second pass walks up to P2_TILES tiles of one set at a time.  Their
-// candidates are listed first (their positions, ascending), and the lanes walk
+// candidates are listed first (their positions), and the lanes walk
 // the list, so that every lane holds a candidate: a 16-bit-a-position filter
 // leaves some 8% of them, spread over every wave, and a round the same of its
 // class.  Several tiles at once, because a tile's own chain of dependent steps
@@ -36,6 +36,13 @@ namespace tp {
 // decision 6.6, 5.7 and 1.9; four rounds of 80 Mbp at k = 25 record 2.0, 2.0
 // and 0.7, decision 2.4, 2.3 and 0.9.
 constexpr uint32_t P2_TILES = 4;
+// The batch's tiles take turns in the list, P2_RUN positions each: homologous
+// tiles (a slab walk's batch) then look a k-mer up at about the same time and hit
+// its line.  8 related genomes of 5 Mbp, k = 25, every position a candidate:
+// decision 0.68 ms listed tile by tile, 0.52, 0.41 and 0.41 with runs of 512, 128
+// and 32; 62 x 5 Mbp with 2.5 bits a position 1.43, 1.42, 1.41 and 1.48 (a wave's
+// lanes in four tiles' stages).
+constexpr uint32_t P2_RUN = 128;
 
 struct P2Tile {
     uint64_t t0;
@@ -124,10 +131,14 @@ __device__ __forceinline__ bool next_batch(const SeqArgs &a, RunCursor &rc, uint
     // a thread lists PER positions
     constexpr uint32_t PER = P2_TILES * TILE / NT;
     static_assert(PER == 8 || PER == 16 || PER == 32, "a piece of one 32-bit word");
+    static_assert(P2_RUN % PER == 0 && TILE % P2_RUN == 0, "whole pieces");
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t bits = ((const uint32_t *)b.w)[threadIdx.x * PER / 32];
+    constexpr uint32_t RUN = P2_RUN / PER;
+    const uint32_t jt = threadIdx.x / RUN % P2_TILES,
+                   p0 = (threadIdx.x / RUN / P2_TILES * RUN + threadIdx.x % RUN) * PER;
+    uint32_t bits = ((const uint32_t *)b.w)[jt * (TILE / 32) + p0 / 32];
     if (PER < 32)
-        bits = bits >> (threadIdx.x * PER & 31u) & ((1u << (PER & 31u)) - 1);
+        bits = bits >> (p0 & 31u) & ((1u << (PER & 31u)) - 1);
     const uint32_t c = (uint32_t)__popc(bits);
     uint32_t x = c;
 #pragma unroll
@@ -145,7 +156,7 @@ __device__ __forceinline__ bool next_batch(const SeqArgs &a, RunCursor &rc, uint
         sum += b.wsum[q];
     }
     for (; bits; bits &= bits - 1)
-        b.at[at++] = (uint16_t)(threadIdx.x * PER + (uint32_t)__builtin_ctz(bits));
+        b.at[at++] = (uint16_t)(jt * TILE + p0 + (uint32_t)__builtin_ctz(bits));
     *total = sum;
     __syncthreads();
     return true;

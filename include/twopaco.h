@@ -306,13 +306,14 @@ typedef struct {
                               (2048 positions each) of its walk per visit,
                               1..64                                          */
     uint32_t fill_binned;  /* fill: 0 = binned unless the filter pool is large
-                              for the positions (more than 24 bytes each and
-                              128 MiB besides) or small for them (a set's
+                              for the positions (more than 64 bytes each, 32
+                              for each hash function with the standard filter,
+                              and 16 MiB besides) or small for them (a set's
                               filter of fewer than 128 regions with more than
                               2^18 positions to a region, or a pool below 4),
-                              else atomic; 1 = atomic (each
-                              edge's words loaded, then an atomicOr for bits
-                              still clear, in HBM); 2 = binned: per chunk of
+                              else atomic; 1 = atomic (each edge's words
+                              loaded, then an atomicOr for bits still clear, in
+                              HBM); 2 = binned: per chunk of
                               positions, every edge's filter effect is
                               written as a 4-byte item (standard filter: one
                               for each of its hash_count bits),

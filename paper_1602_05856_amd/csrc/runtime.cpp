@@ -847,12 +847,19 @@ constexpr int RUN_SPLIT = 1;  // run_impl: redo the run with *split rounds
 // (two passes, at about 4.8 TB/s), and an edge costs about 7 ps binned against
 // 18 ps with atomics, besides a few launches (measured per run of 0.4, 2, 8,
 // 32 and 100 Mbp at k = 25, 16 bits a position: 0.042, 0.048, 0.084, 0.275 and
-// 1.03 ms binned, 0.101, 0.109, 0.197, 0.603 and 1.71 ms atomic).
-constexpr uint64_t BIN_POOL_PER_POSITION = 24;
-constexpr uint64_t BIN_POOL_FREE = 128ull << 20;
+// 1.03 ms binned, 0.101, 0.109, 0.197, 0.603 and 1.71 ms atomic).  The line lies
+// where the two meet, at h = 4 (pool bytes a position: first pass of four sets,
+// atomic / binned): blocked, 0.4 Mbp 84: 0.97, 168: 0.84; 4 Mbp 34: 1.35, 67:
+// 1.06, 134: 0.76; 20 Mbp 54: 1.26, 107: 0.98; 100 Mbp 43: 1.33, 86: 1.04;
+// standard, 0.4 Mbp 168: 1.14, 336: 1.00; 4 Mbp 134: 1.37, 268: 1.10; 20 Mbp
+// 107: 1.44, 215: 1.22 (one set's binned fill counts its bits besides: higher).
+constexpr uint64_t BIN_POOL_PER_POSITION = 64, BIN_POOL_PER_BIT = 32;  // (standard: h bits)
+constexpr uint64_t BIN_POOL_FREE = 16ull << 20;
 
 static bool bin_pool_fits(const tp_plan *p, uint64_t positions) {
-    return p->bloom_words * 4 <= BIN_POOL_PER_POSITION * positions + BIN_POOL_FREE;
+    const uint64_t per = (p->flags & TP_FLAG_BLOCKED_FILTER) ? BIN_POOL_PER_POSITION
+                                                             : BIN_POOL_PER_BIT * p->h;
+    return p->bloom_words * 4 <= per * positions + BIN_POOL_FREE;
 }
 
 // Whether this plan's fill can run binned: a pool within the bucket limit.

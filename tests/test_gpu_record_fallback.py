@@ -75,3 +75,22 @@ def test_a_record_given_up_is_not_tried_again(repetitive):
         plan.run(d_in)
         assert plan.stats()["table_attempts"] == 2
     plan.close()
+
+
+@pytest.mark.parametrize("units, attempts", [(3_000, 1), (20_000, 2)])
+def test_items_without_room_spill_or_give_up(units, attempts):
+    """A motif's k-mers, `units` items each and one block's, against that block's
+    room (its share of the candidates, six standard deviations and 64): some
+    spill, and of the larger number more than the spill takes."""
+    import paper_1602_05856_amd as tp
+    from helpers import to_genomes
+    from test_gpu_record_bins import genomes
+    plan = tp.Plan(to_genomes(genomes(25, units)), 25, 2**18, 3, BLOCKED)
+    plan.config = {"record_binned": 2, "table_shape": 2, "table_load": 0.05}
+    plan.run(plan.upload())
+    st = plan.stats()
+    plan.close()
+    blocks = (st["table_capacity"] - 4096) // 8192
+    mean = st["candidates"] / blocks
+    assert blocks > 512 and units > 1.02 * mean + 6 * (4 * mean) ** 0.5 + 80
+    assert st["table_attempts"] == attempts and (st["record_passes"] > 0) == (attempts == 1)

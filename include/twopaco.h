@@ -410,16 +410,16 @@ typedef struct {
  * graphs 0, pass2_slabs 2 (decision in first-pass order), fill_dedup 1
  * (ignored with the standard filter), table_shape 0, chunk_tiles 1,
  * fill_binned 0, bin_chunk_tiles 0, bloom_bits_per_edge 0 (16),
- * tile_queue 1, record_binned 0, table_budget 0, record_passes 0.  tp_plan_set_config fails with TP_EINVAL outside the
- * ranges above and leaves the plan unchanged. */
+ * tile_queue 1, record_binned 0, table_budget 0, record_passes 0.
+ * tp_plan_set_config fails with TP_EINVAL outside the ranges above and leaves
+ * the plan unchanged. */
 int tp_plan_get_config(const tp_plan *p, tp_config *out);
 int tp_plan_set_config(tp_plan *p, const tp_config *cfg);
 
 /* Autotuner: times the plan's kernels on its own input under candidate
  * configurations (about 48 runs of tp_run; 6 more when some set's filter is
  * auto-sized, whose density it picks among 8, 16 and 32 bits per (k+1)-mer
- * on the whole run; with the blocked filter it also picks the atomic or the
- * binned fill), keeps the fastest per knob and applies it.  With a
+ * on the whole run; it also picks the atomic or the binned fill), keeps the fastest per knob and applies it.  With a
  * cache file, results are keyed by device, k-mer words, flags, position
  * count (power-of-two bucket), set count (bucket) and whether some filter is
  * auto-sized; a

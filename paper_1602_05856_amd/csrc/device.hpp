@@ -147,8 +147,6 @@ template <> struct KT<uint64_t> {
     __device__ static __forceinline__ uint64_t val(uint64_t x, uint32_t L) {
         return rev2(x) >> (64 - 2 * L);
     }
-    __device__ static __forceinline__ uint64_t lo(uint64_t x) { return x; }
-    __device__ static __forceinline__ uint64_t hi(uint64_t) { return 0; }
     __device__ static __forceinline__ uint64_t word(uint64_t x, uint32_t) { return x; }
 };
 
@@ -176,8 +174,6 @@ template <> struct KT<u128> {
         u128 r = ((u128)rev2((uint64_t)x) << 64) | rev2((uint64_t)(x >> 64));
         return r >> (128 - 2 * L);
     }
-    __device__ static __forceinline__ uint64_t lo(u128 x) { return (uint64_t)x; }
-    __device__ static __forceinline__ uint64_t hi(u128 x) { return (uint64_t)(x >> 64); }
     __device__ static __forceinline__ uint64_t word(u128 x, uint32_t i) {
         return i == 0 ? (uint64_t)x : (uint64_t)(x >> 64);
     }
@@ -217,8 +213,6 @@ template <> struct KT<u256> {
         const u256 r(rev2(x.w3), rev2(x.w2), rev2(x.w1), rev2(x.w0));
         return r >> (256 - 2 * L);
     }
-    __device__ static __forceinline__ uint64_t lo(const u256 &x) { return x.w0; }
-    __device__ static __forceinline__ uint64_t hi(const u256 &x) { return x.w1; }
     __device__ static __forceinline__ uint64_t word(const u256 &x, uint32_t i) {
         return u256_word(x, i);
     }

@@ -94,8 +94,6 @@ struct SetDesc {
     uint64_t table_off;         // first slot of its table in the table pools (multiple of 64)
     uint64_t sent_tab_off;      // first slot of its sentinel table in the sentinel pool
     uint32_t table_m, table_e;  // its table has m << e home slots (region: + TABLE_TAIL)
-    uint32_t sent_lo, sent_hi;  // its slice of the sentinel array (2 per string)
-    uint32_t str_lo, str_hi;    // its strings
     uint32_t cls_lo, cls_hi;    // current round: class subranges [cls_lo, cls_hi)
     uint32_t sent_tab_log2;     // its sentinel table has 2^log2 slots (at most half full)
     uint32_t pad;

@@ -401,7 +401,6 @@ hipError_t launch_fill(int W, const SeqArgs &a, const BloomArgs &pool, Counters 
 // offset, stride and pair.  Room per bucket and region is laid out from the
 // edge count (a hash spreads them evenly), so nothing is counted beforehand:
 // an item is written and read once per level, 8 or 16 bytes an edge in all.
-
 //
 // The standard filter's items are one per edge and hash function: the block
 // within the bucket and 6 bits for the bit in it.

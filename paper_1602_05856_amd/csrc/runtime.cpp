@@ -646,13 +646,9 @@ static std::vector<SetDesc> set_descs(const tp_plan *p) {
         } else {
             (void)shape_table(si.table_cap, &d[s].table_m, &d[s].table_e);
         }
-        d[s].sent_lo = 2 * si.str_lo;
-        d[s].sent_hi = 2 * si.str_hi;
         d[s].sent_tab_off = si.sent_tab_off;
         d[s].sent_tab_log2 = si.sent_tab_log2;
         d[s].pad = 0;
-        d[s].str_lo = si.str_lo;
-        d[s].str_hi = si.str_hi;
     }
     return d;
 }
@@ -713,13 +709,9 @@ std::vector<SetDesc> tp::set_descs_for(const tp_plan *p, const std::vector<uint6
             (void)shape_table(caps[s], &d[s].table_m, &d[s].table_e);
         }
         off += caps[s] + TABLE_TAIL;
-        d[s].sent_lo = 2 * si.str_lo;
-        d[s].sent_hi = 2 * si.str_hi;
         d[s].sent_tab_off = si.sent_tab_off;
         d[s].sent_tab_log2 = si.sent_tab_log2;
         d[s].pad = 0;
-        d[s].str_lo = si.str_lo;
-        d[s].str_hi = si.str_hi;
         d[s].cls_lo = d[s].cls_hi = 0;
     }
     *slots = off;

@@ -135,8 +135,7 @@ struct Grid {
     uint32_t n = 0, parts_log2 = 0;  // workgroups of a tile kernel, parts a tile is cut in
 };
 SeqArgs with_queue(SeqArgs a, unsigned int *qbase, int kid, const Grid &grid);
-// Whether the plan's fill can run binned (blocked filter, pool within the
-// bucket limit).
+// Whether the plan's fill can run binned (a pool within the bucket limit).
 bool fill_binnable(const tp_plan *p);
 // Filter sizes of auto-sized sets (at p->cfg.bloom_bits_per_edge) and every
 // set's offset in the filter pool.
@@ -256,7 +255,7 @@ struct tp_plan {
     tp::DevBuf d_keys, d_seq, d_blockcnt, d_blockoff;  // d_seq: the input a reference table names
     tp::DevBuf d_pos, d_vertex, d_strand, d_edges, d_joff;
     tp::DevBuf d_c1u, d_census;            // rounds: union of candidates, class census
-    tp::DevBuf d_bin;                      // binned fill: cursors; binned record: counts, offsets
+    tp::DevBuf d_bin;                      // binned fill: cursors
     tp::DevBuf d_bin_room;                 // binned fill: the bins' places in the scratch
     std::vector<uint64_t> bin_off, bin_roff;  // host copies of it (buckets, regions)
     uint64_t bin_want = 0;                 // the chunk size asked for (0: not laid out),

@@ -4,10 +4,10 @@
 //
 // A plan with auto-sized filters first gets its filter density (bits per
 // (k+1)-mer, on the whole run: a denser filter costs pass 1 more cache
-// misses, a sparser one lets more false candidates into pass 2).  With the
-// blocked filter the atomic or binned fill is chosen next, on fill time,
-// then the fill's deduplication (it
-// changes the fill's LDS use, hence its occupancy), on fill time.  Each
+// misses, a sparser one lets more false candidates into pass 2).  The atomic
+// or binned fill is chosen next, on fill time, then with the blocked filter
+// the atomic fill's deduplication (it changes the fill's LDS use, hence its
+// occupancy), on fill time.  Each
 // kernel is timed by its own HIP events (tp_stats), so one run under a
 // given workgroups-per-CU value times all four tile kernels at that value,
 // and each kernel keeps its own best.  Then the chunk size of the tile
@@ -189,7 +189,7 @@ extern "C" int tp_autotune(tp_plan *p, const uint8_t *d_input, void *stream,
         best.bloom_bits_per_edge = best_bpe;
     }
 
-    // 0b. atomic or binned fill (blocked filter, binnable pool), on fill time
+    // 0b. atomic or binned fill (binnable pool), on fill time
     if (fill_binnable(p)) {
         float ms[3] = {0, 0, 0};
         for (uint32_t v = 1; v <= 2; ++v) {

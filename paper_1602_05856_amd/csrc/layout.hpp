@@ -270,7 +270,7 @@ struct BinArgs {
 // that so: they leave one apply workgroup per CU instead of two), else about
 // 256 buckets of up to 2^21 blocks, split by region afterwards (a batch's
 // longer runs: 654 Mbp over 128 filters of 1.4 GB in all, k_bin_items 4.15 ms
-// against 4.67 with 1024 buckets).  Pools beyond 16 GiB need up to 2048
+// against 4.67 with 1024 buckets; 3.5 since).  Pools beyond 16 GiB need up to 2048
 // buckets, for an item's block bits.
 // The standard filter's items (h to an edge) go to 256 buckets at most:
 // their claims (an atomic per bin and batch) would take as long as the sort.

@@ -702,8 +702,9 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_bin_apply(BloomArgs pool, BinArgs
 
 // Items per thread of k_bin_items.  Twelve leave room for two workgroups per
 // CU, in registers (64, with a few spilled) and LDS, so that one's sort runs
-// beside the other's hashing: 62 x 5 Mbp at k = 25 1.57 ms, against 1.80 with
-// sixteen and one workgroup and 1.69 with eight (more claims).  Four-word
+// beside the other's hashing: 62 x 5 Mbp at k = 25 1.57 ms (1.50 with the runs
+// written by a loop without a test for room), against 1.80 with sixteen and one
+// workgroup and 1.69 with eight (more claims).  Four-word
 // k-mers and rounds (two more k-mers to hash) need the registers of one
 // workgroup per CU.
 template <class T, bool CLASSES> struct ItemsPer {
@@ -974,7 +975,7 @@ __device__ __forceinline__ void query_no_string(uint64_t tile, uint64_t *c1, uin
 // filter sits in the last-level cache (62 x 5 Mbp, b = 2^30, k = 25: 293
 // vector instructions a position and 2.87 ms when k-mers were reversed and
 // shifted in registers, each pair test rotated the block by itself and the
-// sketch and the prefilter hashed on their own; now 204 and 2.28 ms; k = 100
+// sketch and the prefilter hashed on their own; now 200 and 2.29 ms; k = 100
 // 7.0 -> 4.4 ms), by random loads where it does not (1.6 Gbp, a 1 GiB filter:
 // 26.8 -> 26.3 ms).
 template <class T, bool CLASSES>

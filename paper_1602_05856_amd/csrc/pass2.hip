@@ -238,8 +238,9 @@ __device__ __forceinline__ u64x2 load_pair(const TableArgs &t, uint64_t s) {
 // atomic per key word and one to publish it (and those atomics, at the
 // device's ~27 G/s, were the whole record), and the table is cleared, probed
 // and cached at a half to a quarter of the bytes.  62 x 5 Mbp, b = 2^30: 73M
-// keys at k = 63, record 16.3 -> 6.0 ms and decision 6.6 -> 3.9; 135M keys at
-// k = 100, 27.3 -> 8.5 and 10.6 -> 6.2.  The compare reads two to
+// keys at k = 63, record 16.3 -> 6.0 ms and decision 6.6 -> 3.9 (5.2 and 2.8 with
+// the listed walk); 135M keys at k = 100, 27.3 -> 8.5 and 10.6 -> 6.2 (8.1 and
+// 3.7).  The compare reads two to
 // five words of the sequence, mostly lines that neighbouring positions read
 // too (consecutive k-mers were claimed by consecutive positions).
 
